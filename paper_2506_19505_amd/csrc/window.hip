@@ -1,36 +1,88 @@
 // Decode append with an FP16 sliding window of recent tokens (paper Sec. 3.2, last paragraph; window of 32 in
-// Sec. 4).  The window lives in the last W entries of the anchor lists.  One launch per step: a workgroup per
-// (sequence, KV head, K|V) encodes the retiring token's row to its codes (nearest centroid per sub-vector,
-// Sec. 3.1), moves the window one place down and appends the new token's row.  The step is latency-bound
-// (one row per head), so the encode here is plain fp32 FMA work, one centroid per thread at a time, not the MFMA
-// kernel.  With 4096 centroids (d_sub 32 or 16) a thread walks 16 of them per sub-space and the 12-bit codes are packed.
+// Sec. 4).  The window lives in the last W entries of the anchor lists.  One launch per step: the retiring token's row
+// is encoded (nearest centroid per sub-vector, Sec. 3.1), the window moves one place down and the new row is appended.
+//
+// Bound: latency.  A step touches one row per head; what costs is the chain launch -> row and centroid loads -> arg-max
+// -> store, so every load is issued up front and nothing runs in a loop over sub-spaces.  A (sequence, KV head, K|V) is
+// cut by channels: a workgroup encodes the sub-vectors of its own channels and moves the same channels of the window
+// rows, so workgroups share no data and need no order among themselves.  A wave takes a whole sub-space (256 centroids:
+// four per lane) or, with 4096 centroids, an eighth of one, and finds the arg-max with row rotations instead of LDS
+// exchanges.  Neighbouring lanes read one centroid, so that a load instruction covers whole cache lines (one lane per
+// 64-byte centroid cost four times the L1 cycles).  8 KV heads, kernel trace: d_sub 4 / 8 / 16 at batch 1 from
+// 25 / 13 / 10 us (one workgroup looping over the sub-spaces) to 4.0 / 4.0 / 4.6 us, d32m4096 from 35 to 8 us.
 #include "common.h"
 
 namespace antkv {
 
 namespace {
 
-constexpr int kApThreads = 256;   // thread c scores centroids c, c + 256, ... of every sub-space
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v)      // v of another lane of the row (quad permutation, row rotation)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+}
+
+// the wave's maximum / minimum in every lane: row rotations inside 16 lanes, then the four rows through scalar registers
+__device__ __forceinline__ float wave_max_all(float x)
+{
+    x = fmaxf(x, __uint_as_float(dpp<0x121>(__float_as_uint(x))));
+    x = fmaxf(x, __uint_as_float(dpp<0x122>(__float_as_uint(x))));
+    x = fmaxf(x, __uint_as_float(dpp<0x124>(__float_as_uint(x))));
+    x = fmaxf(x, __uint_as_float(dpp<0x128>(__float_as_uint(x))));
+    float r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 16 * i));
+    return fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3]));
+}
+__device__ __forceinline__ uint32_t wave_min_all(uint32_t x)
+{
+    x = min(x, dpp<0x121>(x));
+    x = min(x, dpp<0x122>(x));
+    x = min(x, dpp<0x124>(x));
+    x = min(x, dpp<0x128>(x));
+    uint32_t r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = (uint32_t)__builtin_amdgcn_readlane((int)x, 16 * i);
+    return min(min(r[0], r[1]), min(r[2], r[3]));
+}
+
+// Channels per workgroup and waves: 256 centroids, 32 channels x 4 waves (16 KB of codebook); 4096 centroids, two
+// sub-spaces (their 12-bit codes fill whole bytes) x 16 waves (256 or 512 KB of codebook).
+template <int DSUB, int NC>
+struct Ap {
+    static constexpr int channels = NC == 256 ? 32 : 2 * DSUB;
+    static constexpr int waves = NC == 256 ? 4 : 16;
+    static constexpr int threads = waves * 64;
+    static constexpr int subs = channels / DSUB;                          // sub-spaces of the workgroup
+    static constexpr int waves_per_sub = waves >= subs ? waves / subs : 1;
+    static constexpr int subs_per_wave = waves >= subs ? 1 : subs / waves;
+    static constexpr int chunk = DSUB < 8 ? DSUB : 8;                     // channels of a sub-vector that one lane loads
+    static constexpr int lanes = DSUB / chunk;                            // lanes of a sub-vector: neighbours read it as one line
+    static constexpr int step = 64 / lanes;                               // centroids of one load instruction
+    static constexpr int per_wave = NC / waves_per_sub;                   // centroids of a wave
+    static_assert(threads >= 64 * channels / 8, "a window of 64 rows is one 16-byte piece per thread");
+};
 
 // NC = centroids per sub-space: 256 (one code byte per sub-space) or 4096 (M 12-bit codes packed into 3 M / 2 bytes)
 template <int DSUB, int NC>
-__global__ __launch_bounds__(kApThreads) void append_kernel(
+__global__ __launch_bounds__((Ap<DSUB, NC>::threads)) void append_kernel(
     const half_t* __restrict__ k_new, const half_t* __restrict__ v_new, const half_t* __restrict__ cb_k,
     const half_t* __restrict__ cb_v, uint8_t* __restrict__ codes_k, uint8_t* __restrict__ codes_v, int64_t N_cap,
     int32_t* __restrict__ idx_k, half_t* __restrict__ rows_k, int64_t k_k, int32_t* __restrict__ idx_v,
     half_t* __restrict__ rows_v, int64_t k_v, int64_t N, int W, int Hkv)
 {
+    using P = Ap<DSUB, NC>;
+    typedef half_t piece_t __attribute__((ext_vector_type(P::chunk)));
     constexpr int M = kD / DSUB;
     constexpr int kCodeBytes = NC == 256 ? M : 3 * M / 2;
-    static_assert(NC == 256 || (NC == 4096 && M % 4 == 0), "12-bit codes are packed four to three 16-bit words");
-    __shared__ float s_x[kD];
-    __shared__ float s_val[M][4];
-    __shared__ int s_idx[M][4];
-    __shared__ int s_code[M];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float s_val[P::waves];
+    __shared__ uint32_t s_who[P::waves];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t bg = blockIdx.x;
     const int g = (int)(bg % Hkv);
     const bool is_v = blockIdx.y != 0;
+    const int ch0 = (int)blockIdx.z * P::channels;                               // first channel of the workgroup
     const int64_t kk = is_v ? k_v : k_k;
     half_t* rows = (is_v ? rows_v : rows_k) + (bg * kk + (kk - W)) * kD;          // first window row
     int32_t* idx = (is_v ? idx_v : idx_k) + bg * kk + (kk - W);
@@ -38,83 +90,83 @@ __global__ __launch_bounds__(kApThreads) void append_kernel(
     const half_t* cb = (is_v ? cb_v : cb_k) + (size_t)g * kD * NC;
     uint8_t* codes = (is_v ? codes_v : codes_k) + (bg * N_cap + (N - W)) * kCodeBytes;   // codes of the retiring position
 
+    // window move: row e takes row e + 1 (the last one the new row); one 16-byte piece per thread, read now, written
+    // after the barrier below
+    constexpr int kPieces = P::channels / 8;
+    const int e = tid / kPieces, off = ch0 + 8 * (tid % kPieces);
+    uint4_t mv = {0u, 0u, 0u, 0u};
+    if (e < W) mv = (e + 1 < W) ? *(const uint4_t*)(rows + (e + 1) * kD + off) : *(const uint4_t*)(fresh + off);
+
     // the row that becomes codes: the window's oldest, or the new row itself when there is no window
     const half_t* src = (W > 0) ? rows : fresh;
-    if (tid < kD) s_x[tid] = (float)src[tid];
-    // window moves are read now, written after the barrier below: up to 64 rows x 16 chunks, 4 per thread
-    uint4_t mv[4];
+    const int part = wave % P::waves_per_sub;                                     // the wave's share of its sub-space
+    const int li = lane % P::lanes;                                               // the lane's channels inside a sub-vector
+    float best[P::subs_per_wave];
+    uint32_t who[P::subs_per_wave];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = tid + i * kApThreads, e = t >> 4, part = t & 15;
-        mv[i] = uint4_t{0u, 0u, 0u, 0u};
-        if (e < W) mv[i] = (e + 1 < W) ? ((const uint4_t*)rows)[(e + 1) * 16 + part] : ((const uint4_t*)fresh)[part];
-    }
-    __syncthreads();
-    // thread t scores centroids t, t + 256, ... of every sub-space: x.c - |c|^2 / 2 (largest = nearest)
-#pragma unroll 1
-    for (int m = 0; m < M; ++m) {
+    for (int s = 0; s < P::subs_per_wave; ++s) {
+        const int m = ch0 / DSUB + (wave / P::waves_per_sub) * P::subs_per_wave + s;
+        const uint32_t c_lo = (uint32_t)(part * P::per_wave + lane / P::lanes);
+        const half_t* cen = cb + ((int64_t)m * NC + c_lo) * DSUB + li * P::chunk;
+        const piece_t x = *(const piece_t*)(src + m * DSUB + li * P::chunk);
         float val = -3.0e38f;
-        int who = tid;
-#pragma unroll 1
-        for (int c = tid; c < NC; c += kApThreads) {                 // ascending, strict '>': ties keep the lower index
-            const half_t* cen = cb + ((int64_t)m * NC + c) * DSUB;
-            float cf[DSUB];
-            if constexpr (DSUB == 4) {
-                const half4_t v = *(const half4_t*)cen;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) cf[t] = (float)v[t];
-            } else {
-#pragma unroll
-                for (int u = 0; u < DSUB / 8; ++u) {
-                    const half8_t v = *(const half8_t*)(cen + 8 * u);
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) cf[8 * u + t] = (float)v[t];
-                }
-            }
+        uint32_t c_best = c_lo;
+        // centroids c_lo, c_lo + step, ...: x.c - |c|^2 / 2 (largest = nearest), ascending with a strict '>' so that ties
+        // keep the lower index
+#pragma unroll 16
+        for (int j = 0; j < P::per_wave / P::step; ++j) {
+            const piece_t c = *(const piece_t*)(cen + j * P::step * DSUB);
             float nn = 0.f, dot = 0.f;
 #pragma unroll
-            for (int t = 0; t < DSUB; ++t) { nn = fmaf(cf[t], cf[t], nn); dot = fmaf(s_x[m * DSUB + t], cf[t], dot); }
-            const float sc = fmaf(-0.5f, nn, dot);
-            if (sc > val) { val = sc; who = c; }
+            for (int t = 0; t < P::chunk; t += 2) {                               // fp16 products are exact, sums are fp32
+                const half2_t c2 = {c[t], c[t + 1]}, x2 = {x[t], x[t + 1]};
+                nn = __builtin_amdgcn_fdot2(c2, c2, nn, false);
+                dot = __builtin_amdgcn_fdot2(x2, c2, dot, false);
+            }
+            float sc = fmaf(-0.5f, nn, dot);
+            if constexpr (P::lanes >= 2) sc += __uint_as_float(dpp<0xB1>(__float_as_uint(sc)));   // quad lanes 1 0 3 2
+            if constexpr (P::lanes == 4) sc += __uint_as_float(dpp<0x4E>(__float_as_uint(sc)));   // quad lanes 2 3 0 1
+            if (sc > val) { val = sc; c_best = c_lo + P::step * j; }
         }
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {       // ties go to the lower centroid index
-            const float ov = __shfl_xor(val, off, 64);
-            const int oi = __shfl_xor(who, off, 64);
-            if (ov > val || (ov == val && oi < who)) { val = ov; who = oi; }
-        }
-        if (lane == 0) { s_val[m][wave] = val; s_idx[m][wave] = who; }
+        best[s] = wave_max_all(val);
+        who[s] = wave_min_all(val == best[s] ? c_best : 0xffffffffu);             // the lowest index among equals
     }
-    __syncthreads();
-    if (tid < M) {
-        float val = s_val[tid][0];
-        int who = s_idx[tid][0];
-#pragma unroll
-        for (int w = 1; w < 4; ++w)
-            if (s_val[tid][w] > val || (s_val[tid][w] == val && s_idx[tid][w] < who)) { val = s_val[tid][w]; who = s_idx[tid][w]; }
-        if constexpr (NC == 256) codes[tid] = (uint8_t)who;
-        else s_code[tid] = who;
+    if constexpr (P::waves_per_sub > 1) {
+        if (lane == 0) { s_val[wave] = best[0]; s_who[wave] = who[0]; }
     }
-    if constexpr (NC != 256) {                         // 12-bit codes, little-endian: code m at bits 12 m .. 12 m + 11
-        __syncthreads();
-        if (tid < M / 4) {
-            const uint32_t c0 = (uint32_t)s_code[4 * tid], c1 = (uint32_t)s_code[4 * tid + 1];
-            const uint32_t c2 = (uint32_t)s_code[4 * tid + 2], c3 = (uint32_t)s_code[4 * tid + 3];
-            const uint32_t lo = c0 | (c1 << 12) | (c2 << 24);
-            const uint32_t hi = (c2 >> 8) | (c3 << 4);
-            uint16_t* dst = (uint16_t*)codes + 3 * tid;
-            dst[0] = (uint16_t)lo;
-            dst[1] = (uint16_t)(lo >> 16);
-            dst[2] = (uint16_t)hi;
-        }
-    }
+    __syncthreads();                                                              // window and row are read everywhere
+    if constexpr (NC == 256) {
+        if constexpr (P::waves_per_sub == 1) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = tid + i * kApThreads, e = t >> 4, part = t & 15;
-        if (e < W) {
-            ((uint4_t*)rows)[e * 16 + part] = mv[i];
-            if (part == 0) idx[e] = (int32_t)(N - W + 1 + e);
+            for (int s = 0; s < P::subs_per_wave; ++s)
+                if (lane == 0) codes[ch0 / DSUB + wave * P::subs_per_wave + s] = (uint8_t)who[s];
+        } else if (tid < P::subs) {
+            float val = s_val[tid * P::waves_per_sub];
+            uint32_t c = s_who[tid * P::waves_per_sub];
+#pragma unroll
+            for (int w = 1; w < P::waves_per_sub; ++w)                            // ascending shares, strict '>'
+                if (s_val[tid * P::waves_per_sub + w] > val) { val = s_val[tid * P::waves_per_sub + w]; c = s_who[tid * P::waves_per_sub + w]; }
+            codes[ch0 / DSUB + tid] = (uint8_t)c;
         }
+    } else if (tid == 0) {
+        uint32_t c2[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            float val = s_val[s * P::waves_per_sub];
+            c2[s] = s_who[s * P::waves_per_sub];
+#pragma unroll
+            for (int w = 1; w < P::waves_per_sub; ++w)
+                if (s_val[s * P::waves_per_sub + w] > val) { val = s_val[s * P::waves_per_sub + w]; c2[s] = s_who[s * P::waves_per_sub + w]; }
+        }
+        // 12-bit codes, little-endian, code m at bits 12 m .. 12 m + 11: two codes are three whole bytes
+        uint8_t* dst = codes + 3 * blockIdx.z;
+        dst[0] = (uint8_t)c2[0];
+        dst[1] = (uint8_t)((c2[0] >> 8) | (c2[1] << 4));
+        dst[2] = (uint8_t)(c2[1] >> 4);
+    }
+    if (e < W) {
+        *(uint4_t*)(rows + e * kD + off) = mv;
+        if (blockIdx.z == 0 && tid % kPieces == 0) idx[e] = (int32_t)(N - W + 1 + e);
     }
 }
 
@@ -125,10 +177,10 @@ hipError_t launch_append(const Geom& g, const half_t* k_new, const half_t* v_new
                          int32_t* idx_v, half_t* rows_v, int64_t k_v, int64_t N, int W, hipStream_t st)
 {
     if (g.B == 0) return hipSuccess;
-    dim3 grid((unsigned)(g.B * g.Hkv), 2), block(kApThreads);
 #define ANTKV_AP(DS, NCEN)                                                                                           \
-    hipLaunchKernelGGL((append_kernel<DS, NCEN>), grid, block, 0, st, k_new, v_new, cb_k, cb_v, codes_k, codes_v, N_cap, \
-                       idx_k, rows_k, k_k, idx_v, rows_v, k_v, N, W, g.Hkv)
+    hipLaunchKernelGGL((append_kernel<DS, NCEN>), dim3((unsigned)(g.B * g.Hkv), 2, kD / Ap<DS, NCEN>::channels),        \
+                       dim3(Ap<DS, NCEN>::threads), 0, st, k_new, v_new, cb_k, cb_v, codes_k, codes_v, N_cap, idx_k,    \
+                       rows_k, k_k, idx_v, rows_v, k_v, N, W, g.Hkv)
     if (g.C == 4096 && g.d == 32) ANTKV_AP(32, 4096);
     else if (g.C == 4096) ANTKV_AP(16, 4096);
     else if (g.d == 4) ANTKV_AP(4, 256);
