@@ -5,8 +5,8 @@ import pytest
 import torch
 
 import paper_2506_19505_amd as antkv
-from gpu_util import ATTN_TOL, NEAR_TIE, dev, rel_l2_rows
-from workloads import make_codebooks, make_decode_query, make_qkv
+from gpu_util import ATTN_TOL, NEAR_TIE, dev, rel_l2_rows, unpack12
+from workloads import make_codebooks, make_decode_query, make_qkv, normal_fp16
 
 pytestmark = pytest.mark.gpu
 
@@ -58,6 +58,36 @@ def test_append_then_decode(oracle, d, W, B, Hq, Hkv):
         err = rel_l2_rows(out.cpu().numpy(), want)
         assert err.max() <= ATTN_TOL, f"step {t}: decode relative L2 {err.max():.3e}"
     print(f"d={d} W={W}: {T} appends + decodes ok, last rel-L2 max {err.max():.2e}")
+
+
+@pytest.mark.parametrize("W", [0, 1, 64])
+@pytest.mark.parametrize("d,C", [(4, 256), (8, 256), (16, 256), (32, 4096), (16, 4096)])
+def test_append_ties_and_window_edges(oracle, d, C, W):
+    """Every centroid occurs twice, in the two halves of the codebook (other lanes, other waves): the lower index has to
+    win exactly.  The window's rows move as they are, whatever its length."""
+    B, Hq, Hkv, N = 1, 4, 2, 70
+    M = 128 // d
+    half = normal_fp16(41, "cb12_k", (Hkv, M, C // 2, d))
+    cb = np.concatenate([half, half], axis=2)
+    rows = normal_fp16(42, "win_rows_k", (B, Hkv, W, 128))
+    new = normal_fp16(43, "new_k", (B, Hkv, 128))
+    old = rows[:, :, 0] if W else new
+    want, margin = oracle.encode(old[:, :, None], half, want_margin=True)
+    geom = antkv.Geometry(B, Hq, Hkv, d, n_centroids=C)
+    ck = torch.zeros((B, Hkv, N + 1, geom.code_bytes), dtype=torch.uint8, device="cuda")
+    cv = torch.zeros_like(ck)
+    idx = dev(np.broadcast_to(np.arange(N - W, N), (B, Hkv, W)).astype(np.int32))
+    r, ik, iv = dev(rows), idx, idx.clone()
+    rv = r.clone()
+    antkv.append_token(geom, dev(new), dev(new), N, W, dev(cb), dev(cb), ck, cv, ik, r, iv, rv)
+    for c, i, rr in ((ck, ik, r), (cv, iv, rv)):
+        got = c[:, :, N - W].cpu().numpy()
+        got = (unpack12(got) if C == 4096 else got.astype(np.int32))[:, :, None]
+        assert not ((got != want) & (margin >= NEAR_TIE)).any()
+        assert int(c.ne(0).sum(dim=(0, 1, 3)).nonzero().ne(N - W).sum()) == 0     # no other position was written
+        if W:
+            assert (i.cpu().numpy() == np.arange(N - W + 1, N + 1)).all()
+            assert (rr.cpu().numpy() == np.concatenate([rows[:, :, 1:], new[:, :, None]], axis=2)).all()
 
 
 def test_append_rejects_bad_arguments():
