@@ -15,8 +15,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-# per-file additions: the encode kernel takes maxima of finite scores only
-EXTRA_FLAGS = {"encode.hip": ["-fno-honor-nans"]}
+# per-file additions: the encode kernels take maxima of finite scores only
+EXTRA_FLAGS = {"encode.hip": ["-fno-honor-nans"], "encode12.hip": ["-fno-honor-nans"]}
 
 
 def _hipcc() -> str:

@@ -70,6 +70,24 @@ def test_encode12_duplicate_centroids_and_offsets(oracle, books):
     assert not np.isin(got, np.arange(4000, 4096)).any() and not (got == 33).any()
 
 
+@pytest.mark.parametrize("B,n", [(1, 1), (1, 31), (2, 513), (2, 17003), (2, 33001), (3, 44007)])
+def test_encode12_work_splits(oracle, books, B, n):
+    """From one token (all waves of a workgroup on one group) to several groups per wave and rounds of workgroups; rows at
+    the ends and a sample between against the oracle, ties between far tiles, neighbours and half-waves included."""
+    cb = books[0].copy()
+    cb[:, :, 2048 + 7:2048 + 2047] = cb[:, :, 7:2047]           # most centroids twice
+    cb[:, :, 4] = cb[:, :, 0]                                   # rows 0 and 4 of a tile belong to different half-waves
+    x = np.random.default_rng(n).standard_normal((B, 2, n, 128)).astype(np.float16)
+    x[:, :, :2, :books.d] = cb[:, 0, 4][None, :, None]
+    geom = antkv.Geometry(B, 2, 2, books.d, n_centroids=C)
+    got = unpack12(antkv.encode(geom, dev(x), dev(cb)).cpu().numpy())
+    rows = np.unique(np.concatenate([np.arange(min(n, 70)), np.arange(max(0, n - 70), n),
+                                     np.random.default_rng(n + 1).integers(0, n, 300)]))
+    want, margin = oracle.encode(np.ascontiguousarray(x[:, :, rows]), cb, want_margin=True)
+    check_codes(got[:, :, rows], want, margin)
+    assert (got[:, :, :2, 0] != 4).all() and not np.isin(got, np.arange(2048 + 7, 2048 + 2047)).any()
+
+
 def _decode_case(oracle, books, seed, B, Hq, Hkv, N, k_k, k_v, N_cap=None, scale=None, range_tolerance=False):
     from workloads import make_decode_query, normal_fp16
     rng = np.random.default_rng(seed)
