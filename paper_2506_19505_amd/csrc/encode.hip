@@ -5,14 +5,22 @@
 // and three more carry -||c||^2/2 split into three fp16 terms (hi + mid + lo reproduce the fp32 value) against ones
 // on the token side; for 16-channel sub-vectors the three terms go through a second MFMA.  Centroids sit on the MFMA
 // row axis and tokens on the column axis: a lane then owns one token and sees 16 centroid scores per tile in its
-// accumulator registers, which makes the running arg-max a per-lane affair with compile-time centroid indices
-// (done on groups of 8 scores, see below).  Lanes l and l+32 hold complementary centroid subsets of the
-// same token and are combined once per sub-space.  Ties resolve to the lower centroid index (strict '>'
+// accumulator registers, which makes the running arg-max a per-lane affair: it narrows the winner down to a quad of
+// four neighbouring centroids, whose scores are then looked at once more.  Lanes l and l+32 hold complementary centroid
+// subsets of the same token and are combined once per sub-space.  Ties resolve to the lower centroid index (strict '>'
 // while indices ascend, explicit index compare across the lane pair).
 //
-// One workgroup keeps the whole codebook of one KV head in LDS in operand layout -- the centroids (64 KB fp16) and the
-// three norm terms per centroid -- and walks over 32-token blocks; token sub-vectors are loaded straight from global
-// memory in MFMA operand layout (L1 absorbs the row re-use across sub-spaces).
+// A workgroup (8 waves, two per CU) owns four neighbouring sub-spaces of one KV head -- their four code bytes are one
+// word -- keeps their centroids in LDS in operand layout together with the three norm terms per centroid, and walks over
+// 32-token blocks; token sub-vectors are loaded straight from global memory in MFMA operand layout, one block ahead.
+// Splitting by sub-spaces and not by tokens alone keeps the chip busy for short inputs: a wave's unit is 32 tokens x 4
+// sub-spaces.
+//
+// Bound: VALU issue.  Per tile of 32 x 32 a wave spends 8 instructions on the maximum, 4 on the bookkeeping and, spread
+// over the tiles of a sub-space, about 7 on settling the winner: some 20 at 4.35 clocks, beside which the matrix
+// instruction costs 8 more.  8 heads x 32768 tokens, one call, d_sub 4 / 8 / 16: 156 / 82 / 53 us with one workgroup per
+// head's whole codebook and a group's eight scores kept by selects, 104 / 57 / 39 us now; 2003 tokens: 77 / 39 / 23 us
+// then, 10 now.
 #include "common.h"
 
 namespace antkv {
@@ -24,33 +32,70 @@ namespace {
 __device__ __forceinline__ float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 __device__ __forceinline__ float max2f(float a, float b) { return fmaxf(a, b); }
 
-constexpr int kEncThreads = 1024;
+__device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b, float acc)
+{
+    acc = __builtin_amdgcn_fdot2(half2_t{a[0], a[1]}, half2_t{b[0], b[1]}, acc, false);
+    acc = __builtin_amdgcn_fdot2(half2_t{a[2], a[3]}, half2_t{b[2], b[3]}, acc, false);
+    acc = __builtin_amdgcn_fdot2(half2_t{a[4], a[5]}, half2_t{b[4], b[5]}, acc, false);
+    return __builtin_amdgcn_fdot2(half2_t{a[6], a[7]}, half2_t{b[6], b[7]}, acc, false);
+}
+
+typedef float pair_t __attribute__((ext_vector_type(2)));
+
+constexpr int kEncThreads = 512;
 constexpr int kEncWaves = kEncThreads / 64;
+constexpr int kQuad = 4;               // sub-spaces of a workgroup
 constexpr float kNormScale = 16.f;     // see the norm terms in the kernel: sub-vector norms up to ||c||^2 = 2.09e6 stay finite
 
 // LDS layout per sub-vector width (halfs per centroid): the A operand of a lane is 8 consecutive halfs
-//   d = 4   one array  [M][256][8]  = {c0..c3, n_hi, n_mid, n_lo, 0}: lanes 0-31 read it, lanes 32-63 multiply by zero
-//   d = 8   two arrays [M][256][8]: the centroid (lanes 0-31) and {n_hi, n_mid, n_lo, 0 x 5} (lanes 32-63)
-//   d = 16  the centroid [M][256][16] (lanes 0-31 the first 8 channels, lanes 32-63 the rest) and a second array
-//           [M][256][4] = {n_hi, n_mid, n_lo, 0} for the second MFMA
-constexpr size_t enc_lds_bytes(int d) { return d == 16 ? 65536 + 16384 : 131072; }
+//   d = 4   one array  [4][256][8]  = {c0..c3, n_hi, n_mid, n_lo, 0}: lanes 0-31 read it, lanes 32-63 multiply by zero
+//   d = 8   two arrays [4][256][8]: the centroid (lanes 0-31) and {n_hi, n_mid, n_lo, 0 x 5} (lanes 32-63)
+//   d = 16  the centroid [4][256][16] (lanes 0-31 the first 8 channels, lanes 32-63 the rest) and a second array
+//           [4][256][4] = {n_hi, n_mid, n_lo, 0} for the second MFMA
+// The four rows of a group (centroids 4 i .. 4 i + 3) are permuted by a xor with swizzle(i): the lanes of a gather that
+// reads row e of a different group each then meet all bank quads and not a quarter of them.
+constexpr int enc_row(int d) { return d == 16 ? 16 : 8; }                                // halfs of a row
+constexpr int enc_a_halfs(int d) { return kQuad * kC * (d == 4 ? 8 : 16); }
+constexpr int enc_n_halfs(int d) { return d == 16 ? kQuad * kC * 4 : 8; }
+template <int DSUB>
+__device__ __forceinline__ int swizzle(int group) { return (DSUB == 16 ? group >> 1 : group >> 2) & 3; }
+
+// lower half-wave's and upper half-wave's value of v, in every lane
+__device__ __forceinline__ void halves(uint32_t v, uint32_t& lo, uint32_t& hi)
+{
+    const uint2_t r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    lo = r[0];
+    hi = r[1];
+}
+// lanes 0-31: a summed over the two half-waves; lanes 32-63: b
+__device__ __forceinline__ float fold(float a, float b)
+{
+    const uint2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
 template <int DSUB>
-__global__ __launch_bounds__(kEncThreads) void encode_kernel(
+__global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
     const half_t* __restrict__ x, int64_t xs_b, int64_t xs_h, int64_t xs_t, int64_t n_tok,
     const half_t* __restrict__ cb, uint8_t* __restrict__ codes, int64_t N_cap, int64_t token_offset,
-    int B, int Hkv, int wg_per_head)
+    int B, int Hkv, int chunks)
 {
     constexpr int M = kD / DSUB;
-    extern __shared__ uint4_t smem[];
-    half_t* s_a = (half_t*)smem;                                   // first array (see above)
-    half_t* s_n = s_a + (DSUB == 16 ? 32768 : (DSUB == 8 ? 32768 : 0));   // norm terms (d = 4: inside s_a)
+    constexpr int NQ = M / kQuad;
+    constexpr int kRow = enc_row(DSUB);
+    constexpr int kPlane = kQuad * kC * 8;                                             // d = 8: the second array inside s_a
+    __shared__ __attribute__((aligned(256))) half_t s_a[enc_a_halfs(DSUB)];            // see above
+    __shared__ __attribute__((aligned(16))) half_t s_n[enc_n_halfs(DSUB)];             // d = 16 only: norm terms,
+    __shared__ float s_f[DSUB == 16 ? kQuad * kC : 1];                                 // and their fp32 value
     const int tid = threadIdx.x;
-    const int g = blockIdx.x / wg_per_head, wgi = blockIdx.x % wg_per_head;
+    // heads fastest: with 8 heads each XCD works on one, and the workgroups that read the same token rows share its L2
+    const int g = blockIdx.x % Hkv, quad = (blockIdx.x / Hkv) % NQ, chunk = blockIdx.x / (Hkv * NQ);
 
-    // ---- the codebook of this KV head into LDS, with -||c||^2/2 as three fp16 terms per centroid
-    const half_t* src = cb + (size_t)g * 32768;
-    for (int e = tid; e < M * kC; e += kEncThreads) {              // e = (sub-space, centroid)
+    // ---- the quad's centroids into LDS, with -||c||^2/2 as three fp16 terms per centroid
+    const half_t* src = cb + ((size_t)g * M + quad * kQuad) * kC * DSUB;
+#pragma unroll
+    for (int e = tid; e < kQuad * kC; e += kEncThreads) {          // e = (sub-space, centroid)
+        half_t* row = s_a + (e ^ swizzle<DSUB>(e >> 2)) * kRow;
         float cf[DSUB];
         if constexpr (DSUB == 4) {
             const half4_t v = *(const half4_t*)(src + e * 4);
@@ -62,8 +107,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(
                 const half8_t v = *(const half8_t*)(src + e * DSUB + 8 * u);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) cf[8 * u + t] = (float)v[t];
-                if constexpr (DSUB == 8) *(half8_t*)(s_a + e * 8) = v;
-                else *(half8_t*)(s_a + e * 16 + 8 * u) = v;
+                *(half8_t*)(row + 8 * u) = v;
             }
         }
         float nn = 0.f;
@@ -78,112 +122,154 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(
         const half_t n_lo = (half_t)(r1 - (float)n_mid);
         const half_t z = (half_t)0.f;
         if constexpr (DSUB == 4) {
-            *(half8_t*)(s_a + e * 8) = half8_t{(half_t)cf[0], (half_t)cf[1], (half_t)cf[2], (half_t)cf[3], n_hi, n_mid, n_lo, z};
+            *(half8_t*)row = half8_t{(half_t)cf[0], (half_t)cf[1], (half_t)cf[2], (half_t)cf[3], n_hi, n_mid, n_lo, z};
         } else if constexpr (DSUB == 8) {
-            *(half8_t*)(s_n + e * 8) = half8_t{n_hi, n_mid, n_lo, z, z, z, z, z};
+            *(half8_t*)(row + kPlane) = half8_t{n_hi, n_mid, n_lo, z, z, z, z, z};
         } else {
             *(half4_t*)(s_n + e * 4) = half4_t{n_hi, n_mid, n_lo, z};
+            s_f[e] = -0.5f * nn;
         }
     }
-    __syncthreads();
 
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
     const half_t one = (half_t)kNormScale, zero = (half_t)0.f;        // multiplies the three norm terms
     const half8_t ones3 = {one, one, one, zero, zero, zero, zero, zero};
     const half8_t zeros = {zero, zero, zero, zero, zero, zero, zero, zero};
+    const half8_t bn = (DSUB == 16 && h == 0) ? ones3 : zeros;        // d = 16: token side of the norm terms
     const int64_t blocks_per_b = (n_tok + 31) / 32;
     const int64_t total = (int64_t)B * blocks_per_b;
-    for (int64_t unit = (int64_t)wgi * kEncWaves + wave; unit < total; unit += (int64_t)wg_per_head * kEncWaves) {
+    // token operands of a block's four sub-spaces: the sub-vector in the k slots of the centroid, ones against the
+    // three norm terms
+    auto fetch = [&](int64_t unit, half8_t (&bx)[kQuad]) {
         const int64_t b = unit / blocks_per_b;
         const int64_t tok = (unit % blocks_per_b) * 32 + n;
-        const bool valid = tok < n_tok;
-        const half_t* xr = x + b * xs_b + (int64_t)g * xs_h + (valid ? tok : n_tok - 1) * xs_t;
-        uint8_t* dst = codes + (((int64_t)b * Hkv + g) * N_cap + token_offset + (valid ? tok : 0)) * M;
-
-#pragma unroll 1
-        for (int m4 = 0; m4 < M / 4; ++m4) {
-          uint32_t word = 0u;
+        const half_t* xr = x + b * xs_b + (int64_t)g * xs_h + (tok < n_tok ? tok : n_tok - 1) * xs_t + quad * kQuad * DSUB;
 #pragma unroll
-          for (int mm = 0; mm < 4; ++mm) {
-            const int m = 4 * m4 + mm;
-            // token operand: the sub-vector in the k slots of the centroid, ones against the three norm terms
-            half8_t bx = zeros, bn = zeros;
+        for (int mm = 0; mm < kQuad; ++mm) {
             if constexpr (DSUB == 4) {
+                bx[mm] = zeros;
                 if (h == 0) {
-                    const half4_t v = *(const half4_t*)(xr + m * 4);
-                    bx = half8_t{v[0], v[1], v[2], v[3], one, one, one, zero};
+                    const half4_t v = *(const half4_t*)(xr + mm * 4);
+                    bx[mm] = half8_t{v[0], v[1], v[2], v[3], one, one, one, zero};
                 }
             } else if constexpr (DSUB == 8) {
-                bx = ones3;
-                if (h == 0) bx = *(const half8_t*)(xr + m * 8);
+                bx[mm] = ones3;
+                if (h == 0) bx[mm] = *(const half8_t*)(xr + mm * 8);
             } else {
-                bx = *(const half8_t*)(xr + m * 16 + 8 * h);
-                if (h == 0) bn = ones3;
+                bx[mm] = *(const half8_t*)(xr + mm * 16 + 8 * h);
             }
-            // Running maximum over groups of 8 candidates (registers 8*hf .. 8*hf+7 of a tile).  The group maximum
-            // comes from a max3 tree; when a group raises the running maximum (strictly, so the lowest group wins
-            // ties) its id and its 8 scores are kept.  Which of the 8 it was is settled once per sub-space, from
-            // the kept scores, in ascending index order: 15 VALU ops per 8 candidates instead of 24.
-            float best = -3.0e38f;
-            int gid = 0;
-            float keep[8];
+        }
+    };
+    // this lane's A-operand rows: n of every tile (d = 4, 8: the swizzle alternates between even and odd tiles)
+    const int my_k = DSUB == 16 ? 8 * h : (DSUB == 8 ? kPlane * h : 0);
+    const half_t* ap[2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) keep[e] = -3.0e38f;
-            // this lane's A-operand row of tile 0; a tile is 32 rows further
-            const half_t* ap;
-            const half_t* an = s_n + (m * kC + n) * 4;                                  // d = 16 only
-            if constexpr (DSUB == 4) ap = s_a + (m * kC + n) * 8;
-            else if constexpr (DSUB == 8) ap = (h == 0 ? s_a : s_n) + (m * kC + n) * 8;
-            else ap = s_a + (m * kC + n) * 16 + 8 * h;
-            constexpr int kTileStride = 32 * (DSUB == 16 ? 16 : 8);
+    for (int i = 0; i < 2; ++i) ap[i] = s_a + ((32 * i + n) ^ swizzle<DSUB>((32 * i + n) >> 2)) * kRow + my_k;
+    const half_t* an = s_n + n * 4;                                   // d = 16 only
+
+    half8_t bx[kQuad];
+    int64_t unit = (int64_t)wave * chunks + chunk;
+    if (unit < total) fetch(unit, bx);
+    __syncthreads();
+    while (unit < total) {
+        const int64_t next = unit + (int64_t)chunks * kEncWaves;
+        half8_t nx[kQuad];
+        fetch(next < total ? next : unit, nx);
+        uint32_t word = 0u;
+        float16_t acc[2];
+        half8_t a[2];
+        half4_t a4[2];
+        auto operand = [&](int s) {                                    // step s: sub-space s / 8, tile s % 8
+            a[s & 1] = *(const half8_t*)(ap[s & 1] + (s >> 1) * 64 * kRow);
+            if constexpr (DSUB == 16) a4[s & 1] = *(const half4_t*)(an + s * 32 * 4);
+        };
+        auto scores = [&](int s) {
+            float16_t z;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z[r] = 0.f;
+            acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[s & 1], bx[s >> 3], z, 0, 0, 0);
+            if constexpr (DSUB == 16) {
+                const half4_t v = a4[s & 1];
+                const half8_t a2 = {v[0], v[1], v[2], v[3], zero, zero, zero, zero};
+                acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, bn, acc[s & 1], 0, 0, 0);
+            }
+        };
+        // Running maximum over tiles of 16 candidates per lane.  The tile maximum is a chain of max3 over four quads
+        // (rows 8 q + 4 h .. + 3); when a tile raises the running maximum (strictly, so the lowest tile wins ties) its id
+        // and the chain's value after each quad are kept, by moves under the lanes' mask.  The next tile's product is in
+        // flight meanwhile, with its operand read one tile earlier still.
+        pair_t keep[kQuad][2];                                         // after quads (0, 1), (2, 3) of the best tile
+        int tile[kQuad];
+        operand(0);
+        operand(1);
+        scores(0);
+#pragma unroll
+        for (int mm = 0; mm < kQuad; ++mm) {
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                const half8_t a = *(const half8_t*)(ap + t * kTileStride);
-                float16_t acc;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bx, acc, 0, 0, 0);
-                if constexpr (DSUB == 16) {
-                    const half4_t a4 = *(const half4_t*)(an + t * 32 * 4);
-                    const half8_t a2 = {a4[0], a4[1], a4[2], a4[3], zero, zero, zero, zero};
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, bn, acc, 0, 0, 0);
+                const int s = 8 * mm + t;
+                if (s + 1 < 8 * kQuad) scores(s + 1);
+                if (s + 2 < 8 * kQuad) operand(s + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                const float16_t& v = acc[s & 1];
+                pair_t lo, hi;
+                lo[0] = max3f(max2f(v[0], v[1]), v[2], v[3]);
+                lo[1] = max3f(max3f(lo[0], v[4], v[5]), v[6], v[7]);
+                hi[0] = max3f(max3f(lo[1], v[8], v[9]), v[10], v[11]);
+                hi[1] = max3f(max3f(hi[0], v[12], v[13]), v[14], v[15]);
+                if (t == 0) {
+                    keep[mm][0] = lo;
+                    keep[mm][1] = hi;
+                    tile[mm] = 0;
+                } else if (hi[1] > keep[mm][1][1]) {
+                    asm volatile("v_mov_b64 %0, %2\n\tv_mov_b64 %1, %3" : "+v"(keep[mm][0]), "+v"(keep[mm][1]) : "v"(lo), "v"(hi));
+                    tile[mm] = t;
                 }
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf) {
-                    const int r0 = 8 * hf;
-                    const float m0 = max3f(acc[r0 + 0], acc[r0 + 1], acc[r0 + 2]);
-                    const float m1 = max3f(acc[r0 + 3], acc[r0 + 4], acc[r0 + 5]);
-                    const float m2 = max3f(m0, m1, acc[r0 + 6]);
-                    const float m3 = max2f(m2, acc[r0 + 7]);
-                    const bool better = m3 > best;
-                    best = better ? m3 : best;
-                    gid = better ? (2 * t + hf) : gid;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) keep[e] = better ? acc[r0 + e] : keep[e];
-                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            // the winning group's centroids are 32 t + 16 hf + 8 j2 + 4 h + e (j2 < 2, e < 4), ascending in j = 4 j2 + e
-            int bidx;
-            {
-                const int c_base = 32 * (gid >> 1) + 16 * (gid & 1) + 4 * h;
-                float fbest = keep[0];
-                int jb = 0;
-#pragma unroll
-                for (int j = 1; j < 8; ++j) {
-                    const bool better = keep[j] > fbest;
-                    fbest = better ? keep[j] : fbest;
-                    jb = better ? j : jb;
-                }
-                bidx = c_base + 8 * (jb >> 2) + (jb & 3);
-            }
-            const float ob = __shfl_xor(best, 32, 64);
-            const int oi = __shfl_xor(bidx, 32, 64);
-            if (ob > best || (ob == best && oi < bidx)) bidx = oi;
-            word |= (uint32_t)bidx << (8 * mm);
-          }
-          if (valid && h == 0) *(uint32_t*)(dst + 4 * m4) = word;
         }
+        // The winner is in the first quad whose chain value is the maximum.  The token's two lanes agree on the better
+        // quad (equal scores: the lower one) and settle which of its four centroids it was with packed dot products
+        // (v_dot2_f32_f16), each lane over its own k slots; after the fold lanes 0-31 hold the sums of centroids 0 and 2,
+        // lanes 32-63 those of 1 and 3.
+#pragma unroll
+        for (int mm = 0; mm < kQuad; ++mm) {
+            const float best = keep[mm][1][1];
+            int q = 0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) q += keep[mm][i >> 1][i & 1] < best ? 1 : 0;
+            uint32_t b_lo, b_hi, g_lo, g_hi;
+            halves(__float_as_uint(best), b_lo, b_hi);
+            halves((uint32_t)(8 * tile[mm] + 2 * q + h), g_lo, g_hi);
+            const float f_lo = __uint_as_float(b_lo), f_hi = __uint_as_float(b_hi);
+            const bool up = f_hi > f_lo || (f_hi == f_lo && g_hi < g_lo);
+            const int grp = (int)(up ? g_hi : g_lo);                     // centroids 4 grp .. 4 grp + 3
+            const int at = (mm * kC + 4 * grp + swizzle<DSUB>(grp)) * kRow + my_k;
+            float sc[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sc[e] = dot8(*(const half8_t*)(s_a + (at ^ (e * kRow))), bx[mm], 0.f);
+            float s01 = fold(sc[0], sc[1]), s23 = fold(sc[2], sc[3]);
+            if constexpr (DSUB == 16) {
+                s01 += s_f[mm * kC + 4 * grp + h];
+                s23 += s_f[mm * kC + 4 * grp + 2 + h];
+            }
+            // (compared with the maximum, so that a centroid beyond the norm limit, whose d = 4 score is not a number, loses)
+            const float s_max = max2f(s01, s23);
+            uint32_t m_lo, m_hi, e_lo, e_hi;
+            halves(__float_as_uint(s_max), m_lo, m_hi);
+            halves(s01 == s_max ? (uint32_t)h : (uint32_t)(2 + h), e_lo, e_hi);
+            const float v_lo = __uint_as_float(m_lo), v_hi = __uint_as_float(m_hi);
+            const bool odd = v_lo != max2f(v_lo, v_hi) || (v_lo == v_hi && e_hi < e_lo);
+            word |= (uint32_t)(4 * grp + (int)(odd ? e_hi : e_lo)) << (8 * mm);
+        }
+        const int64_t b = unit / blocks_per_b, tok = (unit % blocks_per_b) * 32 + n;
+        if (tok < n_tok && h == 0)
+            *(uint32_t*)(codes + (((int64_t)b * Hkv + g) * N_cap + token_offset + tok) * M + kQuad * quad) = word;
+#pragma unroll
+        for (int mm = 0; mm < kQuad; ++mm) bx[mm] = nx[mm];
+        unit = next;
     }
 }
 
@@ -193,21 +279,15 @@ hipError_t launch_encode(const Geom& g, const half_t* x, int64_t xs_b, int64_t x
                          const half_t* cb, uint8_t* codes, int64_t N_cap, int64_t token_offset, hipStream_t st)
 {
     if (n_tok == 0 || g.B == 0) return hipSuccess;
+    // two workgroups per CU in total; a workgroup takes every chunks-th block, wave by wave, so that a last uneven round
+    // spreads over all of them
     const int64_t blocks = (int64_t)g.B * ((n_tok + 31) / 32);
-    int64_t wgph = (blocks + kEncWaves - 1) / kEncWaves;
-    const int64_t cap = (256 + g.Hkv - 1) / g.Hkv;   // about one workgroup per CU in total
-    if (wgph > cap) wgph = cap;
-    if (wgph < 1) wgph = 1;
-    const size_t shmem = enc_lds_bytes(g.d);
-    dim3 grid((unsigned)(g.Hkv * wgph)), block(kEncThreads);
-#define ANTKV_ENC(DS)                                                                                           \
-    do {                                                                                                        \
-        hipError_t e = hipFuncSetAttribute((const void*)encode_kernel<DS>,                                      \
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);             \
-        if (e != hipSuccess) return e;                                                                          \
-        hipLaunchKernelGGL(encode_kernel<DS>, grid, block, shmem, st, x, xs_b, xs_h, xs_t, n_tok, cb, codes,    \
-                           N_cap, token_offset, g.B, g.Hkv, (int)wgph);                                         \
-    } while (0)
+    const int groups = g.Hkv * (g.M / kQuad);
+    int64_t chunks = (512 + groups - 1) / groups;
+    if (chunks > blocks) chunks = blocks;
+#define ANTKV_ENC(DS)                                                                                              \
+    hipLaunchKernelGGL(encode_kernel<DS>, dim3((unsigned)(groups * chunks)), dim3(kEncThreads), 0, st, x, xs_b, xs_h, xs_t, \
+                       n_tok, cb, codes, N_cap, token_offset, g.B, g.Hkv, (int)chunks)
     if (g.d == 4) ANTKV_ENC(4);
     else if (g.d == 8) ANTKV_ENC(8);
     else ANTKV_ENC(16);

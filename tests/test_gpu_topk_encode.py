@@ -98,6 +98,26 @@ def test_encode_duplicate_centroids_and_offsets(oracle):
     assert (got[:, :, :20] == 255).all() and (got[:, :, 20 + n:] == 255).all()
 
 
+@pytest.mark.parametrize("d", [4, 8, 16])
+@pytest.mark.parametrize("B,n", [(1, 1), (1, 33), (3, 31), (1, 4097), (2, 9001)])
+def test_encode_work_splits_and_ties(oracle, d, B, n):
+    """From one block of 32 tokens to several blocks per wave; centroids repeated in the same quad of a tile, in the other
+    half-wave's rows, in other quads and in other tiles: the lower index has to win exactly."""
+    M = 128 // d
+    rng = np.random.default_rng(100 * d + n)
+    cb = rng.standard_normal((2, M, 256, d)).astype(np.float16)
+    for lo, hi in ((0, 1), (2, 6), (9, 17), (20, 28), (40, 44), (50, 250), (70, 102), (130, 255)):
+        cb[:, :, hi] = cb[:, :, lo]
+    x = rng.standard_normal((B, 2, n, 128)).astype(np.float16)
+    dup = [0, 2, 9, 20, 40, 50, 70, 130]
+    for t in range(min(n, 32)):                                  # tokens that sit on a repeated centroid
+        x[:, :, t] = cb[:, :, dup[t % 8]].reshape(1, 2, 128)
+    want, margin = oracle.encode(x, cb, want_margin=True)
+    got = antkv.encode(antkv.Geometry(B, 2, 2, d), dev(x), dev(cb)).cpu().numpy()
+    check_codes(got, want, margin)
+    assert not np.isin(got, [1, 6, 17, 28, 44, 250, 102, 255]).any()
+
+
 def test_encode_full_prefill_shape(oracle):
     """32768 new tokens x 8 KV heads, 1-bit VQ: the encode workload at its real size."""
     w = CONFIGS["cfg3"]
