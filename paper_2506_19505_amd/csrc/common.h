@@ -67,6 +67,14 @@ __device__ __forceinline__ void wait_all_loads()
     asm volatile("" ::: "memory");
 }
 
+// Workgroup barrier that orders LDS traffic only: global loads still in flight stay in flight (__syncthreads would wait
+// for every one of them, which turns each barrier into a full memory round trip).  Global stores that
+// other waves read after the barrier need a wait of their own before it.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // order-preserving map float -> uint32 (larger float <=> larger key), any finite sign
 __device__ __forceinline__ uint32_t float_key(float f)
 {

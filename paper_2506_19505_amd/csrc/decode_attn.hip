@@ -94,14 +94,6 @@ __device__ __forceinline__ uint32_t quad_bcast_sel(uint32_t x, int src)
     }
 }
 
-// Workgroup barrier that orders LDS traffic only: global loads still in flight stay in flight (__syncthreads would wait
-// for every one of them, which turns each barrier of the prologue into a full memory round trip).  Global stores that
-// other waves read after the barrier need a wait of their own before it.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // max over the 64 lanes, result uniform
 __device__ __forceinline__ float wave_max_uniform(float v)
 {

@@ -4,10 +4,17 @@
 // holds the update step: per (KV head, sub-space, centroid) the weighted sum of the assigned sub-vectors and the
 // assigned weight, then the weighted mean.
 //
-// Accumulation: a workgroup takes a chunk of tokens and a quarter of the sub-spaces, adds w*x and w into fp32
-// accumulators in LDS (ds_add_f32; laid out [sub-space][channel][centroid] so that the lanes of one instruction
-// spread over the banks by their codes), and flushes the non-zero accumulators to the global sums with hardware float atomics.  Sums are
-// therefore fp32 and their order is not fixed: results agree to fp32 rounding, not bit for bit, from run to run.
+// Accumulation (256 centroids): a workgroup takes one sub-space and walks a range of tokens in chunks of 2048 (d = 16:
+// 1024).  It sorts a chunk's sub-vectors by their code into LDS (counting sort: the rank comes from the histogram's
+// fetch-add), every thread adds up a run of consecutive sorted tokens in registers, and the runs of a code meet without
+// atomics: a code that ends inside a thread's run has exactly one such thread, and a thread ends with exactly one code, so
+// both kinds of partial sums have slots of their own.  Totals stay in registers over the chunks; at the end one addition
+// per centroid and channel goes to the global sums with hardware float atomics.  Sums are fp32 and their order is not
+// fixed: results agree to fp32 rounding, not bit for bit, from run to run.
+// The workgroups of one range's sub-spaces run on one XCD, since they read the same lines of x.  Bound: the latency of
+// the chain of six barriers per chunk (loads, ranks, sums and merge take about 6 us each).  Adding every product into LDS
+// with ds_add_f32, as before, runs at three clocks per lane: 8 heads x 32768 tokens (d8) 195 us, 38 now; sorting indices
+// and gathering the sub-vectors from memory in sorted order thrashes the L2: 55 us.
 // With 4096 centroids (12-bit codes) the sums of one KV head are 2 MB, far beyond LDS, and 4096 targets per sub-space
 // rarely collide, so every thread adds its eight channels straight into the global sums (km_accumulate12).
 #include "common.h"
@@ -17,82 +24,178 @@ namespace antkv {
 namespace {
 
 constexpr int kKmThreads = 256;
-constexpr int kKmChunk = 2048;     // tokens per workgroup
-constexpr int kKmGroups = 4;       // sub-space groups (grid.z)
+constexpr int kKmChunk = 2048;     // tokens per workgroup (4096 centroids)
+constexpr int kKsThreads = 512;    // 256 centroids
+constexpr int ks_per(int d) { return d == 16 ? 2 : 4; }                  // tokens of a chunk per thread
+constexpr int ks_chunk(int d) { return kKsThreads * ks_per(d); }
 
-__global__ __launch_bounds__(256) void km_zero(uint32_t* p, int64_t n)
+__global__ __launch_bounds__(256) void km_zero(uint32_t* a, int64_t n_a, uint32_t* b, int64_t n_b)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
+    if (i < n_a) a[i] = 0u;
+    else if (i < n_a + n_b) b[i - n_a] = 0u;
 }
 
-template <int DSUB>
-__global__ __launch_bounds__(kKmThreads) void km_accumulate(
-    const half_t* __restrict__ x, const float* __restrict__ w, const uint8_t* __restrict__ codes,
-    const half_t* __restrict__ cb, int64_t n_tok, int Hkv, float* __restrict__ sums, float* __restrict__ wsum,
-    double* __restrict__ objective)
+// LDS of km_accumulate: the sorted sub-vectors, weights and codes, later the last runs of the threads (row e at stride
+// kKsThreads + 1: neighbouring e fall on neighbouring banks); runs that ended inside a thread; the centroids
+constexpr size_t km_lds_sort(int d)
 {
-    constexpr int M = kD / DSUB, MG = M / kKmGroups;            // sub-spaces per workgroup: 8 / 4 / 2
-    __shared__ float s_sum[MG * kC * DSUB];                     // 32 KB
-    __shared__ float s_w[MG * kC];
-    const int tid = threadIdx.x;
-    const int64_t bg = blockIdx.y;
-    const int g = (int)(bg % Hkv);
-    const int m0 = blockIdx.z * MG;
-    for (int i = tid; i < MG * kC * DSUB; i += kKmThreads) s_sum[i] = 0.f;
-    for (int i = tid; i < MG * kC; i += kKmThreads) s_w[i] = 0.f;
-    __syncthreads();
-    const int64_t t0 = (int64_t)blockIdx.x * kKmChunk;
-    const int64_t t1 = (t0 + kKmChunk < n_tok) ? t0 + kKmChunk : n_tok;
-    const int mi = tid % MG;                                    // fixed per thread: the stride below is a multiple of MG
-    const int m = m0 + mi;
-    const half_t* cbm = cb + ((int64_t)g * M + m) * kC * DSUB;
+    const size_t sorted = (size_t)ks_chunk(d) * (2 * d + 8), last = (size_t)(d + 1) * (kKsThreads + 1) * 4;
+    return ((sorted > last ? sorted : last) + 15) / 16 * 16;
+}
+constexpr size_t km_lds(int d) { return km_lds_sort(d) + (size_t)kC * (d + 1) * 4 + (size_t)kC * d * 2 + (2 * kC + 4 + 16) * 4; }
+
+// grid: 8 * M * ceil(units / 8) workgroups, a unit being (KV head, range of `range` tokens); `range` is a multiple of the chunk
+template <int DSUB>
+__global__ __launch_bounds__(kKsThreads, 4) void km_accumulate(
+    const half_t* __restrict__ x, const float* __restrict__ w, const uint8_t* __restrict__ codes,
+    const half_t* __restrict__ cb, int64_t n_tok, int64_t total, int64_t range, int Hkv, int units, float* __restrict__ sums,
+    float* __restrict__ wsum, double* __restrict__ objective)
+{
+    constexpr int M = kD / DSUB, NV = DSUB + 1;                 // values of a run: DSUB sums and the weight
+    constexpr int kPer = ks_per(DSUB), kChunk = ks_chunk(DSUB), kStride = kKsThreads + 1;
+    constexpr int kItems = (kC * NV + kKsThreads - 1) / kKsThreads;     // (centroid, value) pairs of a thread
+    typedef half_t vec_t __attribute__((ext_vector_type(DSUB)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    vec_t* s_x = (vec_t*)lds;                                   // sorted sub-vectors,
+    float* s_w = (float*)(s_x + kChunk);                        // weights
+    uint32_t* s_c = (uint32_t*)(s_w + kChunk);                  // and codes
+    float* s_last = (float*)lds;                                // [NV][kStride], after the sorted tokens have been read
+    float* s_end = (float*)(lds + km_lds_sort(DSUB));           // [kC][NV]
+    vec_t* s_cb = (vec_t*)(s_end + kC * NV);
+    uint32_t* s_cnt = (uint32_t*)(s_cb + kC);                   // histogram
+    uint32_t* s_off = s_cnt + kC;                               // first sorted position of a code; [kC] = tokens
+    double* s_obj = (double*)(s_off + kC + 4);                  // one per wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int unit = (int)(blockIdx.x / (8 * M)) * 8 + (int)(blockIdx.x & 7), m = (int)(blockIdx.x >> 3) % M;
+    if (unit >= units) return;
+    const int g = unit % Hkv;
+    const int64_t j_lo = (int64_t)(unit / Hkv) * range;         // tokens are counted over all sequences
+    const int64_t j_hi = total - j_lo < range ? total : j_lo + range;
+
+    int code[kPer];
+    float wt[kPer];
+    vec_t xv[kPer];
+    int64_t seq = j_lo / n_tok, pos = j_lo - seq * n_tok + tid; // this thread's next token: sequence and position in it
+    auto fetch = [&](int64_t j0) {                              // tokens j0 + tid, + kKsThreads, ... of the range
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            code[i] = -1;
+            if (j0 + tid + i * kKsThreads < j_hi) {
+                while (pos >= n_tok) { pos -= n_tok; ++seq; }
+                const int64_t r = (seq * Hkv + g) * n_tok + pos;
+                code[i] = codes[r * M + m];
+                wt[i] = w[r];
+                xv[i] = *(const vec_t*)(x + r * kD + m * DSUB);
+            }
+            pos += kKsThreads;
+        }
+    };
+    fetch(j_lo);
+    for (int i = tid; i < kC; i += kKsThreads) s_cb[i] = *(const vec_t*)(cb + (((int64_t)g * M + m) * kC + i) * DSUB);
+    float sum[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) sum[k] = 0.f;
     double obj = 0.0;
-    for (int64_t t = t0 + tid / MG; t < t1; t += kKmThreads / MG) {
-        const int64_t row = bg * n_tok + t;
-        const float wt = w[row];
-        const int c = codes[row * M + m];
-        float xv[DSUB], cv[DSUB];
-        if constexpr (DSUB == 4) {
-            const half4_t a = *(const half4_t*)(x + row * kD + m * DSUB);
-            const half4_t b = *(const half4_t*)(cbm + c * DSUB);
+    for (int64_t j0 = j_lo; j0 < j_hi; j0 += kChunk) {
+        const int n = (int)(j_hi - j0 < kChunk ? j_hi - j0 : kChunk);
+        if (tid < kC) s_cnt[tid] = 0u;
+        lds_barrier();
+        uint32_t rank[kPer];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { xv[e] = (float)a[e]; cv[e] = (float)b[e]; }
-        } else {
+        for (int i = 0; i < kPer; ++i) rank[i] = code[i] >= 0 ? atomicAdd(&s_cnt[code[i]], 1u) : 0u;
+        lds_barrier();
+        if (tid < 64) {                                         // prefix sums, four codes per lane
+            uint32_t c[4], own = 0u;
 #pragma unroll
-            for (int u = 0; u < DSUB / 8; ++u) {
-                const half8_t a = *(const half8_t*)(x + row * kD + m * DSUB + 8 * u);
-                const half8_t b = *(const half8_t*)(cbm + c * DSUB + 8 * u);
+            for (int i = 0; i < 4; ++i) { c[i] = s_cnt[4 * tid + i]; own += c[i]; }
+            uint32_t pre = own;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) { xv[8 * u + e] = (float)a[e]; cv[8 * u + e] = (float)b[e]; }
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t o = __shfl_up(pre, off, 64);
+                if (tid >= off) pre += o;
+            }
+            pre -= own;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { s_off[4 * tid + i] = pre; pre += c[i]; }
+            if (tid == 63) s_off[kC] = pre;
+        }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (code[i] >= 0) {
+                const uint32_t p = s_off[code[i]] + rank[i];
+                s_x[p] = xv[i];
+                s_w[p] = wt[i];
+                s_c[p] = (uint32_t)code[i];
             }
         }
-        float dist = 0.f;
-        float* acc = &s_sum[mi * DSUB * kC + c];                // [mi][e][c]: for one e the lanes' banks follow their codes
+        lds_barrier();
+        if (j0 + kChunk < j_hi) fetch(j0 + kChunk);             // lands while this chunk is added up
+        const int p0 = kPer * tid, len = n - p0 < kPer ? n - p0 : kPer;   // this thread's sorted positions (len <= 0: none)
+        float acc[NV];
 #pragma unroll
-        for (int e = 0; e < DSUB; ++e) {
-            const float df = xv[e] - cv[e];
-            dist = fmaf(df, df, dist);
-            atomicAdd(acc + e * kC, wt * xv[e]);
+        for (int e = 0; e < NV; ++e) acc[e] = 0.f;
+        int cur = len > 0 ? (int)s_c[p0] : 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (i < len) {
+                const int c = (int)s_c[p0 + i];
+                if (c != cur) {                                 // the run of `cur` ends here and nowhere else
+#pragma unroll
+                    for (int e = 0; e < NV; ++e) { s_end[cur * NV + e] = acc[e]; acc[e] = 0.f; }
+                    cur = c;
+                }
+                const float wi = s_w[p0 + i];
+                const vec_t xi = s_x[p0 + i], cv = s_cb[c];
+                float dist = 0.f;
+#pragma unroll
+                for (int e = 0; e < DSUB; ++e) {
+                    const float xe = (float)xi[e], df = xe - (float)cv[e];
+                    dist = fmaf(df, df, dist);
+                    acc[e] = fmaf(wi, xe, acc[e]);
+                }
+                acc[DSUB] += wi;
+                obj += (double)wi * (double)dist;
+            }
         }
-        atomicAdd(&s_w[mi * kC + c], wt);
-        obj += (double)wt * (double)dist;
-    }
-    // objective: lanes with the same mi (lane % MG, since 64 % MG == 0) combine, then one atomic per wave and sub-space
+        lds_barrier();                                        // the sorted tokens' memory becomes the last runs'
+        if (len > 0) {
 #pragma unroll
-    for (int off = MG; off < 64; off <<= 1) obj += __shfl_xor(obj, off, 64);
-    if ((tid & 63) < MG && objective) unsafeAtomicAdd(objective + (int64_t)g * M + m, obj);
-    __syncthreads();
-    float* gs = sums + ((int64_t)g * M + m0) * kC * DSUB;
-    for (int i = tid; i < MG * kC * DSUB; i += kKmThreads) {   // i = (mi, c, e) in the global [m][c][e] order
-        const int e = i % DSUB, c = (i / DSUB) % kC, mi2 = i / (DSUB * kC);
-        const float v = s_sum[(mi2 * DSUB + e) * kC + c];
-        if (v != 0.f) unsafeAtomicAdd(gs + i, v);
+            for (int e = 0; e < NV; ++e) s_last[e * kStride + tid] = acc[e];
+        }
+        lds_barrier();
+        // a code's sum: the run that ended inside a thread, if any, and the last runs of the threads whose last position
+        // is one of the code's
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const int i = tid + k * kKsThreads;
+            if (i >= kC * NV) continue;
+            const int c = i < kC * DSUB ? i / DSUB : i - kC * DSUB, e = i < kC * DSUB ? i % DSUB : DSUB;
+            const int lo = (int)s_off[c], hi = (int)s_off[c + 1];
+            if (lo == hi) continue;
+            float v = hi % kPer != 0 && hi != n ? s_end[c * NV + e] : 0.f;
+            const int t_hi = hi == n ? (n + kPer - 1) / kPer : hi / kPer;
+            for (int t = lo / kPer; t < t_hi; ++t) v += s_last[e * kStride + t];
+            sum[k] += v;
+        }
+        // (the next chunk's first barrier keeps s_off and s_last until everybody is here)
     }
-    float* gw = wsum + ((int64_t)g * M + m0) * kC;
-    for (int i = tid; i < MG * kC; i += kKmThreads) {
-        const float v = s_w[i];
-        if (v != 0.f) unsafeAtomicAdd(gw + i, v);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) obj += __shfl_xor(obj, off, 64);
+    if (lane == 0) s_obj[wave] = obj;
+    __syncthreads();
+    if (tid == 0 && objective) {
+        double o = 0.0;
+        for (int i = 0; i < kKsThreads / 64; ++i) o += s_obj[i];
+        unsafeAtomicAdd(objective + (int64_t)g * M + m, o);
+    }
+    float* gs = sums + ((int64_t)g * M + m) * kC * DSUB;
+    float* gw = wsum + ((int64_t)g * M + m) * kC;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = tid + k * kKsThreads;
+        if (i < kC * NV && sum[k] != 0.f) unsafeAtomicAdd(i < kC * DSUB ? gs + i : gw + (i - kC * DSUB), sum[k]);
     }
 }
 
@@ -188,20 +291,24 @@ hipError_t launch_t(const Geom& g, const half_t* x, const float* w, int64_t n_to
     float* sums = (float*)(ws + p.off_sums);
     float* wsum = (float*)(ws + p.off_wsum);
     double* obj = objective ? objective : (double*)(ws + p.off_obj);
-    const int64_t n_zero = (int64_t)(p.total / 4);
-    hipLaunchKernelGGL(km_zero, dim3((unsigned)((n_zero + 255) / 256)), dim3(256), 0, st, (uint32_t*)ws, n_zero);
-    if (objective)
-        hipLaunchKernelGGL(km_zero, dim3((unsigned)((g.Hkv * g.M * 2 + 255) / 256)), dim3(256), 0, st, (uint32_t*)objective,
-                           (int64_t)g.Hkv * g.M * 2);
+    const int64_t n_zero = (int64_t)(p.total / 4), n_obj = objective ? (int64_t)g.Hkv * g.M * 2 : 0;
+    hipLaunchKernelGGL(km_zero, dim3((unsigned)((n_zero + n_obj + 255) / 256)), dim3(256), 0, st, (uint32_t*)ws, n_zero,
+                       (uint32_t*)objective, n_obj);
     if (n_tok > 0) {
         if constexpr (WIDE) {
             dim3 grid((unsigned)((n_tok + kKmChunk - 1) / kKmChunk), (unsigned)(g.B * g.Hkv));
             hipLaunchKernelGGL(km_accumulate12<DSUB>, grid, dim3(kKmThreads), 0, st, x, w, codes, cb_in, n_tok, g.Hkv, sums,
                                wsum, obj);
         } else {
-            dim3 grid((unsigned)((n_tok + kKmChunk - 1) / kKmChunk), (unsigned)(g.B * g.Hkv), kKmGroups);
-            hipLaunchKernelGGL(km_accumulate<DSUB>, grid, dim3(kKmThreads), 0, st, x, w, codes, cb_in, n_tok, g.Hkv, sums,
-                               wsum, obj);
+            static const hipError_t setup = hipFuncSetAttribute((const void*)km_accumulate<DSUB>,
+                                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)km_lds(DSUB));
+            if (setup != hipSuccess) return setup;
+            // about two workgroups per CU; a range is whole chunks, since every range adds 256 x (DSUB + 1) values to the sums
+            const int64_t total = (int64_t)g.B * n_tok, pairs = (int64_t)g.Hkv * g.M, chunk = ks_chunk(DSUB);
+            int64_t range = ((total * pairs + 511) / 512 + chunk - 1) / chunk * chunk;
+            const int64_t units = (total + range - 1) / range * g.Hkv;
+            hipLaunchKernelGGL(km_accumulate<DSUB>, dim3((unsigned)((units + 7) / 8 * 8 * g.M)), dim3(kKsThreads), km_lds(DSUB), st,
+                               x, w, codes, cb_in, n_tok, total, range, g.Hkv, (int)units, sums, wsum, obj);
         }
     }
     const int64_t n_cen = (int64_t)g.Hkv * g.M * g.C;

@@ -49,6 +49,18 @@ def test_kmeans_step_small(oracle, d, B, Hkv, n):
     _compare(oracle, x, _weights(5, (B, Hkv, n)), cb, d)
 
 
+@pytest.mark.parametrize("d", [4, 8, 16])
+@pytest.mark.parametrize("B,Hkv,n", [(3, 2, 1), (5, 1, 511), (2, 8, 9000)])
+def test_kmeans_step_ranges_and_skew(oracle, d, B, Hkv, n):
+    """One token, chunks that span sequences, several chunks per range with a ragged tail; more than half of the tokens
+    share their codes, so that one centroid's tokens fill most of every sorted chunk."""
+    _, x, _ = make_qkv(75, B, Hkv, Hkv, n, 1, 128, want_v=False)
+    cb = np.random.default_rng(d).standard_normal((Hkv, 128 // d, 256, d)).astype(np.float16)
+    x[:, :, ::2] = x[:1, :, :1]
+    x[:, :, 3::16] = x[:1, :, :1]
+    _compare(oracle, x, _weights(8, (B, Hkv, n)), cb, d)
+
+
 def test_kmeans_zero_weights_and_no_tokens_keep_the_codebook(oracle):
     _, x, _ = make_qkv(72, 1, 2, 2, 500, 1, 128, want_v=False)
     cb = make_codebooks(72, x, 8, 256, "k", max_sample=500)
