@@ -1,17 +1,19 @@
 // Causal attention over the prompt (paper Sec. 2.1) that also writes the softmax row statistics which the
 // Anchor Score pass consumes (Alg. 1, first step: attention extended to return row maximum and row sum).
 //
-// grid = (query blocks, B*Hkv); 8 waves = HG heads of the group x 8/HG query tiles of 32, HG = min(G, 4), so that
-// every wave has work whatever the group size (4 x 2, 2 x 4 or 1 x 8; larger groups loop over the heads).
-// The waves of a workgroup share each 32-key tile of K and V through double-buffered LDS.
+// A workgroup is 8 waves = G heads of a KV head's group x 8/G query tiles of 32 (4 x 2, 2 x 4 or 1 x 8).  Its waves share
+// the 32-key tiles of K and V, which go from global memory straight into LDS (16 bytes per lane, no registers), four
+// tiles of each in flight or in use.
 //   scores   S^T tile (keys on the MFMA row axis, queries on the column axis): lane (n, kh) owns query n and
-//            16 of the tile's 32 keys, so the running softmax is lane-local up to one exchange between the two
-//            half-waves, which must share the reference because their products meet in one accumulator.
+//            16 of the tile's 32 keys, so the running softmax is lane-local; the two half-waves of a query meet only
+//            when the reference moves and at the end.
 //   output   O^T += V^T P^T, again with queries on the column axis: the B operand is the lane's own 16
 //            probabilities (fp16), the A operand comes out of the V tile through ds_read_b64_tr_b16, and the
 //            accumulator rows of a lane all belong to its query, so a moved reference rescales registers only.
 // Probabilities are exp2 against a per-query reference that trails the running maximum: it moves only when a
 // tile brings a score more than kPMax (log2 units) above it, which keeps fp16 P below 2^kPMax.
+// One step of the loop works on three tiles at once: the softmax of tile t (VALU) is interleaved with the scores of tile
+// t + 1 and the value product of tile t - 1 (16 MFMAs), none of which waits for it.
 #include "common.h"
 
 #include <type_traits>
@@ -20,172 +22,222 @@ namespace antkv {
 
 namespace {
 
-constexpr int kPaThreads = 512;
-constexpr int kKRow = 136;      // halfs per staged K row: 16-byte reads of 16 consecutive rows hit 16 bank quads
-constexpr int kVRow = 160;      // halfs per staged V row (320 B): the 4 rows x 64 bytes that two 16-lane blocks read in one pass hit 64 banks
+constexpr int kPaWaves = 8;
+constexpr int kPaThreads = kPaWaves * 64;
+constexpr int kTileBytes = 32 * kD * 2;                 // a K or V tile: 32 rows of 256 bytes
+constexpr int kRing = 4;                                // tiles of K, and of V, in LDS
 constexpr float kPMax = 12.f;
+constexpr float kMasked = -INFINITY;                    // a score that takes no part
 
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
 typedef __attribute__((address_space(3))) short4_t lds_short4;
+typedef __attribute__((address_space(3))) half8_t lds_half8;
 
-__device__ __forceinline__ half4_t read_tr16(const half_t* p)
+__device__ __forceinline__ float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+
+// Rows of a tile are 256 bytes = 16 chunks of 16 bytes; chunk c of row r sits at place c ^ swz(r).  The 16-byte reads of
+// 16 rows (K) and the 4 rows x 64 bytes of a transposed read (V) then fall on 64 different banks.
+__device__ __forceinline__ int swz(int r) { return 4 * (r & 3) + ((r >> 2) & 3); }
+
+// 16 bytes per lane from `base` + `off` to LDS address `to` + 16 * lane
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t to)
 {
-    const short4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)p);
-    return __builtin_bit_cast(half4_t, v);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "m0", "memory");
 }
 
-__global__ __launch_bounds__(kPaThreads) void prefill_attn_kernel(
+__global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     const half_t* __restrict__ q, const half_t* __restrict__ k, const half_t* __restrict__ v, int64_t N, int64_t Nq,
-    float c1, half_t* __restrict__ out, float* __restrict__ row_max, float* __restrict__ row_sum, int Hq, int Hkv, int G)
+    float c1, half_t* __restrict__ out, float* __restrict__ row_max, float* __restrict__ row_sum, int Hq, int Hkv, int G,
+    int q_blocks)
 {
-    __shared__ __attribute__((aligned(16))) half_t s_k[2][32 * kKRow];
-    __shared__ __attribute__((aligned(16))) half_t s_v[2][32 * kVRow];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_kv[2 * kRing * kTileBytes];     // K ring, V ring
+    lds_byte* lds = (lds_byte*)s_kv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // scalar, so that per-wave conditions are scalar branches
     const int n = lane & 31, kh = lane >> 5;
-    const int64_t qblk = (int64_t)gridDim.x - 1 - blockIdx.x;      // longest rows first
-    const int b = blockIdx.y / Hkv, g = blockIdx.y % Hkv;
-    const int HG = G >= 4 ? 4 : G;                                 // head slots of the workgroup
-    const int qspan = 32 * (8 / HG);                               // query rows per workgroup
-    const int64_t q0 = qblk * qspan + (wave >> (HG >> 1)) * 32;
-    const bool wave_on = q0 < Nq;
+    const int bgs = gridDim.x / q_blocks;                          // B * Hkv
+    const int bg = blockIdx.x % bgs, b = bg / Hkv, g = bg % Hkv;   // (heads fastest: 8 heads, one per XCD)
+    const int64_t qblk = q_blocks - 1 - blockIdx.x / bgs;          // longest rows first
+    const int q_tiles = kPaWaves / G;                              // query tiles of the workgroup
+    const int64_t q0 = (qblk * q_tiles + wave / G) * 32;
+    const int h = g * G + wave % G;
     const int64_t qi = q0 + n;
     const int64_t qrow = qi < Nq ? qi : Nq - 1;
-    const int64_t qpos = N - Nq + qrow;                            // last key this lane's query sees
-    const int64_t tile_last_pos = N - Nq + ((q0 + 31 < Nq) ? q0 + 31 : Nq - 1);
-    const int64_t blk_last_pos = N - Nq + ((qblk * qspan + qspan - 1 < Nq) ? qblk * qspan + qspan - 1 : Nq - 1);
-    const int64_t k_end = blk_last_pos + 1;                        // keys the workgroup walks
-    const int64_t k_hi = tile_last_pos + 1;                        // keys this wave needs
-    const half_t* kbase = k + ((int64_t)b * Hkv + g) * N * kD;
-    const half_t* vbase = v + ((int64_t)b * Hkv + g) * N * kD;
-    const int srow = tid >> 4, schunk = tid & 15;                  // staging: 16 bytes per thread and tile
-    // transposed V reads: inside a 16-lane block, lane 4e + c reads key row e, channels 4c .. 4c+3; blocks 0/1
-    // cover the two channel halves of a 32-channel group, blocks 2/3 the same for the other key half (kh)
-    const int tr_off = (4 * kh + ((lane & 15) >> 2)) * kVRow + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    const int qpos = (int)(N - Nq + qrow);                         // last key this lane's query sees
+    const int first_pos = (int)(N - Nq + q0);                      // position of the tile's first query
+    auto tiles_to = [&](int64_t q_end) { return (int)((N - Nq + (q_end < Nq ? q_end : Nq) + 31) >> 5); };   // key tiles seen by rows < q_end
+    const int n_tiles = tiles_to((qblk + 1) * q_tiles * 32);       // of the workgroup
+    const int my_tiles = q0 < Nq ? tiles_to(q0 + 32) : 0;          // of the wave
+    const half_t* kbase = k + (int64_t)bg * N * kD;
+    const half_t* vbase = v + (int64_t)bg * N * kD;
 
-    for (int h_it = 0; h_it < (G + HG - 1) / HG; ++h_it) {
-        const int hh = HG * h_it + (wave & (HG - 1));
-        const bool head_on = wave_on && hh < G;
-        const int h = g * G + (hh < G ? hh : G - 1);
-        half8_t tq[8];
-        {
-            const half_t* qp = q + (((int64_t)b * Hq + h) * Nq + qrow) * kD;
+    // staging: wave w moves rows 4 w .. 4 w + 3 of a tile, a lane the chunk that belongs at its place of the 1 KB; rows
+    // past the end repeat the last one, tiles past the end the last tile
+    const int srow = 4 * wave + (lane >> 4), last_tile = (int)((N - 1) >> 5);
+    const int last_row = (int)(N - 1) & 31;
+    const uint32_t soff = srow * 256 + (((lane & 15) ^ swz(srow)) << 4);
+    const uint32_t soff_last = (srow < last_row ? srow : last_row) * 256 + (((lane & 15) ^ swz(srow)) << 4);
+    const uint32_t to0 = (uint32_t)(uintptr_t)lds + wave * 1024;
+    auto stage = [&](const half_t* base, int tile, uint32_t slot) {
+        const int tc = tile < last_tile ? tile : last_tile;
+        load_to_lds((const unsigned char*)base + (int64_t)tc * kTileBytes, tc == last_tile ? soff_last : soff, to0 + slot * kTileBytes);
+    };
+    // operand addresses inside a tile: K row n, channels 16 s + 8 kh .. + 7; V transposed: inside a 16-lane block, lane
+    // 4 e + c reads key row e of the lane's four, channels 4 c .. 4 c + 3 of 16; blocks 0/1 cover the two channel halves
+    // of a 32-channel group, blocks 2/3 the same for the other key half
+    uint32_t k_at[8], v_at[4][2];
 #pragma unroll
-            for (int s = 0; s < 8; ++s) tq[s] = *(const half8_t*)(qp + 16 * s + 8 * kh);
-#pragma unroll
-            for (int s = 0; s < 8; ++s) pin(tq[s]);
-            wait_all_loads();
-        }
-        float16_t o[4];
+    for (int s = 0; s < 8; ++s) { k_at[s] = n * 256 + (((2 * s + kh) ^ swz(n)) << 4); pin(k_at[s]); }
+    {
+        const int e = (lane & 15) >> 2, c = lane & 3, blk = (lane >> 4) & 1;
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o[cg][r] = 0.f;
-        float m_ref = kNegBig, m_true = kNegBig, l_run = 0.f;
-        int buf = 0;
-        auto fetch_k = [&](int64_t kt) -> uint4_t {
-            const int64_t row = (kt + srow < N) ? kt + srow : N - 1;
-            return *(const uint4_t*)(kbase + row * kD + 8 * schunk);
-        };
-        auto fetch_v = [&](int64_t kt) -> uint4_t {
-            const int64_t row = (kt + srow < N) ? kt + srow : N - 1;
-            return *(const uint4_t*)(vbase + row * kD + 8 * schunk);
-        };
-        *(uint4_t*)(&s_k[0][srow * kKRow + 8 * schunk]) = fetch_k(0);
-        *(uint4_t*)(&s_v[0][srow * kVRow + 8 * schunk]) = fetch_v(0);
-        __syncthreads();
-        for (int64_t kt = 0; kt < k_end; kt += 32) {
-            const bool more = kt + 32 < k_end;
-            uint4_t nk = {0u, 0u, 0u, 0u}, nv = {0u, 0u, 0u, 0u};
-            if (more) { nk = fetch_k(kt + 32); nv = fetch_v(kt + 32); }
-            if (head_on && kt < k_hi) {
-                float16_t acc;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const half8_t a = *(const half8_t*)(&s_k[buf][n * kKRow + 16 * s + 8 * kh]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, tq[s], acc, 0, 0, 0);   // rows = keys, cols = queries
-                }
-                const bool init = m_ref > kNegBig;
-                const float base = init ? m_ref : 0.f;
-                float p[16];
-                float mx = kNegBig;
-                const int lim = (int)(qpos - kt);                  // key offset <= lim is visible
-                auto scores = [&](auto masked) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        float x = fmaf(acc[r], c1, -base);
-                        if (decltype(masked)::value && 8 * (r >> 2) + 4 * kh + (r & 3) > lim) x = kNegBig;
-                        p[r] = x;
-                        mx = fmaxf(mx, x);
-                    }
-                };
-                // only tiles on the causal diagonal pay for the mask; the branch is uniform
-                if (__builtin_expect(kt + 31 <= N - Nq + q0, 1)) scores(std::false_type{});
-                else scores(std::true_type{});
-                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));            // the two key halves of a query agree on the reference
-                const bool seen = mx > 0.5f * kNegBig;
-                if (seen) m_true = fmaxf(m_true, base + mx);
-                if (seen && !(init && mx <= kPMax)) {              // move the reference to this tile's maximum
-                    const float alpha = init ? fast_exp2(-mx) : 0.f;
-                    l_run *= alpha;
-#pragma unroll
-                    for (int cg = 0; cg < 4; ++cg)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o[cg][r] *= alpha;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) p[r] -= mx;
-                    m_ref = base + mx;
-                }
-                float sum = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    p[r] = fast_exp2(p[r]);
-                    sum += p[r];
-                }
-                l_run += sum;
-                // O^T += V^T P^T: k-slot j of half kh in step s is key 16s + 8(j>>2) + 4kh + (j&3), on both operands
-#pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    half8_t pb;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) pb[j] = (half_t)p[8 * s + j];
-#pragma unroll
-                    for (int cg = 0; cg < 4; ++cg) {
-                        const half_t* vp = &s_v[buf][tr_off + 16 * s * kVRow + 32 * cg];
-                        const half4_t a0 = read_tr16(vp), a1 = read_tr16(vp + 8 * kVRow);
-                        const half8_t a = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-                        o[cg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pb, o[cg], 0, 0, 0);   // rows = channels
-                    }
-                }
+            for (int j = 0; j < 2; ++j) {
+                const int row = 8 * j + 4 * kh + e;
+                v_at[cg][j] = kRing * kTileBytes + row * 256 + (((4 * cg + 2 * blk + (c >> 1)) ^ swz(row)) << 4) + 8 * (c & 1);
+                pin(v_at[cg][j]);
             }
-            if (more) {
-                *(uint4_t*)(&s_k[buf ^ 1][srow * kKRow + 8 * schunk]) = nk;
-                *(uint4_t*)(&s_v[buf ^ 1][srow * kVRow + 8 * schunk]) = nv;
-            }
-            __syncthreads();
-            buf ^= 1;
+    }
+
+    for (int i = 0; i < 4; ++i) stage(kbase, i, i);
+    for (int i = 0; i < 2; ++i) stage(vbase, i, kRing + i);
+    // the V slot of "tile -1" is multiplied with zero probabilities: it has to be finite
+    *(uint4_t*)(s_kv + (2 * kRing - 1) * kTileBytes + tid * 16) = uint4_t{0u, 0u, 0u, 0u};
+    half8_t tq[8];
+    {
+        const half_t* qp = q + (((int64_t)b * Hq + h) * Nq + qrow) * kD + 8 * kh;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) tq[s] = *(const half8_t*)(qp + 16 * s);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) pin(tq[s]);
+    }
+    wait_all_loads();
+    __syncthreads();
+
+    float16_t o[4], sc[2];
+    half8_t p[2][2];
+#pragma unroll
+    for (int cg = 0; cg < 4; ++cg)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[cg][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[1][i][j] = (half_t)0.f;
+    float m_ref = kNegBig, s_max = kMasked, l_run = 0.f;            // reference (log2 units), largest raw score, sum
+    auto k_op = [&](int s, int slot) { return *(lds_half8*)(lds + k_at[s] + slot * kTileBytes); };
+    auto v_op = [&](int i, int slot) {                              // i = 4 * (16-key half) + channel group
+        const lds_byte* at = lds + slot * kTileBytes + (i >> 2) * 16 * 256;
+        const half4_t a = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(at + v_at[i & 3][0])));
+        const half4_t c = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(at + v_at[i & 3][1])));
+        return half8_t{a[0], a[1], a[2], a[3], c[0], c[1], c[2], c[3]};
+    };
+    {
+        float16_t z;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r] = 0.f;
+        sc[0] = z;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(k_op(s, 0), tq[s], sc[0], 0, 0, 0);
+    }
+
+    // what this step and the one before requested (two loads each) may still be in flight
+    auto landed = [] { asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory"); };
+    // step t, T = t mod 4
+    auto step = [&](int t, auto phase) {
+        constexpr int T = decltype(phase)::value;
+        constexpr int kNext = (T + 1) & 3, kPrev = (T + 3) & 3, cur = T & 1, nxt = cur ^ 1;
+        stage(kbase, t + 4, T);                                     // (tiles past the end repeat the last row)
+        stage(vbase, t + 2, kRing + ((T + 2) & 3));
+        float16_t& s = sc[cur];
+        if (__builtin_expect(t * 32 + 31 > first_pos, 0)) {         // the causal diagonal: key offset <= lim is visible
+            const int lim = qpos - t * 32;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + 4 * kh + (r & 3) > lim) s[r] = kMasked;
         }
-        const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-        if (head_on && qi < Nq) {
-            const int64_t row = ((int64_t)b * Hq + h) * Nq + qi;
-            const float inv = 1.f / l_tot;
-            half_t* op = out + row * kD + 4 * kh;
+        s_max = max3f(s_max, s[0], s[1]);
+#pragma unroll
+        for (int r = 2; r < 16; r += 2) s_max = max3f(s_max, s[r], s[r + 1]);
+        float alpha = 1.f;
+        const bool moves = __any(fmaf(s_max, c1, -m_ref) > kPMax);
+        if (__builtin_expect(moves, 0)) {                           // the reference moves to the largest score so far
+            const float m_new = fmaxf(s_max, __shfl_xor(s_max, 32, 64)) * c1;
+            if (m_new - m_ref > kPMax) {
+                alpha = fast_exp2(m_ref - m_new);
+                l_run *= alpha;
+                m_ref = m_new;
+            }
+        }
+        half8_t ka[8], va[8];
+        ka[0] = k_op(0, kNext); va[0] = v_op(0, kPrev);
+        ka[1] = k_op(1, kNext); va[1] = v_op(1, kPrev);
+        float sum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[nxt][r] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (i + 2 < 8) { ka[i + 2] = k_op(i + 2, kNext); va[i + 2] = v_op(i + 2, kPrev); }
+            sc[nxt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ka[i], tq[i], sc[nxt], 0, 0, 0);              // rows = keys, cols = queries
+            float p0 = fast_exp2(fmaf(s[2 * i], c1, -m_ref));
+            sum[0] += p0;
+            o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[i], p[nxt][i >> 2], o[i & 3], 0, 0, 0);   // rows = channels
+            float p1 = fast_exp2(fmaf(s[2 * i + 1], c1, -m_ref));
+            sum[1] += p1;
+            pin(sum[0]);                                            // (the products must not sink below the loop)
+            pin(sum[1]);
+            // k-slot j of half kh in 16-key half i is key 16 i + 8 (j >> 2) + 4 kh + (j & 3), on both operands
+            p[cur][i >> 2][(2 * i) & 7] = (half_t)p0;
+            p[cur][i >> 2][(2 * i + 1) & 7] = (half_t)p1;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        l_run += sum[0] + sum[1];
+        if (__builtin_expect(moves, 0)) {
 #pragma unroll
             for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
-                for (int qd = 0; qd < 4; ++qd) {                  // accumulator rows 8qd + 4kh + e = channels of group cg
-                    half4_t w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = (half_t)(o[cg][4 * qd + e] * inv);
-                    *(half4_t*)(op + 32 * cg + 8 * qd) = w;
-                }
-            if (kh == 0 && row_max) {
-                row_max[row] = m_true * (1.f / kLog2e);
-                row_sum[row] = l_tot * fast_exp2(m_ref - m_true);
-            }
+                for (int r = 0; r < 16; ++r) o[cg][r] *= alpha;
         }
-        __syncthreads();
+        landed();
+    };
+    // Up to three tiles past the wave's last are masked throughout, so that the loop has one end with the registers in the
+    // same roles.  Waves that are done keep staging for the others.
+    int t = 0;
+    for (; t < my_tiles; t += 4) {
+        step(t, std::integral_constant<int, 0>{});
+        step(t + 1, std::integral_constant<int, 1>{});
+        step(t + 2, std::integral_constant<int, 2>{});
+        step(t + 3, std::integral_constant<int, 3>{});
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)                                     // the last tile's value product
+        o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v_op(i, (t + 3) & 3), p[1][i >> 2], o[i & 3], 0, 0, 0);
+    for (; t < ((n_tiles + 3) & ~3); ++t) {                         // (every wave meets the same number of barriers)
+        stage(kbase, t + 4, t & 3);
+        stage(vbase, t + 2, kRing + ((t + 2) & 3));
+        landed();
+    }
+    wait_all_loads();                                               // nothing may land in LDS after the workgroup's end
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    s_max = fmaxf(s_max, __shfl_xor(s_max, 32, 64));
+    if (qi < Nq) {
+        const int64_t row = ((int64_t)b * Hq + h) * Nq + qi;
+        const float inv = 1.f / l_tot;
+        half_t* op = out + row * kD + 4 * kh;
+#pragma unroll
+        for (int cg = 0; cg < 4; ++cg)
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) {                        // accumulator rows 8 qd + 4 kh + e = channels of group cg
+                half4_t w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = (half_t)(o[cg][4 * qd + e] * inv);
+                *(half4_t*)(op + 32 * cg + 8 * qd) = w;
+            }
+        if (kh == 0 && row_max) {
+            row_max[row] = s_max * c1 * (1.f / kLog2e);
+            row_sum[row] = l_tot * fast_exp2(fmaf(-s_max, c1, m_ref));
+        }
     }
 }
 
@@ -194,10 +246,9 @@ __global__ __launch_bounds__(kPaThreads) void prefill_attn_kernel(
 hipError_t launch_prefill_attn(const Geom& g, const half_t* q, const half_t* k, const half_t* v, int64_t N, int64_t Nq,
                                float scale, half_t* out, float* row_max, float* row_sum, hipStream_t st)
 {
-    const int qspan = 32 * (8 / (g.G >= 4 ? 4 : g.G));
-    dim3 grid((unsigned)((Nq + qspan - 1) / qspan), (unsigned)(g.B * g.Hkv));
-    hipLaunchKernelGGL(prefill_attn_kernel, grid, dim3(kPaThreads), 0, st, q, k, v, N, Nq, scale * kLog2e, out, row_max,
-                       row_sum, g.Hq, g.Hkv, g.G);
+    const int64_t qspan = 32 * (kPaWaves / g.G), q_blocks = (Nq + qspan - 1) / qspan;
+    hipLaunchKernelGGL(prefill_attn_kernel, dim3((unsigned)(q_blocks * g.B * g.Hkv)), dim3(kPaThreads), 0, st, q, k, v, N, Nq,
+                       scale * kLog2e, out, row_max, row_sum, g.Hq, g.Hkv, g.G, (int)q_blocks);
     return hipGetLastError();
 }
 
