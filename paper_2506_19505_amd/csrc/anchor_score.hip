@@ -14,7 +14,7 @@
 //            the running column sums are fp64.
 // All contractions are v_mfma_f32_32x32x16_f16 on the raw fp16 Q and K (exact products, fp32 accumulate);
 // the softmax scale is applied to the fp32 result.
-#include "common.h"
+#include "lds_tile.h"
 
 #include <type_traits>
 
@@ -193,15 +193,25 @@ __global__ __launch_bounds__(kAsThreads) __attribute__((amdgpu_waves_per_eu(4, 4
     }
 }
 
-// merge key splits -> c_i = m + log2(l); also ||Q_i||_2.  One 16-lane group per (b, h, i).
+// merge key splits -> c_i = m + log2(l); also ||Q_i||_2.  One 16-lane group per (b, h, i).  Written as tiles of 32 rows,
+// {-c_i x 32, ||Q_i|| x 32}; rows past Nq and one tile behind the last hold {-inf, 0}, which makes their weights zero.
+constexpr int kStatTile = 64;
+
 __global__ __launch_bounds__(256) void ans_finalize_stats(
     const half_t* __restrict__ q, const float* __restrict__ part, int KS, const float* __restrict__ row_max,
-    const float* __restrict__ row_sum, float* __restrict__ c_out, float* __restrict__ nq_out, int64_t n_rows)
+    const float* __restrict__ row_sum, float* __restrict__ stat, int64_t Nq, int q_tiles, int64_t n_heads)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t row = t >> 4;
+    const int64_t slot = t >> 4;                                 // padded row
     const int part_i = (int)(t & 15);
-    if (row >= n_rows) return;
+    const int64_t head = slot / ((int64_t)q_tiles * 32), i = slot - head * q_tiles * 32;
+    if (head > n_heads || (head == n_heads && i >= 32)) return;
+    float* out = stat + (slot >> 5) * kStatTile + (slot & 31);
+    if (head == n_heads || i >= Nq) {
+        if (part_i == 0) { out[0] = -INFINITY; out[32] = 0.f; }
+        return;
+    }
+    const int64_t row = head * Nq + i;
     const half8_t v = *(const half8_t*)(q + row * kD + part_i * 8);
     float s = 0.f;
 #pragma unroll
@@ -210,15 +220,15 @@ __global__ __launch_bounds__(256) void ans_finalize_stats(
     for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
     if (row_max) {
         if (part_i == 0) {
-            nq_out[row] = sqrtf(s);
-            c_out[row] = row_max[row] * kLog2e + log2f(row_sum[row]);
+            out[0] = -(row_max[row] * kLog2e + log2f(row_sum[row]));
+            out[32] = sqrtf(s);
         }
         return;
     }
     // the 16 lanes of the group share the KS partial (reference, sum) pairs, then combine
     float m = kNegBig, l = 0.f;
-    for (int i = part_i; i < KS; i += 16) {
-        const float2 ml = *(const float2*)(part + (row * KS + i) * 2);
+    for (int j = part_i; j < KS; j += 16) {
+        const float2 ml = *(const float2*)(part + (row * KS + j) * 2);
         const float mn = fmaxf(m, ml.x);
         l = l * exp2f(m - mn) + ml.y * exp2f(ml.x - mn);
         m = mn;
@@ -230,138 +240,193 @@ __global__ __launch_bounds__(256) void ans_finalize_stats(
 #pragma unroll
     for (int off = 8; off >= 1; off >>= 1) l += __shfl_xor(l, off, 64);
     if (part_i == 0) {
-        nq_out[row] = sqrtf(s);
-        c_out[row] = mg + log2f(l);
+        out[0] = -(mg + log2f(l));
+        out[32] = sqrtf(s);
     }
 }
 
 // -------------------------------------------------------------------------------------------------
-// phase 2: column reduction.  grid = (key blocks of 256, B*Hkv); each of the 8 waves owns 32 keys.
-// Software-pipelined by one step: while the VALU rebuilds and reduces the probabilities of step t, the
-// matrix pipe already computes the scores of step t+1, so the staged Q tiles run one step ahead of
-// their row statistics (rings of three).
+// phase 2: column reduction.  A workgroup of NW waves walks the (head, query tile) steps that can see its keys; a wave owns
+// KT tiles of 32 keys, kept in registers, and reads the query tile and its row statistics from LDS, where they go straight
+// from global memory, three to four steps ahead.  While the VALU rebuilds and reduces the probabilities of step t the
+// matrix cores compute the scores of step t + 1.
+// Bound: VALU issue, per element one fma, one exp2 (8 clocks), one add and two fma (2.6 each).  32768 x 32768, 32 heads:
+// 8.8 ms with tiles staged through registers and 32 keys per wave, 5.4 ms now.
 // -------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kAsThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void ans_col_reduce(
+template <int KT, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     const half_t* __restrict__ q, const half_t* __restrict__ k, int64_t N, int64_t Nq, float c1,
-    const float* __restrict__ c_row, const float* __restrict__ nq_row, float* __restrict__ ans_k,
-    float* __restrict__ ans_v, int Hq, int Hkv, int G)
+    const float* __restrict__ stat, float* __restrict__ ans_k, float* __restrict__ ans_v, int Hq, int Hkv, int G,
+    int64_t n_bg, int q_tiles)
 {
-    __shared__ __attribute__((aligned(16))) half_t s_q[3][kTileHalfs];     // query tiles of steps t+1, t+2 (and t, spent)
-    __shared__ __attribute__((aligned(16))) float s_c[3][32], s_n[3][32];  // row statistics of steps t, t+1, t+2
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int kRing = 4, kParts = 8 / NW;                   // pieces of 1 KB of a query tile per wave
+    constexpr int kStatBytes = kStatTile * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char s_mem[kRing * (kTileBytes + kStatBytes)];
+    lds_byte* lds = (lds_byte*)s_mem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, kh = lane >> 5;
-    const int b = blockIdx.y / Hkv, g = blockIdx.y % Hkv;
-    const int64_t kblk0 = (int64_t)blockIdx.x * 256;
-    const int64_t k0 = kblk0 + wave * 32;                       // first key of this wave
-    const int64_t key = k0 + n;
-    const int64_t krow = key < N ? key : N - 1;
-    Tile128 tk;
-    load_tile(tk, k + (((int64_t)b * Hkv + g) * N + krow) * kD, kh);
-    wait_all_loads();
+    const int bg = (int)(blockIdx.x % n_bg), b = bg / Hkv, g = bg % Hkv;    // (heads fastest: 8 heads, one per XCD)
+    const int64_t kblk0 = (int64_t)(blockIdx.x / n_bg) * (32 * KT * NW);    // the first keys have the most queries: longest first
+    const int64_t k0 = kblk0 + wave * (32 * KT);                            // first key of this wave
+    half8_t tk[KT][8];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+        const int64_t key = k0 + 32 * kt + n;
+        const half_t* kp = k + ((int64_t)bg * N + (key < N ? key : N - 1)) * kD + 8 * kh;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) tk[kt][s] = *(const half8_t*)(kp + 16 * s);
+    }
     // first query tile that can see a key of this block:  N - Nq + i >= kblk0
     int64_t i_first = kblk0 - (N - Nq);
     if (i_first < 0) i_first = 0;
-    i_first &= ~(int64_t)31;
-    const int n_qt = (int)((Nq - i_first + 31) >> 5);           // query tiles per head
-    const int n_steps = n_qt * G;                                // step = (head of the group, query tile)
-    const int srow = tid >> 4, schunk = tid & 15;
-    // (head, tile) of a step are tracked incrementally: no division in the loop
-    auto fetch = [&](int hh, int qt, float& c_o, float& n_o) -> uint4_t {
-        const int64_t i0 = i_first + (int64_t)qt * 32;
-        const int64_t rbase = ((int64_t)b * Hq + g * G + hh) * Nq;
-        const int64_t qrow = (i0 + srow < Nq) ? i0 + srow : Nq - 1;
-        if (tid < 32) {
-            const bool ok = i0 + tid < Nq;
-            c_o = ok ? c_row[rbase + i0 + tid] : 3.0e38f;       // exp2(-huge) = 0 for rows past the end
-            n_o = ok ? nq_row[rbase + i0 + tid] : 0.f;
-        }
-        return *(const uint4_t*)(q + (rbase + qrow) * kD + 8 * schunk);
-    };
-    auto stage = [&](int slot, const uint4_t& d, float c_o, float n_o) {
-        *(uint4_t*)(&s_q[slot][srow * kRowPad + 8 * schunk]) = d;
-        if (tid < 32) { s_c[slot][tid] = c_o; s_n[slot][tid] = n_o; }
-    };
-    int qt_f = 0, hh_f = 0;                                      // next step to fetch
-    for (int i = 0; i < 2 && i < n_steps; ++i) {
-        float c_o = 0.f, n_o = 0.f;
-        const uint4_t d = fetch(hh_f, qt_f, c_o, n_o);
-        stage(i, d, c_o, n_o);
-        if (++qt_f == n_qt) { qt_f = 0; ++hh_f; }
+    const int qt_first = (int)(i_first >> 5);
+    const int n_qt = q_tiles - qt_first, n_steps = n_qt * G;     // query tiles per head; step = (head of the group, query tile)
+    const int64_t head0 = (int64_t)b * Hq + (int64_t)g * G;
+
+    uint32_t soff[kParts], soff_last[kParts];
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) {
+        soff[i] = stage_off(wave * kParts + i, lane, 31);
+        soff_last[i] = stage_off(wave * kParts + i, lane, (int)(Nq - 1) & 31);
     }
+    const uint32_t to_q = (uint32_t)(uintptr_t)lds, to_s = to_q + kRing * kTileBytes;
+    // the steps are staged in order: from tile to tile, from a head's last tile to the next head's first, and behind the
+    // last step the last tile again with the neutral statistics
+    const int64_t q_wrap = Nq * (kD * 2) - (int64_t)(n_qt - 1) * kTileBytes, s_wrap = (int64_t)(qt_first + 1) * kStatBytes;
+    const unsigned char* q_ptr = (const unsigned char*)(q + (head0 * Nq + (int64_t)qt_first * 32) * kD);
+    const unsigned char* s_ptr = (const unsigned char*)(stat + (head0 * q_tiles + qt_first) * kStatTile);
+    const unsigned char* s_none = (const unsigned char*)(stat + (n_bg / Hkv) * Hq * q_tiles * kStatTile);
+    int q_left = n_steps, s_left = n_steps, q_row = n_qt, s_row = n_qt;      // steps to stage, tiles left of the head
+    auto stage_q = [&](uint32_t slot) {
+        const bool last = q_row == 1;
+#pragma unroll
+        for (int i = 0; i < kParts; ++i)
+            load_to_lds16(q_ptr, last ? soff_last[i] : soff[i], to_q + slot * kTileBytes + (wave * kParts + i) * 1024);
+        if (--q_left > 0) {
+            q_ptr += last ? q_wrap : (int64_t)kTileBytes;
+            q_row = last ? n_qt : q_row - 1;
+        }
+    };
+    auto stage_s = [&](uint32_t slot) {                          // (every wave writes the same values)
+        load_to_lds4(s_left > 0 ? s_ptr : s_none, lane * 4, to_s + slot * kStatBytes);
+        --s_left;
+        const bool last = s_row == 1;
+        s_ptr += last ? s_wrap : (int64_t)kStatBytes;
+        s_row = last ? n_qt : s_row - 1;
+    };
+    uint32_t q_at[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) { q_at[s] = tile_at(n, s, kh); pin(q_at[s]); }
+    const uint32_t s_at = kRing * kTileBytes + 16 * kh;
+    auto q_op = [&](int s, int slot) { return *(lds_half8*)(lds + q_at[s] + slot * kTileBytes); };
+    auto stat_op = [&](int qd, int which, int slot) { return *(lds_float4*)(lds + s_at + slot * kStatBytes + which * 128 + qd * 32); };
+
+    for (int i = 0; i < 4; ++i) stage_q(i);
+    for (int i = 0; i < 3; ++i) stage_s(i);
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) pin(tk[kt][s]);
+    wait_all_loads();
     __syncthreads();
-    float16_t acc_cur;
-    if (n_steps > 0) acc_cur = tile_dot_lds_a(s_q[0], tk, n, kh);   // rows = queries, cols = keys
-    double sum_v = 0.0, sum_k = 0.0;
-    int slot = 0, qt = 0;                                        // ring slot and query tile of the current step
-    const int rel0 = (int)(N - Nq + i_first - k0);               // position of tile 0's first query minus this wave's first key
-    for (int step = 0; step < n_steps; ++step) {
-        const bool more = step + 2 < n_steps;
-        uint4_t nxt = {0u, 0u, 0u, 0u};
-        float c_o = 0.f, n_o = 0.f;
-        if (more) nxt = fetch(hh_f, qt_f, c_o, n_o);
-        const int s1 = slot == 2 ? 0 : slot + 1, s2 = s1 == 2 ? 0 : s1 + 1;
-        const int rel = rel0 + 32 * qt;                          // (position of the tile's first query) - k0
-        const int lim = n - rel;                                 // tile row r sees this lane's key iff r >= lim
-        float pv = 0.f, pk = 0.f;
-        float16_t acc_next;
+    float16_t sc[2][KT];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc_next[r] = 0.f;
-        // scores of step t+1 (slot s1; past the last step the slot holds stale data and the result is dropped)
-        // interleaved in program order with the reduction of step t, two elements per MFMA
-        auto body = [&](auto masked) {
-            float4_t c4 = {0.f, 0.f, 0.f, 0.f}, n4 = {0.f, 0.f, 0.f, 0.f};
-            const half_t* ap = &s_q[s1][n * kRowPad + 8 * kh];
-            half8_t a_op[8];
-            a_op[0] = *(const half8_t*)(ap);
-            a_op[1] = *(const half8_t*)(ap + 16);
+    for (int kt = 0; kt < KT; ++kt) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                if (s + 2 < 8) a_op[s + 2] = *(const half8_t*)(ap + 16 * (s + 2));   // operand reads run two MFMAs ahead
-                acc_next = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_op[s], tk.v[s], acc_next, 0, 0, 0);
-                const int qd = s >> 1;
-                const int rl = 8 * qd + 4 * kh;                  // tile rows rl .. rl+3 live in acc[4qd .. 4qd+3]
-                if ((s & 1) == 0) {
-                    c4 = *(const float4_t*)(&s_c[slot][rl]);
-                    n4 = *(const float4_t*)(&s_n[slot][rl]);
-                }
+        for (int r = 0; r < 16; ++r) sc[0][kt][r] = 0.f;
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const half8_t a = q_op(s, 0);
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) sc[0][kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, tk[kt][s], sc[0][kt], 0, 0, 0);   // rows = queries, cols = keys
+    }
+    __syncthreads();                                             // step 0 stages over the tile that has just been read
+    double sum_v[KT], sum_k[KT];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) sum_v[kt] = sum_k[kt] = 0.0;
+    int qt = 0;                                                  // query tile of the current step
+    const int rel0 = (int)(N - Nq + (int64_t)qt_first * 32 - k0);   // position of tile 0's first query minus this wave's first key
+
+    auto step = [&](auto phase) {                                // a step whose number is T mod 4
+        constexpr int T = decltype(phase)::value;
+        constexpr int kNext = (T + 1) & 3, cur = T & 1, nxt = cur ^ 1;
+        stage_q(T);                                              // step + 4
+        stage_s((T + 3) & 3);                                    // step + 3
+        const int rel = rel0 + 32 * qt;
+        if (__builtin_expect(rel < 32 * KT - 1, 0)) {            // some query of the tile does not see some key of the wave
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                const int lim = n + 32 * kt - rel;               // tile row r sees this lane's key iff r >= lim
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (8 * (r >> 2) + 4 * kh + (r & 3) < lim) sc[cur][kt][r] = -INFINITY;
+            }
+        }
+        if (++qt == n_qt) qt = 0;
+        half8_t a[8];
+        float4_t c4[4], n4[4];
+        a[0] = q_op(0, kNext);
+        c4[0] = stat_op(0, 0, T);
+        n4[0] = stat_op(0, 1, T);
+        a[1] = q_op(1, kNext);
+        float pv[KT], pk[KT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {
+            pv[kt] = pk[kt] = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sc[nxt][kt][r] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {                            // tile rows 8 qd + 4 kh + e live in register 4 qd + e
+            if (i + 2 < 8) a[i + 2] = q_op(i + 2, kNext);
+            if ((i & 1) == 1 && i < 7) { c4[(i >> 1) + 1] = stat_op((i >> 1) + 1, 0, T); n4[(i >> 1) + 1] = stat_op((i >> 1) + 1, 1, T); }
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                sc[nxt][kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], tk[kt][i], sc[nxt][kt], 0, 0, 0);
 #pragma unroll
                 for (int e2 = 0; e2 < 2; ++e2) {
-                    const int e = 2 * (s & 1) + e2;
-                    float arg = fmaf(acc_cur[4 * qd + e], c1, -c4[e]);
-                    if (decltype(masked)::value && rl + e < lim) arg = -3.0e38f;   // causal mask
-                    const float a_ij = fast_exp2(arg);
-                    pv += a_ij;
-                    pk = fmaf(a_ij, fmaf(-a_ij, n4[e], n4[e]), pk);               // a (1 - a) ||q||
+                    const int r = 2 * i + e2;
+                    const float c = c4[r >> 2][r & 3], nn = n4[r >> 2][r & 3];
+                    const float w = fast_exp2(fmaf(sc[cur][kt][r], c1, c));
+                    pv[kt] += w;
+                    pk[kt] = fmaf(w, fmaf(-w, nn, nn), pk[kt]);  // a (1 - a) ||q||
                 }
+                pin(pv[kt]);                                     // (keeps the work where it is written)
+                pin(pk[kt]);
             }
-        };
-        // only tiles on or above the diagonal (some query cannot see some key) pay for the mask; the branch is uniform
-        if (__builtin_expect(rel < 31, 0)) body(std::true_type{});
-        else body(std::false_type{});
-        sum_v += (double)pv;
-        sum_k += (double)pk;
-        if (more) {
-            stage(s2, nxt, c_o, n_o);
-            if (++qt_f == n_qt) { qt_f = 0; ++hh_f; }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();
-        acc_cur = acc_next;
-        slot = s1;
-        if (++qt == n_qt) qt = 0;
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {                        // fp32 per tile, fp64 over tiles
+            sum_v[kt] += (double)pv[kt];
+            sum_k[kt] += (double)pk[kt];
+        }
+        landed_but<2 * (kParts + 1)>();                          // this step's loads and the last one's
+    };
+    for (int t = 0; t < n_steps; t += 4) {                       // (steps past the last have weights of zero)
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+        step(std::integral_constant<int, 2>{});
+        step(std::integral_constant<int, 3>{});
     }
-    // lanes l and l+32 hold complementary query rows of the same key
-    const double ov = __shfl_xor(sum_v, 32, 64), ok = __shfl_xor(sum_k, 32, 64);
-    if (kh == 0 && key < N) {
-        const int64_t o = ((int64_t)b * Hkv + g) * N + key;
-        ans_v[o] = (float)(sum_v + ov);
-        ans_k[o] = (float)(sum_k + ok);
+    wait_all_loads();                                            // nothing may land in LDS after the workgroup's end
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {                            // lanes l and l+32 hold complementary query rows of the same key
+        const double ov = __shfl_xor(sum_v[kt], 32, 64), ok = __shfl_xor(sum_k[kt], 32, 64);
+        const int64_t key = k0 + 32 * kt + n;
+        if (kh == 0 && key < N) {
+            ans_v[(int64_t)bg * N + key] = (float)(sum_v[kt] + ov);
+            ans_k[(int64_t)bg * N + key] = (float)(sum_k[kt] + ok);
+        }
     }
 }
 
 struct AsPlan {
     int KS;
     int64_t keys_per_split;
-    size_t off_part, off_c, off_nq, off_ans_k, off_ans_v, total;
+    size_t off_part, off_stat, off_ans_k, off_ans_v, total;
 };
 
 AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
@@ -381,8 +446,7 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
     const size_t rows = (size_t)g.B * g.Hq * Nq;
     size_t off = 0;
     p.off_part = off; off += align_up(rows * p.KS * 2 * sizeof(float));
-    p.off_c = off;    off += align_up(rows * sizeof(float) + 16);
-    p.off_nq = off;   off += align_up(rows * sizeof(float) + 16);
+    p.off_stat = off; off += align_up(((size_t)g.B * g.Hq * ((Nq + 31) / 32) + 1) * kStatTile * sizeof(float));
     p.off_ans_k = off; off += align_up((size_t)g.B * g.Hkv * N * sizeof(float));
     p.off_ans_v = off; off += align_up((size_t)g.B * g.Hkv * N * sizeof(float));
     p.total = off;
@@ -401,23 +465,29 @@ hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, 
     const AsPlan p = plan(g, N, Nq);
     char* w = (char*)ws;
     float* part = (float*)(w + p.off_part);
-    float* c_row = (float*)(w + p.off_c);
-    float* nq_row = (float*)(w + p.off_nq);
+    float* stat = (float*)(w + p.off_stat);
     if (!ans_k) ans_k = (float*)(w + p.off_ans_k);
     if (!ans_v) ans_v = (float*)(w + p.off_ans_v);
     const float c1 = scale * kLog2e;
-    const int64_t rows = (int64_t)g.B * g.Hq * Nq;
     if (!row_max) {
         const int qspan = 32 * (8 / (g.G >= 4 ? 4 : g.G));
         dim3 grid((unsigned)p.KS, (unsigned)((Nq + qspan - 1) / qspan), (unsigned)(g.B * g.Hkv));
         hipLaunchKernelGGL(ans_row_stats, grid, dim3(kAsThreads), 0, st, q, k, N, Nq, c1, part, g.Hq, g.Hkv, g.G,
                            p.KS, p.keys_per_split);
     }
-    hipLaunchKernelGGL(ans_finalize_stats, dim3((unsigned)((rows * 16 + 255) / 256)), dim3(256), 0, st, q, part, p.KS,
-                       row_max, row_sum, c_row, nq_row, rows);
-    dim3 grid2((unsigned)((N + 255) / 256), (unsigned)(g.B * g.Hkv));
-    hipLaunchKernelGGL(ans_col_reduce, grid2, dim3(kAsThreads), 0, st, q, k, N, Nq, c1, c_row, nq_row, ans_k, ans_v,
-                       g.Hq, g.Hkv, g.G);
+    const int64_t q_tiles = (Nq + 31) / 32, n_heads = (int64_t)g.B * g.Hq, n_bg = (int64_t)g.B * g.Hkv;
+    const int64_t padded = (n_heads * q_tiles + 1) * 32;
+    hipLaunchKernelGGL(ans_finalize_stats, dim3((unsigned)((padded * 16 + 255) / 256)), dim3(256), 0, st, q, part, p.KS,
+                       row_max, row_sum, stat, Nq, (int)q_tiles, n_heads);
+    // 64 keys per wave (the query tiles and statistics are read once for two key tiles) while that fills the chip and the
+    // walk over the queries is long beside loading the keys (131072 keys, 32 queries: 92 us against 80); smaller workgroups
+    // otherwise
+#define ANTKV_CR(KT, NW)                                                                                                  \
+    hipLaunchKernelGGL((ans_col_reduce<KT, NW>), dim3((unsigned)((N + 32 * KT * NW - 1) / (32 * KT * NW) * n_bg)), dim3(NW * 64), \
+                       0, st, q, k, N, Nq, c1, stat, ans_k, ans_v, g.Hq, g.Hkv, g.G, n_bg, (int)q_tiles)
+    if (Nq > 256 && (N + 511) / 512 * n_bg >= 512) ANTKV_CR(2, 8);
+    else ANTKV_CR(1, 4);
+#undef ANTKV_CR
     return hipGetLastError();
 }
 

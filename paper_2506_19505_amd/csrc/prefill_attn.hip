@@ -14,7 +14,10 @@
 // tile brings a score more than kPMax (log2 units) above it, which keeps fp16 P below 2^kPMax.
 // One step of the loop works on three tiles at once: the softmax of tile t (VALU) is interleaved with the scores of tile
 // t + 1 and the value product of tile t - 1 (16 MFMAs), none of which waits for it.
-#include "common.h"
+// Bound: the matrix cores under the power limit.  32768 tokens, 32 heads (8.8 TFLOP): with tiles staged through registers
+// and softmax and products in turn 10.9 ms (matrix cores 38 % busy at 1.97 GHz), now 8.2 ms = 1.07 PFLOP/s (63 % at
+// 1.61 GHz).  2 x 1531 tokens, 32 KV heads: 101 -> 55 us.
+#include "lds_tile.h"
 
 #include <type_traits>
 
@@ -24,26 +27,11 @@ namespace {
 
 constexpr int kPaWaves = 8;
 constexpr int kPaThreads = kPaWaves * 64;
-constexpr int kTileBytes = 32 * kD * 2;                 // a K or V tile: 32 rows of 256 bytes
 constexpr int kRing = 4;                                // tiles of K, and of V, in LDS
 constexpr float kPMax = 12.f;
 constexpr float kMasked = -INFINITY;                    // a score that takes no part
 
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-typedef __attribute__((address_space(3))) short4_t lds_short4;
-typedef __attribute__((address_space(3))) half8_t lds_half8;
-
 __device__ __forceinline__ float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
-
-// Rows of a tile are 256 bytes = 16 chunks of 16 bytes; chunk c of row r sits at place c ^ swz(r).  The 16-byte reads of
-// 16 rows (K) and the 4 rows x 64 bytes of a transposed read (V) then fall on 64 different banks.
-__device__ __forceinline__ int swz(int r) { return 4 * (r & 3) + ((r >> 2) & 3); }
-
-// 16 bytes per lane from `base` + `off` to LDS address `to` + 16 * lane
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t to)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "m0", "memory");
-}
 
 __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     const half_t* __restrict__ q, const half_t* __restrict__ k, const half_t* __restrict__ v, int64_t N, int64_t Nq,
@@ -73,21 +61,19 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
 
     // staging: wave w moves rows 4 w .. 4 w + 3 of a tile, a lane the chunk that belongs at its place of the 1 KB; rows
     // past the end repeat the last one, tiles past the end the last tile
-    const int srow = 4 * wave + (lane >> 4), last_tile = (int)((N - 1) >> 5);
-    const int last_row = (int)(N - 1) & 31;
-    const uint32_t soff = srow * 256 + (((lane & 15) ^ swz(srow)) << 4);
-    const uint32_t soff_last = (srow < last_row ? srow : last_row) * 256 + (((lane & 15) ^ swz(srow)) << 4);
+    const int last_tile = (int)((N - 1) >> 5);
+    const uint32_t soff = stage_off(wave, lane, 31), soff_last = stage_off(wave, lane, (int)(N - 1) & 31);
     const uint32_t to0 = (uint32_t)(uintptr_t)lds + wave * 1024;
     auto stage = [&](const half_t* base, int tile, uint32_t slot) {
         const int tc = tile < last_tile ? tile : last_tile;
-        load_to_lds((const unsigned char*)base + (int64_t)tc * kTileBytes, tc == last_tile ? soff_last : soff, to0 + slot * kTileBytes);
+        load_to_lds16((const unsigned char*)base + (int64_t)tc * kTileBytes, tc == last_tile ? soff_last : soff, to0 + slot * kTileBytes);
     };
     // operand addresses inside a tile: K row n, channels 16 s + 8 kh .. + 7; V transposed: inside a 16-lane block, lane
     // 4 e + c reads key row e of the lane's four, channels 4 c .. 4 c + 3 of 16; blocks 0/1 cover the two channel halves
     // of a 32-channel group, blocks 2/3 the same for the other key half
     uint32_t k_at[8], v_at[4][2];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) { k_at[s] = n * 256 + (((2 * s + kh) ^ swz(n)) << 4); pin(k_at[s]); }
+    for (int s = 0; s < 8; ++s) { k_at[s] = tile_at(n, s, kh); pin(k_at[s]); }
     {
         const int e = (lane & 15) >> 2, c = lane & 3, blk = (lane >> 4) & 1;
 #pragma unroll
@@ -141,9 +127,8 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
 #pragma unroll
         for (int s = 0; s < 8; ++s) sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(k_op(s, 0), tq[s], sc[0], 0, 0, 0);
     }
+    __syncthreads();                                                // step 0 stages over the tile that has just been read
 
-    // what this step and the one before requested (two loads each) may still be in flight
-    auto landed = [] { asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory"); };
     // step t, T = t mod 4
     auto step = [&](int t, auto phase) {
         constexpr int T = decltype(phase)::value;
@@ -199,7 +184,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[cg][r] *= alpha;
         }
-        landed();
+        landed_but<4>();                                            // this step's two loads and the last one's
     };
     // Up to three tiles past the wave's last are masked throughout, so that the loop has one end with the registers in the
     // same roles.  Waves that are done keep staging for the others.
@@ -216,7 +201,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     for (; t < ((n_tiles + 3) & ~3); ++t) {                         // (every wave meets the same number of barriers)
         stage(kbase, t + 4, t & 3);
         stage(vbase, t + 2, kRing + ((t + 2) & 3));
-        landed();
+        landed_but<4>();
     }
     wait_all_loads();                                               // nothing may land in LDS after the workgroup's end
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);

@@ -37,6 +37,13 @@ def test_anchor_select_small(oracle, B, Hq, Hkv, N, Nq):
     _run(oracle, 21, B, Hq, Hkv, N, Nq, anchor_count(N))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(4, 16, 16, 4200, 300), (8, 16, 8, 4096, 257), (16, 16, 4, 4353, 289)])
+def test_anchor_select_wide_key_blocks(oracle, B, Hq, Hkv, N, Nq):
+    """Enough (head, key block) pairs for the column reduction with 64 keys per wave; ragged keys, ragged queries and a
+    diagonal that starts inside a key block, for one, two and four heads per KV head."""
+    _run(oracle, 27, B, Hq, Hkv, N, Nq, 40)
+
+
 def test_anchor_select_k_edges(oracle):
     _run(oracle, 22, 1, 4, 1, 200, 200, 0)
     _run(oracle, 22, 1, 4, 1, 200, 200, 200)

@@ -39,6 +39,14 @@ def test_prefill_attn_small(oracle, B, Hq, Hkv, N, Nq):
     _check(oracle, 61, B, Hq, Hkv, N, Nq, 1.0 / np.sqrt(128))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(1, 4, 4, 33, 33), (1, 4, 1, 127, 127), (2, 4, 2, 129, 65), (1, 8, 8, 600, 600),
+                                           (3, 8, 2, 161, 161), (1, 2, 1, 391, 390), (1, 4, 1, 1025, 700)])
+def test_prefill_attn_tile_edges(oracle, B, Hq, Hkv, N, Nq):
+    """Every number of key tiles modulo the loop's four, waves of one workgroup that end at different tiles, windows that
+    start inside a tile."""
+    _check(oracle, 64, B, Hq, Hkv, N, Nq, 1.0 / np.sqrt(128))
+
+
 def test_prefill_attn_wide_score_range(oracle):
     """Scores spread over a few hundred log2 units: the softmax reference has to move many times per row."""
     _check(oracle, 62, 1, 4, 2, 700, 700, 1.0 / np.sqrt(128), q_gain=12.0)
