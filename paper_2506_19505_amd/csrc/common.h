@@ -106,6 +106,7 @@ hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b
 // workspace's counters and returns the first-level histograms, uint32 [2 n_rows][2 * kTopkBins] (row r < n_rows belongs
 // to scores row r, row n_rows + r to scores_b row r; the first kTopkBins words of a row count float_key(score) >> 21);
 // the producer adds every score it writes to them; `finish` selects from there without reading the scores for a histogram.
+// Rows that one workgroup selects by itself need no histograms: `begin` then returns NULL.
 constexpr int kTopkBins = 2048;
 uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st);
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,

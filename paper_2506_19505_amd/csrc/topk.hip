@@ -14,6 +14,10 @@
 //      == tau; a row whose keys agree in 22 bits for more than the list holds is walked by that workgroup instead;
 //   5. an ordered emission pass writes the positions of all keys > tau plus the lowest-positioned keys == tau
 //      needed to reach k, in ascending position order.
+// Rows of up to 32768 scores fit the registers of one workgroup: topk_row does all of it in one launch (the six launches
+// above cost 38 us for 128 rows of 1531 scores, this one 6).  The kernels for
+// longer rows are bound by latency up to some 100000 scores and by reading the scores twice beyond: 16 rows of 840000
+// scores, not 16-byte aligned, counting and listing 31 -> 26 us, emission (whose threads read 128 bytes each) 78 -> 19 us.
 #include "common.h"
 
 namespace antkv {
@@ -74,7 +78,7 @@ __device__ __forceinline__ const float* row_scores(const float* scores, const fl
 }
 
 // per-row header in the workspace
-enum { kHeadCount = 0, kHeadTau = 1, kHeadNeedEq = 2, kHeadWords = 8 };
+enum { kHeadCount = 0, kHeadTau = 1, kHeadNeedEq = 2, kHeadCrowded = 3, kHeadWords = 8 };
 
 __global__ __launch_bounds__(kTopkThreads) void topk_hist0(const float* __restrict__ scores,
                                                            const float* __restrict__ scores_b, int rows_a, int64_t N,
@@ -121,13 +125,35 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t* hist0 = ws_hist + row * 2 * kBins;
     uint32_t* hist1 = hist0 + kBins;
+    if (LEVEL == 2 && head[row * kHeadWords + kHeadCrowded] == 0u) return;
+    // the slice's scores, requested before the histogram is searched
+    const int64_t lo = (int64_t)blockIdx.x * kSlice;
+    const int64_t hi = (lo + kSlice < N) ? lo + kSlice : N;
+    const float* src = row_scores(scores, scores_b, rows_a, row, N);
+    constexpr int kPer = kSlice / kTopkThreads;                 // 32 scores per thread, in 8 groups of 4
+    uint32_t key[kPer];
+    const bool fast = hi - lo == kSlice && (((uintptr_t)(src + lo)) & 15) == 0;
+    // element j of the thread sits at position lo + pos(j)
+    auto pos = [&](int j) -> int { return fast ? 4 * (tid + kTopkThreads * (j >> 2)) + (j & 3) : tid + kTopkThreads * j; };
+    if (fast) {
+#pragma unroll
+        for (int j = 0; j < kPer / 4; ++j) {
+            const float4_t v = *(const float4_t*)(src + lo + 4 * (tid + kTopkThreads * j));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(v[e]);
+        }
+    } else {                                                    // past the end: key 0, below every score's and in no bin that is looked at
+        const int n_own = (int)(hi - lo);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) key[j] = pos(j) < n_own ? float_key(src[lo + pos(j)]) : 0u;
+    }
     uint32_t d0, k_rem;
     find_digit(hist0, kBins, k, d0, k_rem, sh);
     const bool crowded = hist0[d0] > cap;                       // the same for every workgroup of the row
     uint32_t prefix = d0;                                       // keys that match it are the candidates of this level
     bool list = !crowded;
+    if (LEVEL == 1 && crowded && blockIdx.x == 0 && tid == 0) head[row * kHeadWords + kHeadCrowded] = 1u;
     if (LEVEL == 2) {
-        if (!crowded) return;
         uint32_t d1;
         find_digit(hist1, kBins, k_rem, d1, k_rem, sh);
         prefix = (d0 << 11) | d1;
@@ -138,35 +164,13 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
         for (int i = tid; i < kBins; i += kTopkThreads) lh[i] = 0u;
         __syncthreads();
     }
-    const int64_t lo = (int64_t)blockIdx.x * kSlice;
-    const int64_t hi = (lo + kSlice < N) ? lo + kSlice : N;
-    const float* src = row_scores(scores, scores_b, rows_a, row, N);
-    constexpr int kPer = kSlice / kTopkThreads;                 // 32 scores per thread, in 8 groups of 4
-    uint32_t key[kPer];
-    const bool fast = hi - lo == kSlice && (((uintptr_t)(src + lo)) & 15) == 0;
-    // element j of the thread sits at position lo + pos(j)
-    auto pos = [&](int j) -> int64_t {
-        return fast ? 4 * (tid + kTopkThreads * (j >> 2)) + (j & 3) : (int64_t)tid + (int64_t)kTopkThreads * j;
-    };
-    if (fast) {
-#pragma unroll
-        for (int j = 0; j < kPer / 4; ++j) {
-            const float4_t v = *(const float4_t*)(src + lo + 4 * (tid + kTopkThreads * j));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(v[e]);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) key[j] = (lo + pos(j) < hi) ? float_key(src[lo + pos(j)]) : 0u;
-    }
     uint32_t gt = 0, eq = 0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-        const bool in = fast || lo + pos(j) < hi;
         const uint32_t p = key[j] >> kShift;
         // LEVEL 2 counts only keys of bin d0 (higher bins were counted by LEVEL 1)
-        gt += in && p > prefix && (LEVEL == 1 || (key[j] >> 21) == d0);
-        eq += in && p == prefix;
+        gt += p > prefix && (LEVEL == 1 || (key[j] >> 21) == d0);
+        eq += p == prefix;
     }
     // block-wide: total of gt, exclusive prefix of eq
     uint32_t ieq = eq;
@@ -196,8 +200,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
         uint2_t* out = cand + row * (int64_t)cap;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const bool in = fast || lo + pos(j) < hi;
-            if (in && (key[j] >> kShift) == prefix) {
+            if ((key[j] >> kShift) == prefix) {
                 if (at < cap) out[at] = uint2_t{key[j], (uint32_t)(lo + pos(j))};
                 ++at;
             }
@@ -205,8 +208,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     } else if (LEVEL == 1) {                                    // crowded bin: its next 11 bits go to the second histogram
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const bool in = fast || lo + pos(j) < hi;
-            if (in && (key[j] >> 21) == d0) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
+            if ((key[j] >> 21) == d0) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
         }
         __syncthreads();
         for (int i = tid; i < kBins; i += kTopkThreads)
@@ -294,15 +296,42 @@ __global__ __launch_bounds__(kResolveThreads) void topk_resolve(const float* __r
     }
 }
 
+// Writes a wave's selected positions: keys > tau and, up to need_eq of the row, keys == tau.  key[j] of lane l is the score
+// at position lo + 64 j (lo includes the lane), so positions ascend over (j, lane); run_gt / run_eq count what lies before.
+template <int PER>
+__device__ __forceinline__ void emit_ordered(const uint32_t (&key)[PER], uint32_t tau, uint32_t need_eq, uint32_t run_gt,
+                                             uint32_t run_eq, int lane, int64_t lo, int32_t* __restrict__ out)
+{
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint64_t mg = __ballot(key[j] > tau), me = __ballot(key[j] == tau);
+        if ((mg | me) == 0ull) continue;                         // uniform, the usual case at 1 %
+        const uint32_t my_gt = run_gt + (uint32_t)__popcll(mg & below), my_eq = run_eq + (uint32_t)__popcll(me & below);
+        if (key[j] > tau) out[my_gt + (my_eq < need_eq ? my_eq : need_eq)] = (int32_t)(lo + 64 * j);
+        else if (key[j] == tau && my_eq < need_eq) out[my_gt + my_eq] = (int32_t)(lo + 64 * j);
+        run_gt += (uint32_t)__popcll(mg);
+        run_eq += (uint32_t)__popcll(me);
+    }
+}
+
 __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restrict__ scores,
                                                           const float* __restrict__ scores_b, int rows_a, int64_t N,
                                                           uint32_t k, const uint32_t* __restrict__ head,
                                                           const uint32_t* __restrict__ counts, int n_slices,
                                                           int32_t* __restrict__ idx, int32_t* __restrict__ idx_b)
 {
-    __shared__ uint32_t red[2][4];
+    __shared__ uint32_t red[4][4];
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // a wave owns 2048 consecutive scores, 64 at a time (coalesced whatever the row's alignment), kept as keys; requested
+    // ahead of the counts, whose latency they share
+    constexpr int kPer = kSlice / kTopkThreads;
+    const int64_t lo = (int64_t)blockIdx.x * kSlice + wave * (64 * kPer) + lane;
+    const float* src = row_scores(scores, scores_b, rows_a, row, N);
+    uint32_t key[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? __float_as_uint(src[lo + 64 * j]) : 0xffffffffu;   // (key 0: no score has it)
     const uint32_t tau = head[row * kHeadWords + kHeadTau], need_eq = head[row * kHeadWords + kHeadNeedEq];
     // keys > tau and == tau in the slices before this one
     uint32_t bgt = 0, beq = 0;
@@ -313,61 +342,73 @@ __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restric
     bgt = wave_sum_u32(bgt);
     beq = wave_sum_u32(beq);
     if (lane == 0) { red[0][wave] = bgt; red[1][wave] = beq; }
-    __syncthreads();
-    const uint32_t base_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-    const uint32_t base_eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-    __syncthreads();
-    // each thread owns 32 consecutive scores of the slice
-    const int64_t lo = (int64_t)blockIdx.x * kSlice + (int64_t)tid * (kSlice / kTopkThreads);
-    int64_t hi = lo + kSlice / kTopkThreads;
-    if (hi > N) hi = N;
-    const float* src = row_scores(scores, scores_b, rows_a, row, N);
-    // the thread's 32 scores are read once (16-byte loads when the row allows it) and kept as keys
-    constexpr int kPer = kSlice / kTopkThreads;
-    static_assert(kPer == 32, "a thread owns 32 consecutive scores");
-    uint32_t key[kPer];
-    const int n_own = (hi > lo) ? (int)(hi - lo) : 0;
-    if (n_own == kPer && (((uintptr_t)(src + lo)) & 15) == 0) {
 #pragma unroll
-        for (int j = 0; j < kPer / 4; ++j) {
-            const float4_t v = *(const float4_t*)(src + lo + 4 * j);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(v[e]);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) key[j] = (j < n_own) ? float_key(src[lo + j]) : 0u;
-    }
+    for (int j = 0; j < kPer; ++j) key[j] = float_key(__uint_as_float(key[j]));
     uint32_t gt = 0, eq = 0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-        gt += (j < n_own) && (key[j] > tau);
-        eq += (j < n_own) && (key[j] == tau);
+        gt += (uint32_t)__popcll(__ballot(key[j] > tau));
+        eq += (uint32_t)__popcll(__ballot(key[j] == tau));
     }
-    uint32_t igt = gt, ieq = eq;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        uint32_t a = __shfl_up(igt, off, 64), b = __shfl_up(ieq, off, 64);
-        if (lane >= off) { igt += a; ieq += b; }
-    }
-    if (lane == 63) { red[0][wave] = igt; red[1][wave] = ieq; }
+    if (lane == 0) { red[2][wave] = gt; red[3][wave] = eq; }
     __syncthreads();
-    uint32_t run_gt = base_gt + igt - gt, run_eq = base_eq + ieq - eq;
+    uint32_t run_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3], run_eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    for (int w = 0; w < wave; ++w) { run_gt += red[2][w]; run_eq += red[3][w]; }
+    int32_t* out = (row < rows_a) ? idx + row * (int64_t)k : idx_b + (row - rows_a) * (int64_t)k;
+    emit_ordered<kPer>(key, tau, need_eq, run_gt, run_eq, lane, lo, out);
+}
+
+// A whole row of at most 1024 * PER scores in one workgroup: the k-th largest key by three rounds of histograms in LDS (11,
+// 11 and 10 bits), then the ordered emission.  Bound: the chain of barriers of the three rounds.
+constexpr int kRowThreads = 1024;
+
+template <int PER>
+__global__ __launch_bounds__(kRowThreads) void topk_row(const float* __restrict__ scores, const float* __restrict__ scores_b,
+                                                        int rows_a, int N, uint32_t k, int32_t* __restrict__ idx,
+                                                        int32_t* __restrict__ idx_b)
+{
+    __shared__ uint32_t lh[3][kBins];
+    __shared__ uint32_t sh[2 + kRowThreads / 64];
+    __shared__ uint32_t red[2][kRowThreads / 64];
+    const int64_t row = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float* src = row_scores(scores, scores_b, rows_a, row, N);
+    const int lo = wave * (64 * PER) + lane;                     // a wave owns 64 * PER consecutive scores
+    uint32_t key[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) key[j] = lo + 64 * j < N ? float_key(src[lo + 64 * j]) : 0u;   // (no score has key 0)
+    for (int i = tid; i < 3 * kBins; i += kRowThreads) (&lh[0][0])[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (lo + 64 * j < N) atomicAdd(&lh[0][key[j] >> 21], 1u);
+    __syncthreads();
+    uint32_t d0, d1, d2, k_rem, need_eq;
+    find_digit<kRowThreads>(lh[0], kBins, k, d0, k_rem, sh);
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if ((key[j] >> 21) == d0 && lo + 64 * j < N) atomicAdd(&lh[1][(key[j] >> 10) & 2047u], 1u);
+    __syncthreads();
+    find_digit<kRowThreads>(lh[1], kBins, k_rem, d1, k_rem, sh);
+    const uint32_t prefix22 = (d0 << 11) | d1;
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if ((key[j] >> 10) == prefix22 && lo + 64 * j < N) atomicAdd(&lh[2][key[j] & 1023u], 1u);
+    __syncthreads();
+    find_digit<kRowThreads>(lh[2], 1024, k_rem, d2, need_eq, sh);
+    const uint32_t tau = (d0 << 21) | (d1 << 10) | d2;
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        gt += (uint32_t)__popcll(__ballot(key[j] > tau));
+        eq += (uint32_t)__popcll(__ballot(key[j] == tau));
+    }
+    if (lane == 0) { red[0][wave] = gt; red[1][wave] = eq; }
+    __syncthreads();
+    uint32_t run_gt = 0, run_eq = 0;
     for (int w = 0; w < wave; ++w) { run_gt += red[0][w]; run_eq += red[1][w]; }
     int32_t* out = (row < rows_a) ? idx + row * (int64_t)k : idx_b + (row - rows_a) * (int64_t)k;
-    if (gt == 0 && (eq == 0 || run_eq >= need_eq)) return;       // nothing of this thread is selected
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        if (j < n_own) {
-            if (key[j] > tau) {
-                out[run_gt + (run_eq < need_eq ? run_eq : need_eq)] = (int32_t)(lo + j);
-                ++run_gt;
-            } else if (key[j] == tau) {
-                if (run_eq < need_eq) out[run_gt + run_eq] = (int32_t)(lo + j);
-                ++run_eq;
-            }
-        }
-    }
+    emit_ordered<PER>(key, tau, need_eq, run_gt, run_eq, lane, lo, out);
 }
 
 __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4_t* __restrict__ x, int64_t N,
@@ -458,10 +499,29 @@ hipError_t topk_select(const float* scores, int32_t* idx, const float* scores_b,
 
 }  // namespace
 
+// A row in one workgroup needs no workspace.  Beyond 32 scores per thread they no longer fit the registers, and the few
+// workgroups of a long row would leave the chip idle.
+static bool topk_in_rows(int64_t N) { return N <= 32 * kRowThreads; }
+
+static hipError_t launch_topk_rows(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
+                                   int64_t N, int64_t k, hipStream_t st)
+{
+    const unsigned rows = (unsigned)(scores_b ? 2 * n_rows : n_rows);
+#define ANTKV_TR(PER)                                                                                                    \
+    hipLaunchKernelGGL(topk_row<PER>, dim3(rows), dim3(kRowThreads), 0, st, scores, scores_b, (int)n_rows, (int)N, (uint32_t)k, \
+                       idx, idx_b)
+    if (N <= 2 * kRowThreads) ANTKV_TR(2);
+    else if (N <= 8 * kRowThreads) ANTKV_TR(8);
+    else ANTKV_TR(32);
+#undef ANTKV_TR
+    return hipGetLastError();
+}
+
 hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
                         int64_t N, int64_t k, void* ws, hipStream_t st)
 {
     if (k == 0 || n_rows == 0) return hipSuccess;
+    if (topk_in_rows(N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
     const int64_t rows = scores_b ? 2 * n_rows : n_rows;
     uint32_t* hist = topk_clear(rows, N, ws, st);
     const TopkPlan p = topk_plan(rows, N);
@@ -470,12 +530,16 @@ hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b
     return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
 }
 
-uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st) { return topk_clear(2 * n_rows, N, ws, st); }
+uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st)
+{
+    return topk_in_rows(N) ? nullptr : topk_clear(2 * n_rows, N, ws, st);
+}
 
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
                                int64_t N, int64_t k, void* ws, hipStream_t st)
 {
     if (k == 0 || n_rows == 0) return hipSuccess;
+    if (topk_in_rows(N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
     return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
 }
 

@@ -48,6 +48,19 @@ def test_topk_scores_crowded_into_one_bin(oracle):
         assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), oracle.topk(s, k))
 
 
+@pytest.mark.parametrize("N", [2047, 2048, 2049, 8192, 8195, 32767, 32768, 32769, 40963])
+def test_topk_row_sizes(oracle, N):
+    """Both sides of the sizes at which another kernel takes a row, rows that are not 16-byte aligned, and rows whose scores
+    crowd into one bin of the first histogram with long runs of ties, of either sign."""
+    rng = np.random.default_rng(N)
+    s = np.exp(3.0 * rng.standard_normal((4, N))).astype(np.float32)
+    s[1] = 1.0 + 0.2 * rng.random(N)
+    s[2] = np.round(s[1] * 64) / 64
+    s[3] = -s[2]
+    for k in (1, N // 100, N - 1, N):
+        assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), oracle.topk(s, k))
+
+
 @pytest.mark.parametrize("d", [4, 8, 16])
 @pytest.mark.parametrize("B,Hq,Hkv,n", [(2, 4, 2, 333), (1, 8, 8, 70)])
 def test_encode_matches_oracle(oracle, d, B, Hq, Hkv, n):
