@@ -130,6 +130,19 @@ __device__ __forceinline__ float lane_bcast(float v, int src_lane)
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src_lane));
 }
 
+// Table entries of two heads: x rounded to a multiple of its unit, q = rint(x * inv) with |q| <= kLutMax, as the two signed
+// bytes (lo, -hi), q = lo + 128 hi with lo = q mod 128.  kRound pushes the fraction out of the mantissa, so that the low
+// half of the sum is q itself; two heads are then split in packed 16-bit arithmetic: lo - 256 hi = 3 lo - 2 q.
+constexpr float kRound = 12582912.f;   // 1.5 * 2^23
+__device__ __forceinline__ uint32_t table_pair(float x0, float x1, float inv0, float inv1)
+{
+    typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+    const uint32_t a = __float_as_uint(fmaf(x0, inv0, kRound)), b = __float_as_uint(fmaf(x1, inv1, kRound));
+    const uint32_t q2 = __builtin_amdgcn_perm(b, a, 0x05040100u);
+    const ushort2_t lo = __builtin_bit_cast(ushort2_t, q2 & 0x007f007fu);
+    return __builtin_bit_cast(uint32_t, (ushort2_t)(lo * (unsigned short)3 - __builtin_bit_cast(ushort2_t, q2) * (unsigned short)2));
+}
+
 // first index in arr[0..n) whose value is >= key; executed by a whole wave, result uniform
 __device__ int wave_lower_bound(const int32_t* __restrict__ arr, int n, int key, int lane)
 {
@@ -257,12 +270,12 @@ __device__ void wg_merge_and_store(char* smem, float (&m_ref)[kNH], float (&l_su
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float* s_red = (float*)(smem + Lds<DSUB>::red);
-    __syncthreads();   // everyone is done with the tables and the staging area
+    lds_barrier();     // everyone is done with the tables and the staging area
     if (lane == 0) {
 #pragma unroll
         for (int h = 0; h < kNH; ++h) { s_red[wave * 8 + h] = m_ref[h]; s_red[wave * 8 + 4 + h] = l_sum[h]; }
     }
-    __syncthreads();
+    lds_barrier();
     static_assert(kDaWaves <= 16, "one row of 16 lanes covers the waves");
     float m_all[kNH], l_all[kNH];
     {
@@ -285,18 +298,35 @@ __device__ void wg_merge_and_store(char* smem, float (&m_ref)[kNH], float (&l_su
 #pragma unroll
         for (int rho = 0; rho < 4; ++rho)
             s_mrg[(wave * 4 + cls) * kD + 16 * (4 * a + ((cls + rho) & 3)) + n] = acc[a][rho] * f;
-    __syncthreads();
+    lds_barrier();
+    // 64 rows (wave, class) to 8 with 16-byte reads, then the 8 to one
+    constexpr int kParts = kDaThreads / kD, kRows = kDaWaves * 4 / kParts;
+    float4_t* s_sum = (float4_t*)(smem + Lds<DSUB>::pst);            // [part][channel] x 4 heads (the staging areas are free by now)
+    static_assert(kParts * kD * 16 <= kDaWaves * kStgBytes, "the parts fit the staging areas");
+    {
+        const float4_t* src = s_mrg + (tid >> 7) * kRows * kD + (tid & (kD - 1));
+        float4_t v[kRows];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) v[u] = src[u * kD];
+#pragma unroll
+        for (int off = kRows / 2; off >= 1; off >>= 1)
+#pragma unroll
+            for (int u = 0; u < off; ++u) v[u] += v[u + off];
+        s_sum[tid] = v[0];
+    }
+    lds_barrier();
     if (tid < kNH * kD) {
         const int h = tid & 3, dim = tid >> 2;                   // consecutive threads read consecutive dwords
-        const float* src = (const float*)s_mrg + dim * 4 + h;
-        float s4[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-        for (int w = 0; w < kDaWaves * 4; w += 4) {
+        const float* src = (const float*)s_sum + tid;
+        float s8[kParts];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) s4[u] += src[(w + u) * kD * 4];
-        }
+        for (int u = 0; u < kParts; ++u) s8[u] = src[u * kD * 4];
+#pragma unroll
+        for (int off = kParts / 2; off >= 1; off >>= 1)
+#pragma unroll
+            for (int u = 0; u < off; ++u) s8[u] += s8[u + off];
         if (h < nheads) {
-            const float s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+            const float s = s8[0];
             float* dst = part_bg + ((int64_t)h * slots + slot) * (kD + 2);
             // Device-scope stores: they write through this die's L2, so the merging workgroup (possibly
             // on another die) can read them without any cache write-back.
@@ -375,15 +405,16 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
 
     int* s_misc = (int*)(smem + L::red + kDaWaves * 32);
     uint32_t* s_mask = (uint32_t*)(smem + L::mask);
-    // The first anchor tile of this wave (tile sp + S * wave of the (sequence, KV head)'s tiles): its tokens, their cross
+    // The first anchor tile of this wave (of tiles sp, sp + S, ... of the (sequence, KV head)'s tiles): its tokens, their cross
     // membership and their code rows are fetched during the prologue, while the memory system is idle, so that the
     // tile itself is left with a single round trip (the FP16 rows).
-    const int T_first = sp + p.S * wave;
+    // The last wave takes the first tile: a short range has no stream tile for the last waves.
+    const int T_first = sp + p.S * (kDaWaves - 1 - wave);
     int pre_tok = 0, pre_info = 0;
     uint32_t pre_codes[CW];
 #pragma unroll
     for (int i = 0; i < CW; ++i) pre_codes[i] = 0u;
-    // (long-list kernels: a wave often has a second tile, sp + S * (wave + 16); the same is fetched for it, so that the
+    // (long-list kernels: a wave often has a second tile, S * 16 further; the same is fetched for it, so that the
     // second tile too is left with one round trip, its FP16 rows)
     int pre2_tok = 0, pre2_info = 0;
     uint32_t pre2_codes[CW];
@@ -673,15 +704,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
         uint2_t ent[NJ];
 #pragma unroll
         for (int j = 0; j < (GIVEN ? 0 : NJ); ++j) {
-            uint32_t hw[kNH];
-#pragma unroll
-            for (int h = 0; h < kNH; ++h) {
-                const int qv = (int)rintf(val[j][h] * inv_q[h]);     // |qv| <= kLutMax
-                const int hi = (qv + 64) >> 7;                          // qv = lo + 128 * hi, lo in [-64, 63]
-                const int lo = qv - 128 * hi;
-                hw[h] = ((uint32_t)lo & 0xffu) | (((uint32_t)(-hi) & 0xffu) << 8);
-            }
-            ent[j] = uint2_t{hw[0] | (hw[1] << 16), hw[2] | (hw[3] << 16)};
+            ent[j] = uint2_t{table_pair(val[j][0], val[j][1], inv_q[0], inv_q[1]), table_pair(val[j][2], val[j][3], inv_q[2], inv_q[3])};
         }
         // The lanes of a block hold the same sub-space for 16 different codes, i.e. 16 rows at the same bank.  In
         // round r a lane therefore stores entry (r + code) mod NJ, and starts with copy (code / 4) mod REPS of it:
@@ -706,16 +729,14 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
             static_assert(!WIDE || REPS >= 2, "the residual entries live in the slots of the copies");
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
-                uint32_t hw[kNH];
+                float rest[kNH], unit[kNH];
 #pragma unroll
                 for (int h = 0; h < kNH; ++h) {
-                    const float first = rintf(val[j][h] * inv_q[h]);
-                    const int qv = (int)rintf((val[j][h] - first * quantum[h]) * (inv_q[h] * (2.f * kLutMax)));
-                    const int hi = (qv + 64) >> 7;
-                    const int lo = qv - 128 * hi;
-                    hw[h] = ((uint32_t)lo & 0xffu) | (((uint32_t)(-hi) & 0xffu) << 8);
+                    const float first = fmaf(val[j][h], inv_q[h], kRound) - kRound;
+                    rest[h] = val[j][h] - first * quantum[h];
+                    unit[h] = inv_q[h] * (2.f * kLutMax);
                 }
-                ent[j] = uint2_t{hw[0] | (hw[1] << 16), hw[2] | (hw[3] << 16)};
+                ent[j] = uint2_t{table_pair(rest[0], rest[1], unit[0], unit[1]), table_pair(rest[2], rest[3], unit[2], unit[3])};
             }
             if (ent_on) {
 #pragma unroll
@@ -1471,9 +1492,55 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
         s_misc[10] = (int)(unsigned int)__hip_atomic_fetch_add(&p.done[bg], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
     __syncthreads();
     if (s_misc[10] == p.S) {
+        auto ld = [](const float* q) { return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        constexpr int kOneRound = 32;
+        if (p.S <= kOneRound) {
+            // one round trip: statistics and accumulators of all slots are requested together (two threads per (head,
+            // channel), every second slot each), the weights are worked out while the accumulators are on their way
+            const int S = p.S;
+            float m = kNegBig, l = 0.f;
+            if (tid < kNH * kOneRound) {
+                const int h = tid >> 5, sl = tid & 31;
+                if (h < nheads && sl < S) {
+                    const float* ps = part_bg + ((int64_t)h * S + sl) * (kD + 2) + kD;
+                    m = ld(ps);
+                    l = ld(ps + 1);
+                }
+            }
+            const int half = tid >> 9, hd = tid & (kNH * kD - 1), h = hd >> 7, dim = hd & (kD - 1);
+            float v[kOneRound / 2];
+#pragma unroll
+            for (int u = 0; u < kOneRound / 2; ++u) {
+                const int sl = 2 * u + half;
+                v[u] = (h < nheads && sl < S) ? ld(part_bg + ((int64_t)h * S + sl) * (kD + 2) + dim) : 0.f;
+            }
+            float* s_w = (float*)(smem + L::mrg);                   // [4 heads][32]: slot weights 2^(m_s - m)
+            float* s_tot = s_w + kNH * kOneRound;                   // [4]: total l per head
+            float* s_half = s_tot + kNH;                            // [4][128]: the second thread's share
+            if (tid < kNH * kOneRound) {
+                float mm = row16_max(m);
+                mm = fmaxf(mm, __shfl_xor(mm, 16, 64));
+                const float w = fast_exp2(m - mm);                  // (slots that do not exist: l = 0 and no accumulator)
+                float t = row16_sum(l * w);
+                t += __shfl_xor(t, 16, 64);
+                s_w[tid] = w;
+                if ((tid & 31) == 0) s_tot[tid >> 5] = t;
+            }
+            lds_barrier();
+            float a = 0.f;
+#pragma unroll
+            for (int u = 0; u < kOneRound / 2; ++u) a = fmaf(v[u], s_w[h * kOneRound + 2 * u + half], a);
+            if (half) s_half[hd] = a;
+            lds_barrier();
+            if (!half && h < nheads) {
+                a += s_half[hd];
+                const float lt = s_tot[h];
+                p.out[((int64_t)b * p.Hq + h0 + h) * kD + dim] = (half_t)(lt > 0.f ? a / lt : 0.f);
+            }
+            return;
+        }
         // S can be a few hundred: the statistics of all slots go through LDS first (one round of loads), then every
         // (head, channel) thread sums its column with eight independent loads in flight.
-        auto ld = [](const float* q) { return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
         float* s_w = (float*)(smem + L::mrg);                       // [4 heads][S]: slot weights 2^(m_s - m) (table area is free now)
         float* s_tot = s_w + kNH * 1024;                            // [4]: total l per head
         const int S = p.S;
