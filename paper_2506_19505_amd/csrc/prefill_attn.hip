@@ -129,13 +129,8 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     }
     __syncthreads();                                                // step 0 stages over the tile that has just been read
 
-    // step t, T = t mod 4
-    auto step = [&](int t, auto phase) {
-        constexpr int T = decltype(phase)::value;
-        constexpr int kNext = (T + 1) & 3, kPrev = (T + 3) & 3, cur = T & 1, nxt = cur ^ 1;
-        stage(kbase, t + 4, T);                                     // (tiles past the end repeat the last row)
-        stage(vbase, t + 2, kRing + ((T + 2) & 3));
-        float16_t& s = sc[cur];
+    // before the exponentials of tile t: mask, largest score, reference; true if it moves (o has to be rescaled by alpha)
+    auto open_tile = [&](float16_t& s, int t, float& alpha) {
         if (__builtin_expect(t * 32 + 31 > first_pos, 0)) {         // the causal diagonal: key offset <= lim is visible
             const int lim = qpos - t * 32;
 #pragma unroll
@@ -145,7 +140,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
         s_max = max3f(s_max, s[0], s[1]);
 #pragma unroll
         for (int r = 2; r < 16; r += 2) s_max = max3f(s_max, s[r], s[r + 1]);
-        float alpha = 1.f;
+        alpha = 1.f;
         const bool moves = __any(fmaf(s_max, c1, -m_ref) > kPMax);
         if (__builtin_expect(moves, 0)) {                           // the reference moves to the largest score so far
             const float m_new = fmaxf(s_max, __shfl_xor(s_max, 32, 64)) * c1;
@@ -155,6 +150,24 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
                 m_ref = m_new;
             }
         }
+        return moves;
+    };
+    auto rescale = [&](float alpha) {
+#pragma unroll
+        for (int cg = 0; cg < 4; ++cg)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[cg][r] *= alpha;
+    };
+
+    // step t, T = t mod 4
+    auto step = [&](int t, auto phase) {
+        constexpr int T = decltype(phase)::value;
+        constexpr int kNext = (T + 1) & 3, kPrev = (T + 3) & 3, cur = T & 1, nxt = cur ^ 1;
+        stage(kbase, t + 4, T);                                     // (tiles past the end repeat the last row)
+        stage(vbase, t + 2, kRing + ((T + 2) & 3));
+        float16_t& s = sc[cur];
+        float alpha;
+        const bool moves = open_tile(s, t, alpha);
         half8_t ka[8], va[8];
         ka[0] = k_op(0, kNext); va[0] = v_op(0, kPrev);
         ka[1] = k_op(1, kNext); va[1] = v_op(1, kPrev);
@@ -178,29 +191,50 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
             __builtin_amdgcn_sched_barrier(0);
         }
         l_run += sum[0] + sum[1];
-        if (__builtin_expect(moves, 0)) {
-#pragma unroll
-            for (int cg = 0; cg < 4; ++cg)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o[cg][r] *= alpha;
-        }
+        if (__builtin_expect(moves, 0)) rescale(alpha);
         landed_but<4>();                                            // this step's two loads and the last one's
     };
-    // Up to three tiles past the wave's last are masked throughout, so that the loop has one end with the registers in the
-    // same roles.  Waves that are done keep staging for the others.
+    // Whole groups of four tiles are interleaved; up to three more go one after the other, so that the loop has one end with
+    // the registers in the same roles (four ends spill).  No tile past the wave's last is touched: its V rows, which no
+    // query of the wave sees, would meet zero probabilities (inf * 0).
     int t = 0;
-    for (; t < my_tiles; t += 4) {
+    for (; t + 4 <= my_tiles; t += 4) {
         step(t, std::integral_constant<int, 0>{});
         step(t + 1, std::integral_constant<int, 1>{});
         step(t + 2, std::integral_constant<int, 2>{});
         step(t + 3, std::integral_constant<int, 3>{});
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i)                                     // the last tile's value product
-        o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v_op(i, (t + 3) & 3), p[1][i >> 2], o[i & 3], 0, 0, 0);
-    for (; t < ((n_tiles + 3) & ~3); ++t) {                         // (every wave meets the same number of barriers)
+    auto stage_ahead = [&](int t) {
         stage(kbase, t + 4, t & 3);
         stage(vbase, t + 2, kRing + ((t + 2) & 3));
+    };
+    auto last_product = [&](int t) {                                // the value product of tile t - 1
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v_op(i, (t + 3) & 3), p[1][i >> 2], o[i & 3], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);                          // (V has been read before another wave stages over it)
+    };
+#pragma unroll 1
+    for (; t < my_tiles; ++t) {
+        stage_ahead(t);
+        last_product(t);
+        float alpha;
+        if (open_tile(sc[0], t, alpha)) rescale(alpha);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float e = fast_exp2(fmaf(sc[0][r], c1, -m_ref));
+            l_run += e;
+            p[1][r >> 3][r & 7] = (half_t)e;
+            sc[0][r] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(k_op(i, (t + 1) & 3), tq[i], sc[0], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        landed_but<4>();
+    }
+    last_product(t);
+    for (; t < n_tiles; ++t) {                                      // waves that are done keep staging for the others
+        stage_ahead(t);
         landed_but<4>();
     }
     wait_all_loads();                                               // nothing may land in LDS after the workgroup's end

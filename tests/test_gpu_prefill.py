@@ -47,6 +47,21 @@ def test_prefill_attn_tile_edges(oracle, B, Hq, Hkv, N, Nq):
     _check(oracle, 64, B, Hq, Hkv, N, Nq, 1.0 / np.sqrt(128))
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (2, 2)])
+def test_prefill_attn_later_rows_stay_unseen(oracle, Hq, Hkv):
+    """Rows of K and V behind a query's 32-key tile take no part in its result, whatever they hold."""
+    N, seen, scale = 700, 320, 1.0 / np.sqrt(128)
+    q, k, v = make_qkv(65, 1, Hq, Hkv, N, N, 128)
+    k[:, :, seen:], v[:, :, seen:] = np.nan, np.inf
+    out, rm, rs = antkv.prefill_attn(antkv.Geometry(1, Hq, Hkv, 8), dev(q), dev(k), dev(v), scale)
+    want, wm, wl = oracle.prefill_attn(np.ascontiguousarray(q[:, :, :seen]), np.ascontiguousarray(k[:, :, :seen]),
+                                       np.ascontiguousarray(v[:, :, :seen]), scale)
+    got = out.cpu().numpy().astype(np.float64)[:, :, :seen]
+    assert (np.linalg.norm(got - want, axis=-1) <= OUT_TOL * np.linalg.norm(want, axis=-1)).all()
+    np.testing.assert_allclose(rm.cpu().numpy()[:, :, :seen], wm, rtol=2e-6, atol=2e-6)
+    np.testing.assert_allclose(rs.cpu().numpy()[:, :, :seen], wl, rtol=1e-4)
+
+
 def test_prefill_attn_wide_score_range(oracle):
     """Scores spread over a few hundred log2 units: the softmax reference has to move many times per row."""
     _check(oracle, 62, 1, 4, 2, 700, 700, 1.0 / np.sqrt(128), q_gain=12.0)
