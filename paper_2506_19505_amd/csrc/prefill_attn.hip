@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     __syncthreads();                                                // step 0 stages over the tile that has just been read
 
     // before the exponentials of tile t: mask, largest score, reference; true if it moves (o has to be rescaled by alpha)
-    auto open_tile = [&](float16_t& s, int t, float& alpha) {
+    auto open_tile = [&](float16_t& s, int t, float& alpha) __attribute__((always_inline)) {
         if (__builtin_expect(t * 32 + 31 > first_pos, 0)) {         // the causal diagonal: key offset <= lim is visible
             const int lim = qpos - t * 32;
 #pragma unroll
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
         }
         return moves;
     };
-    auto rescale = [&](float alpha) {
+    auto rescale = [&](float alpha) __attribute__((always_inline)) {
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     };
 
     // step t, T = t mod 4
-    auto step = [&](int t, auto phase) {
+    auto step = [&](int t, auto phase) __attribute__((always_inline)) {
         constexpr int T = decltype(phase)::value;
         constexpr int kNext = (T + 1) & 3, kPrev = (T + 3) & 3, cur = T & 1, nxt = cur ^ 1;
         stage(kbase, t + 4, T);                                     // (tiles past the end repeat the last row)
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
         stage(kbase, t + 4, t & 3);
         stage(vbase, t + 2, kRing + ((t + 2) & 3));
     };
-    auto last_product = [&](int t) {                                // the value product of tile t - 1
+    auto last_product = [&](int t) __attribute__((always_inline)) {                                // the value product of tile t - 1
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v_op(i, (t + 3) & 3), p[1][i >> 2], o[i & 3], 0, 0, 0);
