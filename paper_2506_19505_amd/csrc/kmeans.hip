@@ -15,17 +15,19 @@
 // the chain of six barriers per chunk (loads, ranks, sums and merge take about 6 us each).  Adding every product into LDS
 // with ds_add_f32, as before, runs at three clocks per lane: 8 heads x 32768 tokens (d8) 195 us, 38 now; sorting indices
 // and gathering the sub-vectors from memory in sorted order thrashes the L2: 55 us.
-// With 4096 centroids (12-bit codes) the sums of one KV head are 2 MB, far beyond LDS, and 4096 targets per sub-space
-// rarely collide, so every thread adds its eight channels straight into the global sums (km_accumulate12).
+// With 4096 centroids (12-bit codes) a workgroup owns up to 512 centroids of one sub-space, picks their tokens out of all
+// codes and writes the new centroids itself (km_update12).
 #include "common.h"
 
 namespace antkv {
 
 namespace {
 
-constexpr int kKmThreads = 256;
-constexpr int kKmChunk = 2048;     // tokens per workgroup (4096 centroids)
 constexpr int kKsThreads = 512;    // 256 centroids
+constexpr int kKwThreads = 1024;   // 4096 centroids
+constexpr int kKwCodes = 512;      // most centroids of a workgroup
+constexpr int kKwList = 8192;      // sorted tokens in LDS
+constexpr int kKwLook = 32768;     // tokens of a chunk: about 4096 of them are the workgroup's
 constexpr int ks_per(int d) { return d == 16 ? 2 : 4; }                  // tokens of a chunk per thread
 constexpr int ks_chunk(int d) { return kKsThreads * ks_per(d); }
 
@@ -199,54 +201,194 @@ __global__ __launch_bounds__(kKsThreads, 4) void km_accumulate(
     }
 }
 
-// 4096 centroids, codes packed 12 bits each (code m at bits 12 m .. 12 m + 11 of the token's row).  A thread owns one
-// 16-byte chunk (8 channels) of a token row: tid % 16 = chunk, 16 tokens per pass of the workgroup.
-template <int DSUB>
-__global__ __launch_bounds__(kKmThreads) void km_accumulate12(
-    const half_t* __restrict__ x, const float* __restrict__ w, const uint8_t* __restrict__ codes,
-    const half_t* __restrict__ cb, int64_t n_tok, int Hkv, float* __restrict__ sums, float* __restrict__ wsum,
-    double* __restrict__ objective)
+// 4096 centroids, codes packed 12 bits each (code m at bits 12 m .. 12 m + 11 of the token's row).  A workgroup owns `cw`
+// centroids of one sub-space and walks all tokens in chunks: it counts the codes of its own range, sorts those tokens by
+// code in LDS, and DSUB / 8 lanes each add up a window of consecutive sorted tokens, gathering their sub-vectors.  A run
+// belongs to the window that it starts in, which alone adds to its centroid's sums in LDS; what a window continues of the
+// run before it has a slot of its own and is added after a barrier.  No atomics on sums, so they are the same in every run
+// up to the order inside a code (ranks come from fetch-adds).
+// Bound: latency of the count, sort and gather passes of a chunk.  Every product added to the global sums with hardware float
+// atomics, as before, runs at the L2's atomic rate (35 M additions for 8 heads x 32768 tokens).
+constexpr int kw_groups(int d) { return kKwThreads / (d / 8); }
+constexpr size_t kw_lds(int d)
 {
-    constexpr int M = kD / DSUB, LPM = DSUB / 8, CB = 3 * M / 2, NC = 4096;
-    const int tid = threadIdx.x;
-    const int64_t bg = blockIdx.y;
-    const int g = (int)(bg % Hkv);
-    const int u = tid & 15;                                      // chunk of the row: channels 8 u .. 8 u + 7
-    const int m = u / LPM, part = u % LPM;                       // sub-space and the chunk's place inside it
-    const int64_t t0 = (int64_t)blockIdx.x * kKmChunk;
-    const int64_t t1 = (t0 + kKmChunk < n_tok) ? t0 + kKmChunk : n_tok;
-    const half_t* cbm = cb + ((int64_t)g * M + m) * NC * DSUB;
-    float* sm = sums + ((int64_t)g * M + m) * NC * DSUB;
-    float* wm = wsum + ((int64_t)g * M + m) * NC;
-    double obj = 0.0;
-    for (int64_t t = t0 + (tid >> 4); t < t1; t += kKmThreads / 16) {
-        const int64_t row = bg * n_tok + t;
-        const float wt = w[row];
-        // the 12 bits of code m start at bit 12 m of the row: two bytes hold them
-        const uint8_t* cr = codes + row * CB + (12 * m >> 3);
-        const uint32_t two = (uint32_t)cr[0] | ((uint32_t)cr[1] << 8);
-        const int c = (int)((two >> ((12 * m) & 7)) & 0xFFFu);
-        const half8_t a = *(const half8_t*)(x + row * kD + 8 * u);
-        const half8_t b = *(const half8_t*)(cbm + (int64_t)c * DSUB + 8 * part);
-        float dist = 0.f;
-        float* acc = sm + (int64_t)c * DSUB + 8 * part;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float xv = (float)a[e];
-            const float df = xv - (float)b[e];
-            dist = fmaf(df, df, dist);
-            const float v = wt * xv;
-            if (v != 0.f) unsafeAtomicAdd(acc + e, v);
+    return (size_t)kKwList * 4 + (size_t)(kKwCodes + kw_groups(d)) * (d + 1) * 4 + (kKwCodes + 4 + kKwCodes) * 4 + 16 * 8;
+}
+
+// grid: Hkv * M * (4096 / cw) workgroups, heads fastest (8 heads, one per XCD)
+template <int DSUB>
+__global__ __launch_bounds__(kKwThreads) void km_update12(
+    const half_t* __restrict__ x, const float* __restrict__ w, const uint8_t* __restrict__ codes,
+    const half_t* __restrict__ cb_in, half_t* __restrict__ cb_out, float* __restrict__ wsum_out,
+    double* __restrict__ objective, int64_t n_tok, int64_t total, int Hkv, int cw)
+{
+    constexpr int M = kD / DSUB, L = DSUB / 8, CB = 3 * M / 2, NC = 4096, NV = DSUB + 1, NG = kw_groups(DSUB);
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    uint32_t* s_list = (uint32_t*)lds;                          // code << 16 | token, sorted by code
+    float* s_sum = (float*)(s_list + kKwList);                  // [kKwCodes][NV]: DSUB sums and the weight
+    float* s_first = s_sum + kKwCodes * NV;                     // [NG][NV]: what a window continues
+    uint32_t* s_off = (uint32_t*)(s_first + NG * NV);           // first sorted position of a code; [kKwCodes] = tokens
+    uint32_t* s_cur = s_off + kKwCodes + 4;                     // histogram, then the next free position of a code
+    double* s_obj = (double*)(s_cur + kKwCodes);                // one per wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ranges = NC / cw;
+    const int g = (int)(blockIdx.x % Hkv), rest = (int)(blockIdx.x / Hkv), m = rest / ranges, c0 = rest % ranges * cw;
+    const int gi = tid / L, part = tid % L;                     // the thread's window, and its channels 8 part .. 8 part + 7
+    const int64_t gm = (int64_t)g * M + m;
+    const half_t* cen = cb_in + (gm * NC + c0) * DSUB + 8 * part;
+    const uint8_t* code_at = codes + (12 * m >> 3);             // the 12 bits of code m: in two bytes of the row
+    const int code_shift = (12 * m) & 7;
+    for (int i = tid; i < kKwCodes * NV; i += kKwThreads) s_sum[i] = 0.f;
+
+    int64_t seq0 = 0, pos0 = 0;                                 // first token of the chunk (counted over all sequences)
+    auto row_of = [&](int t) {
+        int64_t seq = seq0, pos = pos0 + t;                     // (pos0 + t < n_tok + 32768 fits 32 bits)
+        if (pos >= n_tok) {
+            const uint32_t more = (uint32_t)pos / (uint32_t)n_tok;
+            seq += more;
+            pos -= (int64_t)more * n_tok;
         }
-        if (part == 0 && wt != 0.f) unsafeAtomicAdd(wm + c, wt);
-        obj += (double)wt * (double)dist;
-    }
-    // objective of sub-space m: the LPM chunk lanes and the four token slots of a wave (lanes u, u+16, u+32, u+48)
+        return (seq * Hkv + g) * n_tok + pos;
+    };
+    auto each_own = [&](int len, auto&& f) {                    // f(token, code - c0) for the chunk's tokens of this range
+        for (int t0 = tid; t0 < len; t0 += 8 * kKwThreads) {
+            uint32_t two[8];
 #pragma unroll
-    for (int off = 1; off < LPM; off <<= 1) obj += __shfl_xor(obj, off, 64);
-    obj += __shfl_xor(obj, 16, 64);
-    obj += __shfl_xor(obj, 32, 64);
-    if ((tid & 63) < 16 && part == 0 && objective) unsafeAtomicAdd(objective + (int64_t)g * M + m, obj);
+            for (int u = 0; u < 8; ++u) {
+                const int t = t0 + u * kKwThreads;
+                two[u] = 0u;
+                if (t < len) {
+                    const uint8_t* cr = code_at + row_of(t) * CB;
+                    two[u] = (uint32_t)cr[0] | ((uint32_t)cr[1] << 8);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t c = ((two[u] >> code_shift) & 0xFFFu) - (uint32_t)c0;
+                const int t = t0 + u * kKwThreads;
+                if (t < len && c < (uint32_t)cw) f(t, c);
+            }
+        }
+    };
+    double obj = 0.0;
+    for (int64_t j0 = 0; j0 < total;) {
+        int len = (int)(total - j0 < kKwLook ? total - j0 : kKwLook);
+        for (;;) {                                              // at most twice: kKwList tokens always fit the list
+            if (tid < kKwCodes) s_cur[tid] = 0u;
+            __syncthreads();
+            each_own(len, [&](int, uint32_t c) { atomicAdd(&s_cur[c], 1u); });
+            __syncthreads();
+            if (tid < 64) {                                     // prefix sums, eight codes per lane
+                uint32_t c[kKwCodes / 64], own = 0u;
+#pragma unroll
+                for (int i = 0; i < kKwCodes / 64; ++i) { c[i] = s_cur[kKwCodes / 64 * tid + i]; own += c[i]; }
+                uint32_t pre = own;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t o = __shfl_up(pre, off, 64);
+                    if (tid >= off) pre += o;
+                }
+                pre -= own;
+#pragma unroll
+                for (int i = 0; i < kKwCodes / 64; ++i) {
+                    s_off[kKwCodes / 64 * tid + i] = pre;
+                    s_cur[kKwCodes / 64 * tid + i] = pre;
+                    pre += c[i];
+                }
+                if (tid == 63) s_off[kKwCodes] = pre;
+            }
+            __syncthreads();
+            if (s_off[kKwCodes] <= kKwList) break;
+            len = kKwList;                                      // (crowded codes: a shorter chunk)
+        }
+        const int n = (int)s_off[kKwCodes];
+        each_own(len, [&](int t, uint32_t c) { s_list[atomicAdd(&s_cur[c], 1u)] = (c << 16) | (uint32_t)t; });
+        __syncthreads();
+
+        const int per = n > 8 * NG ? (n + NG - 1) / NG : 8;     // sorted positions of a window
+        const int p0 = gi * per, p1 = p0 + per < n ? p0 + per : n;
+        float acc[8], wacc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+        int cur = p0 < p1 ? (int)(s_list[p0] >> 16) : 0;
+        bool continues = p0 < p1 && (int)s_off[cur] < p0;
+        auto flush = [&] {
+            float* to = continues ? s_first + gi * NV : s_sum + cur * NV;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float* at = to + 8 * part + e;
+                *at = continues ? acc[e] : *at + acc[e];
+                acc[e] = 0.f;
+            }
+            if (part == 0) to[DSUB] = continues ? wacc : to[DSUB] + wacc;
+            wacc = 0.f;
+            continues = false;
+        };
+        for (int p = p0; p < p1; p += 4) {
+            half8_t xv[4], cv[4];
+            float wt[4];
+            int c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t e = s_list[p + u < p1 ? p + u : p];
+                const int64_t r = row_of((int)(e & 0xFFFFu));
+                c[u] = (int)(e >> 16);
+                wt[u] = w[r];
+                xv[u] = *(const half8_t*)(x + r * kD + m * DSUB + 8 * part);
+                cv[u] = *(const half8_t*)(cen + (int64_t)c[u] * DSUB);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (p + u < p1) {
+                    if (c[u] != cur) { flush(); cur = c[u]; }
+                    float dist = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float xe = (float)xv[u][e], df = xe - (float)cv[u][e];
+                        dist = fmaf(df, df, dist);
+                        acc[e] = fmaf(wt[u], xe, acc[e]);
+                    }
+                    wacc += wt[u];
+                    obj += (double)wt[u] * (double)dist;
+                }
+            }
+        }
+        if (p0 < p1) flush();
+        __syncthreads();
+        for (int i = tid; i < kKwCodes * NV; i += kKwThreads) { // the windows that a run goes on in
+            const int c = i / NV, e = i - c * NV, lo = (int)s_off[c], hi = (int)s_off[c + 1];
+            if (lo == hi) continue;
+            float v = 0.f;
+            for (int k = lo / per + 1; k * per < hi; ++k) v += s_first[k * NV + e];
+            s_sum[i] += v;
+        }
+        j0 += len;
+        pos0 += len;
+        seq0 += pos0 / n_tok;
+        pos0 %= n_tok;
+        // (the next chunk's first two barriers keep s_off, s_first and s_list until everybody is here)
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) obj += __shfl_xor(obj, off, 64);
+    if (lane == 0) s_obj[wave] = obj;
+    __syncthreads();
+    if (tid == 0 && objective) {
+        double o = 0.0;
+        for (int i = 0; i < kKwThreads / 64; ++i) o += s_obj[i];
+        unsafeAtomicAdd(objective + gm, o);
+    }
+    // weighted means; a centroid without assigned weight keeps its old value
+    for (int i = tid; i < cw * L; i += kKwThreads) {            // (kKwThreads is a multiple of L: `part` is i % L)
+        const int c = i / L;
+        const float* sum = s_sum + c * NV;
+        const float ws = sum[DSUB];
+        const half8_t old = *(const half8_t*)(cen + (int64_t)c * DSUB);
+        half8_t to;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) to[e] = ws > 0.f ? (half_t)(sum[8 * part + e] / ws) : old[e];
+        *(half8_t*)(cb_out + (gm * NC + c0 + c) * DSUB + 8 * part) = to;
+        if (part == 0 && wsum_out) wsum_out[gm * NC + c0 + c] = ws;
+    }
 }
 
 // weighted means; a centroid without assigned weight keeps its old value
@@ -283,7 +425,7 @@ KmPlan km_plan(const Geom& g)
     return p;
 }
 
-template <int DSUB, bool WIDE>
+template <int DSUB>
 hipError_t launch_t(const Geom& g, const half_t* x, const float* w, int64_t n_tok, const half_t* cb_in, half_t* cb_out,
                     const uint8_t* codes, float* wsum_out, double* objective, char* ws, hipStream_t st)
 {
@@ -295,26 +437,40 @@ hipError_t launch_t(const Geom& g, const half_t* x, const float* w, int64_t n_to
     hipLaunchKernelGGL(km_zero, dim3((unsigned)((n_zero + n_obj + 255) / 256)), dim3(256), 0, st, (uint32_t*)ws, n_zero,
                        (uint32_t*)objective, n_obj);
     if (n_tok > 0) {
-        if constexpr (WIDE) {
-            dim3 grid((unsigned)((n_tok + kKmChunk - 1) / kKmChunk), (unsigned)(g.B * g.Hkv));
-            hipLaunchKernelGGL(km_accumulate12<DSUB>, grid, dim3(kKmThreads), 0, st, x, w, codes, cb_in, n_tok, g.Hkv, sums,
-                               wsum, obj);
-        } else {
-            static const hipError_t setup = hipFuncSetAttribute((const void*)km_accumulate<DSUB>,
-                                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)km_lds(DSUB));
-            if (setup != hipSuccess) return setup;
-            // about two workgroups per CU; a range is whole chunks, since every range adds 256 x (DSUB + 1) values to the sums
-            const int64_t total = (int64_t)g.B * n_tok, pairs = (int64_t)g.Hkv * g.M, chunk = ks_chunk(DSUB);
-            int64_t range = ((total * pairs + 511) / 512 + chunk - 1) / chunk * chunk;
-            const int64_t units = (total + range - 1) / range * g.Hkv;
-            hipLaunchKernelGGL(km_accumulate<DSUB>, dim3((unsigned)((units + 7) / 8 * 8 * g.M)), dim3(kKsThreads), km_lds(DSUB), st,
-                               x, w, codes, cb_in, n_tok, total, range, g.Hkv, (int)units, sums, wsum, obj);
-        }
+        static const hipError_t setup = hipFuncSetAttribute((const void*)km_accumulate<DSUB>,
+                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)km_lds(DSUB));
+        if (setup != hipSuccess) return setup;
+        // about two workgroups per CU; a range is whole chunks, since every range adds 256 x (DSUB + 1) values to the sums
+        const int64_t total = (int64_t)g.B * n_tok, pairs = (int64_t)g.Hkv * g.M, chunk = ks_chunk(DSUB);
+        int64_t range = ((total * pairs + 511) / 512 + chunk - 1) / chunk * chunk;
+        const int64_t units = (total + range - 1) / range * g.Hkv;
+        hipLaunchKernelGGL(km_accumulate<DSUB>, dim3((unsigned)((units + 7) / 8 * 8 * g.M)), dim3(kKsThreads), km_lds(DSUB), st,
+                           x, w, codes, cb_in, n_tok, total, range, g.Hkv, (int)units, sums, wsum, obj);
     }
     const int64_t n_cen = (int64_t)g.Hkv * g.M * g.C;
     const int64_t n_fin = n_cen * (DSUB < 8 ? 1 : DSUB / 8);
     hipLaunchKernelGGL(km_finalize<DSUB>, dim3((unsigned)((n_fin + 255) / 256)), dim3(256), 0, st, sums, wsum, cb_in,
                        cb_out, wsum_out, n_cen);
+    return hipGetLastError();
+}
+
+template <int DSUB>
+hipError_t launch_wide(const Geom& g, const half_t* x, const float* w, int64_t n_tok, const half_t* cb_in, half_t* cb_out,
+                       const uint8_t* codes, float* wsum_out, double* objective, hipStream_t st)
+{
+    static const hipError_t setup = hipFuncSetAttribute((const void*)km_update12<DSUB>,
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kw_lds(DSUB));
+    if (setup != hipSuccess) return setup;
+    if (objective) {
+        const int64_t n_obj = (int64_t)g.Hkv * g.M * 2;
+        hipLaunchKernelGGL(km_zero, dim3((unsigned)((n_obj + 255) / 256)), dim3(256), 0, st, (uint32_t*)objective, n_obj,
+                           (uint32_t*)nullptr, (int64_t)0);
+    }
+    // every workgroup looks at all codes of its sub-space: no more of them than fill the chip
+    int cw = kKwCodes;
+    while (cw > 64 && (int64_t)g.Hkv * g.M * (4096 / cw) < 256) cw /= 2;
+    hipLaunchKernelGGL(km_update12<DSUB>, dim3((unsigned)(g.Hkv * g.M * (4096 / cw))), dim3(kKwThreads), kw_lds(DSUB), st, x, w,
+                       codes, cb_in, cb_out, wsum_out, objective, n_tok, (int64_t)g.B * n_tok, g.Hkv, cw);
     return hipGetLastError();
 }
 
@@ -328,13 +484,13 @@ hipError_t launch_kmeans_update(const Geom& g, const half_t* x, const float* w, 
                                 hipStream_t st)
 {
     if (g.C == 4096) {
-        if (g.d == 32) return launch_t<32, true>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
-        return launch_t<16, true>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
+        if (g.d == 32) return launch_wide<32>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, st);
+        return launch_wide<16>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, st);
     }
     switch (g.d) {
-    case 4: return launch_t<4, false>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
-    case 8: return launch_t<8, false>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
-    default: return launch_t<16, false>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
+    case 4: return launch_t<4>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
+    case 8: return launch_t<8>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
+    default: return launch_t<16>(g, x, w, n_tok, cb_in, cb_out, codes, wsum_out, objective, (char*)ws, st);
     }
 }
 

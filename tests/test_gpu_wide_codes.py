@@ -318,6 +318,26 @@ def test_kmeans12_step(oracle, books, B, n):
     print(f"d{books.d} n={n}: near-tie codes {soft}, centroids without weight {int(empty.sum())} of {empty.size}")
 
 
+@pytest.mark.parametrize("B,n,distinct", [(3, 13001, 2), (1, 32769, 40), (5, 4099, 4099)])
+def test_kmeans12_update_crowded(oracle, books, B, n, distinct):
+    """More tokens of one range of centroids than a sorted chunk holds, runs over many windows, chunks that end inside a
+    sequence.  Sums of up to 32 products per window, 256 windows and 5 chunks in fp32: within 300 * 2^-24 of the sum of
+    magnitudes."""
+    _, rows, _ = make_qkv(107, B, 2, 2, distinct, 1, 128, want_v=False)
+    x = rows[:, :, np.random.default_rng(n).integers(0, distinct, n)]
+    w = np.random.default_rng(n + 1).gamma(0.5, 1.0, size=(B, 2, n)).astype(np.float32)
+    cb = books[0]
+    new, codes, wsum, obj = antkv.kmeans_step(antkv.Geometry(B, 2, 2, books.d, n_centroids=C), dev(x), dev(w), dev(cb))
+    codes_h = unpack12(codes.cpu().numpy())
+    want, want_w, want_obj = oracle.kmeans_update(x, w, codes_h, cb)
+    mag, _, _ = oracle.kmeans_update(np.abs(x), w, codes_h, np.abs(cb))
+    np.testing.assert_allclose(wsum.cpu().numpy(), want_w, rtol=2e-5, atol=1e-30)
+    np.testing.assert_allclose(obj.cpu().numpy(), want_obj, rtol=2e-5)
+    got = new.cpu().numpy()
+    assert np.array_equal(got[want_w == 0], cb[want_w == 0])
+    assert (np.abs(got.astype(np.float64) - want) <= np.abs(want) * 2.0 ** -10 + 2.0 ** -24 + 4e-5 * mag).all()
+
+
 def test_kmeans12_iterations_descend(oracle, books):
     _, x, _ = make_qkv(103, 2, 2, 2, 6000, 1, 128, want_v=False)
     w = np.random.default_rng(3).gamma(0.5, 1.0, size=(2, 2, 6000)).astype(np.float32)
