@@ -150,6 +150,15 @@ struct DecodeArgs {
 };
 int set_decode_options(int options);   // ANTKV_DECODE_* mask; returns the previous mask
 int decode_num_splits(const Geom& g, int64_t N);
+// Token ranges per (sequence, KV head) for kernels of one workgroup per CU: at most 256 workgroups in all, since a 257th waits
+// for a whole range and nearly doubles the launch, and at least about 1024 tokens each.  24 pairs x 57003 tokens, keys before
+// RoPE: with 11 ranges (264 workgroups) the score kernel takes 77 us and the decode kernel 36, with 10 ranges 51 and 22.
+inline int64_t token_ranges(int64_t pairs, int64_t N)
+{
+    const int64_t fill = pairs > 0 && pairs < 256 ? 256 / pairs : 1, most = (N + 1023) / 1024;
+    const int64_t S = fill < most ? fill : most;
+    return S < 1 ? 1 : S;
+}
 size_t decode_workspace_bytes(const Geom& g, int64_t N, int64_t k_k, int64_t k_v, bool want_ans);
 hipError_t launch_decode_attn(const Geom& g, const DecodeArgs& a, void* ws, hipStream_t st);
 // scores_out fp32 = scale * log2(e) * q_h . RoPE_{pos0 + j}(K_eff[j]) for the group's heads (K_eff: the FP16 anchor row or the

@@ -857,10 +857,7 @@ D12Plan d12_plan(const Geom& g, int64_t N)
 {
     D12Plan pl;
     const int64_t bgc = (int64_t)g.B * g.Hkv;
-    int64_t S = (256 + bgc - 1) / bgc;                                 // about one workgroup per CU
-    const int64_t s_max = (N + 1023) / 1024;
-    if (S > s_max) S = s_max;
-    if (S < 1) S = 1;
+    int64_t S = token_ranges(bgc, N);
     int64_t chunk = ((N + S - 1) / S + 63) / 64 * 64;
     if (chunk > kChunkMax) chunk = kChunkMax;
     if (chunk < 64) chunk = 64;

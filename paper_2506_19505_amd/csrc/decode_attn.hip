@@ -1939,10 +1939,7 @@ DaPlan da_plan(const Geom& g, int64_t N, int64_t k_k, int64_t k_v, bool want_ans
 {
     DaPlan pl;
     const int64_t bg = (int64_t)g.B * g.Hkv;
-    int64_t S = (256 + bg - 1) / bg;                 // about one stream workgroup per CU
-    const int64_t max_S = (N + 1023) / 1024;         // at least ~1024 tokens per split
-    if (S > max_S) S = max_S;
-    if (S < 1) S = 1;
+    const int64_t S = token_ranges(bg, N);
     int64_t chunk = (N + S - 1) / S;
     chunk = (chunk + 63) / 64 * 64;
     if (chunk > 32768) chunk = 32768;

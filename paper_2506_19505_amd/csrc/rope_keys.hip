@@ -444,10 +444,7 @@ hipError_t launch_rope_scores(const Geom& g, const half_t* q, float scale, const
     p.N = N; p.N_cap = N_cap; p.pos0 = pos0; p.k = (int)k_k; p.Hq = g.Hq; p.Hkv = g.Hkv; p.G = g.G;
     p.c1 = scale * kLog2e; p.log2_base = log2(rope_base);
     const int64_t bg = (int64_t)g.B * g.Hkv;
-    int64_t S = (256 + bg - 1) / bg;                                  // about one workgroup per CU
-    const int64_t max_S = (N + 1023) / 1024;
-    if (S > max_S) S = max_S;
-    if (S < 1) S = 1;
+    const int64_t S = token_ranges(bg, N);
     int64_t chunk = ((N + S - 1) / S + kRsTile - 1) / kRsTile * kRsTile;
     p.chunk = chunk;
     p.S = (int)((N + chunk - 1) / chunk);

@@ -55,6 +55,14 @@ def test_decode_small(oracle, d, B, Hq, Hkv, N):
     _check_out(got, want, f"decode d={d} N={N}")
 
 
+@pytest.mark.parametrize("B,Hkv,N", [(3, 8, 11300), (3, 1, 90000), (43, 3, 2100), (257, 1, 70)])
+def test_decode_pair_counts(oracle, B, Hkv, N):
+    """Numbers of (sequence, KV head) pairs that do not divide the 256 workgroups of a launch, and more pairs than that."""
+    c = _cache_from_kv(oracle, 36, B, Hkv, Hkv, N, 8, 5, 5, anchors="random")
+    got, want = _run_decode(oracle, c, antkv.Geometry(B, Hkv, Hkv, 8), 1 / np.sqrt(128))
+    _check_out(got, want, f"decode B={B} Hkv={Hkv} N={N}")
+
+
 @pytest.mark.parametrize("G", [1, 2])
 def test_decode_other_group_sizes(oracle, G):
     B, Hkv, N, d = 1, 2, 700, 8
