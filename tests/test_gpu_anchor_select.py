@@ -44,6 +44,12 @@ def test_anchor_select_wide_key_blocks(oracle, B, Hq, Hkv, N, Nq):
     _run(oracle, 27, B, Hq, Hkv, N, Nq, 40)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(1, 4, 1, 1024, 31), (1, 4, 2, 1025, 32), (2, 2, 2, 2081, 33), (1, 8, 2, 9217, 64)])
+def test_anchor_select_key_ranges(oracle, B, Hq, Hkv, N, Nq):
+    """Phase 1 of a query window split over keys: one range, a last range of a few keys, queries inside the last ranges."""
+    _run(oracle, 28, B, Hq, Hkv, N, Nq, anchor_count(N))
+
+
 def test_anchor_select_k_edges(oracle):
     _run(oracle, 22, 1, 4, 1, 200, 200, 0)
     _run(oracle, 22, 1, 4, 1, 200, 200, 200)
