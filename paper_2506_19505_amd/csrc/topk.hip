@@ -133,6 +133,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     constexpr int kPer = kSlice / kTopkThreads;                 // 32 scores per thread, in 8 groups of 4
     uint32_t key[kPer];
     const bool fast = hi - lo == kSlice && (((uintptr_t)(src + lo)) & 15) == 0;
+    const int n_own = (int)(hi - lo);
     // element j of the thread sits at position lo + pos(j)
     auto pos = [&](int j) -> int { return fast ? 4 * (tid + kTopkThreads * (j >> 2)) + (j & 3) : tid + kTopkThreads * j; };
     if (fast) {
@@ -142,11 +143,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
 #pragma unroll
             for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(v[e]);
         }
-    } else {                                                    // past the end: key 0, below every score's and in no bin that is looked at
-        const int n_own = (int)(hi - lo);
+    } else {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) key[j] = pos(j) < n_own ? float_key(src[lo + pos(j)]) : 0u;
     }
+    // (negative NaNs share the lowest bin with the zeros past the end: those are left out by position)
+    auto in = [&](int j) -> bool { return fast || pos(j) < n_own; };
     uint32_t d0, k_rem;
     find_digit(hist0, kBins, k, d0, k_rem, sh);
     const bool crowded = hist0[d0] > cap;                       // the same for every workgroup of the row
@@ -169,8 +171,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     for (int j = 0; j < kPer; ++j) {
         const uint32_t p = key[j] >> kShift;
         // LEVEL 2 counts only keys of bin d0 (higher bins were counted by LEVEL 1)
-        gt += p > prefix && (LEVEL == 1 || (key[j] >> 21) == d0);
-        eq += p == prefix;
+        gt += in(j) && p > prefix && (LEVEL == 1 || (key[j] >> 21) == d0);
+        eq += in(j) && p == prefix;
     }
     // block-wide: total of gt, exclusive prefix of eq
     uint32_t ieq = eq;
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
         uint2_t* out = cand + row * (int64_t)cap;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            if ((key[j] >> kShift) == prefix) {
+            if (in(j) && (key[j] >> kShift) == prefix) {
                 if (at < cap) out[at] = uint2_t{key[j], (uint32_t)(lo + pos(j))};
                 ++at;
             }
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     } else if (LEVEL == 1) {                                    // crowded bin: its next 11 bits go to the second histogram
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            if ((key[j] >> 21) == d0) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
+            if (in(j) && (key[j] >> 21) == d0) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
         }
         __syncthreads();
         for (int i = tid; i < kBins; i += kTopkThreads)

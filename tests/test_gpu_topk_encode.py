@@ -61,6 +61,21 @@ def test_topk_row_sizes(oracle, N):
         assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), oracle.topk(s, k))
 
 
+def test_topk_negative_nans_in_a_short_last_slice():
+    """NaNs with the sign bit and a full payload have the lowest keys of all, the bin that unused registers of the last
+    slice fall into as well: one score in that slice, and a candidate list that holds the NaNs but not 8191 entries more."""
+    N, n_nan = 32768 + 8192 + 1, 2000
+    rng = np.random.default_rng(5)
+    s = rng.random((2, N)).astype(np.float32)
+    nan = np.sort(rng.permutation(N - 1)[:n_nan])
+    s.view(np.uint32)[:, nan] = 0xffffe000 + (np.arange(n_nan) % 7).astype(np.uint32)
+    bits = s.view(np.uint32)
+    key = np.where(bits >> 31 == 1, ~bits, bits | 0x80000000)
+    for k in (N - n_nan + 1, N - 1000, N):
+        want = np.sort(np.argsort(0xffffffff - key.astype(np.int64), axis=1, kind="stable")[:, :k], axis=1)
+        assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("d", [4, 8, 16])
 @pytest.mark.parametrize("B,Hq,Hkv,n", [(2, 4, 2, 333), (1, 8, 8, 70)])
 def test_encode_matches_oracle(oracle, d, B, Hq, Hkv, n):
