@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -37,9 +38,6 @@ class Geometry:
     D: int = 128
     n_centroids: int = 256
 
-    def __post_init__(self):
-        object.__setattr__(self, "_c", self.c())      # built once: a call passes it by reference and reads it only
-
     @property
     def M(self) -> int:
         return self.D // self.d_sub
@@ -51,6 +49,11 @@ class Geometry:
 
     def c(self) -> _Geom:
         return _Geom(self.B, self.Hq, self.Hkv, self.D, self.d_sub, self.n_centroids)
+
+    @functools.cached_property
+    def _c(self) -> _Geom:
+        """Built on first use: a call passes it by reference and only reads it."""
+        return self.c()
 
 
 def lib_path() -> str:

@@ -144,3 +144,14 @@ def test_decode_options_and_prerope_argument_errors(lib):
     assert call(10000.0, 1, 0, ws=None) == EWORKSPACE
     assert call(10000.0, 1, 0, nbytes=ws_bytes - 1) == EWORKSPACE
 
+
+
+def test_geometry_restored_from_its_fields():
+    """A Geometry saved with its six fields only, as a pickle or a copied __dict__ holds them, is complete."""
+    import pickle
+
+    geom = antkv.Geometry(2, 32, 8, 16, n_centroids=4096)
+    saved = object.__new__(antkv.Geometry)
+    saved.__dict__.update(B=2, Hq=32, Hkv=8, d_sub=16, D=128, n_centroids=4096)
+    for g in (saved, pickle.loads(pickle.dumps(geom))):
+        assert g == geom and bytes(g._c) == bytes(geom.c())
