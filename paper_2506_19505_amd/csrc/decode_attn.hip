@@ -130,14 +130,22 @@ __device__ __forceinline__ float lane_bcast(float v, int src_lane)
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src_lane));
 }
 
-// Table entries of two heads: x rounded to a multiple of its unit, q = rint(x * inv) with |q| <= kLutMax, as the two signed
-// bytes (lo, -hi), q = lo + 128 hi with lo = q mod 128.  kRound pushes the fraction out of the mantissa, so that the low
-// half of the sum is q itself; two heads are then split in packed 16-bit arithmetic: lo - 256 hi = 3 lo - 2 q.
 constexpr float kRound = 12582912.f;   // 1.5 * 2^23
+// kRound + rint(x * inv) for |x * inv| < 2^22: the addition pushes the fraction out of the mantissa, so that the low bits of the
+// sum are the rounded product.  The product is rounded to fp32 first; a fused multiply-add rounds once, and one table entry in
+// a thousand would be a unit off what rint of the product gives.
+__device__ __forceinline__ float round_product(float x, float inv)
+{
+#pragma clang fp contract(off)
+    return x * inv + kRound;
+}
+// Table entries of two heads: x rounded to a multiple of its unit, q = rint(x * inv) with |q| <= kLutMax, as the two signed
+// bytes (lo, -hi), q = lo + 128 hi with lo = q mod 128.  The low half of round_product is q itself; two heads are then split in
+// packed 16-bit arithmetic: lo - 256 hi = 3 lo - 2 q.
 __device__ __forceinline__ uint32_t table_pair(float x0, float x1, float inv0, float inv1)
 {
     typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
-    const uint32_t a = __float_as_uint(fmaf(x0, inv0, kRound)), b = __float_as_uint(fmaf(x1, inv1, kRound));
+    const uint32_t a = __float_as_uint(round_product(x0, inv0)), b = __float_as_uint(round_product(x1, inv1));
     const uint32_t q2 = __builtin_amdgcn_perm(b, a, 0x05040100u);
     const ushort2_t lo = __builtin_bit_cast(ushort2_t, q2 & 0x007f007fu);
     return __builtin_bit_cast(uint32_t, (ushort2_t)(lo * (unsigned short)3 - __builtin_bit_cast(ushort2_t, q2) * (unsigned short)2));
@@ -299,34 +307,29 @@ __device__ void wg_merge_and_store(char* smem, float (&m_ref)[kNH], float (&l_su
         for (int rho = 0; rho < 4; ++rho)
             s_mrg[(wave * 4 + cls) * kD + 16 * (4 * a + ((cls + rho) & 3)) + n] = acc[a][rho] * f;
     lds_barrier();
-    // 64 rows (wave, class) to 8 with 16-byte reads, then the 8 to one
-    constexpr int kParts = kDaThreads / kD, kRows = kDaWaves * 4 / kParts;
-    float4_t* s_sum = (float4_t*)(smem + Lds<DSUB>::pst);            // [part][channel] x 4 heads (the staging areas are free by now)
-    static_assert(kParts * kD * 16 <= kDaWaves * kStgBytes, "the parts fit the staging areas");
+    // 64 rows (wave, class) to four chains, every fourth row each, then the four to one.  A thread takes two heads of a channel
+    // of a chain, its 16 reads of 8 bytes in flight together (8 heads, 4096 tokens, d8: the call takes 15.3 us; with eight rows and
+    // 16-byte reads per thread 16.5, with 64 four-byte reads per thread 17.2).
+    typedef float pair_t __attribute__((ext_vector_type(2)));
+    constexpr int kChains = 4, kRows = kDaWaves * 4 / kChains;
+    static_assert(kDaThreads == kChains * kD * kNH / 2, "a thread per chain, channel and pair of heads");
+    pair_t* s_sum = (pair_t*)(smem + Lds<DSUB>::pst);                // [chain][channel] x 4 heads (the staging areas are free by now)
+    static_assert(kDaThreads * 8 <= kDaWaves * kStgBytes, "the chains fit the staging areas");
     {
-        const float4_t* src = s_mrg + (tid >> 7) * kRows * kD + (tid & (kD - 1));
-        float4_t v[kRows];
+        const pair_t* src = (const pair_t*)s_mrg + (tid >> 8) * kD * 2 + (tid & (2 * kD - 1));
+        pair_t v[kRows], sum = {0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < kRows; ++u) v[u] = src[u * kD];
+        for (int u = 0; u < kRows; ++u) v[u] = src[u * kChains * kD * 2];
 #pragma unroll
-        for (int off = kRows / 2; off >= 1; off >>= 1)
-#pragma unroll
-            for (int u = 0; u < off; ++u) v[u] += v[u + off];
-        s_sum[tid] = v[0];
+        for (int u = 0; u < kRows; ++u) sum += v[u];
+        s_sum[tid] = sum;
     }
     lds_barrier();
     if (tid < kNH * kD) {
         const int h = tid & 3, dim = tid >> 2;                   // consecutive threads read consecutive dwords
         const float* src = (const float*)s_sum + tid;
-        float s8[kParts];
-#pragma unroll
-        for (int u = 0; u < kParts; ++u) s8[u] = src[u * kD * 4];
-#pragma unroll
-        for (int off = kParts / 2; off >= 1; off >>= 1)
-#pragma unroll
-            for (int u = 0; u < off; ++u) s8[u] += s8[u + off];
         if (h < nheads) {
-            const float s = s8[0];
+            const float s = (src[0] + src[kNH * kD]) + (src[2 * kNH * kD] + src[3 * kNH * kD]);
             float* dst = part_bg + ((int64_t)h * slots + slot) * (kD + 2);
             // Device-scope stores: they write through this die's L2, so the merging workgroup (possibly
             // on another die) can read them without any cache write-back.
@@ -405,11 +408,10 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
 
     int* s_misc = (int*)(smem + L::red + kDaWaves * 32);
     uint32_t* s_mask = (uint32_t*)(smem + L::mask);
-    // The first anchor tile of this wave (of tiles sp, sp + S, ... of the (sequence, KV head)'s tiles): its tokens, their cross
+    // The first anchor tile of this wave (tile sp + S * wave of the (sequence, KV head)'s tiles): its tokens, their cross
     // membership and their code rows are fetched during the prologue, while the memory system is idle, so that the
     // tile itself is left with a single round trip (the FP16 rows).
-    // The last wave takes the first tile: a short range has no stream tile for the last waves.
-    const int T_first = sp + p.S * (kDaWaves - 1 - wave);
+    const int T_first = sp + p.S * wave;
     int pre_tok = 0, pre_info = 0;
     uint32_t pre_codes[CW];
 #pragma unroll
@@ -732,7 +734,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
                 float rest[kNH], unit[kNH];
 #pragma unroll
                 for (int h = 0; h < kNH; ++h) {
-                    const float first = fmaf(val[j][h], inv_q[h], kRound) - kRound;
+                    const float first = round_product(val[j][h], inv_q[h]) - kRound;
                     rest[h] = val[j][h] - first * quantum[h];
                     unit[h] = inv_q[h] * (2.f * kLutMax);
                 }
@@ -1495,9 +1497,10 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
         auto ld = [](const float* q) { return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
         constexpr int kOneRound = 32;
         if (p.S <= kOneRound) {
-            // one round trip: statistics and accumulators of all slots are requested together (two threads per (head,
-            // channel), every second slot each), the weights are worked out while the accumulators are on their way
-            const int S = p.S;
+            // one round trip: statistics and accumulators of all slots are requested together, the weights are worked out while
+            // the accumulators are on their way.  Eight sums per (head, channel), slot s in sum s mod 8 and the slots behind
+            // the last eight in the first, as with more slots; two threads share them.
+            const int S = p.S, rest0 = S & ~7;
             float m = kNegBig, l = 0.f;
             if (tid < kNH * kOneRound) {
                 const int h = tid >> 5, sl = tid & 31;
@@ -1508,12 +1511,15 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
                 }
             }
             const int half = tid >> 9, hd = tid & (kNH * kD - 1), h = hd >> 7, dim = hd & (kD - 1);
-            float v[kOneRound / 2];
+            const float* pb = part_bg + (int64_t)h * S * (kD + 2) + dim;
+            float v[kOneRound / 8][4], r[7];
 #pragma unroll
-            for (int u = 0; u < kOneRound / 2; ++u) {
-                const int sl = 2 * u + half;
-                v[u] = (h < nheads && sl < S) ? ld(part_bg + ((int64_t)h * S + sl) * (kD + 2) + dim) : 0.f;
-            }
+            for (int i = 0; i < kOneRound / 8; ++i)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    v[i][u] = (h < nheads && 8 * i < rest0) ? ld(pb + (8 * i + 4 * half + u) * (kD + 2)) : 0.f;
+#pragma unroll
+            for (int u = 0; u < 7; ++u) r[u] = (h < nheads && !half && rest0 + u < S) ? ld(pb + (rest0 + u) * (kD + 2)) : 0.f;
             float* s_w = (float*)(smem + L::mrg);                   // [4 heads][32]: slot weights 2^(m_s - m)
             float* s_tot = s_w + kNH * kOneRound;                   // [4]: total l per head
             float* s_half = s_tot + kNH;                            // [4][128]: the second thread's share
@@ -1521,21 +1527,30 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
                 float mm = row16_max(m);
                 mm = fmaxf(mm, __shfl_xor(mm, 16, 64));
                 const float w = fast_exp2(m - mm);                  // (slots that do not exist: l = 0 and no accumulator)
-                float t = row16_sum(l * w);
+                float t = l * w;                                    // summed over lane distances 16, 8, 4, 2, 1, as wave_sum does
                 t += __shfl_xor(t, 16, 64);
+                t += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, t), 0x128, 0xf, 0xf, true));   // row_ror:8
+                t += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, t), 0x124, 0xf, 0xf, true));   // row_ror:4
+                t += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, t), 0x4E, 0xf, 0xf, true));    // quad_perm [2,3,0,1]
+                t += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, t), 0xB1, 0xf, 0xf, true));    // quad_perm [1,0,3,2]
                 s_w[tid] = w;
                 if ((tid & 31) == 0) s_tot[tid >> 5] = t;
             }
             lds_barrier();
-            float a = 0.f;
+            const float* w_h = s_w + h * kOneRound;
+            float a[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < kOneRound / 2; ++u) a = fmaf(v[u], s_w[h * kOneRound + 2 * u + half], a);
-            if (half) s_half[hd] = a;
+            for (int i = 0; i < kOneRound / 8; ++i)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) a[u] = fmaf(v[i][u], w_h[8 * i + 4 * half + u], a[u]);
+#pragma unroll
+            for (int u = 0; u < 7; ++u) a[0] = fmaf(r[u], rest0 + u < S ? w_h[rest0 + u] : 0.f, a[0]);
+            const float own = (a[0] + a[1]) + (a[2] + a[3]);
+            if (half) s_half[hd] = own;
             lds_barrier();
             if (!half && h < nheads) {
-                a += s_half[hd];
                 const float lt = s_tot[h];
-                p.out[((int64_t)b * p.Hq + h0 + h) * kD + dim] = (half_t)(lt > 0.f ? a / lt : 0.f);
+                p.out[((int64_t)b * p.Hq + h0 + h) * kD + dim] = (half_t)(lt > 0.f ? (own + s_half[hd]) / lt : 0.f);
             }
             return;
         }

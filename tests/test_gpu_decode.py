@@ -404,3 +404,27 @@ def test_decode_random_shapes(oracle):
         geom = antkv.Geometry(B, Hq, Hkv, d)
         res, want = _run_decode(oracle, c, geom, 1 / np.sqrt(128), N=N)
         _check_out(res, want, f"case {case}: B{B} Hkv{Hkv} G{G} d{d} N{N}/{N_cap} anchors {k_k}/{k_v}")
+
+
+def _step_in_fixed_order(d, N):
+    """A decode step whose ranges hold at most one tile per wave: nothing in it is handed out dynamically."""
+    B, Hq, Hkv, M, k = 1, 8, 2, 128 // d, 70
+    geom = antkv.Geometry(B, Hq, Hkv, d)
+    codes = [dev(random_codes(9, w, B, Hkv, N, M)) for w in "kv"]
+    books = [dev(normal_fp16(9, w, (Hkv, M, 256, d))) for w in "kv"]
+    idx = [dev(random_anchor_sets(9, w, B, Hkv, N, k).astype(np.int32)) for w in "kv"]
+    rows = [dev(normal_fp16(9, "rows_" + w, (B, Hkv, k, 128))) for w in "kv"]
+    q = dev(normal_fp16(9, "q_decode", (B, Hq, 128)))
+    return antkv.decode_attn(geom, q, 1 / np.sqrt(128), *codes, *books, idx[0], rows[0], idx[1], rows[1]).cpu().numpy()
+
+
+# 3 and 20 ranges: sums over the waves, over eight slots at a time and over the slots that are left
+@pytest.mark.parametrize("d,N,bits", [(4, 2500, "77a12fd33050ce04"), (8, 2500, "7f583cc3e891b0e0"), (16, 2500, "6f110897e67013e2"),
+                                      (4, 20000, "180519fc40281f89"), (8, 20000, "6d93124f18e111dc"), (16, 20000, "b60fb7e787f6cc4c")])
+def test_decode_rounding_is_pinned(d, N, bits):
+    """The assignment of tiles to waves (each wave rounds its fp16 weights against a reference of its own), the rounding of the
+    table entries and the order of the fp32 sums are part of the result: a short step repeats itself bit for bit, from one
+    version of the library to the next.  `bits` is the digest of the output."""
+    import hashlib
+
+    assert hashlib.sha256(_step_in_fixed_order(d, N).tobytes()).hexdigest()[:16] == bits
