@@ -131,24 +131,28 @@ __device__ __forceinline__ float lane_bcast(float v, int src_lane)
 }
 
 constexpr float kRound = 12582912.f;   // 1.5 * 2^23
-// kRound + rint(x * inv) for |x * inv| < 2^22: the addition pushes the fraction out of the mantissa, so that the low bits of the
-// sum are the rounded product.  The product is rounded to fp32 first; a fused multiply-add rounds once, and one table entry in
-// a thousand would be a unit off what rint of the product gives.
+// rint(x * inv) + kRound + BIAS for |x * inv| < 2^22 and a small even BIAS: the addition pushes the fraction out of the mantissa,
+// so that the low bits of the sum are the rounded product plus BIAS.  The product is rounded to fp32 first; a fused multiply-add
+// rounds once, and one table entry in a thousand would be a unit off what rint of the product gives.
+template <int BIAS>
 __device__ __forceinline__ float round_product(float x, float inv)
 {
 #pragma clang fp contract(off)
-    return x * inv + kRound;
+    return x * inv + (kRound + (float)BIAS);
 }
-// Table entries of two heads: x rounded to a multiple of its unit, q = rint(x * inv) with |q| <= kLutMax, as the two signed
-// bytes (lo, -hi), q = lo + 128 hi with lo = q mod 128.  The low half of round_product is q itself; two heads are then split in
-// packed 16-bit arithmetic: lo - 256 hi = 3 lo - 2 q.
+// Table entries of two heads: x in units of 1 / inv, q = rint(x * inv), as the two signed bytes (lo, -hi) with q = lo + 128 hi and
+// lo in [-64, 63], which holds |q| <= 16319.  First entries reach kLutMax = 16256, residual entries of the wide table up to 60
+// more: inv and the quantum are rounded, and 16256 levels of that error in units of quantum / 32512 come to as much.  The low half
+// of round_product is u = q + 64; two heads are then split in packed 16-bit arithmetic: with v = u mod 128, lo = v - 64 and
+// -256 hi = 2 (v - u), whose low byte is zero.
 __device__ __forceinline__ uint32_t table_pair(float x0, float x1, float inv0, float inv1)
 {
     typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
-    const uint32_t a = __float_as_uint(round_product(x0, inv0)), b = __float_as_uint(round_product(x1, inv1));
-    const uint32_t q2 = __builtin_amdgcn_perm(b, a, 0x05040100u);
-    const ushort2_t lo = __builtin_bit_cast(ushort2_t, q2 & 0x007f007fu);
-    return __builtin_bit_cast(uint32_t, (ushort2_t)(lo * (unsigned short)3 - __builtin_bit_cast(ushort2_t, q2) * (unsigned short)2));
+    const uint32_t a = __float_as_uint(round_product<64>(x0, inv0)), b = __float_as_uint(round_product<64>(x1, inv1));
+    const uint32_t u2 = __builtin_amdgcn_perm(b, a, 0x05040100u);
+    const ushort2_t u = __builtin_bit_cast(ushort2_t, u2), v = __builtin_bit_cast(ushort2_t, u2 & 0x007f007fu);
+    const uint32_t hi = __builtin_bit_cast(uint32_t, (ushort2_t)((v - u) * (unsigned short)2));
+    return hi | (__builtin_bit_cast(uint32_t, (ushort2_t)(v + (unsigned short)192)) & 0x00ff00ffu);
 }
 
 // first index in arr[0..n) whose value is >= key; executed by a whole wave, result uniform
@@ -726,7 +730,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
             }
         }
         if constexpr (WIDE) {
-            // Residual entries, in units of quantum / (2 kLutMax) (|.| <= kLutMax), replace the odd copies: copy c of
+            // Residual entries, in units of quantum / (2 kLutMax) (|.| <= kLutMax + 60), replace the odd copies: copy c of
             // sub-space m is then the pair of slots m + 2 M c (first entry) and m + M + 2 M c (residual).
             static_assert(!WIDE || REPS >= 2, "the residual entries live in the slots of the copies");
 #pragma unroll
@@ -734,7 +738,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
                 float rest[kNH], unit[kNH];
 #pragma unroll
                 for (int h = 0; h < kNH; ++h) {
-                    const float first = round_product(val[j][h], inv_q[h]) - kRound;
+                    const float first = round_product<0>(val[j][h], inv_q[h]) - kRound;
                     rest[h] = val[j][h] - first * quantum[h];
                     unit[h] = inv_q[h] * (2.f * kLutMax);
                 }

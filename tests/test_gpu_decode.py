@@ -128,6 +128,53 @@ def test_decode_wide_table(oracle, d, gain):
     _check_out(got, want, f"wide table d={d} query gain {gain}")
 
 
+def _residuals(scale, a, x):
+    """Residual entries of the wide table, in its units, for entries c1 * a * x of a table whose largest entry is c1 * a * 16256:
+    the kernel's own fp32 steps."""
+    f = np.float32
+    c1 = f(f(scale) * f(1.4426950408889634))
+    val = (f(a) * x.astype(f)) * c1
+    r = np.abs(f(a) * f(16256) * c1)
+    inv, quantum = f(16256) / r, r / f(16256)
+    rest = (val.astype(np.float64) - np.rint(val * inv).astype(np.float64) * np.float64(quantum)).astype(f)
+    return np.rint(rest * (inv * f(32512)))
+
+
+@pytest.mark.parametrize("d", [8, 16])
+@pytest.mark.parametrize("scale,a", [(0.004019, 1.0), (0.013349, 1.171875), (0.03955, -1.1328125)])     # R_h 94, 367, 1051
+def test_decode_wide_table_residuals_at_half_a_quantum(oracle, d, scale, a):
+    """Entries half a quantum above a multiple of it: their residuals reach -16256 units and, with the rounding of the quantum and
+    of its reciprocal, a few units more.  Tokens with such entries compete with tokens half a quantum below them, whose V rows
+    are -1/2 times theirs: a residual that is off by one quantum shifts the weights by 0.4 % (R_h = 94) to 4.5 % (1051) and the
+    output by about three times that."""
+    B, Hq, Hkv, M, C = 1, 4, 1, 128 // d, 256
+    x = np.arange(16000, 16016) + 0.5
+    res = _residuals(scale, a, x)
+    x = x[res < -16256]
+    assert x.size == 16 and _residuals(scale, a, x - 0.5).min() > -16256
+    n = x.size
+    hi = np.floor(np.concatenate([x, x - 0.5]) / 8) * 8                       # fp16 holds multiples of 8 and the rest beside them
+    cbk = np.zeros((Hkv, M, C, d), np.float16)
+    cbk[0, 0, 1:2 * n + 1, 0], cbk[0, 0, 1:2 * n + 1, 1] = hi, np.concatenate([x, x - 0.5]) - hi
+    cbk[0, 0, 255, 0] = 16256                                                # sets the range; no token has it
+    cbv = normal_fp16(41, "v", (Hkv, M, C, d))
+    cbv[:, :, 2] = -0.5 * cbv[:, :, 1]
+    N = 64 * n
+    ck, cv = np.zeros((B, Hkv, N, M), np.uint8), np.zeros((B, Hkv, N, M), np.uint8)
+    ck[..., 0] = 1 + np.arange(N) % (2 * n)
+    cv[:] = np.where(np.arange(N) % (2 * n) < n, 1, 2)[None, None, :, None]
+    q = np.zeros((B, Hq, 128), np.float16)
+    q[0, :, :2] = np.array([a, -a, 1.3125, -1.3125])[:, None]
+    none = np.zeros((B, Hkv, 0), np.int32), np.zeros((B, Hkv, 0, 128), np.float16)
+    c = dict(q=q, ck=ck, cv=cv, cbk=cbk, cbv=cbv, ik=none[0], rk=none[1], iv=none[0], rv=none[1])
+    prev = antkv.set_decode_options(antkv.DECODE_WIDE_TABLE)
+    try:
+        got, want = _run_decode(oracle, c, antkv.Geometry(B, Hq, Hkv, d), scale)
+    finally:
+        antkv.set_decode_options(prev)
+    _check_out(got, want, f"wide table, d={d}, R_h {abs(a) * 16256 * scale * 1.4427:.0f}")
+
+
 def test_decode_tiny_contexts(oracle):
     B, Hq, Hkv, d = 2, 4, 1, 8
     for N in (1, 2, 63, 64, 65):
