@@ -46,6 +46,7 @@ constexpr int kEncThreads = 512;
 constexpr int kEncWaves = kEncThreads / 64;
 constexpr int kQuad = 4;               // sub-spaces of a workgroup
 constexpr float kNormScale = 16.f;     // see the norm terms in the kernel: sub-vector norms up to ||c||^2 = 2.09e6 stay finite
+constexpr float kNormLimit = 2.f * 65520.f * kNormScale;               // from here on the first term rounds to infinity
 
 // LDS layout per sub-vector width (halfs per centroid): the A operand of a lane is 8 consecutive halfs
 //   d = 4   one array  [4][256][8]  = {c0..c3, n_hi, n_mid, n_lo, 0}: lanes 0-31 read it, lanes 32-63 multiply by zero
@@ -87,24 +88,26 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
     __shared__ __attribute__((aligned(256))) half_t s_a[enc_a_halfs(DSUB)];            // see above
     __shared__ __attribute__((aligned(16))) half_t s_n[enc_n_halfs(DSUB)];             // d = 16 only: norm terms,
     __shared__ float s_f[DSUB == 16 ? kQuad * kC : 1];                                 // and their fp32 value
+    __shared__ uint64_t s_good[kQuad * kC / 64];                                       // centroids within the norm limit
+    static_assert(kQuad * kC / 64 == 16, "16 lanes read the words");
     const int tid = threadIdx.x;
     // heads fastest: with 8 heads each XCD works on one, and the workgroups that read the same token rows share its L2
     const int g = blockIdx.x % Hkv, quad = (blockIdx.x / Hkv) % NQ, chunk = blockIdx.x / (Hkv * NQ);
 
     // ---- the quad's centroids into LDS, with -||c||^2/2 as three fp16 terms per centroid
     const half_t* src = cb + ((size_t)g * M + quad * kQuad) * kC * DSUB;
-#pragma unroll
-    for (int e = tid; e < kQuad * kC; e += kEncThreads) {          // e = (sub-space, centroid)
+    // row e = (sub-space, centroid) takes centroid `from`; false if that one is beyond the norm limit (or not finite)
+    auto stage = [&](int e, int from) -> bool {
         half_t* row = s_a + (e ^ swizzle<DSUB>(e >> 2)) * kRow;
         float cf[DSUB];
         if constexpr (DSUB == 4) {
-            const half4_t v = *(const half4_t*)(src + e * 4);
+            const half4_t v = *(const half4_t*)(src + from * 4);
 #pragma unroll
             for (int t = 0; t < 4; ++t) cf[t] = (float)v[t];
         } else {
 #pragma unroll
             for (int u = 0; u < DSUB / 8; ++u) {
-                const half8_t v = *(const half8_t*)(src + e * DSUB + 8 * u);
+                const half8_t v = *(const half8_t*)(src + from * DSUB + 8 * u);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) cf[8 * u + t] = (float)v[t];
                 *(half8_t*)(row + 8 * u) = v;
@@ -129,6 +132,12 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
             *(half4_t*)(s_n + e * 4) = half4_t{n_hi, n_mid, n_lo, z};
             s_f[e] = -0.5f * nn;
         }
+        return __float_as_uint(nn) < __float_as_uint(kNormLimit);      // (as integers: a NaN is above every number)
+    };
+#pragma unroll
+    for (int e = tid; e < kQuad * kC; e += kEncThreads) {
+        const uint64_t good = __ballot(stage(e, e));
+        if ((tid & 63) == 0) s_good[e >> 6] = good;
     }
 
     const int lane = tid & 63;
@@ -173,6 +182,22 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
     int64_t unit = (int64_t)wave * chunks + chunk;
     if (unit < total) fetch(unit, bx);
     __syncthreads();
+    // Centroids beyond the norm limit are never chosen: their terms, which are infinities and NaN, give way to a copy of the
+    // sub-space's first good centroid.  A copy behind it loses the tie; one before it is told by its index.
+    int first_good[kQuad] = {0, 0, 0, 0};
+    if (__builtin_expect(__any(s_good[lane & 15] != ~0ull), 0)) {     // (the same in every wave)
+#pragma unroll
+        for (int mm = 0; mm < kQuad; ++mm) {
+            for (int i = kC / 64 - 1; i >= 0; --i) {
+                const uint64_t good = s_good[mm * (kC / 64) + i];
+                if (good != 0ull) first_good[mm] = 64 * i + __builtin_ctzll(good);
+            }
+            first_good[mm] = __builtin_amdgcn_readfirstlane(first_good[mm]);
+        }
+        for (int e = tid; e < kQuad * kC; e += kEncThreads)
+            if ((s_good[e >> 6] >> (e & 63) & 1) == 0) stage(e, (e & ~(kC - 1)) + first_good[e / kC]);
+        __syncthreads();
+    }
     while (unit < total) {
         const int64_t next = unit + (int64_t)chunks * kEncWaves;
         half8_t nx[kQuad];
@@ -255,14 +280,14 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
                 s01 += s_f[mm * kC + 4 * grp + h];
                 s23 += s_f[mm * kC + 4 * grp + 2 + h];
             }
-            // (compared with the maximum, so that a centroid beyond the norm limit, whose d = 4 score is not a number, loses)
             const float s_max = max2f(s01, s23);
             uint32_t m_lo, m_hi, e_lo, e_hi;
             halves(__float_as_uint(s_max), m_lo, m_hi);
             halves(s01 == s_max ? (uint32_t)h : (uint32_t)(2 + h), e_lo, e_hi);
             const float v_lo = __uint_as_float(m_lo), v_hi = __uint_as_float(m_hi);
             const bool odd = v_lo != max2f(v_lo, v_hi) || (v_lo == v_hi && e_hi < e_lo);
-            word |= (uint32_t)(4 * grp + (int)(odd ? e_hi : e_lo)) << (8 * mm);
+            const int code = 4 * grp + (int)(odd ? e_hi : e_lo);
+            word |= (uint32_t)(code > first_good[mm] ? code : first_good[mm]) << (8 * mm);
         }
         const int64_t b = unit / blocks_per_b, tok = (unit % blocks_per_b) * 32 + n;
         if (tok < n_tok && h == 0)

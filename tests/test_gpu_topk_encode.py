@@ -108,6 +108,35 @@ def test_encode_large_magnitudes(oracle, d):
     print(f"d={d}: largest ||c||^2 {norms.max():.3g}, near-tie disagreements {soft}")
 
 
+@pytest.mark.parametrize("d", [4, 8, 16])
+@pytest.mark.parametrize("over", ["first tile", "leading quads", "scattered", "all but the last", "infinite and NaN"])
+def test_encode_never_chooses_oversize_centroids(d, over):
+    """Centroids beyond ||c||^2 = 2.09e6 (and ones that are not finite) are never chosen, not even by a token that equals one: the
+    codes are the nearest among the others, wherever in the tiles and quads of the arg-max the oversize ones sit."""
+    B, Hkv, n, M, C = 1, 2, 200, 128 // d, 256
+    rng = np.random.default_rng(d)
+    bad = {"first tile": np.arange(32), "leading quads": np.r_[0:4, 40:44, 68:76], "scattered": rng.permutation(C)[:60],
+           "all but the last": np.arange(C - 1), "infinite and NaN": np.r_[0, 5, 33, 255]}[over]
+    cb = rng.standard_normal((Hkv, M, C, d)).astype(np.float16)
+    x = rng.standard_normal((B, Hkv, n, 128)).astype(np.float16)
+    size = np.sqrt(rng.uniform(2.1e6, 4e6, bad.size) / d)[:, None]           # ||c||^2 = 2.1e6 .. 4e6
+    cb[:, :, bad] = (size * rng.choice([-1.0, 1.0], (bad.size, d))).astype(np.float16)
+    x[..., :50, :] = cb[:, :, bad[np.arange(50) % bad.size]].transpose(0, 2, 1, 3).reshape(Hkv, 50, 128)
+    if over == "infinite and NaN":
+        cb[:, :, bad[0]], cb[:, :, bad[1]], cb[:, :, bad[2]], cb[:, :, bad[3], 0] = np.inf, np.nan, -np.inf, np.nan
+    good = np.setdiff1d(np.arange(C), bad)
+    got = antkv.encode(antkv.Geometry(B, Hkv, Hkv, d), dev(x), dev(cb)).cpu().numpy()
+    assert np.isin(got, good).all()
+    c = cb[:, :, good].astype(np.float64)
+    xs = x.astype(np.float64).reshape(B, Hkv, n, M, d)
+    score = np.einsum("bgnmd,gmcd->bgnmc", xs, c) - 0.5 * (c ** 2).sum(-1)[None, :, None]
+    mine = np.take_along_axis(score, np.searchsorted(good, got.astype(np.int64))[..., None], -1)[..., 0]
+    # d products of |x_i c_i| <= |x| |c| and the norm, summed in fp32
+    slack = (d + 4) * 2.0 ** -24 * (np.linalg.norm(xs, axis=-1) * np.sqrt((c ** 2).sum(-1).max()) + 0.5 * (c ** 2).sum(-1).max())
+    assert (mine >= score.max(-1) - 2 * slack).all()
+    assert (got == good[score.argmax(-1)])[..., 50:, :].mean() > 0.999
+
+
 def test_encode_duplicate_centroids_and_offsets(oracle):
     # fewer sample tokens than centroids -> duplicated centroids: the lower index must win exactly
     B, Hq, Hkv, n, d = 1, 2, 1, 100, 8
