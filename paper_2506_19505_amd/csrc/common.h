@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/antkv.h"
+#include "once_per_device.h"
 
 namespace antkv {
 
@@ -29,6 +30,19 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;   // stands for -inf in running maxima (exp2 of it is 0)
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
+
+template <typename Set>
+inline hipError_t on_this_device(OncePerDevice& once, Set&& set)
+{
+    int device = -1;
+    const hipError_t e = hipGetDevice(&device);
+    return e != hipSuccess ? e : once(device, set);
+}
+// lets `kernel` use `bytes` of dynamic LDS on the current device
+inline hipError_t allow_lds(OncePerDevice& once, const void* kernel, size_t bytes)
+{
+    return on_this_device(once, [=] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
+}
 
 // ---- device helpers -------------------------------------------------------------------------
 __device__ __forceinline__ float wave_max(float v)

@@ -881,11 +881,12 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, hipSt
 {
     const D12Plan pl = d12_plan(g, a.N);
     constexpr size_t lds = d12_lds(DS);
-    static const hipError_t setup = []() {
+    static OncePerDevice once;
+    const hipError_t setup = on_this_device(once, []() {
         const hipError_t e1 = hipFuncSetAttribute((const void*)decode12_kernel<DS, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e1 != hipSuccess) return e1;
         return hipFuncSetAttribute((const void*)decode12_kernel<DS, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    }();
+    });
     if (setup != hipSuccess) return setup;
     if ((int64_t)g.B * g.Hkv * pl.S > 0x7fffffffLL) return hipErrorInvalidValue;
     if ((int64_t)g.B * g.Hkv * a.k_v * kD * 2 >= 0x7fffffffLL) return hipErrorInvalidValue;   // 31-bit byte offsets into rows_v
@@ -908,13 +909,14 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, hipSt
     }
     hipLaunchKernelGGL(decode12_merge, dim3((unsigned)(g.B * g.Hq)), dim3(kD), 0, st, (const float*)p.part, p.S, a.out);
     if (a.ans_k && a.N > 0) {
-        static const hipError_t setup_ans = []() {
+        static OncePerDevice once_ans;
+        const hipError_t setup_ans = on_this_device(once_ans, []() {
             hipError_t e1 = hipFuncSetAttribute((const void*)d12_ans_kernel<DS, 0>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                 (int)kD12AnsLds);
             if (e1 != hipSuccess) return e1;
             return hipFuncSetAttribute((const void*)d12_ans_kernel<DS, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)kD12AnsLds);
-        }();
+        });
         if (setup_ans != hipSuccess) return setup_ans;
         D12AnsParams d;
         d.q = a.q; d.codes_k = a.codes_k; d.idx_k = a.idx_k; d.rows_k = a.rows_k; d.tab = p.tab;

@@ -2015,9 +2015,10 @@ static hipError_t launch_decode_t(const Geom& g, const DecodeArgs& a, void* ws, 
     }
     if (pl.S > 1024) return hipErrorInvalidValue;        // the in-kernel merge keeps one weight per slot in LDS
     const size_t shmem = Lds<DSUB>::total;
-    // One-time set-up per instantiation (and per process): raise the dynamic LDS limit, and make sure the kernel has
+    // One-time set-up per instantiation and device: raise the dynamic LDS limit, and make sure the kernel has
     // no static LDS — its table gathers use absolute LDS addresses, which assumes the dynamic block starts at 0.
-    static const hipError_t setup = [] {
+    static OncePerDevice once;
+    hipError_t e = on_this_device(once, [] {
         for (const void* f : {(const void*)decode_attn_kernel<DSUB, 0>, (const void*)decode_attn_kernel<DSUB, 1>,
                               (const void*)decode_attn_kernel<DSUB, 2>, (const void*)decode_attn_kernel<DSUB, 3>,
                               (const void*)decode_attn_kernel<DSUB, 4>, (const void*)decode_attn_kernel<DSUB, 5>,
@@ -2031,8 +2032,7 @@ static hipError_t launch_decode_t(const Geom& g, const DecodeArgs& a, void* ws, 
             if (r != hipSuccess) return r;
         }
         return hipSuccess;
-    }();
-    hipError_t e = setup;
+    });
     if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)((int64_t)g.B * g.Hkv * pl.S);
     // anchor lists between 3073 and 16384 entries go through the kernels that hold them in the table areas
@@ -2059,13 +2059,14 @@ static hipError_t launch_decode_t(const Geom& g, const DecodeArgs& a, void* ws, 
         d.S = pl.S; d.chunk = pl.chunk;
         d.hist = a.topk_hist;
         const size_t sh2 = (size_t)(g.M < 16 ? 16 : g.M) * 256 * 16 + kNH * kD * 4 + kDaWaves * 32 + 64 + 4096 + 2 * kTopkBins * 4;
-        static const hipError_t ans_setup = [sh2]() {              // once per process and DSUB
+        static OncePerDevice once_ans;
+        const hipError_t ans_setup = on_this_device(once_ans, [sh2]() {
             hipError_t e1 = hipFuncSetAttribute((const void*)decode_ans_kernel<DSUB, 0>,
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh2);
             if (e1 != hipSuccess) return e1;
             return hipFuncSetAttribute((const void*)decode_ans_kernel<DSUB, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)sh2);
-        }();
+        });
         if (ans_setup != hipSuccess) return ans_setup;
         const unsigned grid2 = (unsigned)((int64_t)g.B * g.Hkv * pl.S);
         hipLaunchKernelGGL((decode_ans_kernel<DSUB, 0>), dim3(grid2), dim3(kDaThreads), sh2, st, d);

@@ -284,8 +284,8 @@ static hipError_t launch_encode12_t(const Geom& g, const half_t* x, int64_t xs_b
                                     int64_t n_tok, const half_t* cb, uint8_t* codes, int64_t N_cap,
                                     int64_t token_offset, hipStream_t st)
 {
-    static const hipError_t setup = hipFuncSetAttribute((const void*)encode12_kernel<DS>,
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)e12_lds(DS));
+    static OncePerDevice once;
+    const hipError_t setup = allow_lds(once, (const void*)encode12_kernel<DS>, e12_lds(DS));
     if (setup != hipSuccess) return setup;
     const int64_t groups = (n_tok + 31) / 32;
     const int chunks = e12_chunks(groups, (int64_t)g.B * g.Hkv * (g.M / 2), e12_groups(DS));

@@ -438,8 +438,8 @@ hipError_t launch_t(const Geom& g, const half_t* x, const float* w, int64_t n_to
     hipLaunchKernelGGL(km_zero, dim3((unsigned)((n_zero + n_obj + 255) / 256)), dim3(256), 0, st, (uint32_t*)ws, n_zero,
                        (uint32_t*)objective, n_obj);
     if (n_tok > 0) {
-        static const hipError_t setup = hipFuncSetAttribute((const void*)km_accumulate<DSUB>,
-                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)km_lds(DSUB));
+        static OncePerDevice once;
+        const hipError_t setup = allow_lds(once, (const void*)km_accumulate<DSUB>, km_lds(DSUB));
         if (setup != hipSuccess) return setup;
         // about two workgroups per CU; a range is whole chunks, since every range adds 256 x (DSUB + 1) values to the sums
         const int64_t total = (int64_t)g.B * n_tok, pairs = (int64_t)g.Hkv * g.M, chunk = ks_chunk(DSUB);
@@ -459,8 +459,8 @@ template <int DSUB>
 hipError_t launch_wide(const Geom& g, const half_t* x, const float* w, int64_t n_tok, const half_t* cb_in, half_t* cb_out,
                        const uint8_t* codes, float* wsum_out, double* objective, hipStream_t st)
 {
-    static const hipError_t setup = hipFuncSetAttribute((const void*)km_update12<DSUB>,
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kw_lds(DSUB));
+    static OncePerDevice once;
+    const hipError_t setup = allow_lds(once, (const void*)km_update12<DSUB>, kw_lds(DSUB));
     if (setup != hipSuccess) return setup;
     if (objective) {
         const int64_t n_obj = (int64_t)g.Hkv * g.M * 2;

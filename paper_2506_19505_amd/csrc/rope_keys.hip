@@ -452,16 +452,16 @@ hipError_t launch_rope_scores(const Geom& g, const half_t* q, float scale, const
     hipError_t e = hipSuccess;
 #define ANTKV_RS12(DS, STY)                                                                                                \
     do {                                                                                                                   \
-        static const hipError_t once = hipFuncSetAttribute((const void*)rope_scores12_kernel<DS, STY>,                     \
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kR12Lds);           \
-        if (once != hipSuccess) return once;                                                                               \
+        static OncePerDevice once;                                                                                         \
+        const hipError_t setup = allow_lds(once, (const void*)rope_scores12_kernel<DS, STY>, kR12Lds);                     \
+        if (setup != hipSuccess) return setup;                                                                             \
         hipLaunchKernelGGL((rope_scores12_kernel<DS, STY>), grid, dim3(kR12Threads), kR12Lds, st, p);                      \
     } while (0)
 #define ANTKV_RS(DS, STY)                                                                                                  \
     do {                                                                                                                   \
-        static const hipError_t once = hipFuncSetAttribute((const void*)rope_scores_kernel<DS, STY>,                       \
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kRsLds);            \
-        if (once != hipSuccess) return once;                                                                               \
+        static OncePerDevice once;                                                                                         \
+        const hipError_t setup = allow_lds(once, (const void*)rope_scores_kernel<DS, STY>, kRsLds);                        \
+        if (setup != hipSuccess) return setup;                                                                             \
         hipLaunchKernelGGL((rope_scores_kernel<DS, STY>), grid, dim3(kRsThreads), kRsLds, st, p);                          \
     } while (0)
     if (g.C != kC) {
