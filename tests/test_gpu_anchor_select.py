@@ -44,6 +44,18 @@ def test_anchor_select_wide_key_blocks(oracle, B, Hq, Hkv, N, Nq):
     _run(oracle, 27, B, Hq, Hkv, N, Nq, 40)
 
 
+@pytest.mark.parametrize("Nq", [32, 33, 65, 97, 129, 161])
+@pytest.mark.parametrize("Hq", [2, 4])
+def test_anchor_select_step_counts(oracle, Hq, Nq):
+    """Every remainder of the column reduction's (head, query tile) steps by four, from one step on."""
+    _run(oracle, 29, 1, Hq, 2, 410, Nq, 17)
+
+
+@pytest.mark.parametrize("Nq", [257, 289, 321, 353])
+def test_anchor_select_step_counts_wide_key_blocks(oracle, Nq):
+    _run(oracle, 30, 4, 16, 16, 4100, Nq, 40)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(1, 4, 1, 1024, 31), (1, 4, 2, 1025, 32), (2, 2, 2, 2081, 33), (1, 8, 2, 9217, 64)])
 def test_anchor_select_key_ranges(oracle, B, Hq, Hkv, N, Nq):
     """Phase 1 of a query window split over keys: one range, a last range of a few keys, queries inside the last ranges."""
