@@ -16,8 +16,8 @@
 //      needed to reach k, in ascending position order.
 // Rows of up to 32768 scores fit the registers of one workgroup: topk_row does all of it in one launch (the six launches
 // above cost 38 us for 128 rows of 1531 scores, this one 6).  The kernels for
-// longer rows are bound by latency up to some 100000 scores and by reading the scores twice beyond: 16 rows of 840000
-// scores, not 16-byte aligned, counting and listing 31 -> 26 us, emission (whose threads read 128 bytes each) 78 -> 19 us.
+// longer rows are bound by latency up to some 100000 scores and by reading the scores twice beyond.  16 rows of 840000
+// scores, whole call: 78 us if the rows are 16-byte aligned, 94 if not; 256 rows of 40000: 54 us.
 #include "common.h"
 
 namespace antkv {
@@ -126,7 +126,6 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     uint32_t* hist0 = ws_hist + row * 2 * kBins;
     uint32_t* hist1 = hist0 + kBins;
     if (LEVEL == 2 && head[row * kHeadWords + kHeadCrowded] == 0u) return;
-    // the slice's scores, requested before the histogram is searched
     const int64_t lo = (int64_t)blockIdx.x * kSlice;
     const int64_t hi = (lo + kSlice < N) ? lo + kSlice : N;
     const float* src = row_scores(scores, scores_b, rows_a, row, N);
@@ -134,21 +133,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     uint32_t key[kPer];
     const bool fast = hi - lo == kSlice && (((uintptr_t)(src + lo)) & 15) == 0;
     const int n_own = (int)(hi - lo);
-    // element j of the thread sits at position lo + pos(j)
-    auto pos = [&](int j) -> int { return fast ? 4 * (tid + kTopkThreads * (j >> 2)) + (j & 3) : tid + kTopkThreads * j; };
-    if (fast) {
-#pragma unroll
-        for (int j = 0; j < kPer / 4; ++j) {
-            const float4_t v = *(const float4_t*)(src + lo + 4 * (tid + kTopkThreads * j));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(v[e]);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) key[j] = pos(j) < n_own ? float_key(src[lo + pos(j)]) : 0u;
-    }
+    // element j of the thread sits at position lo + pos(j); there are `own` of them
+    const int first = fast ? 4 * tid : tid;
+    auto pos = [&](int j) -> int { return first + (fast ? 4 * kTopkThreads * (j >> 2) + (j & 3) : kTopkThreads * j); };
+    int own = fast ? kPer : (n_own - tid + kTopkThreads - 1) / kTopkThreads;
     // (negative NaNs share the lowest bin with the zeros past the end: those are left out by position)
-    auto in = [&](int j) -> bool { return fast || pos(j) < n_own; };
+    auto in = [&](int j) -> bool { return j < own; };
     uint32_t d0, k_rem;
     find_digit(hist0, kBins, k, d0, k_rem, sh);
     const bool crowded = hist0[d0] > cap;                       // the same for every workgroup of the row
@@ -165,6 +155,17 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     if (LEVEL == 1 && crowded) {
         for (int i = tid; i < kBins; i += kTopkThreads) lh[i] = 0u;
         __syncthreads();
+    }
+    if (fast) {
+#pragma unroll
+        for (int j = 0; j < kPer / 4; ++j) {
+            const float4_t v = *(const float4_t*)(src + lo + 4 * (tid + kTopkThreads * j));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(v[e]);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) key[j] = j < own ? float_key(src[lo + tid + kTopkThreads * j]) : 0u;
     }
     uint32_t gt = 0, eq = 0;
 #pragma unroll
@@ -196,6 +197,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
         s_base = (list && tot_eq) ? atomicAdd(&head[row * kHeadWords + kHeadCount], tot_eq) : 0u;
     }
     __syncthreads();
+    // (Compared again below: kept, 64 results spilled scalar registers and cost a wave per SIMD; 16 rows of 840000 25 us, now
+    // 21, 256 rows of 40000 24 and 19.)
+    pin(own);
+    pin(prefix);
     if (list) {
         if (eq == 0) return;
         uint32_t at = s_base + off_eq;
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     } else if (LEVEL == 1) {                                    // crowded bin: its next 11 bits go to the second histogram
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            if (in(j) && (key[j] >> 21) == d0) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
+            if (in(j) && (key[j] >> 21) == prefix) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
         }
         __syncthreads();
         for (int i = tid; i < kBins; i += kTopkThreads)
@@ -326,14 +331,26 @@ __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restric
     __shared__ uint32_t red[4][4];
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // a wave owns 2048 consecutive scores, 64 at a time (coalesced whatever the row's alignment), kept as keys; requested
-    // ahead of the counts, whose latency they share
+    // Scores are requested ahead of the counts, whose latency they share, and kept as keys.  A whole, 16-byte aligned slice: a
+    // thread owns 32 consecutive scores; any other: a wave owns 2048 consecutive ones, 64 at a time (coalesced).  16 rows of
+    // 840000: aligned 14 us by threads, 20 by waves; 840003 scores, not aligned, 87 by threads (a dword at a time), 16 by waves.
     constexpr int kPer = kSlice / kTopkThreads;
-    const int64_t lo = (int64_t)blockIdx.x * kSlice + wave * (64 * kPer) + lane;
+    const int64_t slice_lo = (int64_t)blockIdx.x * kSlice;
     const float* src = row_scores(scores, scores_b, rows_a, row, N);
+    const bool fast = slice_lo + kSlice <= N && (((uintptr_t)(src + slice_lo)) & 15) == 0;
+    const int64_t lo = slice_lo + (fast ? tid * kPer : wave * (64 * kPer) + lane);
     uint32_t key[kPer];
+    if (fast) {
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? __float_as_uint(src[lo + 64 * j]) : 0xffffffffu;   // (key 0: no score has it)
+        for (int j = 0; j < kPer / 4; ++j) {
+            const float4_t v = *(const float4_t*)(src + lo + 4 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) key[4 * j + e] = __float_as_uint(v[e]);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? __float_as_uint(src[lo + 64 * j]) : 0xffffffffu;
+    }
     const uint32_t tau = head[row * kHeadWords + kHeadTau], need_eq = head[row * kHeadWords + kHeadNeedEq];
     // keys > tau and == tau in the slices before this one
     uint32_t bgt = 0, beq = 0;
@@ -346,18 +363,49 @@ __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restric
     if (lane == 0) { red[0][wave] = bgt; red[1][wave] = beq; }
 #pragma unroll
     for (int j = 0; j < kPer; ++j) key[j] = float_key(__uint_as_float(key[j]));
-    uint32_t gt = 0, eq = 0;
+    uint32_t gt = 0, eq = 0, my_gt = 0, my_eq = 0;               // of the wave; of the thread and, then, of the lanes up to it
+    if (fast) {
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        gt += (uint32_t)__popcll(__ballot(key[j] > tau));
-        eq += (uint32_t)__popcll(__ballot(key[j] == tau));
+        for (int j = 0; j < kPer; ++j) { my_gt += key[j] > tau; my_eq += key[j] == tau; }
+        gt = my_gt;
+        eq = my_eq;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t a = __shfl_up(gt, off, 64), b = __shfl_up(eq, off, 64);
+            if (lane >= off) { gt += a; eq += b; }
+        }
+        if (lane == 63) { red[2][wave] = gt; red[3][wave] = eq; }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            gt += (uint32_t)__popcll(__ballot(key[j] > tau));
+            eq += (uint32_t)__popcll(__ballot(key[j] == tau));
+        }
+        if (lane == 0) { red[2][wave] = gt; red[3][wave] = eq; }
     }
-    if (lane == 0) { red[2][wave] = gt; red[3][wave] = eq; }
     __syncthreads();
     uint32_t run_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3], run_eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
     for (int w = 0; w < wave; ++w) { run_gt += red[2][w]; run_eq += red[3][w]; }
     int32_t* out = (row < rows_a) ? idx + row * (int64_t)k : idx_b + (row - rows_a) * (int64_t)k;
-    emit_ordered<kPer>(key, tau, need_eq, run_gt, run_eq, lane, lo, out);
+    if (!fast) {
+        // (Past the end keys are 0, the lowest.  The NaN 0xffffffff has it too, but at earlier positions, and need_eq counts
+        // only those.)
+        emit_ordered<kPer>(key, tau, need_eq, run_gt, run_eq, lane, lo, out);
+        return;
+    }
+    run_gt += gt - my_gt;
+    run_eq += eq - my_eq;
+    if (my_gt == 0 && (my_eq == 0 || run_eq >= need_eq)) return; // nothing of this thread is selected
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (key[j] > tau) {
+            out[run_gt + (run_eq < need_eq ? run_eq : need_eq)] = (int32_t)(lo + j);
+            ++run_gt;
+        } else if (key[j] == tau) {
+            if (run_eq < need_eq) out[run_gt + run_eq] = (int32_t)(lo + j);
+            ++run_eq;
+        }
+    }
 }
 
 // A whole row of at most 1024 * PER scores in one workgroup: the k-th largest key by three rounds of histograms in LDS (11,
@@ -378,7 +426,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row(const float* __restrict_
     const int lo = wave * (64 * PER) + lane;                     // a wave owns 64 * PER consecutive scores
     uint32_t key[PER];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) key[j] = lo + 64 * j < N ? float_key(src[lo + 64 * j]) : 0u;   // (no score has key 0)
+    for (int j = 0; j < PER; ++j) key[j] = lo + 64 * j < N ? float_key(src[lo + 64 * j]) : 0u;   // (the lowest key: see topk_emit)
     for (int i = tid; i < 3 * kBins; i += kRowThreads) (&lh[0][0])[i] = 0u;
     __syncthreads();
 #pragma unroll

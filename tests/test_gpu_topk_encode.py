@@ -76,6 +76,35 @@ def test_topk_negative_nans_in_a_short_last_slice():
         assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("N", [1000, 2048, 8191, 32767, 32768, 40960, 40961, 49156, 73728])
+def test_topk_lowest_key_at_the_threshold(N):
+    """NaNs 0xffffffff have the lowest key of all, 0, which the registers past a row's end hold as well: the threshold is that
+    key, in one launch per row and in many, with whole and partial last slices, rows aligned to 16 bytes and not."""
+    rng = np.random.default_rng(N)
+    n_nan = N // 5
+    s = rng.random((3, N)).astype(np.float32)
+    bits = s.view(np.uint32)
+    for r, at in enumerate((rng.permutation(N)[:n_nan], np.arange(n_nan), np.arange(N - n_nan, N))):
+        bits[r, at] = 0xffffffff
+    key = np.where(bits == 0xffffffff, 0, bits | 0x80000000).astype(np.int64)
+    for k in (N - n_nan, N - n_nan + 1, N - n_nan // 2, N):
+        want = np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1)
+        assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("N", [32772, 40960, 65536, 73729])
+def test_topk_ties_across_slices(oracle, N):
+    """Ties at the threshold that run over threads, waves and slices, rows that are 16-byte aligned and rows that are not."""
+    rng = np.random.default_rng(N)
+    s = np.exp(rng.standard_normal((4, N))).astype(np.float32)
+    s[0, ::2] = 1.0                                            # every thread has some
+    s[1, 8000:24800] = 1.0                                     # a run over two slice ends
+    s[2] = 1.0
+    s[3, rng.permutation(N)[:50]] = 1.0
+    for k in (1, N // 100, N // 3, N // 2, N - 1):
+        assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), oracle.topk(s, k))
+
+
 @pytest.mark.parametrize("d", [4, 8, 16])
 @pytest.mark.parametrize("B,Hq,Hkv,n", [(2, 4, 2, 333), (1, 8, 8, 70)])
 def test_encode_matches_oracle(oracle, d, B, Hq, Hkv, n):
