@@ -550,8 +550,17 @@ hipError_t topk_select(const float* scores, int32_t* idx, const float* scores_b,
 }  // namespace
 
 // A row in one workgroup needs no workspace.  Beyond 32 scores per thread they no longer fit the registers, and the few
-// workgroups of a long row would leave the chip idle.
+// workgroups of a long row would leave the chip idle: 16 rows of 32768 take 22 us in one launch and 27 in six, 256 rows 23 and 38.
 static bool topk_in_rows(int64_t N) { return N <= 32 * kRowThreads; }
+
+// The same where the producer of the scores could count them for the first histogram: the longer launches then save a read of
+// the scores, and fewer than 64 aligned rows of more than 16384 are quicker that way.  Decode step with re-selection, d_sub 8,
+// 16 rows of 24576 / 32768: 62 / 64 us counted, 66 / 70 in one launch; 256 rows 113 / 132 and 106 / 126; 16 rows of 20001,
+// not aligned, 71 and 64; 16 rows of 16384 60 and 62, of 12288 64 and 61.
+static bool topk_in_rows_counted(int64_t rows, int64_t N)
+{
+    return topk_in_rows(N) && (N <= 16384 || rows >= 64 || N % 4 != 0);
+}
 
 static hipError_t launch_topk_rows(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
                                    int64_t N, int64_t k, hipStream_t st)
@@ -582,14 +591,14 @@ hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b
 
 uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st)
 {
-    return topk_in_rows(N) ? nullptr : topk_clear(2 * n_rows, N, ws, st);
+    return topk_in_rows_counted(2 * n_rows, N) ? nullptr : topk_clear(2 * n_rows, N, ws, st);
 }
 
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
                                int64_t N, int64_t k, void* ws, hipStream_t st)
 {
     if (k == 0 || n_rows == 0) return hipSuccess;
-    if (topk_in_rows(N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
+    if (topk_in_rows_counted(2 * n_rows, N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
     return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
 }
 

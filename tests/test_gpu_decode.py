@@ -293,6 +293,24 @@ def test_decode_time_anchor_score_and_reselection(oracle, d, N):
     print(f"re-selection near-tie disagreements: {soft}")
 
 
+@pytest.mark.parametrize("d,C", [(8, 256), (32, 4096)])
+@pytest.mark.parametrize("Hkv,N", [(2, 16384), (2, 16385), (2, 16388), (2, 32768), (2, 32772), (32, 16388)])
+def test_reselection_is_the_top_k_of_the_scores(oracle, d, C, Hkv, N):
+    """Both sides of the sizes at which the selection goes from one launch to counted scores: the sets are those of the scores
+    that the call returns, exactly."""
+    geom = antkv.Geometry(1, 4 * Hkv, Hkv, d, n_centroids=C)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    normal = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes = torch.randint(0, 256, (1, Hkv, N, geom.code_bytes), dtype=torch.uint8, device="cuda", generator=gen)
+    cb = normal(Hkv, 128 // d, C, d)
+    idx = torch.arange(0, N, 97, dtype=torch.int32, device="cuda").expand(1, Hkv, -1).contiguous()
+    rows = normal(1, Hkv, idx.shape[-1], 128)
+    _, ans_k, ans_v, rk, rv = antkv.decode_attn(geom, normal(1, 4 * Hkv, 128), 1 / np.sqrt(128), codes, codes, cb, cb, idx, rows,
+                                                idx, rows, N=N, k_resel=N // 100)
+    for got, score in ((rk, ans_k), (rv, ans_v)):
+        assert np.array_equal(got.cpu().numpy(), oracle.topk(score.cpu().numpy(), N // 100))
+
+
 @pytest.mark.parametrize("k_v", [0, 13])
 def test_decode_time_anchor_score_without_key_anchors(oracle, k_v):
     """Scores and re-selection on a cache whose K list is empty (null list pointers): nothing of that list may be read."""
