@@ -57,16 +57,6 @@ __device__ __forceinline__ float16_t tile_dot_lds_a(const half_t* __restrict__ s
     return acc;
 }
 
-__device__ __forceinline__ float16_t tile_dot(const Tile128& a, const Tile128& b)
-{
-    float16_t acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.v[s], b.v[s], acc, 0, 0, 0);
-    return acc;
-}
-
 // -------------------------------------------------------------------------------------------------
 // phase 1: partial row statistics.  grid = (key splits, query blocks, B*Hkv); 8 waves = HG heads of the
 // group x 8/HG query tiles of 32 with HG = min(G, 4), so that no wave idles for small groups (larger groups loop).

@@ -163,7 +163,6 @@ struct DecodeArgs {
     const float* given_scores = nullptr;
 };
 int set_decode_options(int options);   // ANTKV_DECODE_* mask; returns the previous mask
-int decode_num_splits(const Geom& g, int64_t N);
 // Token ranges per (sequence, KV head) for kernels of one workgroup per CU: at most 256 workgroups in all, since a 257th waits
 // for a whole range and nearly doubles the launch, and at least about 1024 tokens each.  24 pairs x 57003 tokens, keys before
 // RoPE: with 11 ranges (264 workgroups) the score kernel takes 77 us and the decode kernel 36, with 10 ranges 51 and 22.

@@ -1977,8 +1977,6 @@ DaPlan da_plan(const Geom& g, int64_t N, int64_t k_k, int64_t k_v, bool want_ans
 
 }  // namespace
 
-int decode_num_splits(const Geom& g, int64_t N) { return da_plan(g, N, 0, 0, false).S; }
-
 size_t decode_workspace_bytes(const Geom& g, int64_t N, int64_t k_k, int64_t k_v, bool want_ans)
 {
     return da_plan(g, N, k_k, k_v, want_ans).total;
