@@ -277,7 +277,9 @@ int antkv_prefill_attn(const antkv_geom* geom, const void* q, const void* k, con
  *   objective    optional fp64 [Hkv][M]: sum_j w_j ||x_j - codebook_in[code_j]||^2 per sub-space, i.e. the weighted
  *                distortion after the assignment and before the update
  *   workspace    antkv_kmeans_step_workspace(geom) bytes, 256-byte aligned; may hold any bytes on entry
- * Sums are fp32 and added with atomics: the new centroids agree to fp32 rounding from run to run, not bit for bit.
+ * Sums are fp32 in an order that varies (256 centroids: partial sums meet by atomics; 4096 centroids: tokens are sorted with
+ * atomics and added up by the workgroup that owns the centroid, without the workspace): the new centroids agree to fp32
+ * rounding from run to run, not bit for bit.
  * n_tok == 0 copies the codebook.  Errors: EINVAL, EUNSUPPORTED, EWORKSPACE, ELAUNCH.
  */
 size_t antkv_kmeans_step_workspace(const antkv_geom* geom);

@@ -163,9 +163,11 @@ struct DecodeArgs {
     const float* given_scores = nullptr;
 };
 int set_decode_options(int options);   // ANTKV_DECODE_* mask; returns the previous mask
-// Token ranges per (sequence, KV head) for kernels of one workgroup per CU: at most 256 workgroups in all, since a 257th waits
-// for a whole range and nearly doubles the launch, and at least about 1024 tokens each.  24 pairs x 57003 tokens, keys before
-// RoPE: with 11 ranges (264 workgroups) the score kernel takes 77 us and the decode kernel 36, with 10 ranges 51 and 22.
+// Token ranges per (sequence, KV head) for kernels of one workgroup per CU: at most 256 workgroups in all (more than 256 pairs:
+// one each), since a 257th waits for a whole range and nearly doubles the launch, and at least about 1024 tokens each.  24 pairs
+// x 57003 tokens, keys before RoPE: with 11 ranges (264 workgroups) the score kernel takes 77 us and the decode kernel 36, with
+// 10 ranges 51 and 22.  The decode kernels hold at most 32768 tokens of a range: beyond 65536 tokens 96 pairs come to 288
+// workgroups, two whole ranges and a short one each; 69000 tokens, d_sub 8, take 93 us that way, in even thirds 111.
 inline int64_t token_ranges(int64_t pairs, int64_t N)
 {
     const int64_t fill = pairs > 0 && pairs < 256 ? 256 / pairs : 1, most = (N + 1023) / 1024;

@@ -417,7 +417,7 @@ struct KmPlan {
 
 KmPlan km_plan(const Geom& g)
 {
-    KmPlan p;
+    KmPlan p;                                                   // (with 4096 centroids nothing of it is read or written)
     size_t off = 0;
     p.off_sums = off; off += align_up((size_t)g.Hkv * kD * g.C * sizeof(float));      // M * d_sub = D
     p.off_wsum = off; off += align_up((size_t)g.Hkv * g.M * g.C * sizeof(float));

@@ -322,7 +322,7 @@ def test_kmeans12_step(oracle, books, B, n):
 def test_kmeans12_update_crowded(oracle, books, B, n, distinct):
     """More tokens of one range of centroids than a sorted chunk holds, runs over many windows, chunks that end inside a
     sequence.  Sums of up to 32 products per window, 256 windows and 5 chunks in fp32: within 300 * 2^-24 of the sum of
-    magnitudes."""
+    magnitudes.  The weights are such a sum too, so a mean is within twice that, and its division rounds once more."""
     _, rows, _ = make_qkv(107, B, 2, 2, distinct, 1, 128, want_v=False)
     x = rows[:, :, np.random.default_rng(n).integers(0, distinct, n)]
     w = np.random.default_rng(n + 1).gamma(0.5, 1.0, size=(B, 2, n)).astype(np.float32)
@@ -335,7 +335,7 @@ def test_kmeans12_update_crowded(oracle, books, B, n, distinct):
     np.testing.assert_allclose(obj.cpu().numpy(), want_obj, rtol=2e-5)
     got = new.cpu().numpy()
     assert np.array_equal(got[want_w == 0], cb[want_w == 0])
-    assert (np.abs(got.astype(np.float64) - want) <= np.abs(want) * 2.0 ** -10 + 2.0 ** -24 + 4e-5 * mag).all()
+    assert (np.abs(got.astype(np.float64) - want) <= np.abs(want) * 2.0 ** -10 + 2.0 ** -24 + 601 * 2.0 ** -24 * mag).all()
 
 
 def test_kmeans12_iterations_descend(oracle, books):
