@@ -302,9 +302,17 @@ static hipError_t launch_encode12_t(const Geom& g, const half_t* x, int64_t xs_b
 hipError_t launch_encode12(const Geom& g, const half_t* x, int64_t xs_b, int64_t xs_h, int64_t xs_t, int64_t n_tok,
                            const half_t* cb, uint8_t* codes, int64_t N_cap, int64_t token_offset, hipStream_t st)
 {
-    if (n_tok == 0 || g.B == 0) return hipSuccess;
-    return g.d == 32 ? launch_encode12_t<32>(g, x, xs_b, xs_h, xs_t, n_tok, cb, codes, N_cap, token_offset, st)
-                     : launch_encode12_t<16>(g, x, xs_b, xs_h, xs_t, n_tok, cb, codes, N_cap, token_offset, st);
+    if (g.B == 0) return hipSuccess;
+    // the token chunks (of at least 1536 tokens when there are many) are the grid's second axis, which ends at 65536
+    constexpr int64_t kMost = 1 << 26;
+    for (int64_t t = 0; t < n_tok; t += kMost) {
+        const int64_t n = n_tok - t < kMost ? n_tok - t : kMost;
+        const hipError_t e =
+            g.d == 32 ? launch_encode12_t<32>(g, x + t * xs_t, xs_b, xs_h, xs_t, n, cb, codes, N_cap, token_offset + t, st)
+                      : launch_encode12_t<16>(g, x + t * xs_t, xs_b, xs_h, xs_t, n, cb, codes, N_cap, token_offset + t, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace antkv

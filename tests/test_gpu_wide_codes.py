@@ -88,6 +88,25 @@ def test_encode12_work_splits(oracle, books, B, n):
     assert (got[:, :, :2, 0] != 4).all() and not np.isin(got, np.arange(2048 + 7, 2048 + 2047)).any()
 
 
+def test_encode12_more_tokens_than_one_launch_takes(books):
+    """The tokens of one head beyond what the grid's second axis (65536 chunks of 1536 or 2048 tokens) holds: rows at the ends and
+    at every seam get the codes that a call on them alone gives."""
+    n, off = 65536 * (1536 if books.d == 32 else 2048) + 77, 3
+    geom = antkv.Geometry(1, 1, 1, books.d, n_centroids=C)
+    cb = dev(books[0][:1])
+    x = torch.empty((1, 1, n, 128), dtype=torch.float16, device="cuda")
+    block = torch.randn((1 << 20, 128), dtype=torch.float16, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    for t in range(0, n, 1 << 20):                             # rows repeat, turned by one more channel each time
+        x[0, 0, t:t + (1 << 20)] = block[:min(1 << 20, n - t)].roll(t >> 20, dims=1)
+    codes = torch.full((1, 1, n + off + 5, books.nbytes), 0xEE, dtype=torch.uint8, device="cuda")
+    antkv.encode(geom, x, cb, codes, off)
+    assert (codes[:, :, :off] == 0xEE).all() and (codes[:, :, n + off:] == 0xEE).all()
+    for at in (0, 1 << 26, n - 40000, n):
+        lo, hi = max(0, at - 3000), min(n, at + 3000)
+        part = antkv.encode(geom, x[:, :, lo:hi].contiguous(), cb)
+        assert torch.equal(codes[:, :, off + lo:off + hi], part), (lo, hi)
+
+
 def _decode_case(oracle, books, seed, B, Hq, Hkv, N, k_k, k_v, N_cap=None, scale=None, range_tolerance=False):
     from workloads import make_decode_query, normal_fp16
     rng = np.random.default_rng(seed)
