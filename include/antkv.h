@@ -153,6 +153,8 @@ int antkv_gather_rows(const antkv_geom* geom, const void* x, int64_t N, const in
  *            ans_k[j] = sum_h p_hj (1 - p_hj) ||q_h||_2
  *   resel_idx_k, resel_idx_v  int32 [B][Hkv][k_resel] or NULL: top-k_resel positions of those scores
  *            (ascending, ties to the lower position).  Needs ans_k / ans_v respectively to be non-NULL.
+ * For long contexts of 12-bit codes the workspace includes softmax weights of every token (8 bytes per token and KV head);
+ * a smaller one that holds everything else is not refused, the step then takes longer.
  * N == 0 writes zeros.  Errors: EINVAL, EUNSUPPORTED, EWORKSPACE, ELAUNCH.
  */
 size_t antkv_decode_attn_workspace(const antkv_geom* geom, int64_t N, int64_t k_k, int64_t k_v,
@@ -212,8 +214,8 @@ int antkv_decode_attn_prerope(const antkv_geom* geom, const void* q, float scale
  * scratch (per-workgroup partial results and arrival words; for 12-bit codes also the K-side table) lives in an
  * array of ANTKV_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held until the process ends.
  * The call allocates nothing and frees nothing.  A shape whose scratch need
- * (antkv_decode_attn_workspace(geom, N, k_k, k_v, 0)) exceeds ANTKV_STATIC_SCRATCH_BYTES is refused with
- * ANTKV_EWORKSPACE before anything is enqueued.  All calls on one GPU share that GPU's array: calls that
+ * (antkv_decode_attn_workspace(geom, N, k_k, k_v, 0), for 12-bit codes without the per-token weights in it) exceeds
+ * ANTKV_STATIC_SCRATCH_BYTES is refused with ANTKV_EWORKSPACE before anything is enqueued.  All calls on one GPU share that GPU's array: calls that
  * overlap in time on one GPU (different streams, or this call next to another thread's) race and must be
  * serialised by the caller; nothing in the array has to be cleared between calls.
  */

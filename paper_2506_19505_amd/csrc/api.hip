@@ -82,9 +82,10 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
     const bool want_ans = ans_k || ans_v;
     if (want_ans && !(ans_k && ans_v)) return ANTKV_EINVAL;   // the two scores are produced together
     if (wide) {
-        const size_t off_topk = align_up(decode12_workspace_bytes(g, N));
-        const size_t need = off_topk + (k_resel > 0 ? align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0);
-        if (!workspace || misaligned(workspace, 256) || workspace_bytes < need) return ANTKV_EWORKSPACE;
+        const size_t topk_bytes = k_resel > 0 ? align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0;
+        const size_t least = align_up(decode12_workspace_least(g, N)), best = align_up(decode12_workspace_bytes(g, N));
+        if (!workspace || misaligned(workspace, 256) || workspace_bytes < least + topk_bytes) return ANTKV_EWORKSPACE;
+        const size_t off_topk = workspace_bytes < best + topk_bytes ? least : best;
         hipStream_t st = (hipStream_t)stream;
         DecodeArgs a;
         a.q = (const half_t*)q; a.scale = scale; a.codes_k = codes_k; a.codes_v = codes_v; a.N = N; a.N_cap = N_cap;
@@ -95,7 +96,7 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
         // with both index sets wanted, the score pass counts its scores into the selection's first histogram
         const bool fused = N > 0 && k_resel > 0 && resel_idx_k && resel_idx_v;
         a.topk_hist = fused ? launch_topk2_begin((int64_t)g.B * g.Hkv, N, (char*)workspace + off_topk, st) : nullptr;
-        if (launch_decode12(g, a, workspace, st) != hipSuccess) return ANTKV_ELAUNCH;
+        if (launch_decode12(g, a, workspace, off_topk, st) != hipSuccess) return ANTKV_ELAUNCH;
         if (N > 0 && k_resel > 0 && (resel_idx_k || resel_idx_v)) {
             char* w = (char*)workspace;
             const int64_t rows = (int64_t)g.B * g.Hkv;
@@ -345,14 +346,20 @@ int antkv_append_token(const antkv_geom* geom, const void* k_new, const void* v_
     return e == hipSuccess ? ANTKV_OK : ANTKV_ELAUNCH;
 }
 
-size_t antkv_decode_attn_workspace(const antkv_geom* geom, int64_t N, int64_t k_k, int64_t k_v, int64_t k_resel)
+// least: what the call does not refuse; otherwise what it can use
+static size_t decode_need(const antkv_geom* geom, int64_t N, int64_t k_k, int64_t k_v, int64_t k_resel, bool least)
 {
     Geom g;
     if (check_geom(geom, g) || N < 0 || k_k < 0 || k_v < 0 || k_resel < 0) return 0;
     if (g.C != kC)
-        return align_up(decode12_workspace_bytes(g, N)) +
+        return align_up(least ? decode12_workspace_least(g, N) : decode12_workspace_bytes(g, N)) +
                (k_resel > 0 ? align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0);
     return dec_plan(g, N, k_k, k_v, k_resel, true).total;
+}
+
+size_t antkv_decode_attn_workspace(const antkv_geom* geom, int64_t N, int64_t k_k, int64_t k_v, int64_t k_resel)
+{
+    return decode_need(geom, N, k_k, k_v, k_resel, false);
 }
 
 int antkv_decode_attn(const antkv_geom* geom, const void* q, float scale, const uint8_t* codes_k,
@@ -400,7 +407,7 @@ int antkv_decode_attn_prerope(const antkv_geom* geom, const void* q, float scale
     if (!codes_k || !cb_k || misaligned(codes_k, 16) || misaligned(cb_k, 16)) return ANTKV_EINVAL;
     if (k_k > 0 && (!idx_k || !rows_k || misaligned(rows_k, 16))) return ANTKV_EINVAL;
     if (!q || misaligned(q, 16) || !(scale > 0.f)) return ANTKV_EINVAL;
-    const size_t need = antkv_decode_attn_prerope_workspace(geom, N, k_v);
+    const size_t need = prerope_score_bytes(g, N) + align_up(decode_need(geom, N, 0, k_v, 0, true));
     if (!workspace || misaligned(workspace, 256) || workspace_bytes < need) return ANTKV_EWORKSPACE;
     // The rotated keys are never written out: a first pass leaves q . RoPE(K_eff) of every token and head (FP16 anchor
     // rows included) in the workspace, and the decode kernels take their scores from there instead of from a table.
@@ -422,7 +429,7 @@ int antkv_decode_attn_static(const antkv_geom* geom, const void* q, float scale,
     const int rc = check_geom(geom, g);
     if (rc) return rc;
     if (N < 0 || k_k < 0 || k_v < 0) return ANTKV_EINVAL;
-    const size_t need = antkv_decode_attn_workspace(geom, N, k_k, k_v, 0);
+    const size_t need = decode_need(geom, N, k_k, k_v, 0, true);
     if (need > (size_t)ANTKV_STATIC_SCRATCH_BYTES) return ANTKV_EWORKSPACE;   // shape beyond the built-in scratch
     void* ws = nullptr;
     const int rs = static_scratch(&ws);

@@ -20,25 +20,13 @@
 //              the centroids) as the source.
 //   merge      waves through LDS, workgroups through a partial (max, sum, accumulator) per head and a second
 //              small kernel.
-#include "common.h"
+#include "decode12.h"
 
 #include <type_traits>
 
 namespace antkv {
 
 namespace {
-
-constexpr int kT12 = 1024;               // threads
-constexpr int kW12 = kT12 / 64;          // waves
-constexpr int kC12 = 4096;
-constexpr int kNH = 4;                   // head slots of a query group (G <= 4)
-constexpr int kChunkMax = 32768;         // tokens per workgroup (bitmaps of 1024 words)
-constexpr float kEmptyRef12 = -1.0e4f;   // softmax reference before any token: finite, far above the masked score
-constexpr int kLutMax12 = 32767;
-constexpr int kTabThreads = 256;
-constexpr int tab_blocks(int ds) { return (kD / ds) * kC12 / (kTabThreads * 4); }   // per (sequence, KV head), 4 entries per thread
-constexpr int heads_per_table(int ds) { return ds == 32 ? 4 : 2; }                  // heads whose int16 table fits 128 KB
-constexpr float kPShift12 = 12.f;        // weights are kept scaled by 2^12 so that small ones stay normal in fp16
 
 struct D12Params {
     const half_t* q;
@@ -47,7 +35,7 @@ struct D12Params {
     const int32_t *idx_k, *idx_v;
     const half_t *rows_k, *rows_v;
     float* part;                          // [B][Hq][S][kD + 2]
-    const float4_t* tab;                  // [B][Hkv][M][4096] fp32 scores of the four heads, from d12_table_kernel
+    const float2* tab;                    // [B][Hkv][2 pairs of heads][M][4096] fp32 scores, from d12_table_kernel
     const float* tab_amax;                // [B][Hkv][table blocks][4] per-block maxima of |score|
     int64_t N, N_cap;
     int k_k, k_v;
@@ -58,66 +46,12 @@ struct D12Params {
                                           // codes, the table and the K anchor list are not used then)
 };
 
-__device__ __forceinline__ float dot8f(const half8_t& a, const half8_t& b, float acc)
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const half2_t x = {a[2 * i], a[2 * i + 1]}, y = {b[2 * i], b[2 * i + 1]};
-        acc = __builtin_amdgcn_fdot2(x, y, acc, false);
-    }
-    return acc;
-}
-
-// first position in ascending idx[0..n) whose value is >= target; 64-ary search, every lane returns the same value
-__device__ __forceinline__ int lower_bound64(const int32_t* __restrict__ idx, int n, int target, int lane)
-{
-    int lo = 0, hi = n;                                   // the answer lies in [lo, hi]
-    while (hi > lo) {
-        const int len = hi - lo;
-        const int step = (len + 63) / 64;                 // 64 probes at lo + lane * step cover [lo, hi)
-        const int pos = lo + lane * step;
-        const bool below = pos < hi && idx[pos] < target;
-        const int cnt = (int)__popcll(__ballot(below));   // the list ascends, so these lanes form a prefix
-        if (cnt == 0) { hi = lo; break; }
-        int nhi = lo + cnt * step;                        // probe cnt is not below the target (or past the end)
-        if (nhi > hi) nhi = hi;
-        lo = lo + (cnt - 1) * step + 1;                   // probe cnt - 1 is below it
-        hi = nhi;                                         // hi - lo <= step - 1 < len: the loop ends
-    }
-    return lo;
-}
-
-// a token's code words: 48 or 96 bits, code m at bits 12 m .. 12 m + 11
-template <int DS>
-__device__ __forceinline__ void load_cw(const uint8_t* __restrict__ base, int64_t tok, uint32_t (&w)[3])
-{
-    if constexpr (DS == 32) {
-        const uint16_t* s = (const uint16_t*)(base + tok * 6);
-        w[0] = (uint32_t)s[0] | ((uint32_t)s[1] << 16);
-        w[1] = (uint32_t)s[2];
-        w[2] = 0u;
-    } else {
-        const uint32_t* s = (const uint32_t*)(base + tok * 12);
-        w[0] = s[0];
-        w[1] = s[1];
-        w[2] = s[2];
-    }
-}
-
-__device__ __forceinline__ uint32_t code12(const uint32_t (&w)[3], int m)
-{
-    const int bit = 12 * m, d = bit >> 5, sh = bit & 31;       // m is a compile-time constant wherever this is called
-    uint32_t v = w[d] >> sh;
-    if (sh > 20) v |= w[d + 1] << (32 - sh);
-    return v & 0xFFFu;
-}
-
 // fp32 table of c1 q_h . centroid for one (sequence, KV head): every workgroup of the decode kernel that works on this
 // pair needs the same M x 4096 x 4 values, so they are computed once here (the K codebook is read once instead of
 // once per decode workgroup) and only quantised into LDS there.
 template <int kD12>
 __global__ __launch_bounds__(kTabThreads) void d12_table_kernel(const half_t* __restrict__ q, const half_t* __restrict__ cb_k,
-                                                                float c1, int Hq, int Hkv, int G, float4_t* __restrict__ tab,
+                                                                float c1, int Hq, int Hkv, int G, float2* __restrict__ tab,
                                                                 float* __restrict__ tab_amax)
 {
     __shared__ __attribute__((aligned(16))) half_t s_q[kNH * kD];
@@ -128,26 +62,29 @@ __global__ __launch_bounds__(kTabThreads) void d12_table_kernel(const half_t* __
     const int bg = blockIdx.x, b = bg / Hkv, g = bg % Hkv;
     for (int i = tid; i < kNH * kD; i += kTabThreads)
         s_q[i] = ((i >> 7) < G) ? q[((int64_t)b * Hq + g * G) * kD + i] : (half_t)0.f;
+    // (all four centroids of the thread are requested before the first is used)
+    const int e0 = blockIdx.y * 4 * kTabThreads + tid;                 // entry = (sub-space, code)
+    half8_t cv[4][kD12 / 8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int u = 0; u < kD12 / 8; ++u) cv[k][u] = *(const half8_t*)(cb_k + ((int64_t)g * kM12 * kC12 + e0 + k * kTabThreads) * kD12 + 8 * u);
     __syncthreads();
     float amax[kNH] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int k = 0; k < 4; ++k) {
-        const int e = (blockIdx.y * 4 + k) * kTabThreads + tid;        // entry = (sub-space, code)
-        const int m = e / kC12;
-        const half_t* cp = cb_k + ((int64_t)g * kM12 * kC12 + e) * kD12;
-        half8_t cv[kD12 / 8];
 #pragma unroll
-        for (int u = 0; u < kD12 / 8; ++u) cv[u] = *(const half8_t*)(cp + 8 * u);
+    for (int k = 0; k < 4; ++k) {
+        const int e = e0 + k * kTabThreads, m = e / kC12;
         float4_t o;
 #pragma unroll
         for (int h = 0; h < kNH; ++h) {
             float d = 0.f;
 #pragma unroll
-            for (int u = 0; u < kD12 / 8; ++u) d = dot8f(cv[u], *(const half8_t*)(s_q + h * kD + m * kD12 + 8 * u), d);
+            for (int u = 0; u < kD12 / 8; ++u) d = dot8f(cv[k][u], *(const half8_t*)(s_q + h * kD + m * kD12 + 8 * u), d);
             o[h] = d * c1;
             amax[h] = fmaxf(amax[h], fabsf(o[h]));
         }
-        tab[(int64_t)bg * kM12 * kC12 + e] = o;
+        tab[(int64_t)(2 * bg) * kM12 * kC12 + e] = float2{o[0], o[1]};
+        tab[(int64_t)(2 * bg + 1) * kM12 * kC12 + e] = float2{o[2], o[3]};
     }
 #pragma unroll
     for (int h = 0; h < kNH; ++h) {
@@ -242,11 +179,13 @@ __global__ __launch_bounds__(kT12) void decode12_kernel(const D12Params p)
             inv_q[h] = a > 0.f ? (float)kLutMax12 / a : 0.f;
             lut_q[h] = a * (1.0f / (float)kLutMax12);
         }
-        const float4_t* tb = p.tab + (int64_t)bg * kM12 * kC12;
+        const float2* tb = p.tab + (int64_t)(2 * bg + (NHT == 4 ? 0 : walk)) * kM12 * kC12;
 #pragma unroll 4
         for (int e = tid; e < kM12 * kC12; e += kT12) {
-            const float4_t sc = tb[e];
+            const float2 s01 = tb[e];
             if constexpr (NHT == 4) {
+                const float2 s23 = tb[kM12 * kC12 + e];
+                const float sc[4] = {s01.x, s01.y, s23.x, s23.y};
                 int q16[4];
 #pragma unroll
                 for (int h = 0; h < 4; ++h) q16[h] = (int)rintf(sc[h] * inv_q[h]);
@@ -255,7 +194,7 @@ __global__ __launch_bounds__(kT12) void decode12_kernel(const D12Params p)
                 w[1] = ((uint32_t)q16[2] & 0xFFFFu) | ((uint32_t)q16[3] << 16);
                 s_lut[e] = w;
             } else {
-                const int qa = (int)rintf((walk ? sc[2] : sc[0]) * inv_q[0]), qb = (int)rintf((walk ? sc[3] : sc[1]) * inv_q[1]);
+                const int qa = (int)rintf(s01.x * inv_q[0]), qb = (int)rintf(s01.y * inv_q[1]);
                 s_lut[e] = ((uint32_t)qa & 0xFFFFu) | ((uint32_t)qb << 16);
             }
         }
@@ -647,7 +586,7 @@ struct D12AnsParams {
     const uint8_t* codes_k;
     const int32_t* idx_k;
     const half_t* rows_k;
-    const float4_t* tab;
+    const float2* tab;
     float* stat_part;                     // [B][Hq][S][2]
     float *ans_k, *ans_v;                 // [B][Hkv][N]
     int64_t N, N_cap;
@@ -708,12 +647,12 @@ __global__ __launch_bounds__(kT12) void d12_ans_kernel(const D12AnsParams p)
         __syncthreads();                                               // the previous walk no longer reads the table or s_red
         if (tid < 2 * kD) s_qf[tid] = ((tid >> 7) < nh) ? (float)p.q[((int64_t)b * p.Hq + hfirst) * kD + tid] : 0.f;
         {
-            const float4_t* tb = p.tab + (int64_t)bg * kM12 * kC12;
+            const float2* tb = p.tab + (int64_t)(2 * bg + (NHA * hh) / 2) * kM12 * kC12;
 #pragma unroll 4
             for (int e = tid; e < kM12 * kC12; e += kT12) {
-                const float4_t t = tb[e];
-                if constexpr (NHA == 2) s_lut[e] = hh ? float2{t[2], t[3]} : float2{t[0], t[1]};
-                else s_lut[e] = hh == 0 ? t[0] : (hh == 1 ? t[1] : (hh == 2 ? t[2] : t[3]));
+                const float2 t = tb[e];
+                if constexpr (NHA == 2) s_lut[e] = t;
+                else s_lut[e] = (hh & 1) ? t.y : t.x;
             }
         }
         __syncthreads();
@@ -849,11 +788,12 @@ __global__ __launch_bounds__(kT12) void d12_ans_kernel(const D12AnsParams p)
 }
 
 struct D12Plan {
-    int S, chunk;
-    size_t off_part, off_tab, off_amax, off_stat, off_early, total;
+    int S, chunk, S2, slots;              // S2: token ranges of d12_values_kernel (by_code)
+    int64_t range;
+    size_t off_part, off_tab, off_amax, off_stat, off_early, off_wts, off_ref, total;
 };
 
-D12Plan d12_plan(const Geom& g, int64_t N)
+D12Plan d12_plan(const Geom& g, int64_t N, bool by_code)
 {
     D12Plan pl;
     const int64_t bgc = (int64_t)g.B * g.Hkv;
@@ -865,21 +805,43 @@ D12Plan d12_plan(const Geom& g, int64_t N)
     if (S < 1) S = 1;
     pl.S = (int)S;
     pl.chunk = (int)chunk;
+    pl.S2 = 0;
+    pl.range = 64;
+    if (by_code) {                                                     // a workgroup per CU: ranges x pairs of sub-spaces
+        int64_t S2 = 256 / (bgc * (g.M / 2));
+        if (S2 > (N + 2047) / 2048) S2 = (N + 2047) / 2048;
+        if (S2 < 1) S2 = 1;
+        pl.range = ((N + S2 - 1) / S2 + 63) / 64 * 64;
+        if (pl.range < 64) pl.range = 64;
+        pl.S2 = (int)((N + pl.range - 1) / pl.range);
+    }
+    pl.slots = pl.S + pl.S2;
     size_t off = 0;
-    pl.off_part = off; off += align_up((size_t)g.B * g.Hq * S * (kD + 2) * sizeof(float));
+    pl.off_part = off; off += align_up((size_t)g.B * g.Hq * pl.slots * (kD + 2) * sizeof(float));
     pl.off_tab = off;  off += align_up((size_t)g.B * g.Hkv * g.M * kC12 * sizeof(float4_t));
     pl.off_amax = off; off += align_up((size_t)g.B * g.Hkv * tab_blocks(g.d) * kNH * sizeof(float));
     pl.off_stat = off; off += align_up((size_t)g.B * g.Hq * S * 2 * sizeof(float));
     pl.off_early = off;                                                // first-walk scores: only where a table holds fewer heads than the group has
-    if (g.G > heads_per_table(g.d)) off += align_up((size_t)g.B * g.Hkv * N * sizeof(float2));
+    if (g.G > heads_per_table(g.d) && !by_code) off += align_up((size_t)g.B * g.Hkv * N * sizeof(float2));
+    pl.off_wts = off;
+    if (by_code) off += align_up((size_t)(g.G > 2 ? 2 : 1) * bgc * N * sizeof(uint32_t));
+    pl.off_ref = off;
+    if (by_code) off += align_up((size_t)bgc * ((N + 63) / 64) * kNH * sizeof(float));
     pl.total = off;
     return pl;
 }
 
+// The values are added up by code (decode12_by_code.hip) where a workgroup of its second kernel has enough tokens: clearing the
+// 2 x 4096 sums and multiplying them by their centroids costs it 15 (d16) or 20 us whatever their number, a token then takes a
+// fraction of the gather's time.  One step, gather and by code, us: d32, 8 KV heads (16 ranges) 200000 tokens 61 and 65, 420000
+// 102 and 81, 840000 169 and 102; 64 heads (2 ranges) 16000 57 and 60, 33333 81 and 67; d16, 8 heads (8 ranges) 50000 61 and 63,
+// 70000 67 and 66, 840000 308 and 153; 64 heads (1 range) 4096 54 and 56, 9001 66 and 59, 70000 229 and 106.
+bool d12_by_code(const Geom& g, int64_t N) { return d12_plan(g, N, true).range >= (g.d == 32 ? 14336 : 8192); }
+
 template <int DS>
-hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, hipStream_t st)
+hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool by_code, hipStream_t st)
 {
-    const D12Plan pl = d12_plan(g, a.N);
+    const D12Plan pl = d12_plan(g, a.N, by_code);
     constexpr size_t lds = d12_lds(DS);
     static OncePerDevice once;
     const hipError_t setup = on_this_device(once, []() {
@@ -894,20 +856,30 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, hipSt
     p.q = a.q; p.codes_k = a.codes_k; p.codes_v = a.codes_v; p.cb_k = a.cb_k; p.cb_v = a.cb_v;
     p.idx_k = a.idx_k; p.idx_v = a.idx_v; p.rows_k = a.rows_k; p.rows_v = a.rows_v;
     char* w = (char*)ws;
-    p.part = (float*)(w + pl.off_part); p.tab = (const float4_t*)(w + pl.off_tab); p.tab_amax = (const float*)(w + pl.off_amax);
+    p.part = (float*)(w + pl.off_part); p.tab = (const float2*)(w + pl.off_tab); p.tab_amax = (const float*)(w + pl.off_amax);
     p.N = a.N; p.N_cap = a.N_cap; p.k_k = (int)a.k_k; p.k_v = (int)a.k_v;
     p.c1 = a.scale * kLog2e; p.Hq = g.Hq; p.Hkv = g.Hkv; p.G = g.G; p.S = a.N > 0 ? pl.S : 0; p.chunk = pl.chunk;
     p.early = (float2*)(w + pl.off_early);
     p.given = (const float4_t*)a.given_scores;
     if (a.given_scores && (a.k_k != 0 || a.ans_k || a.ans_v)) return hipErrorInvalidValue;     // the scores cover the K anchors already
-    if (a.N > 0 && a.given_scores) {
+    if (a.N > 0 && !a.given_scores)
+        hipLaunchKernelGGL(d12_table_kernel<DS>, dim3((unsigned)(g.B * g.Hkv), tab_blocks(DS)), dim3(kTabThreads), 0, st, a.q,
+                           a.cb_k, p.c1, g.Hq, g.Hkv, g.G, (float2*)(w + pl.off_tab), (float*)(w + pl.off_amax));
+    if (a.N > 0 && by_code) {
+        D12LongParams l;
+        l.q = p.q; l.codes_k = p.codes_k; l.codes_v = p.codes_v; l.cb_v = p.cb_v; l.idx_k = p.idx_k; l.idx_v = p.idx_v;
+        l.rows_k = p.rows_k; l.rows_v = p.rows_v; l.tab = p.tab; l.tab_amax = p.tab_amax; l.given = p.given; l.part = p.part;
+        l.wts = (uint32_t*)(w + pl.off_wts); l.tile_ref = (float*)(w + pl.off_ref); l.N = p.N; l.N_cap = p.N_cap; l.range = pl.range;
+        l.k_k = p.k_k; l.k_v = p.k_v; l.c1 = p.c1; l.Hq = p.Hq; l.Hkv = p.Hkv; l.G = p.G; l.S = pl.S; l.chunk = pl.chunk;
+        l.S2 = pl.S2; l.slots = pl.slots;
+        const hipError_t e = launch_decode12_by_code(g, l, st);
+        if (e != hipSuccess) return e;
+    } else if (a.N > 0 && a.given_scores) {
         hipLaunchKernelGGL((decode12_kernel<DS, true>), dim3((unsigned)(g.B * g.Hkv * pl.S)), dim3(kT12), lds, st, p);
     } else if (a.N > 0) {
-        hipLaunchKernelGGL(d12_table_kernel<DS>, dim3((unsigned)(g.B * g.Hkv), tab_blocks(DS)), dim3(kTabThreads), 0, st, a.q,
-                           a.cb_k, p.c1, g.Hq, g.Hkv, g.G, (float4_t*)(w + pl.off_tab), (float*)(w + pl.off_amax));
         hipLaunchKernelGGL((decode12_kernel<DS, false>), dim3((unsigned)(g.B * g.Hkv * pl.S)), dim3(kT12), lds, st, p);
     }
-    hipLaunchKernelGGL(decode12_merge, dim3((unsigned)(g.B * g.Hq)), dim3(kD), 0, st, (const float*)p.part, p.S, a.out);
+    hipLaunchKernelGGL(decode12_merge, dim3((unsigned)(g.B * g.Hq)), dim3(kD), 0, st, (const float*)p.part, a.N > 0 ? pl.slots : 0, a.out);
     if (a.ans_k && a.N > 0) {
         static OncePerDevice once_ans;
         const hipError_t setup_ans = on_this_device(once_ans, []() {
@@ -932,11 +904,13 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, hipSt
 
 }  // namespace
 
-size_t decode12_workspace_bytes(const Geom& g, int64_t N) { return d12_plan(g, N).total; }
+size_t decode12_workspace_bytes(const Geom& g, int64_t N) { return d12_plan(g, N, d12_by_code(g, N)).total; }
+size_t decode12_workspace_least(const Geom& g, int64_t N) { return d12_plan(g, N, false).total; }
 
-hipError_t launch_decode12(const Geom& g, const DecodeArgs& a, void* ws, hipStream_t st)
+hipError_t launch_decode12(const Geom& g, const DecodeArgs& a, void* ws, size_t ws_bytes, hipStream_t st)
 {
-    return g.d == 32 ? launch_decode12_t<32>(g, a, ws, st) : launch_decode12_t<16>(g, a, ws, st);
+    const bool by_code = d12_by_code(g, a.N) && ws_bytes >= d12_plan(g, a.N, true).total;
+    return g.d == 32 ? launch_decode12_t<32>(g, a, ws, by_code, st) : launch_decode12_t<16>(g, a, ws, by_code, st);
 }
 
 }  // namespace antkv
