@@ -42,6 +42,14 @@ __device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b, float 
 
 typedef float pair_t __attribute__((ext_vector_type(2)));
 
+// lanes 0-31: a's value of either half-wave in (a, b), lanes 32-63: b's
+__device__ __forceinline__ void cross(uint32_t& a, uint32_t& b)
+{
+    const uint2_t r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
 constexpr int kEncThreads = 512;
 constexpr int kEncWaves = kEncThreads / 64;
 constexpr int kQuad = 4;               // sub-spaces of a workgroup
@@ -61,20 +69,6 @@ constexpr int enc_n_halfs(int d) { return d == 16 ? kQuad * kC * 4 : 8; }
 template <int DSUB>
 __device__ __forceinline__ int swizzle(int group) { return (DSUB == 16 ? group >> 1 : group >> 2) & 3; }
 
-// lower half-wave's and upper half-wave's value of v, in every lane
-__device__ __forceinline__ void halves(uint32_t v, uint32_t& lo, uint32_t& hi)
-{
-    const uint2_t r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    lo = r[0];
-    hi = r[1];
-}
-// lanes 0-31: a summed over the two half-waves; lanes 32-63: b
-__device__ __forceinline__ float fold(float a, float b)
-{
-    const uint2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 template <int DSUB>
 __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
     const half_t* __restrict__ x, int64_t xs_b, int64_t xs_h, int64_t xs_t, int64_t n_tok,
@@ -87,7 +81,7 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
     constexpr int kPlane = kQuad * kC * 8;                                             // d = 8: the second array inside s_a
     __shared__ __attribute__((aligned(256))) half_t s_a[enc_a_halfs(DSUB)];            // see above
     __shared__ __attribute__((aligned(16))) half_t s_n[enc_n_halfs(DSUB)];             // d = 16 only: norm terms,
-    __shared__ float s_f[DSUB == 16 ? kQuad * kC : 1];                                 // and their fp32 value
+    __shared__ __attribute__((aligned(16))) float s_f[kQuad * kC];                     // -||c||^2 / 2 in fp32
     __shared__ uint64_t s_good[kQuad * kC / 64];                                       // centroids within the norm limit
     static_assert(kQuad * kC / 64 == 16, "16 lanes read the words");
     const int tid = threadIdx.x;
@@ -130,8 +124,8 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
             *(half8_t*)(row + kPlane) = half8_t{n_hi, n_mid, n_lo, z, z, z, z, z};
         } else {
             *(half4_t*)(s_n + e * 4) = half4_t{n_hi, n_mid, n_lo, z};
-            s_f[e] = -0.5f * nn;
         }
+        s_f[e] = -0.5f * nn;
         return __float_as_uint(nn) < __float_as_uint(kNormLimit);      // (as integers: a NaN is above every number)
     };
 #pragma unroll
@@ -184,25 +178,28 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
     __syncthreads();
     // Centroids beyond the norm limit are never chosen: their terms, which are infinities and NaN, give way to a copy of the
     // sub-space's first good centroid.  A copy behind it loses the tie; one before it is told by its index.
-    int first_good[kQuad] = {0, 0, 0, 0};
+    int first_good[kQuad / 2] = {0, 0};                               // of sub-space 2 i (lanes 0-31) or 2 i + 1
     if (__builtin_expect(__any(s_good[lane & 15] != ~0ull), 0)) {     // (the same in every wave)
+        int first[kQuad];
 #pragma unroll
         for (int mm = 0; mm < kQuad; ++mm) {
+            first[mm] = 0;
             for (int i = kC / 64 - 1; i >= 0; --i) {
                 const uint64_t good = s_good[mm * (kC / 64) + i];
-                if (good != 0ull) first_good[mm] = 64 * i + __builtin_ctzll(good);
+                if (good != 0ull) first[mm] = 64 * i + __builtin_ctzll(good);
             }
-            first_good[mm] = __builtin_amdgcn_readfirstlane(first_good[mm]);
+            first[mm] = __builtin_amdgcn_readfirstlane(first[mm]);
         }
         for (int e = tid; e < kQuad * kC; e += kEncThreads)
-            if ((s_good[e >> 6] >> (e & 63) & 1) == 0) stage(e, (e & ~(kC - 1)) + first_good[e / kC]);
+            if ((s_good[e >> 6] >> (e & 63) & 1) == 0) stage(e, (e & ~(kC - 1)) + first[e / kC]);
+#pragma unroll
+        for (int i = 0; i < kQuad / 2; ++i) first_good[i] = h ? first[2 * i + 1] : first[2 * i];
         __syncthreads();
     }
     while (unit < total) {
         const int64_t next = unit + (int64_t)chunks * kEncWaves;
         half8_t nx[kQuad];
         fetch(next < total ? next : unit, nx);
-        uint32_t word = 0u;
         float16_t acc[2];
         half8_t a[2];
         half4_t a4[2];
@@ -221,11 +218,12 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
                 acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, bn, acc[s & 1], 0, 0, 0);
             }
         };
-        // Running maximum over tiles of 16 candidates per lane.  The tile maximum is a chain of max3 over four quads
-        // (rows 8 q + 4 h .. + 3); when a tile raises the running maximum (strictly, so the lowest tile wins ties) its id
-        // and the chain's value after each quad are kept, by moves under the lanes' mask.  The next tile's product is in
-        // flight meanwhile, with its operand read one tile earlier still.
-        pair_t keep[kQuad][2];                                         // after quads (0, 1), (2, 3) of the best tile
+        // Running maximum over tiles of 16 candidates per lane: a chain of max3 over the best so far and four quads (rows
+        // 8 q + 4 h .. + 3).  When a tile raises it (strictly, so the lowest tile wins ties) the tile's id and the chain's value
+        // after each of the first three quads are kept, by moves under the lanes' mask (every lane is active before and
+        // after).  The next tile's product is in flight meanwhile, with its operand read one tile earlier still.
+        pair_t keep[kQuad];                                            // chain after quads 0, 1 of the best tile,
+        float keep2[kQuad], best[kQuad];                               // after quad 2, and its end
         int tile[kQuad];
         operand(0);
         operand(1);
@@ -239,56 +237,79 @@ __global__ __launch_bounds__(kEncThreads, 4) void encode_kernel(
                 if (s + 2 < 8 * kQuad) operand(s + 2);
                 __builtin_amdgcn_sched_barrier(0);
                 const float16_t& v = acc[s & 1];
-                pair_t lo, hi;
-                lo[0] = max3f(max2f(v[0], v[1]), v[2], v[3]);
+                pair_t lo;
+                lo[0] = max3f(t == 0 ? max2f(v[0], v[1]) : max3f(best[mm], v[0], v[1]), v[2], v[3]);
                 lo[1] = max3f(max3f(lo[0], v[4], v[5]), v[6], v[7]);
-                hi[0] = max3f(max3f(lo[1], v[8], v[9]), v[10], v[11]);
-                hi[1] = max3f(max3f(hi[0], v[12], v[13]), v[14], v[15]);
+                const float hi = max3f(max3f(lo[1], v[8], v[9]), v[10], v[11]);
+                const float top = max3f(max3f(hi, v[12], v[13]), v[14], v[15]);
                 if (t == 0) {
-                    keep[mm][0] = lo;
-                    keep[mm][1] = hi;
+                    keep[mm] = lo;
+                    keep2[mm] = hi;
                     tile[mm] = 0;
-                } else if (hi[1] > keep[mm][1][1]) {
-                    asm volatile("v_mov_b64 %0, %2\n\tv_mov_b64 %1, %3" : "+v"(keep[mm][0]), "+v"(keep[mm][1]) : "v"(lo), "v"(hi));
-                    tile[mm] = t;
+                } else {
+                    asm volatile("v_cmpx_gt_f32 vcc, %6, %7\n\tv_mov_b64 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5\n\ts_mov_b64 exec, -1"
+                                 : "+v"(keep[mm]), "+v"(keep2[mm]), "+v"(tile[mm])
+                                 : "v"(lo), "v"(hi), "n"(t), "v"(top), "v"(best[mm])
+                                 : "vcc");
                 }
+                best[mm] = top;
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // The winner is in the first quad whose chain value is the maximum.  The token's two lanes agree on the better
-        // quad (equal scores: the lower one) and settle which of its four centroids it was with packed dot products
-        // (v_dot2_f32_f16), each lane over its own k slots; after the fold lanes 0-31 hold the sums of centroids 0 and 2,
-        // lanes 32-63 those of 1 and 3.
+        // The winner is in the first quad whose chain value is the maximum.  Two sub-spaces are settled at once, lanes 0-31 for the
+        // first and 32-63 for the second: the token's two candidates (equal scores: the lower quad) change places between
+        // the half-waves, as the sub-vectors do, and a lane scores the four centroids of its quad with packed dot products
+        // (v_dot2_f32_f16) and takes the lowest index among equals.
+        uint32_t pair_codes[kQuad / 2];
 #pragma unroll
-        for (int mm = 0; mm < kQuad; ++mm) {
-            const float best = keep[mm][1][1];
-            int q = 0;
+        for (int pr = 0; pr < kQuad / 2; ++pr) {
+            uint32_t grp[2];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) q += keep[mm][i >> 1][i & 1] < best ? 1 : 0;
-            uint32_t b_lo, b_hi, g_lo, g_hi;
-            halves(__float_as_uint(best), b_lo, b_hi);
-            halves((uint32_t)(8 * tile[mm] + 2 * q + h), g_lo, g_hi);
-            const float f_lo = __uint_as_float(b_lo), f_hi = __uint_as_float(b_hi);
-            const bool up = f_hi > f_lo || (f_hi == f_lo && g_hi < g_lo);
-            const int grp = (int)(up ? g_hi : g_lo);                     // centroids 4 grp .. 4 grp + 3
-            const int at = (mm * kC + 4 * grp + swizzle<DSUB>(grp)) * kRow + my_k;
+            for (int i = 0; i < 2; ++i) {
+                const int mm = 2 * pr + i;
+                const int q = (keep[mm][0] < best[mm] ? 1 : 0) + (keep[mm][1] < best[mm] ? 1 : 0) + (keep2[mm] < best[mm] ? 1 : 0);
+                grp[i] = (uint32_t)(8 * tile[mm] + 2 * q + h);
+            }
+            uint32_t b0 = __float_as_uint(best[2 * pr]), b1 = __float_as_uint(best[2 * pr + 1]);
+            cross(b0, b1);                                             // of this lane's sub-space: lower, upper half-wave
+            cross(grp[0], grp[1]);
+            const float top0 = __uint_as_float(b0), top1 = __uint_as_float(b1);
+            const bool up = top1 > top0 || (top1 == top0 && grp[1] < grp[0]);
+            const int gr = (int)(up ? grp[1] : grp[0]);                // centroids 4 gr .. 4 gr + 3
+            uint4_t x0 = __builtin_bit_cast(uint4_t, bx[2 * pr]), x1 = __builtin_bit_cast(uint4_t, bx[2 * pr + 1]);
+#pragma unroll
+            for (int i = 0; i < (DSUB == 4 ? 2 : 4); ++i) {            // x0: channels 0 .. 7, x1 (d = 16): the others
+                uint32_t a0 = x0[i], a1 = x1[i];
+                cross(a0, a1);
+                x0[i] = a0;
+                x1[i] = a1;
+            }
+            const int sub = (2 * pr + h) * kC;
+            const half_t* rows = s_a + (sub + 4 * gr) * kRow;
+            const int at = swizzle<DSUB>(gr) * kRow;
+            const float4_t nrm = *(const float4_t*)(s_f + sub + 4 * gr);
             float sc[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sc[e] = dot8(*(const half8_t*)(s_a + (at ^ (e * kRow))), bx[mm], 0.f);
-            float s01 = fold(sc[0], sc[1]), s23 = fold(sc[2], sc[3]);
-            if constexpr (DSUB == 16) {
-                s01 += s_f[mm * kC + 4 * grp + h];
-                s23 += s_f[mm * kC + 4 * grp + 2 + h];
+            for (int e = 0; e < 4; ++e) {
+                const half_t* row = rows + (at ^ (e * kRow));
+                if constexpr (DSUB == 4) {
+                    const half4_t c = *(const half4_t*)row;
+                    const half4_t xv = __builtin_bit_cast(half4_t, uint2_t{x0[0], x0[1]});
+                    sc[e] = __builtin_amdgcn_fdot2(half2_t{c[0], c[1]}, half2_t{xv[0], xv[1]}, nrm[e], false);
+                    sc[e] = __builtin_amdgcn_fdot2(half2_t{c[2], c[3]}, half2_t{xv[2], xv[3]}, sc[e], false);
+                } else {
+                    sc[e] = dot8(*(const half8_t*)row, __builtin_bit_cast(half8_t, x0), nrm[e]);
+                    if constexpr (DSUB == 16) sc[e] = dot8(*(const half8_t*)(row + 8), __builtin_bit_cast(half8_t, x1), sc[e]);
+                }
             }
-            const float s_max = max2f(s01, s23);
-            uint32_t m_lo, m_hi, e_lo, e_hi;
-            halves(__float_as_uint(s_max), m_lo, m_hi);
-            halves(s01 == s_max ? (uint32_t)h : (uint32_t)(2 + h), e_lo, e_hi);
-            const float v_lo = __uint_as_float(m_lo), v_hi = __uint_as_float(m_hi);
-            const bool odd = v_lo != max2f(v_lo, v_hi) || (v_lo == v_hi && e_hi < e_lo);
-            const int code = 4 * grp + (int)(odd ? e_hi : e_lo);
-            word |= (uint32_t)(code > first_good[mm] ? code : first_good[mm]) << (8 * mm);
+            const float s_max = max2f(max3f(sc[0], sc[1], sc[2]), sc[3]);
+            const int e = sc[0] == s_max ? 0 : (sc[1] == s_max ? 1 : (sc[2] == s_max ? 2 : 3));
+            const int code = 4 * gr + e;
+            pair_codes[pr] = (uint32_t)(code > first_good[pr] ? code : first_good[pr]);
         }
+        uint32_t word = pair_codes[0] | pair_codes[1] << 16, word_hi = word;
+        cross(word, word_hi);                                          // sub-spaces 0 and 2, 1 and 3
+        word |= word_hi << 8;
         const int64_t b = unit / blocks_per_b, tok = (unit % blocks_per_b) * 32 + n;
         if (tok < n_tok && h == 0)
             *(uint32_t*)(codes + (((int64_t)b * Hkv + g) * N_cap + token_offset + tok) * M + kQuad * quad) = word;
