@@ -204,6 +204,20 @@ def test_encode_work_splits_and_ties(oracle, d, B, n):
     assert not np.isin(got, [1, 6, 17, 28, 44, 250, 102, 255]).any()
 
 
+@pytest.mark.parametrize("d,n", [(4, 24448), (4, 24513), (8, 48960), (8, 49025)])
+def test_encode_workgroups_per_cu(oracle, d, n):
+    """Two KV heads at the token counts (382 and 384, 765 and 767 units of 64) around which the launch goes from two to three
+    workgroups per CU: every unit is encoded once, in its place."""
+    rng = np.random.default_rng(n)
+    cb = rng.standard_normal((2, 128 // d, 256, d)).astype(np.float16)
+    x = rng.standard_normal((1, 2, n, 128)).astype(np.float16)
+    codes = torch.full((1, 2, n + 9, 128 // d), 0xEE, dtype=torch.uint8, device="cuda")
+    codes = antkv.encode(antkv.Geometry(1, 2, 2, d), dev(x), dev(cb), codes, 5).cpu().numpy()
+    assert (codes[:, :, :5] == 0xEE).all() and (codes[:, :, n + 5:] == 0xEE).all()
+    want, margin = oracle.encode(x, cb, want_margin=True)
+    check_codes(codes[:, :, 5:n + 5], want, margin)
+
+
 def test_encode_full_prefill_shape(oracle):
     """32768 new tokens x 8 KV heads, 1-bit VQ: the encode workload at its real size."""
     w = CONFIGS["cfg3"]
