@@ -3,21 +3,24 @@
 //
 // Exact radix select on an order-preserving 32-bit key:
 //   1. histogram of the top 11 key bits per row;
-//   2. every workgroup (slice of 8192 scores) finds the bin d0 that holds the k-th largest key and counts its keys in
-//      higher bins.  If bin d0 holds few keys (at most N/8 + 4096, the usual case for heavy-tailed scores) the
-//      workgroup appends its keys of that bin, with their positions, to the row's candidate list; otherwise (scores
-//      crowded into a narrow range) it adds them to a second histogram over the next 11 bits;
-//   3. only for rows that took the second branch: the same once more, one level down (count the keys of bin d0
-//      above the second digit d1, list the keys with prefix (d0, d1)); workgroups of other rows return at once;
-//   4. one workgroup per row selects the exact k-th largest key tau among the candidates (radix rounds on the
-//      remaining bits, histograms in LDS) and adds the candidates' share to the per-slice counts of keys > tau and
-//      == tau; a row whose keys agree in 22 bits for more than the list holds is walked by that workgroup instead;
-//   5. an ordered emission pass writes the positions of all keys > tau plus the lowest-positioned keys == tau
-//      needed to reach k, in ascending position order.
-// Rows of up to 32768 scores fit the registers of one workgroup: topk_row does all of it in one launch (the six launches
+//   2. every workgroup (slice of 8192 scores) finds the bin d0 that holds the k-th largest key.  If the keys of that bin and
+//      above are few (at most N/8 + 4096 + k, the usual case for heavy-tailed scores) the workgroup appends its own ones, with
+//      their positions and in their order, to the row's list, as a segment of it; otherwise (scores crowded into a narrow
+//      range) it adds its keys of bin d0 to a second histogram over the next 11 bits;
+//   3. only for rows that took the second branch: the same once more, one level down (the keys from prefix (d0, d1) up are
+//      listed); workgroups of other rows return at once;
+//   4. one workgroup per row selects the exact k-th largest key tau among the list's (radix rounds on the remaining bits,
+//      histograms in LDS) and counts every slice's keys > tau and == tau; a row whose keys agree in 22 bits for more than the
+//      list holds is walked by that workgroup instead;
+//   5. an ordered emission pass over the segments (over the scores of a row that is not listed) writes the positions of all
+//      keys > tau plus the lowest-positioned keys == tau needed to reach k, in ascending position order.  (By the one
+//      workgroup per row of step 4 it took 20 us for 16 rows of 840000.)
+// The scores are read once, or twice where the producer has not counted them for the first histogram.
+// Rows of up to 32768 scores fit the registers of one workgroup: topk_row does all of it in one launch (the launches
 // above cost 38 us for 128 rows of 1531 scores, this one 6).  The kernels for
-// longer rows are bound by latency up to some 100000 scores and by reading the scores twice beyond.  16 rows of 840000
-// scores, whole call: 78 us if the rows are 16-byte aligned, 94 if not; 256 rows of 40000: 54 us.
+// longer rows are bound by latency up to some 100000 scores and by reading the scores beyond.  16 rows of
+// 840000 scores whose histogram the producer counted, kernel trace: 61 us when step 2 listed bin d0 alone and step 5 read all
+// scores again, 46 now; 256 rows of 40000 with the histogram 57 and 47.
 #include "common.h"
 
 namespace antkv {
@@ -78,7 +81,7 @@ __device__ __forceinline__ const float* row_scores(const float* scores, const fl
 }
 
 // per-row header in the workspace
-enum { kHeadCount = 0, kHeadTau = 1, kHeadNeedEq = 2, kHeadCrowded = 3, kHeadWords = 8 };
+enum { kHeadCount = 0, kHeadTau = 1, kHeadNeedEq = 2, kHeadCrowded = 3, kHeadUnlisted = 4, kHeadWords = 8 };
 
 __global__ __launch_bounds__(kTopkThreads) void topk_hist0(const float* __restrict__ scores,
                                                            const float* __restrict__ scores_b, int rows_a, int64_t N,
@@ -107,129 +110,143 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist0(const float* __restri
         if (lh[i]) atomicAdd(&hist[i], lh[i]);
 }
 
-// LEVEL 1: per slice, count the keys above bin d0; list the keys of bin d0, or (crowded bin) histogram their next
-// 11 bits.  LEVEL 2, rows with a crowded bin only: count the keys of bin d0 above the second digit d1 and list the
-// keys with prefix (d0, d1).
+// Keys of a slice in a thread.  A whole, 16-byte aligned slice: a thread owns 32 consecutive scores; any other: a wave owns 2048
+// consecutive ones, 64 at a time (coalesced), element j of lane l at 64 j + l.  (16 rows of 840000, listing: aligned 14 us by
+// threads, 20 by waves; 840003 scores, not aligned, 87 by threads (a dword at a time), 16 by waves.)
+constexpr int kPer = kSlice / kTopkThreads;
+
+// LEVEL 1: list the keys from bin d0 up, or (crowded) histogram the next 11 bits of bin d0's.  LEVEL 2, crowded rows only: list
+// the keys from the prefix (d0, d1) up.  segs: [rows][slices] (start, length) of the slice's segment of the row's list.
 template <int LEVEL>
 __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __restrict__ scores,
                                                              const float* __restrict__ scores_b, int rows_a, int64_t N,
                                                              uint32_t k, uint32_t* __restrict__ ws_hist,
-                                                             uint32_t* __restrict__ head, uint32_t* __restrict__ counts,
+                                                             uint32_t* __restrict__ head, uint2_t* __restrict__ segs,
                                                              int n_slices, uint2_t* __restrict__ cand, uint32_t cap)
 {
     __shared__ uint32_t lh[LEVEL == 1 ? kBins : 1];
     __shared__ uint32_t sh[8];
-    __shared__ uint32_t red[2][4];
+    __shared__ uint32_t red[4];
     __shared__ uint32_t s_base;
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t* hist0 = ws_hist + row * 2 * kBins;
     uint32_t* hist1 = hist0 + kBins;
     if (LEVEL == 2 && head[row * kHeadWords + kHeadCrowded] == 0u) return;
-    const int64_t lo = (int64_t)blockIdx.x * kSlice;
-    const int64_t hi = (lo + kSlice < N) ? lo + kSlice : N;
+    // the scores are requested ahead of the histogram, whose latency they share
+    const int64_t slice_lo = (int64_t)blockIdx.x * kSlice;
     const float* src = row_scores(scores, scores_b, rows_a, row, N);
-    constexpr int kPer = kSlice / kTopkThreads;                 // 32 scores per thread, in 8 groups of 4
+    const bool fast = slice_lo + kSlice <= N && (((uintptr_t)(src + slice_lo)) & 15) == 0;
+    const int64_t lo = slice_lo + (fast ? tid * kPer : wave * (64 * kPer) + lane);
     uint32_t key[kPer];
-    const bool fast = hi - lo == kSlice && (((uintptr_t)(src + lo)) & 15) == 0;
-    const int n_own = (int)(hi - lo);
-    // element j of the thread sits at position lo + pos(j); there are `own` of them
-    const int first = fast ? 4 * tid : tid;
-    auto pos = [&](int j) -> int { return first + (fast ? 4 * kTopkThreads * (j >> 2) + (j & 3) : kTopkThreads * j); };
-    int own = fast ? kPer : (n_own - tid + kTopkThreads - 1) / kTopkThreads;
-    // (negative NaNs share the lowest bin with the zeros past the end: those are left out by position)
-    auto in = [&](int j) -> bool { return j < own; };
+    if (fast) {
+#pragma unroll
+        for (int j = 0; j < kPer / 4; ++j) {
+            const float4_t v = *(const float4_t*)(src + lo + 4 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) key[4 * j + e] = __float_as_uint(v[e]);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? __float_as_uint(src[lo + 64 * j]) : 0xffffffffu;
+    }
+    // (past the end keys are 0, the lowest; the NaN 0xffffffff has it too, so those are left out by position)
+    const int own = fast ? kPer : (lo < N ? (int)((N - lo + 63) / 64 < kPer ? (N - lo + 63) / 64 : kPer) : 0);
     uint32_t d0, k_rem;
     find_digit(hist0, kBins, k, d0, k_rem, sh);
-    const bool crowded = hist0[d0] > cap;                       // the same for every workgroup of the row
-    uint32_t prefix = d0;                                       // keys that match it are the candidates of this level
-    bool list = !crowded;
-    if (LEVEL == 1 && crowded && blockIdx.x == 0 && tid == 0) head[row * kHeadWords + kHeadCrowded] = 1u;
+    const bool crowded = k - k_rem + hist0[d0] > cap;           // the same for every workgroup of the row
+    uint32_t prefix = d0;                                       // the keys from it up are listed
     if (LEVEL == 2) {
         uint32_t d1;
         find_digit(hist1, kBins, k_rem, d1, k_rem, sh);
         prefix = (d0 << 11) | d1;
-        list = hist1[d1] <= cap;
+        if (k - k_rem + hist1[d1] > cap) return;                // topk_resolve walks the row
     }
     constexpr int kShift = LEVEL == 1 ? 21 : 10;
-    if (LEVEL == 1 && crowded) {
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) key[j] = float_key(__uint_as_float(key[j]));
+    if (LEVEL == 1 && crowded) {                                // bin d0's next 11 bits go to the second histogram
+        if (blockIdx.x == 0 && tid == 0) head[row * kHeadWords + kHeadCrowded] = 1u;
         for (int i = tid; i < kBins; i += kTopkThreads) lh[i] = 0u;
         __syncthreads();
-    }
-    if (fast) {
 #pragma unroll
-        for (int j = 0; j < kPer / 4; ++j) {
-            const float4_t v = *(const float4_t*)(src + lo + 4 * (tid + kTopkThreads * j));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(v[e]);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) key[j] = j < own ? float_key(src[lo + tid + kTopkThreads * j]) : 0u;
-    }
-    uint32_t gt = 0, eq = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const uint32_t p = key[j] >> kShift;
-        // LEVEL 2 counts only keys of bin d0 (higher bins were counted by LEVEL 1)
-        gt += in(j) && p > prefix && (LEVEL == 1 || (key[j] >> 21) == d0);
-        eq += in(j) && p == prefix;
-    }
-    // block-wide: total of gt, exclusive prefix of eq
-    uint32_t ieq = eq;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t a = __shfl_up(ieq, off, 64);
-        if (lane >= off) ieq += a;
-    }
-    gt = wave_sum_u32(gt);
-    if (lane == 63) red[1][wave] = ieq;
-    if (lane == 0) red[0][wave] = gt;
-    __syncthreads();
-    uint32_t off_eq = ieq - eq;
-    for (int w = 0; w < wave; ++w) off_eq += red[1][w];
-    const uint32_t tot_eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-    if (tid == 0) {
-        uint32_t* c = counts + (row * n_slices + blockIdx.x) * 2;
-        const uint32_t tot_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        if (LEVEL == 1) { c[0] = tot_gt; c[1] = 0u; }
-        else c[0] += tot_gt;                                    // this workgroup owns its slice's counters
-        s_base = (list && tot_eq) ? atomicAdd(&head[row * kHeadWords + kHeadCount], tot_eq) : 0u;
-    }
-    __syncthreads();
-    // (Compared again below: kept, 64 results spilled scalar registers and cost a wave per SIMD; 16 rows of 840000 25 us, now
-    // 21, 256 rows of 40000 24 and 19.)
-    pin(own);
-    pin(prefix);
-    if (list) {
-        if (eq == 0) return;
-        uint32_t at = s_base + off_eq;
-        uint2_t* out = cand + row * (int64_t)cap;
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            if (in(j) && (key[j] >> kShift) == prefix) {
-                if (at < cap) out[at] = uint2_t{key[j], (uint32_t)(lo + pos(j))};
-                ++at;
-            }
-        }
-    } else if (LEVEL == 1) {                                    // crowded bin: its next 11 bits go to the second histogram
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            if (in(j) && (key[j] >> 21) == prefix) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
-        }
+        for (int j = 0; j < kPer; ++j)
+            if (j < own && (key[j] >> 21) == d0) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
         __syncthreads();
         for (int i = tid; i < kBins; i += kTopkThreads)
             if (lh[i]) atomicAdd(&hist1[i], lh[i]);
+        return;
+    }
+    // entries of the thread (aligned slices) or of the wave, and what comes before them in the slice
+    uint32_t mine = 0, incl;
+    if (fast) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) mine += (key[j] >> kShift) >= prefix;
+        incl = mine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t a = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += a;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) mine += (uint32_t)__popcll(__ballot(j < own && (key[j] >> kShift) >= prefix));
+        incl = mine;
+    }
+    if (lane == 63) red[wave] = incl;
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t n = red[0] + red[1] + red[2] + red[3];
+        s_base = n ? atomicAdd(&head[row * kHeadWords + kHeadCount], n) : 0u;
+        segs[row * n_slices + blockIdx.x] = uint2_t{s_base, n};
+    }
+    __syncthreads();
+    uint32_t at = s_base + incl - mine;
+    for (int w = 0; w < wave; ++w) at += red[w];
+    uint2_t* out = cand + row * (int64_t)cap;
+    // (compared again: kept, 32 results spilled scalar registers and cost a wave per SIMD)
+    pin(prefix);
+    if (fast) {
+        if (mine == 0) return;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            if ((key[j] >> kShift) >= prefix) {
+                if (at < cap) out[at] = uint2_t{key[j], (uint32_t)(lo + j)};
+                ++at;
+            }
+        }
+    } else {
+        const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const bool in = j < own && (key[j] >> kShift) >= prefix;
+            const uint64_t m = __ballot(in);
+            if (m == 0ull) continue;
+            const uint32_t my = at + (uint32_t)__popcll(m & below);
+            if (in && my < cap) out[my] = uint2_t{key[j], (uint32_t)(lo + 64 * j)};
+            at += (uint32_t)__popcll(m);
+        }
     }
 }
 
-// per row: exact k-th largest key among the candidates, and the candidates' share of the per-slice counts
+// one more in lh[bin] for every lane that calls; lanes with the first one's bin are counted by one atomic
+__device__ __forceinline__ void count_in(uint32_t* lh, uint32_t bin)
+{
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+    const uint64_t same = __ballot(bin == first);
+    if (bin != first) atomicAdd(&lh[bin], 1u);
+    else if (__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)) == 0u)
+        atomicAdd(&lh[first], (uint32_t)__popcll(same));
+}
+
+// per row: exact k-th largest key among the listed ones (or among all, where the list does not hold them), and the keys > tau
+// and == tau of every slice
 constexpr int kResolveThreads = 1024;
 
 __global__ __launch_bounds__(kResolveThreads) void topk_resolve(const float* __restrict__ scores,
                                                              const float* __restrict__ scores_b, int rows_a, int64_t N,
                                                              uint32_t k, const uint32_t* __restrict__ ws_hist,
-                                                             uint32_t* __restrict__ head, uint32_t* __restrict__ counts,
+                                                             uint32_t* __restrict__ head, uint2_t* __restrict__ counts,
                                                              int n_slices, const uint2_t* __restrict__ cand, uint32_t cap)
 {
     __shared__ uint32_t lh[kBins];
@@ -241,65 +258,65 @@ __global__ __launch_bounds__(kResolveThreads) void topk_resolve(const float* __r
     const uint32_t* hist1 = hist0 + kBins;
     uint32_t d0, d1 = 0, d2, k_rem, need_eq;
     find_digit<kResolveThreads>(hist0, kBins, k, d0, k_rem, sh);
-    const bool crowded = hist0[d0] > cap;
-    uint32_t n_cand = hist0[d0];
+    uint32_t n_list = k - k_rem + hist0[d0];
+    const bool crowded = n_list > cap;
     bool listed = true;
     if (crowded) {
         find_digit<kResolveThreads>(hist1, kBins, k_rem, d1, k_rem, sh);
-        n_cand = hist1[d1];
-        listed = n_cand <= cap;                                  // else more than the list holds agree in 22 bits: walk the row
+        n_list = k - k_rem + hist1[d1];
+        listed = n_list <= cap;                                  // else more than the list holds agree in 22 bits: walk the row
     }
-    const uint32_t prefix22 = (d0 << 11) | d1;
     const uint2_t* list = cand + row * (int64_t)cap;
     const float* src = row_scores(scores, scores_b, rows_a, row, N);
+    constexpr int kAhead = 8;                                    // loads of a thread in flight
     auto for_each = [&](auto fn) {
-        if (listed) {
-            for (uint32_t i = tid; i < n_cand; i += kResolveThreads) fn(list[i][0], list[i][1]);
-        } else {
-            for (int64_t i = tid; i < N; i += kResolveThreads) {
-                const uint32_t key = float_key(src[i]);
-                if ((key >> 10) == prefix22) fn(key, (uint32_t)i);
+        const int64_t n = listed ? (int64_t)n_list : N;
+        for (int64_t i0 = tid; i0 < n; i0 += kAhead * kResolveThreads) {
+            uint2_t e[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int64_t i = i0 + u * kResolveThreads, at = i < n ? i : n - 1;
+                if (listed) e[u] = list[at];
+                else e[u] = uint2_t{__float_as_uint(src[at]), (uint32_t)at};
             }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (i0 + u * kResolveThreads < n) fn(listed ? e[u][0] : float_key(__uint_as_float(e[u][0])), e[u][1]);
         }
     };
-    if (!crowded) {                                              // the candidates share d0 only: round on bits 20..10
+    if (!crowded) {                                              // the k-th key shares d0 only: round on bits 20..10
         for (int i = tid; i < kBins; i += kResolveThreads) lh[i] = 0u;
         __syncthreads();
-        for_each([&](uint32_t key, uint32_t) { atomicAdd(&lh[(key >> 10) & 2047u], 1u); });
+        for_each([&](uint32_t key, uint32_t) { if ((key >> 21) == d0) count_in(lh, (key >> 10) & 2047u); });
         __syncthreads();
         find_digit<kResolveThreads>(lh, kBins, k_rem, d1, k_rem, sh);
     }
+    const uint32_t prefix22 = (d0 << 11) | d1;
     for (int i = tid; i < kBins; i += kResolveThreads) lh[i] = 0u;
     __syncthreads();
-    for_each([&](uint32_t key, uint32_t) { if (((key >> 10) & 2047u) == d1) atomicAdd(&lh[key & 1023u], 1u); });
+    for_each([&](uint32_t key, uint32_t) { if ((key >> 10) == prefix22) count_in(lh, key & 1023u); });
     __syncthreads();
     find_digit<kResolveThreads>(lh, 1024, k_rem, d2, need_eq, sh);
-    const uint32_t tau = (d0 << 21) | (d1 << 10) | d2;
-    // the candidates' share of the per-slice counts.  Thousands of candidates fall into a few slices, so they are
-    // counted in LDS first (one global add per slice afterwards) whenever the row has at most 2048 slices.
-    uint32_t* c = counts + row * (int64_t)n_slices * 2;
-    if (n_slices <= kBins) {
+    const uint32_t tau = (prefix22 << 10) | d2;
+    // counts per slice, in LDS for 2048 slices at a time
+    uint2_t* c = counts + row * (int64_t)n_slices;
+    for (int s0 = 0; s0 < n_slices; s0 += kBins) {
         __syncthreads();
         for (int i = tid; i < kBins; i += kResolveThreads) { lh[i] = 0u; lh_eq[i] = 0u; }
         __syncthreads();
         for_each([&](uint32_t key, uint32_t i) {
-            if (key > tau) atomicAdd(&lh[i / kSlice], 1u);
-            else if (key == tau) atomicAdd(&lh_eq[i / kSlice], 1u);
+            const uint32_t s = i / kSlice - (uint32_t)s0;
+            if (s >= (uint32_t)kBins) return;                    // (neighbours in the list are in one slice)
+            if (key > tau) count_in(lh, s);
+            else if (key == tau) count_in(lh_eq, s);
         });
         __syncthreads();
-        for (int i = tid; i < n_slices; i += kResolveThreads) {    // this workgroup is the only writer of the row's counts now
-            if (lh[i]) c[i * 2] += lh[i];
-            if (lh_eq[i]) c[i * 2 + 1] += lh_eq[i];
-        }
-    } else {
-        for_each([&](uint32_t key, uint32_t i) {
-            if (key > tau) atomicAdd(&c[(i / kSlice) * 2], 1u);
-            else if (key == tau) atomicAdd(&c[(i / kSlice) * 2 + 1], 1u);
-        });
+        for (int i = tid; i < kBins && s0 + i < n_slices; i += kResolveThreads) c[s0 + i] = uint2_t{lh[i], lh_eq[i]};
     }
     if (tid == 0) {
         head[row * kHeadWords + kHeadTau] = tau;
         head[row * kHeadWords + kHeadNeedEq] = need_eq;
+        head[row * kHeadWords + kHeadUnlisted] = listed ? 0u : 1u;
     }
 }
 
@@ -322,89 +339,75 @@ __device__ __forceinline__ void emit_ordered(const uint32_t (&key)[PER], uint32_
     }
 }
 
+// A wave per 2048 scores of the slice, or per quarter of its segment of the list: coalesced, ranked through ballots.
 __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restrict__ scores,
                                                           const float* __restrict__ scores_b, int rows_a, int64_t N,
                                                           uint32_t k, const uint32_t* __restrict__ head,
-                                                          const uint32_t* __restrict__ counts, int n_slices,
+                                                          const uint2_t* __restrict__ counts, const uint2_t* __restrict__ segs,
+                                                          int n_slices, const uint2_t* __restrict__ cand, uint32_t cap,
                                                           int32_t* __restrict__ idx, int32_t* __restrict__ idx_b)
 {
     __shared__ uint32_t red[4][4];
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // Scores are requested ahead of the counts, whose latency they share, and kept as keys.  A whole, 16-byte aligned slice: a
-    // thread owns 32 consecutive scores; any other: a wave owns 2048 consecutive ones, 64 at a time (coalesced).  16 rows of
-    // 840000: aligned 14 us by threads, 20 by waves; 840003 scores, not aligned, 87 by threads (a dword at a time), 16 by waves.
-    constexpr int kPer = kSlice / kTopkThreads;
-    const int64_t slice_lo = (int64_t)blockIdx.x * kSlice;
-    const float* src = row_scores(scores, scores_b, rows_a, row, N);
-    const bool fast = slice_lo + kSlice <= N && (((uintptr_t)(src + slice_lo)) & 15) == 0;
-    const int64_t lo = slice_lo + (fast ? tid * kPer : wave * (64 * kPer) + lane);
-    uint32_t key[kPer];
-    if (fast) {
-#pragma unroll
-        for (int j = 0; j < kPer / 4; ++j) {
-            const float4_t v = *(const float4_t*)(src + lo + 4 * j);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * j + e] = __float_as_uint(v[e]);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? __float_as_uint(src[lo + 64 * j]) : 0xffffffffu;
-    }
+    const uint2_t seg = segs[row * n_slices + blockIdx.x];
     const uint32_t tau = head[row * kHeadWords + kHeadTau], need_eq = head[row * kHeadWords + kHeadNeedEq];
+    const bool listed = head[row * kHeadWords + kHeadUnlisted] == 0u;
     // keys > tau and == tau in the slices before this one
     uint32_t bgt = 0, beq = 0;
     for (int s = tid; s < (int)blockIdx.x; s += kTopkThreads) {
-        bgt += counts[(row * n_slices + s) * 2];
-        beq += counts[(row * n_slices + s) * 2 + 1];
+        const uint2_t c = counts[row * n_slices + s];
+        bgt += c[0];
+        beq += c[1];
     }
-    bgt = wave_sum_u32(bgt);
-    beq = wave_sum_u32(beq);
-    if (lane == 0) { red[0][wave] = bgt; red[1][wave] = beq; }
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) key[j] = float_key(__uint_as_float(key[j]));
-    uint32_t gt = 0, eq = 0, my_gt = 0, my_eq = 0;               // of the wave; of the thread and, then, of the lanes up to it
-    if (fast) {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) { my_gt += key[j] > tau; my_eq += key[j] == tau; }
-        gt = my_gt;
-        eq = my_eq;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t a = __shfl_up(gt, off, 64), b = __shfl_up(eq, off, 64);
-            if (lane >= off) { gt += a; eq += b; }
+    const uint2_t* list = cand + row * (int64_t)cap;
+    int32_t* out = (row < rows_a) ? idx + row * (int64_t)k : idx_b + (row - rows_a) * (int64_t)k;
+    uint32_t key[kPer];
+    uint32_t gt = 0, eq = 0;
+    const int64_t lo = (int64_t)blockIdx.x * kSlice + wave * (64 * kPer) + lane;
+    // the wave's entries of the segment
+    const uint32_t quarter = (seg[1] + 255) / 256 * 64, e_lo = wave * quarter, e_hi = e_lo + quarter < seg[1] ? e_lo + quarter : seg[1];
+    if (listed) {
+        for (uint32_t i = e_lo + lane; i < e_hi; i += 64) {
+            const uint32_t x = list[seg[0] + i][0];
+            gt += x > tau;
+            eq += x == tau;
         }
-        if (lane == 63) { red[2][wave] = gt; red[3][wave] = eq; }
+        gt = wave_sum_u32(gt);
+        eq = wave_sum_u32(eq);
     } else {
+        const float* src = row_scores(scores, scores_b, rows_a, row, N);
+        // (Past the end keys are 0, the lowest.  The NaN 0xffffffff has it too, but at earlier positions, and need_eq counts
+        // only those.)
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? float_key(src[lo + 64 * j]) : 0u;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             gt += (uint32_t)__popcll(__ballot(key[j] > tau));
             eq += (uint32_t)__popcll(__ballot(key[j] == tau));
         }
-        if (lane == 0) { red[2][wave] = gt; red[3][wave] = eq; }
     }
+    bgt = wave_sum_u32(bgt);
+    beq = wave_sum_u32(beq);
+    if (lane == 0) { red[0][wave] = bgt; red[1][wave] = beq; red[2][wave] = gt; red[3][wave] = eq; }
     __syncthreads();
     uint32_t run_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3], run_eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
     for (int w = 0; w < wave; ++w) { run_gt += red[2][w]; run_eq += red[3][w]; }
-    int32_t* out = (row < rows_a) ? idx + row * (int64_t)k : idx_b + (row - rows_a) * (int64_t)k;
-    if (!fast) {
-        // (Past the end keys are 0, the lowest.  The NaN 0xffffffff has it too, but at earlier positions, and need_eq counts
-        // only those.)
+    if (!listed) {
         emit_ordered<kPer>(key, tau, need_eq, run_gt, run_eq, lane, lo, out);
         return;
     }
-    run_gt += gt - my_gt;
-    run_eq += eq - my_eq;
-    if (my_gt == 0 && (my_eq == 0 || run_eq >= need_eq)) return; // nothing of this thread is selected
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        if (key[j] > tau) {
-            out[run_gt + (run_eq < need_eq ? run_eq : need_eq)] = (int32_t)(lo + j);
-            ++run_gt;
-        } else if (key[j] == tau) {
-            if (run_eq < need_eq) out[run_gt + run_eq] = (int32_t)(lo + j);
-            ++run_eq;
-        }
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (uint32_t i0 = e_lo; i0 < e_hi; i0 += 64) {
+        const bool in = i0 + lane < e_hi;
+        const uint2_t e = list[seg[0] + (in ? i0 + lane : e_lo)];
+        const bool is_gt = in && e[0] > tau, is_eq = in && e[0] == tau;
+        const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
+        const uint32_t my_gt = run_gt + (uint32_t)__popcll(mg & below), my_eq = run_eq + (uint32_t)__popcll(me & below);
+        if (is_gt) out[my_gt + (my_eq < need_eq ? my_eq : need_eq)] = (int32_t)e[1];
+        else if (is_eq && my_eq < need_eq) out[my_gt + my_eq] = (int32_t)e[1];
+        run_gt += (uint32_t)__popcll(mg);
+        run_eq += (uint32_t)__popcll(me);
     }
 }
 
@@ -426,7 +429,8 @@ __global__ __launch_bounds__(kRowThreads) void topk_row(const float* __restrict_
     const int lo = wave * (64 * PER) + lane;                     // a wave owns 64 * PER consecutive scores
     uint32_t key[PER];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) key[j] = lo + 64 * j < N ? float_key(src[lo + 64 * j]) : 0u;   // (the lowest key: see topk_emit)
+    for (int j = 0; j < PER; ++j) key[j] = lo + 64 * j < N ? float_key(src[lo + 64 * j]) : 0u;   // (the lowest key; the NaN
+                                                                 // 0xffffffff has it too, but at earlier positions, and need_eq counts only those)
     for (int i = tid; i < 3 * kBins; i += kRowThreads) (&lh[0][0])[i] = 0u;
     __syncthreads();
 #pragma unroll
@@ -482,20 +486,23 @@ namespace {
 struct TopkPlan {
     int n_slices;
     uint32_t cap;                      // candidate entries per row
-    size_t off_hist, off_head, off_counts, off_cand, total;
+    size_t off_hist, off_head, off_segs, off_counts, off_cand, total;
 };
 
-TopkPlan topk_plan(int64_t rows, int64_t N)
+TopkPlan topk_plan(int64_t rows, int64_t N, int64_t k)
 {
     TopkPlan p;
     p.n_slices = (int)((N + kSlice - 1) / kSlice);
     if (p.n_slices < 1) p.n_slices = 1;
-    // the bin of the k-th key usually holds a few percent of a row; a fuller bin makes topk_resolve walk the row
-    p.cap = (uint32_t)(N / 8 + 4096);
+    // the keys listed are the k and the rest of a bin, which usually holds a few percent of a row; more keys that agree in 22
+    // bits make topk_resolve walk the row
+    const int64_t cap = N / 8 + 4096 + k;
+    p.cap = (uint32_t)(cap < N ? cap : N);
     size_t off = 0;
     p.off_hist = off;   off += align_up((size_t)rows * 2 * kBins * 4);            // two histogram levels per row
     p.off_head = off;   off += align_up((size_t)rows * kHeadWords * 4);     // directly after the histograms: zeroed together
-    p.off_counts = off; off += align_up((size_t)rows * p.n_slices * 2 * 4);
+    p.off_segs = off;   off += align_up((size_t)rows * p.n_slices * sizeof(uint2_t));
+    p.off_counts = off; off += align_up((size_t)rows * p.n_slices * sizeof(uint2_t));
     p.off_cand = off;   off += align_up((size_t)rows * p.cap * sizeof(uint2_t));
     p.total = off;
     return p;
@@ -505,8 +512,7 @@ TopkPlan topk_plan(int64_t rows, int64_t N)
 
 size_t topk_workspace_bytes(int64_t n_rows, int64_t N, int64_t k)
 {
-    (void)k;
-    return topk_plan(n_rows, N).total;
+    return topk_plan(n_rows, N, k).total;
 }
 
 // Two score arrays of n_rows rows each can be selected in one go (scores_b / idx_b may be NULL): the launches then
@@ -516,9 +522,9 @@ namespace {
 // clears the histograms and headers of `rows` rows
 uint32_t* topk_clear(int64_t rows, int64_t N, void* ws, hipStream_t st)
 {
-    const TopkPlan p = topk_plan(rows, N);
+    const TopkPlan p = topk_plan(rows, N, 0);                   // (the list is the last part)
     uint32_t* hist = (uint32_t*)((char*)ws + p.off_hist);
-    const int64_t nz = (int64_t)(p.off_counts / 4);             // histograms and headers
+    const int64_t nz = (int64_t)(p.off_segs / 4);             // histograms and headers
     hipLaunchKernelGGL(zero_u32, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, hist, nz);
     return hist;
 }
@@ -528,22 +534,23 @@ hipError_t topk_select(const float* scores, int32_t* idx, const float* scores_b,
                        int64_t N, int64_t k, void* ws, hipStream_t st)
 {
     const int64_t rows = scores_b ? 2 * n_rows : n_rows;
-    const TopkPlan p = topk_plan(rows, N);
+    const TopkPlan p = topk_plan(rows, N, k);
     char* w = (char*)ws;
     uint32_t* hist = (uint32_t*)(w + p.off_hist);
     uint32_t* head = (uint32_t*)(w + p.off_head);
-    uint32_t* counts = (uint32_t*)(w + p.off_counts);
+    uint2_t* segs = (uint2_t*)(w + p.off_segs);
+    uint2_t* counts = (uint2_t*)(w + p.off_counts);
     uint2_t* cand = (uint2_t*)(w + p.off_cand);
     const int ra = (int)n_rows;
     dim3 grid(p.n_slices, (unsigned)rows);
     hipLaunchKernelGGL(topk_collect<1>, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k, hist, head,
-                       counts, p.n_slices, cand, p.cap);
+                       segs, p.n_slices, cand, p.cap);
     hipLaunchKernelGGL(topk_collect<2>, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k, hist, head,
-                       counts, p.n_slices, cand, p.cap);
+                       segs, p.n_slices, cand, p.cap);
     hipLaunchKernelGGL(topk_resolve, dim3((unsigned)rows), dim3(kResolveThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k,
                        hist, head, counts, p.n_slices, cand, p.cap);
-    hipLaunchKernelGGL(topk_emit, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k, head, counts,
-                       p.n_slices, idx, idx_b);
+    hipLaunchKernelGGL(topk_emit, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k, head, counts, segs,
+                       p.n_slices, cand, p.cap, idx, idx_b);
     return hipGetLastError();
 }
 
@@ -583,7 +590,7 @@ hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b
     if (topk_in_rows(N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
     const int64_t rows = scores_b ? 2 * n_rows : n_rows;
     uint32_t* hist = topk_clear(rows, N, ws, st);
-    const TopkPlan p = topk_plan(rows, N);
+    const TopkPlan p = topk_plan(rows, N, k);
     dim3 grid(p.n_slices, (unsigned)rows);
     hipLaunchKernelGGL(topk_hist0, grid, dim3(kTopkThreads), 0, st, scores, scores_b, (int)n_rows, N, hist);
     return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);

@@ -105,6 +105,25 @@ def test_topk_ties_across_slices(oracle, N):
         assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), oracle.topk(s, k))
 
 
+@pytest.mark.parametrize("N", [33000, 65543])
+@pytest.mark.parametrize("k", [1, 327, 4125, 20000, -1, 0])
+def test_topk_listed_crowded_and_walked(oracle, N, k):
+    """Long rows of every kind in one call: few keys in the threshold's bin, a crowded bin, ties in 22 bits for more keys than the
+    list holds (zeros, as exponentials that underflow leave them), all scores equal; k from one to all of them."""
+    k = k if k > 0 else N + k                                  # N - 1 and N
+    rng = np.random.default_rng(N + k)
+    rows = np.empty((6, N), np.float32)
+    rows[0] = np.exp(2 * rng.standard_normal(N)) / N
+    rows[1] = 5 + 0.2 * rng.standard_normal(N)
+    rows[2] = 0
+    rows[2, rng.choice(N, N // 300, replace=False)] = rng.random(N // 300)
+    rows[3] = -1.5
+    rows[4] = np.round(rng.standard_normal(N) * 50) / 50
+    rows[5] = 1 + rng.integers(0, 3, N) * np.float32(2.0 ** -23)
+    got = antkv.topk(dev(rows), k).cpu().numpy()
+    assert np.array_equal(got, oracle.topk(rows, k))
+
+
 @pytest.mark.parametrize("d", [4, 8, 16])
 @pytest.mark.parametrize("B,Hq,Hkv,n", [(2, 4, 2, 333), (1, 8, 8, 70)])
 def test_encode_matches_oracle(oracle, d, B, Hq, Hkv, n):
