@@ -1638,13 +1638,14 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
 {
     constexpr int M = kD / DSUB;
     constexpr int CW = M / 4;
-    // The table is code-major, [256 codes][SLOTS] entries of 4 heads x fp32 (16 bytes), slot s holding sub-space s mod M:
-    // the bank group of an entry (slot mod 16) then depends on the slot alone, and the 16 lanes of an LDS pass, which
-    // visit sub-space (step XOR lane) in copy (lane / M), hit 16 different groups whatever the codes are.
+    // The table is code-major, rows of 256 bytes: 16 slots of 4 heads x fp32 (16 bytes), slot s holding sub-space s mod M (d = 4:
+    // two such tables, sub-spaces 0-15 and 16-31): the bank group of an entry then depends on the slot alone, and the
+    // 16 lanes of an LDS pass, which visit sub-space (step XOR lane) in copy (lane / M), hit 16 different groups whatever
+    // the codes are.  The address code << 8 | slot << 4 is one v_perm_b32 of the code dword and a per-lane constant.
     constexpr int SLOTS = M < 16 ? 16 : M;
     extern __shared__ uint4_t smem_u4[];
     char* smem = (char*)smem_u4;
-    float4_t* s_lut = (float4_t*)smem;                      // [256][SLOTS] x 4 heads fp32
+    float4_t* s_lut = (float4_t*)smem;                      // [SLOTS / 16][256][16] x 4 heads fp32
     float* s_qf = (float*)(smem + SLOTS * 256 * 16);        // [4][128]
     float* s_red = s_qf + kNH * kD;                         // [waves][8]
     int* s_misc = (int*)(s_red + kDaWaves * 8);             // 16 ints
@@ -1730,7 +1731,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
                 o[h] = s * p.c1;
             }
 #pragma unroll
-            for (int c = 0; c < SLOTS / M; ++c) s_lut[(e & 255) * SLOTS + m + M * c] = o;
+            for (int c = 0; c < SLOTS / M; ++c) s_lut[(m >> 4) * 4096 + (e & 255) * 16 + (m & 15) + M * c] = o;
         }
     }
     if (scan_list) {
@@ -1792,19 +1793,23 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
 
     // PASS 0 keeps, per lane and head, a sum of exp2(score - reference); the reference only moves when a score
     // exceeds it by more than 64 (or on the lane's first token), so the common token costs one exp2 per head.
-    auto consume = [&](const float (&s)[kNH], int64_t tok) {
+    auto consume = [&](const float (&s)[kNH], int64_t tok, bool on) {
         if (PASS == 0) {
+            float over = 0.f;
 #pragma unroll
-            for (int h = 0; h < kNH; ++h) {
-                const float x = s[h] - m_run[h];
-                if (x > 64.f) {                                  // first token (reference = kNegBig) or a big jump
-                    l_run[h] = l_run[h] * fast_exp2(-x) + 1.f;
-                    m_run[h] = s[h];
-                } else {
-                    l_run[h] += fast_exp2(x);
+            for (int h = 0; h < kNH; ++h) over = fmaxf(over, s[h] - m_run[h]);
+            if (__any(on && over > 64.f)) {
+#pragma unroll
+                for (int h = 0; h < kNH; ++h) {
+                    if (on && s[h] - m_run[h] > 64.f) {
+                        l_run[h] *= fast_exp2(m_run[h] - s[h]);
+                        m_run[h] = s[h];
+                    }
                 }
             }
-        } else {
+#pragma unroll
+            for (int h = 0; h < kNH; ++h) l_run[h] += fast_exp2(on ? s[h] - m_run[h] : kNegBig);
+        } else if (on) {
             float av = 0.f, ak = 0.f;
 #pragma unroll
             for (int h = 0; h < kNH; ++h) {
@@ -1826,67 +1831,82 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
 
     // ---- code stream: one token per lane, code loads one round ahead; tokens with an FP16 K row are left to
     // the loop below
-    auto load_kw = [&](int64_t tok, uint32_t (&kw)[CW]) {
-        if (CW == 2) { const uint2_t a = *(const uint2_t*)(ck + tok * M); kw[0] = a[0]; kw[1] = a[1]; }
+    const uint8_t* ckr = ck + t0 * M;
+    const int n_tok = (int)(t1 - t0);
+    auto load_kw = [&](int rel, uint32_t (&kw)[CW]) {
+        const uint8_t* src = ckr + (uint32_t)(rel < n_tok ? rel : n_tok - 1) * (uint32_t)M;
+        if (CW == 2) { const uint2_t a = *(const uint2_t*)src; kw[0] = a[0]; kw[1] = a[1]; }
         else {
 #pragma unroll
             for (int i = 0; i < CW / 4; ++i) {
-                const uint4_t a = *(const uint4_t*)(ck + tok * M + 16 * i);
+                const uint4_t a = *(const uint4_t*)(src + 16 * i);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) kw[4 * i + e] = a[e];
             }
         }
     };
     // lane constants of the conflict-free walk: at step st the lane reads sub-space st ^ r
-    const int r = lane & (M - 1);
-    const uint32_t slot0 = (uint32_t)(r + (M < 16 ? M * ((lane / M) & (16 / M - 1)) : 0)) * 16u;   // byte offset of the slot at step 0
-    uint32_t sh4[4];                                              // bit offset of the code byte for step st: sh4[st & 3]
+    const int r = lane & (M - 1), copy = M < 16 ? M * ((lane / M) & (16 / M - 1)) : 0;
+    uint32_t slots[M < 16 ? M / 4 : 4], sel[4];                   // slot bytes of four steps; which bytes make the address of step st & 3
 #pragma unroll
-    for (int e = 0; e < 4; ++e) sh4[e] = 8u * (uint32_t)(e ^ (r & 3));
-    const char* lut_bytes = (const char*)s_lut;
-    // code loads run kAhead rounds ahead of their use (more than one round in flight did not pay)
-    constexpr int kAhead = 1;
-    uint32_t kw_q[kAhead][CW];
+    for (int i = 0; i < (M < 16 ? M / 4 : 4); ++i) {
+        slots[i] = 0u;
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-#pragma unroll
-        for (int i = 0; i < CW; ++i) kw_q[u][i] = 0u;
-        if (t0 + tid + (int64_t)u * kDaThreads < t1) load_kw(t0 + tid + (int64_t)u * kDaThreads, kw_q[u]);
+        for (int e = 0; e < 4; ++e) slots[i] |= (uint32_t)(((((4 * i + e) ^ r) & 15) + copy) << 4) << (8 * e);
     }
-    for (int64_t tok0 = t0 + tid; tok0 < t1; tok0 += (int64_t)kAhead * kDaThreads) {
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int64_t tok = tok0 + (int64_t)u * kDaThreads;
-            uint32_t kw[CW];
+    for (int e = 0; e < 4; ++e) sel[e] = 0x0c0c0000u | (uint32_t)(4 + (e ^ (r & 3))) << 8 | (uint32_t)e;
+    const uint32_t upper = (uint32_t)(r >> 4) << 16;              // d = 4: the table of sub-space r
+    const char* lut_bytes = (const char*)s_lut;
+    uint32_t kw_next[CW];
+    load_kw(tid, kw_next);
+#pragma unroll 1
+    for (int rel = tid; rel - tid < n_tok; rel += kDaThreads) {
+        uint32_t kw[CW];
 #pragma unroll
-            for (int i = 0; i < CW; ++i) kw[i] = kw_q[u][i];
-            if (tok + (int64_t)kAhead * kDaThreads < t1) load_kw(tok + (int64_t)kAhead * kDaThreads, kw_q[u]);
-            if (tok >= t1) continue;
-            // code dwords XOR-permuted by r / 4, so that step st finds its dword at the compile-time index st / 4
+        for (int i = 0; i < CW; ++i) kw[i] = kw_next[i];
+        load_kw(rel + kDaThreads, kw_next);
+        const bool on = rel < n_tok && ((s_mask[(rel >> 5) & 1023] >> (rel & 31)) & 1u) == 0u;
+        // code dwords XOR-permuted by r / 4, so that step st finds its dword at the compile-time index st / 4
 #pragma unroll
-            for (int bit = 0; (4 << bit) < M; ++bit) {
-                const bool sw = (r >> (2 + bit)) & 1;
+        for (int bit = 0; (4 << bit) < M; ++bit) {
+            const bool sw = (r >> (2 + bit)) & 1;
 #pragma unroll
-                for (int i = 0; i < CW; ++i) {
-                    if (!(i & (1 << bit))) {
-                        const uint32_t a = kw[i], c = kw[i | (1 << bit)];
-                        kw[i] = sw ? c : a;
-                        kw[i | (1 << bit)] = sw ? a : c;
-                    }
+            for (int i = 0; i < CW; ++i) {
+                if (!(i & (1 << bit))) {
+                    const uint32_t a = kw[i], c = kw[i | (1 << bit)];
+                    kw[i] = sw ? c : a;
+                    kw[i | (1 << bit)] = sw ? a : c;
                 }
             }
-            float s[kNH] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int st = 0; st < M; ++st) {
-                const uint32_t code = __builtin_amdgcn_ubfe(kw[st >> 2], sh4[st & 3], 8u);
-                const uint32_t off = (code * (uint32_t)(SLOTS * 16)) | (slot0 ^ (uint32_t)(16 * st));
-                const float4_t e = *(const float4_t*)(lut_bytes + off);
-#pragma unroll
-                for (int h = 0; h < kNH; ++h) s[h] += e[h];
-            }
-            const int rel = (int)(tok - t0);
-            if (!((s_mask[rel >> 5] >> (rel & 31)) & 1u)) consume(s, tok);
         }
+        float s[kNH] = {0.f, 0.f, 0.f, 0.f};
+        // Four steps' table entries are added up while the next four are on their way.  (pinned: the compiler otherwise moves the
+        // sums into the branch that uses them, behind all the reads; for d = 4 those spilled, and pass 1 spent 265 us on
+        // 8 x 200000 tokens instead of 26)
+        float4_t ent[2][4];
+        auto request = [&](int q) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                uint32_t off = __builtin_amdgcn_perm(kw[q], slots[q & 3], sel[k]);
+                if constexpr (M == 32) off |= q < 4 ? upper : upper ^ 0x10000u;
+                ent[q & 1][k] = *(const float4_t*)(lut_bytes + off);
+            }
+        };
+        request(0);
+#pragma unroll
+        for (int q = 0; q < M / 4; ++q) {
+            if (q + 1 < M / 4) request(q + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int h = 0; h < kNH; ++h) s[h] += ent[q & 1][k][h];
+#pragma unroll
+            for (int h = 0; h < kNH; ++h) pin(s[h]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        consume(s, t0 + rel, on);
     }
     // ---- K-anchored tokens: the prefetched rounds, then any further ones
     {
@@ -1905,7 +1925,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
                 for (int e = 0; e < 8; ++e) d = fmaf(qv[h][e], (float)v[e], d);
                 s[h] = row16_sum(d) * p.c1;
             }
-            if (tok >= 0 && l16 == 0) consume(s, tok);
+            consume(s, tok, tok >= 0 && l16 == 0);
         };
 #pragma unroll
         for (int u = 0; u < kPre; ++u)
