@@ -88,9 +88,12 @@ __global__ __launch_bounds__(kRsThreads) void rope_scores_kernel(const RsParams 
             }
             *(uint4_t*)(smem + kRsTab + code * kRsRow + w16 * 16) = v;
         }
+        double* s_theta = (double*)(smem + kRsQ);                      // one fp64 exponential per pair (the queries' area is idle)
+        if (tid < 64) s_theta[tid] = exp2(-(2.0 * tid / kD) * p.log2_base);
+        __syncthreads();
         for (int e = tid; e < 64 * 64; e += kRsThreads) {
             const int pair = e >> 6, l = e & 63;
-            const double th = exp2(-(2.0 * pair / kD) * p.log2_base);
+            const double th = s_theta[pair];
             float c0, s0, c1, s1;
             angle_of(l, th, c0, s0);
             angle_of(l + 64, th, c1, s1);
