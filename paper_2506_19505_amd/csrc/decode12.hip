@@ -20,6 +20,8 @@
 //              the centroids) as the source.
 //   merge      waves through LDS, workgroups through a partial (max, sum, accumulator) per head and a second
 //              small kernel.
+// Long contexts take the kernels of decode12_by_code.hip instead, which add the values up by code (rule: d12_by_code below);
+// the table and merge kernels here serve both.
 #include "decode12.h"
 
 #include <type_traits>
