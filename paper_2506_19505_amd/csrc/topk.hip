@@ -489,21 +489,26 @@ struct TopkPlan {
     size_t off_hist, off_head, off_segs, off_counts, off_cand, total;
 };
 
-TopkPlan topk_plan(int64_t rows, int64_t N, int64_t k)
+// ws_bytes: the list, which comes last, takes what k needs or what there is
+TopkPlan topk_plan(int64_t rows, int64_t N, int64_t k, size_t ws_bytes)
 {
     TopkPlan p;
     p.n_slices = (int)((N + kSlice - 1) / kSlice);
     if (p.n_slices < 1) p.n_slices = 1;
     // the keys listed are the k and the rest of a bin, which usually holds a few percent of a row; more keys that agree in 22
     // bits make topk_resolve walk the row
-    const int64_t cap = N / 8 + 4096 + k;
-    p.cap = (uint32_t)(cap < N ? cap : N);
+    int64_t cap = N / 8 + 4096 + k;
+    if (cap > N) cap = N;
     size_t off = 0;
     p.off_hist = off;   off += align_up((size_t)rows * 2 * kBins * 4);            // two histogram levels per row
     p.off_head = off;   off += align_up((size_t)rows * kHeadWords * 4);     // directly after the histograms: zeroed together
     p.off_segs = off;   off += align_up((size_t)rows * p.n_slices * sizeof(uint2_t));
     p.off_counts = off; off += align_up((size_t)rows * p.n_slices * sizeof(uint2_t));
-    p.off_cand = off;   off += align_up((size_t)rows * p.cap * sizeof(uint2_t));
+    p.off_cand = off;
+    const size_t room = ws_bytes > off && rows > 0 ? (ws_bytes - off) / ((size_t)rows * sizeof(uint2_t)) : 0;
+    if ((size_t)cap > room) cap = (int64_t)room;
+    p.cap = (uint32_t)cap;
+    off += align_up((size_t)rows * p.cap * sizeof(uint2_t));
     p.total = off;
     return p;
 }
@@ -512,7 +517,15 @@ TopkPlan topk_plan(int64_t rows, int64_t N, int64_t k)
 
 size_t topk_workspace_bytes(int64_t n_rows, int64_t N, int64_t k)
 {
-    return topk_plan(n_rows, N, k).total;
+    return topk_plan(n_rows, N, k, SIZE_MAX).total;
+}
+
+// A list of N/8 + 4096 entries less the segments: large k then make rows go the way of crowded ones
+size_t topk_workspace_least(int64_t n_rows, int64_t N, int64_t k)
+{
+    const TopkPlan p = topk_plan(n_rows, N, k, SIZE_MAX);
+    const size_t least = p.off_counts + align_up((size_t)n_rows * (N / 8 + 4096) * sizeof(uint2_t));
+    return least < p.total ? least : p.total;
 }
 
 // Two score arrays of n_rows rows each can be selected in one go (scores_b / idx_b may be NULL): the launches then
@@ -522,7 +535,7 @@ namespace {
 // clears the histograms and headers of `rows` rows
 uint32_t* topk_clear(int64_t rows, int64_t N, void* ws, hipStream_t st)
 {
-    const TopkPlan p = topk_plan(rows, N, 0);                   // (the list is the last part)
+    const TopkPlan p = topk_plan(rows, N, 0, SIZE_MAX);         // (the list is the last part)
     uint32_t* hist = (uint32_t*)((char*)ws + p.off_hist);
     const int64_t nz = (int64_t)(p.off_segs / 4);             // histograms and headers
     hipLaunchKernelGGL(zero_u32, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, hist, nz);
@@ -531,10 +544,10 @@ uint32_t* topk_clear(int64_t rows, int64_t N, void* ws, hipStream_t st)
 
 // everything after the first-level histogram
 hipError_t topk_select(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                       int64_t N, int64_t k, void* ws, hipStream_t st)
+                       int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st)
 {
     const int64_t rows = scores_b ? 2 * n_rows : n_rows;
-    const TopkPlan p = topk_plan(rows, N, k);
+    const TopkPlan p = topk_plan(rows, N, k, ws_bytes);
     char* w = (char*)ws;
     uint32_t* hist = (uint32_t*)(w + p.off_hist);
     uint32_t* head = (uint32_t*)(w + p.off_head);
@@ -584,16 +597,16 @@ static hipError_t launch_topk_rows(const float* scores, int32_t* idx, const floa
 }
 
 hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                        int64_t N, int64_t k, void* ws, hipStream_t st)
+                        int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st)
 {
     if (k == 0 || n_rows == 0) return hipSuccess;
     if (topk_in_rows(N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
     const int64_t rows = scores_b ? 2 * n_rows : n_rows;
     uint32_t* hist = topk_clear(rows, N, ws, st);
-    const TopkPlan p = topk_plan(rows, N, k);
+    const TopkPlan p = topk_plan(rows, N, k, ws_bytes);
     dim3 grid(p.n_slices, (unsigned)rows);
     hipLaunchKernelGGL(topk_hist0, grid, dim3(kTopkThreads), 0, st, scores, scores_b, (int)n_rows, N, hist);
-    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
+    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, ws_bytes, st);
 }
 
 uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st)
@@ -602,17 +615,17 @@ uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st
 }
 
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                               int64_t N, int64_t k, void* ws, hipStream_t st)
+                               int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st)
 {
     if (k == 0 || n_rows == 0) return hipSuccess;
     if (topk_in_rows_counted(2 * n_rows, N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
-    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
+    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, ws_bytes, st);
 }
 
 hipError_t launch_topk(const float* scores, int64_t n_rows, int64_t N, int64_t k, int32_t* idx, void* ws,
-                       hipStream_t st)
+                       size_t ws_bytes, hipStream_t st)
 {
-    return launch_topk2(scores, idx, nullptr, nullptr, n_rows, N, k, ws, st);
+    return launch_topk2(scores, idx, nullptr, nullptr, n_rows, N, k, ws, ws_bytes, st);
 }
 
 hipError_t launch_gather_rows(const Geom& g, const half_t* x, int64_t N, const int32_t* idx, int64_t k,

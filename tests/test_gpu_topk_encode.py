@@ -124,6 +124,23 @@ def test_topk_listed_crowded_and_walked(oracle, N, k):
     assert np.array_equal(got, oracle.topk(rows, k))
 
 
+@pytest.mark.parametrize("N", [33000, 65543])
+@pytest.mark.parametrize("k", [20, 4125, 20000, 32999])
+def test_topk_workspace_of_a_smaller_k(oracle, N, k):
+    """A workspace sized for k = 1 serves any k: the list then holds fewer keys than k, and the row is walked."""
+    s = np.exp(np.random.default_rng(N + k).standard_normal((3, N))).astype(np.float32)
+    s[1] = np.round(s[1], 2)
+    s[2] = 0.25
+    lib = antkv.load_library()
+    ws = torch.full((lib.antkv_topk_workspace(3, N, 1) + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    idx = torch.full((3, k), -1, dtype=torch.int32, device="cuda")
+    x = dev(s)
+    assert lib.antkv_topk(x.data_ptr(), 3, N, k, idx.data_ptr(), ws.data_ptr(), ws.numel() - 4096, None) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy(), oracle.topk(s, k))
+    assert bool((ws[-4096:] == 0x5a).all())
+
+
 @pytest.mark.parametrize("d", [4, 8, 16])
 @pytest.mark.parametrize("B,Hq,Hkv,n", [(2, 4, 2, 333), (1, 8, 8, 70)])
 def test_encode_matches_oracle(oracle, d, B, Hq, Hkv, n):
