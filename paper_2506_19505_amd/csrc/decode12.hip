@@ -810,7 +810,7 @@ D12Plan d12_plan(const Geom& g, int64_t N, bool by_code)
     pl.S2 = 0;
     pl.range = 64;
     if (by_code) {                                                     // a workgroup per CU: ranges x pairs of sub-spaces
-        int64_t S2 = 256 / (bgc * (g.M / 2));
+        int64_t S2 = bgc > 0 ? 256 / (bgc * (g.M / 2)) : 1;
         if (S2 > (N + 2047) / 2048) S2 = (N + 2047) / 2048;
         if (S2 < 1) S2 = 1;
         pl.range = ((N + S2 - 1) / S2 + 63) / 64 * 64;

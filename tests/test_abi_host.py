@@ -155,3 +155,20 @@ def test_geometry_restored_from_its_fields():
     saved.__dict__.update(B=2, Hq=32, Hkv=8, d_sub=16, D=128, n_centroids=4096)
     for g in (saved, pickle.loads(pickle.dumps(geom))):
         assert g == geom and bytes(g._c) == bytes(geom.c())
+
+
+def test_decode_of_an_empty_batch(lib):
+    """B = 0 is a batch that a decode step answers with nothing to do; the size queries answer it too, for both code widths."""
+    fake = ctypes.c_void_p(4096)
+    for d, C in ((4, 256), (8, 256), (16, 256), (32, 4096), (16, 4096)):
+        g = _g(B=0, d=d, C=C)
+        ref = ctypes.byref(g)
+        for N in (0, 1, 1000, 840000):
+            for k_resel in (0, N // 100):
+                assert lib.antkv_decode_attn_workspace(ref, N, 0, 0, k_resel) == 0
+                assert lib.antkv_decode_attn_workspace(ref, N, N // 100, N // 50, k_resel) == 0
+            assert lib.antkv_decode_attn_prerope_workspace(ref, N, N // 100) == 0
+            assert lib.antkv_decode_attn(ref, fake, 0.1, fake, fake, N, N, fake, fake, None, None, 0, None, None, 0, fake, None, None,
+                                         None, None, 0, None, 0, None) == OK
+            assert lib.antkv_decode_attn_prerope(ref, fake, 0.1, fake, fake, N, N, fake, fake, None, None, 0, None, None, 0, 10000.0, 1, 0,
+                                                 fake, None, 0, None) == OK
