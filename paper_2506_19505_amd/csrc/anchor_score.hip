@@ -431,7 +431,7 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
     const int qspan = 32 * (8 / (g.G >= 4 ? 4 : g.G));          // query rows per workgroup of phase 1
     const int64_t qblocks = (Nq + qspan - 1) / qspan;
     const int64_t base_wgs = (int64_t)g.B * g.Hkv * qblocks;
-    int64_t ks = (1024 + base_wgs - 1) / base_wgs;
+    int64_t ks = base_wgs > 0 ? (1024 + base_wgs - 1) / base_wgs : 1;
     // Ranges of 1024 keys: a window's phase 1 has no other parallelism (131072 keys x 32 queries x 8 heads: 102 us with ranges of
     // 4096, one workgroup per CU; 77 with these).
     const int64_t max_ks = (N + 1023) / 1024;

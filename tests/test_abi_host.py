@@ -172,3 +172,14 @@ def test_decode_of_an_empty_batch(lib):
                                          None, None, 0, None, 0, None) == OK
             assert lib.antkv_decode_attn_prerope(ref, fake, 0.1, fake, fake, N, N, fake, fake, None, None, 0, None, None, 0, 10000.0, 1, 0,
                                                  fake, None, 0, None) == OK
+
+
+def test_anchor_select_of_an_empty_batch(lib):
+    """As above for the selection: B = 0 has nothing to do, and the size query says so instead of dividing by it."""
+    fake = ctypes.c_void_p(4096)
+    for d, C in ((8, 256), (32, 4096)):
+        g = _g(B=0, d=d, C=C)
+        for N, Nq in ((1, 1), (1000, 32), (4096, 4096)):
+            assert lib.antkv_anchor_select_workspace(ctypes.byref(g), N, Nq, 1) >= 0
+            assert lib.antkv_anchor_select(ctypes.byref(g), fake, fake, N, Nq, 0.1, 1, None, None, None, None, fake, fake, None, 0,
+                                           None) == OK
