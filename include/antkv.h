@@ -155,8 +155,9 @@ int antkv_gather_rows(const antkv_geom* geom, const void* x, int64_t N, const in
  *            ans_k[j] = sum_h p_hj (1 - p_hj) ||q_h||_2
  *   resel_idx_k, resel_idx_v  int32 [B][Hkv][k_resel] or NULL: top-k_resel positions of those scores
  *            (ascending, ties to the lower position).  Needs ans_k / ans_v respectively to be non-NULL.
- * For long contexts of 12-bit codes the workspace includes softmax weights of every token (8 bytes per token and KV head);
- * a smaller one that holds everything else is not refused, the step then takes longer.
+ * For long contexts of 12-bit codes the workspace includes softmax weights of every token (8 bytes per token and KV head) and,
+ * for d_sub 16, scores of the V list's entries (16 bytes each); a smaller one that holds everything else is not refused,
+ * the step then takes longer.
  * N == 0 writes zeros.  Errors: EINVAL, EUNSUPPORTED, EWORKSPACE, ELAUNCH.
  */
 size_t antkv_decode_attn_workspace(const antkv_geom* geom, int64_t N, int64_t k_k, int64_t k_v,

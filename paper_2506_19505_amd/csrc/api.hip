@@ -87,7 +87,7 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
     if (want_ans && !(ans_k && ans_v)) return ANTKV_EINVAL;   // the two scores are produced together
     if (wide) {
         const size_t topk_bytes = k_resel > 0 ? align_up(topk_workspace_least(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0;
-        const size_t least = align_up(decode12_workspace_least(g, N)), best = align_up(decode12_workspace_bytes(g, N));
+        const size_t least = align_up(decode12_workspace_least(g, N)), best = align_up(decode12_workspace_bytes(g, N, k_v));
         if (!workspace || misaligned(workspace, 256) || workspace_bytes < least + topk_bytes) return ANTKV_EWORKSPACE;
         const size_t off_topk = workspace_bytes < best + topk_bytes ? least : best;
         hipStream_t st = (hipStream_t)stream;
@@ -358,7 +358,7 @@ static size_t decode_need(const antkv_geom* geom, int64_t N, int64_t k_k, int64_
     Geom g;
     if (check_geom(geom, g) || N < 0 || k_k < 0 || k_v < 0 || k_resel < 0) return 0;
     if (g.C != kC)
-        return align_up(least ? decode12_workspace_least(g, N) : decode12_workspace_bytes(g, N)) +
+        return align_up(least ? decode12_workspace_least(g, N) : decode12_workspace_bytes(g, N, k_v)) +
                (k_resel > 0 ? align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0);
     return dec_plan(g, N, k_k, k_v, k_resel, true).total;
 }

@@ -182,7 +182,7 @@ hipError_t launch_decode_attn(const Geom& g, const DecodeArgs& a, void* ws, hipS
 hipError_t launch_rope_scores(const Geom& g, const half_t* q, float scale, const uint8_t* codes_k, int64_t N, int64_t N_cap,
                               const half_t* cb_k, const int32_t* idx_k, const half_t* rows_k, int64_t k_k, double rope_base,
                               int rope_style, int64_t pos0, float* scores_out, hipStream_t st);
-size_t decode12_workspace_bytes(const Geom& g, int64_t N);    // what launch_decode12 can use,
+size_t decode12_workspace_bytes(const Geom& g, int64_t N, int64_t k_v);    // what launch_decode12 can use,
 size_t decode12_workspace_least(const Geom& g, int64_t N);    // and what it can do with
 hipError_t launch_decode12(const Geom& g, const DecodeArgs& a, void* ws, size_t ws_bytes, hipStream_t st);
 

@@ -46,6 +46,12 @@ __device__ __forceinline__ int lower_bound64(const int32_t* __restrict__ idx, in
     return lo;
 }
 
+template <int N>
+__device__ __forceinline__ float row_ror_add(float v)              // plus the value of the lane N places further round in the row of 16
+{
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + N, 0xf, 0xf, true));
+}
+
 // a token's code words: 48 or 96 bits, code m at bits 12 m .. 12 m + 11
 template <int DS>
 __device__ __forceinline__ void load_cw(const uint8_t* __restrict__ base, int64_t tok, uint32_t (&w)[3])
@@ -82,7 +88,9 @@ struct D12LongParams {
     const float* tab_amax;                // [B][Hkv][table blocks][4] per-block maxima of |score|
     const float4_t* given;                // or, instead of a table, [B][Hkv][N] the four heads' scores (then k_k is 0)
     float* part;                          // [B][Hq][slots][kD + 2]: S slots of the first kernel, S2 of the second
-    uint32_t* wts;                        // [pairs of heads][B][Hkv][N] weights, two fp16; both negative: a V-anchored token
+    uint32_t* wts;                        // [pairs of heads][B][Hkv][N] weights, two fp16; both negative: a V-anchored token, where
+                                          // it is scored apart -1 if it is not in the K list
+    const float4_t* v_scores;             // those scores: [B][Hkv][k_v] of four heads
     float* tile_ref;                      // [B][Hkv][tiles of 64 tokens][4] the references they were taken against
     int64_t N, N_cap, range;              // range: tokens of a workgroup of the second kernel, a multiple of 64
     int k_k, k_v;

@@ -48,24 +48,76 @@ struct D12Params {
                                           // codes, the table and the K anchor list are not used then)
 };
 
+// scores of the V list's entries for the by-code kernels
+struct D12VScores {
+    const uint8_t* codes_k;
+    const int32_t* idx_v;
+    float4_t* out;                        // [B][Hkv][k_v]
+    int64_t N_cap;
+    int k_v;
+};
+
+constexpr int kVI = 4, kVBlock = kTabThreads / 16 * kVI;               // entries of a workgroup
+
+// 16 lanes per entry, eight channels each: the centroids of its K codes times q, in fp32
+template <int kD12>
+__device__ __forceinline__ void v_scores_block(const D12VScores& p, const half_t* __restrict__ cb_k, const half_t* s_q, float c1, int bg,
+                                               int g, int block)
+{
+    constexpr int kM12 = kD / kD12, CB = 3 * kM12 / 2, LPM = kD12 / 8;
+    const int lane = threadIdx.x & 63, grp = lane >> 4, li = lane & 15, m = li / LPM;
+    const int first = block * kVBlock + (threadIdx.x >> 6) * (4 * kVI) + grp;
+    half8_t cv[kVI];
+    int tok[kVI];
+#pragma unroll
+    for (int i = 0; i < kVI; ++i) tok[i] = p.idx_v[(int64_t)bg * p.k_v + (first + 4 * i < p.k_v ? first + 4 * i : p.k_v - 1)];
+#pragma unroll
+    for (int i = 0; i < kVI; ++i) {
+        const uint8_t* c = p.codes_k + ((int64_t)bg * p.N_cap + tok[i]) * CB + m + (m >> 1);
+        const uint32_t code = ((uint32_t)c[0] | (uint32_t)c[1] << 8) >> (4 * (m & 1)) & 0xFFFu;
+        cv[i] = *(const half8_t*)(cb_k + (((int64_t)g * kM12 + m) * kC12 + code) * kD12 + 8 * (li % LPM));
+    }
+    __syncthreads();                                                   // q is in LDS
+#pragma unroll
+    for (int i = 0; i < kVI; ++i) {
+        float4_t o;
+#pragma unroll
+        for (int h = 0; h < kNH; ++h) {
+            float d = dot8f(cv[i], *(const half8_t*)(s_q + h * kD + 8 * li), 0.f);
+            d = row_ror_add<8>(d);
+            d = row_ror_add<4>(d);
+            d = row_ror_add<2>(d);
+            o[h] = row_ror_add<1>(d) * c1;
+        }
+        if (li == 0 && first + 4 * i < p.k_v) p.out[(int64_t)bg * p.k_v + first + 4 * i] = o;
+    }
+}
+
 // fp32 table of c1 q_h . centroid for one (sequence, KV head): every workgroup of the decode kernel that works on this
 // pair needs the same M x 4096 x 4 values, so they are computed once here (the K codebook is read once instead of
-// once per decode workgroup) and only quantised into LDS there.
+// once per decode workgroup) and only quantised into LDS there.  `pairs` workgroups, one per (sequence, KV head), for each block
+// of the table; those behind them score the V list's entries meanwhile.
 template <int kD12>
 __global__ __launch_bounds__(kTabThreads) void d12_table_kernel(const half_t* __restrict__ q, const half_t* __restrict__ cb_k,
-                                                                float c1, int Hq, int Hkv, int G, float2* __restrict__ tab,
-                                                                float* __restrict__ tab_amax)
+                                                                float c1, int Hq, int Hkv, int G, int pairs, float2* __restrict__ tab,
+                                                                float* __restrict__ tab_amax, const D12VScores vs)
 {
     __shared__ __attribute__((aligned(16))) half_t s_q[kNH * kD];
     __shared__ float s_red[kTabThreads / 64][kNH];
     constexpr int kM12 = kD / kD12;
     constexpr int kTabBlocks = tab_blocks(kD12);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bg = blockIdx.x, b = bg / Hkv, g = bg % Hkv;
+    const int bg = blockIdx.x % pairs, block = blockIdx.x / pairs, b = bg / Hkv, g = bg % Hkv;
     for (int i = tid; i < kNH * kD; i += kTabThreads)
         s_q[i] = ((i >> 7) < G) ? q[((int64_t)b * Hq + g * G) * kD + i] : (half_t)0.f;
+    if constexpr (heads_per_table(kD12) < kNH) {
+        if (block >= kTabBlocks) {
+            v_scores_block<kD12>(vs, cb_k, s_q, c1, bg, g, block - kTabBlocks);
+            return;
+        }
+    }
     // (all four centroids of the thread are requested before the first is used)
-    const int e0 = blockIdx.y * 4 * kTabThreads + tid;                 // entry = (sub-space, code)
+    const int e0 = block * 4 * kTabThreads + tid;                      // entry = (sub-space, code)
     half8_t cv[4][kD12 / 8];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -97,7 +149,7 @@ __global__ __launch_bounds__(kTabThreads) void d12_table_kernel(const half_t* __
     if (tid < kNH) {
         float a = 0.f;
         for (int w = 0; w < kTabThreads / 64; ++w) a = fmaxf(a, s_red[w][tid]);
-        tab_amax[((int64_t)bg * kTabBlocks + blockIdx.y) * kNH + tid] = a;
+        tab_amax[((int64_t)bg * kTabBlocks + block) * kNH + tid] = a;
     }
 }
 
@@ -792,10 +844,10 @@ __global__ __launch_bounds__(kT12) void d12_ans_kernel(const D12AnsParams p)
 struct D12Plan {
     int S, chunk, S2, slots;              // S2: token ranges of d12_values_kernel (by_code)
     int64_t range;
-    size_t off_part, off_tab, off_amax, off_stat, off_early, off_wts, off_ref, total;
+    size_t off_part, off_tab, off_amax, off_stat, off_early, off_wts, off_ref, off_vsc, total;
 };
 
-D12Plan d12_plan(const Geom& g, int64_t N, bool by_code)
+D12Plan d12_plan(const Geom& g, int64_t N, int64_t k_v, bool by_code)
 {
     D12Plan pl;
     const int64_t bgc = (int64_t)g.B * g.Hkv;
@@ -829,6 +881,8 @@ D12Plan d12_plan(const Geom& g, int64_t N, bool by_code)
     if (by_code) off += align_up((size_t)(g.G > 2 ? 2 : 1) * bgc * N * sizeof(uint32_t));
     pl.off_ref = off;
     if (by_code) off += align_up((size_t)bgc * ((N + 63) / 64) * kNH * sizeof(float));
+    pl.off_vsc = off;
+    if (by_code && heads_per_table(g.d) < kNH) off += align_up((size_t)bgc * k_v * sizeof(float4_t));
     pl.total = off;
     return pl;
 }
@@ -838,12 +892,12 @@ D12Plan d12_plan(const Geom& g, int64_t N, bool by_code)
 // fraction of the gather's time.  One step, gather and by code, us: d32, 8 KV heads (16 ranges) 200000 tokens 61 and 65, 420000
 // 102 and 81, 840000 169 and 102; 64 heads (2 ranges) 16000 57 and 60, 33333 81 and 67; d16, 8 heads (8 ranges) 50000 61 and 63,
 // 70000 67 and 66, 840000 308 and 153; 64 heads (1 range) 4096 54 and 56, 9001 66 and 59, 70000 229 and 106.
-bool d12_by_code(const Geom& g, int64_t N) { return d12_plan(g, N, true).range >= (g.d == 32 ? 14336 : 8192); }
+bool d12_by_code(const Geom& g, int64_t N) { return d12_plan(g, N, 0, true).range >= (g.d == 32 ? 14336 : 8192); }
 
 template <int DS>
 hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool by_code, hipStream_t st)
 {
-    const D12Plan pl = d12_plan(g, a.N, by_code);
+    const D12Plan pl = d12_plan(g, a.N, a.k_v, by_code);
     constexpr size_t lds = d12_lds(DS);
     static OncePerDevice once;
     const hipError_t setup = on_this_device(once, []() {
@@ -864,14 +918,17 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool 
     p.early = (float2*)(w + pl.off_early);
     p.given = (const float4_t*)a.given_scores;
     if (a.given_scores && (a.k_k != 0 || a.ans_k || a.ans_v)) return hipErrorInvalidValue;     // the scores cover the K anchors already
-    if (a.N > 0 && !a.given_scores)
-        hipLaunchKernelGGL(d12_table_kernel<DS>, dim3((unsigned)(g.B * g.Hkv), tab_blocks(DS)), dim3(kTabThreads), 0, st, a.q,
-                           a.cb_k, p.c1, g.Hq, g.Hkv, g.G, (float2*)(w + pl.off_tab), (float*)(w + pl.off_amax));
+    const D12VScores vs = {p.codes_k, p.idx_v, (float4_t*)(w + pl.off_vsc), p.N_cap, p.k_v};
+    if (a.N > 0 && !a.given_scores) {
+        const int64_t blocks = tab_blocks(DS) + (by_code && heads_per_table(DS) < kNH ? (a.k_v + kVBlock - 1) / kVBlock : 0);
+        hipLaunchKernelGGL(d12_table_kernel<DS>, dim3((unsigned)(g.B * g.Hkv * blocks)), dim3(kTabThreads), 0, st, a.q, a.cb_k, p.c1, g.Hq,
+                           g.Hkv, g.G, g.B * g.Hkv, (float2*)(w + pl.off_tab), (float*)(w + pl.off_amax), vs);
+    }
     if (a.N > 0 && by_code) {
         D12LongParams l;
         l.q = p.q; l.codes_k = p.codes_k; l.codes_v = p.codes_v; l.cb_v = p.cb_v; l.idx_k = p.idx_k; l.idx_v = p.idx_v;
         l.rows_k = p.rows_k; l.rows_v = p.rows_v; l.tab = p.tab; l.tab_amax = p.tab_amax; l.given = p.given; l.part = p.part;
-        l.wts = (uint32_t*)(w + pl.off_wts); l.tile_ref = (float*)(w + pl.off_ref); l.N = p.N; l.N_cap = p.N_cap; l.range = pl.range;
+        l.wts = (uint32_t*)(w + pl.off_wts); l.v_scores = vs.out; l.tile_ref = (float*)(w + pl.off_ref); l.N = p.N; l.N_cap = p.N_cap; l.range = pl.range;
         l.k_k = p.k_k; l.k_v = p.k_v; l.c1 = p.c1; l.Hq = p.Hq; l.Hkv = p.Hkv; l.G = p.G; l.S = pl.S; l.chunk = pl.chunk;
         l.S2 = pl.S2; l.slots = pl.slots;
         const hipError_t e = launch_decode12_by_code(g, l, st);
@@ -906,12 +963,12 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool 
 
 }  // namespace
 
-size_t decode12_workspace_bytes(const Geom& g, int64_t N) { return d12_plan(g, N, d12_by_code(g, N)).total; }
-size_t decode12_workspace_least(const Geom& g, int64_t N) { return d12_plan(g, N, false).total; }
+size_t decode12_workspace_bytes(const Geom& g, int64_t N, int64_t k_v) { return d12_plan(g, N, k_v, d12_by_code(g, N)).total; }
+size_t decode12_workspace_least(const Geom& g, int64_t N) { return d12_plan(g, N, 0, false).total; }
 
 hipError_t launch_decode12(const Geom& g, const DecodeArgs& a, void* ws, size_t ws_bytes, hipStream_t st)
 {
-    const bool by_code = d12_by_code(g, a.N) && ws_bytes >= d12_plan(g, a.N, true).total;
+    const bool by_code = d12_by_code(g, a.N) && ws_bytes >= d12_plan(g, a.N, a.k_v, true).total;
     return g.d == 32 ? launch_decode12_t<32>(g, a, ws, by_code, st) : launch_decode12_t<16>(g, a, ws, by_code, st);
 }
 

@@ -12,6 +12,8 @@
 //            lanes each, scores from the FP16 rows, values added up here.
 //   d12_values_kernel   a workgroup per token range and pair of sub-spaces.  Weights as fixed point into W_h[code], the V list's
 //            rows times their tokens' weights, W_h times the centroids at the end.
+// Where a table does not hold every head (d16) a V-anchored token outside the K list is scored in fp32, as in decode12_kernel: by
+// workgroups beside those of d12_table_kernel.  Its weight then counts in d12_values_kernel alone.
 // Bound: d12_values_kernel by the LDS atomics (64-bit, two heads each: 13 clocks per wave instruction on random codes; a
 // float atomic takes 192), d12_weights_kernel by VALU issue.  Gathering centroids costs 37 clocks per KB as pieces of 64 bytes
 // (d32) and 73 as pieces of 32 (d16).
@@ -38,11 +40,6 @@ __device__ __forceinline__ float swap_add16(float a, float b)      // even rows 
 {
     const uint2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-template <int N>
-__device__ __forceinline__ float row_ror_add(float v)              // plus the value of the lane N places further round in the row of 16
-{
-    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + N, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float all_max(float v)                  // of the wave, in every lane
 {
@@ -81,6 +78,7 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
 {
     constexpr int M = kD / DS, CB = 3 * M / 2;
     constexpr int NHT = GIVEN ? kNH : heads_per_table(DS);             // heads of a walk over the tokens
+    constexpr bool kVApart = NHT < kNH;                                // V entries outside the K list are scored elsewhere
     constexpr int kTabBlocks = tab_blocks(DS);
     constexpr int kPairs = M * kC12 / 2 / kT12;                        // pairs of neighbouring table entries per thread and plane
     constexpr int kReq = kPairs * (heads_per_table(DS) / 2);           // 16-byte pieces of the table per thread
@@ -287,6 +285,11 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
                 const uint2_t mk = *(const uint2_t*)(s_mask + 2 * ((2 * tile + (lane >> 5)) & 1023));
                 off[u] = (mk[0] >> bit & 1u) != 0u;
                 mark[u] = (mk[1] >> bit & 1u) * 0x80008000u;
+                if constexpr (kVApart) {                               // a weight of 0 here, and -1 as the mark
+                    if (off[u]) mark[u] = 0u;
+                    off[u] = off[u] || mark[u] != 0u;
+                    mark[u] = mark[u] != 0u ? 0xBC00BC00u : 0u;
+                }
                 if (u == 1 && tile >= n_tiles) off[u] = true;
                 if constexpr (GIVEN) {
 #pragma unroll
@@ -465,7 +468,8 @@ constexpr int kSec = 1792;
 constexpr size_t kVLds = (size_t)128 * 1024 + kSec * 16 + 2 * kNH * sizeof(float);
 static_assert(kVLds <= 160 * 1024, "LDS budget");
 
-template <int DS>
+// SCORED: the V list's entries come with scores, not with the stream's weights
+template <int DS, bool SCORED>
 __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
 {
     constexpr int M = kD / DS, CB = 3 * M / 2, NP = M / 2;
@@ -490,23 +494,6 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
     constexpr int LR = 2 * DS / 8, RP = 64 / LR;
     const int v_step = p.S2 * kW12 * RP;
     int ve = (r * kW12 + wave) * RP + lane / LR;
-    int vtok[kUV];
-    uint4_t vrow[kUV];
-    float vw[kUV][kNH];
-    auto fetch_entries = [&]() {
-        const int32_t* idx_v = p.idx_v + (int64_t)bg * p.k_v;
-        const half_t* rows = p.rows_v + (int64_t)bg * p.k_v * kD + 2 * DS * pr + 8 * (lane % LR);
-#pragma unroll
-        for (int u = 0; u < kUV; ++u) {
-            const int e = ve + u * v_step;
-            vtok[u] = -1;
-            vrow[u] = uint4_t{0u, 0u, 0u, 0u};
-            if (e < p.k_v) {
-                vtok[u] = idx_v[e];
-                vrow[u] = *(const uint4_t*)(rows + (int64_t)e * kD);
-            }
-        }
-    };
 #pragma unroll
     for (int i = 0; i < 8; ++i) smem_u4[i * kT12 + tid] = uint4_t{0u, 0u, 0u, 0u};
     // Reference of the sequence and sum of the range's weights against it, from the ranges of d12_weights_kernel.  The fixed-point
@@ -537,24 +524,6 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
         top[h] = s_top[h];
         shift[h] = s_exp[h] - top[h];
     }
-    auto weigh_entries = [&]() {                                       // (K-anchored tokens are settled there: their weight is 0)
-        uint32_t w[kUV][2];
-        float4_t ref[kUV];
-#pragma unroll
-        for (int u = 0; u < kUV; ++u) {
-            const int tok = vtok[u] < 0 ? 0 : vtok[u];
-            w[u][0] = wt[0][tok];
-            w[u][1] = wt[1][tok];
-            ref[u] = refs[tok >> 6];
-        }
-#pragma unroll
-        for (int u = 0; u < kUV; ++u)
-#pragma unroll
-            for (int h = 0; h < kNH; ++h) {
-                const half2_t w2 = __builtin_bit_cast(half2_t, w[u][h >> 1]);
-                vw[u][h] = vtok[u] < 0 ? 0.f : -(float)w2[h & 1] * fast_exp2(ref[u][h] - top[h]);
-            }
-    };
     const int coff = (3 * pr) & ~1, cshift = 8 * ((3 * pr) & 1);       // the pair's three bytes of a row lie in two 16-bit words
     const uint8_t* cv = p.codes_v + (int64_t)bg * p.N_cap * CB + coff;
 
@@ -621,16 +590,77 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
         lds_barrier();
     }
 
-    // ---- the V list's rows times their tokens' weights
-    float av[kNH][8];
+    // ---- the V list's rows times their tokens' weights: those that the stream left (negative; a K-anchored token, whose weight is 0,
+    // is settled there), or of the entry's score, against the wave's largest so far
+    float av[kNH][8], m_v[kNH], l_v[kNH];
 #pragma unroll
-    for (int h = 0; h < kNH; ++h)
+    for (int h = 0; h < kNH; ++h) {
+        m_v[h] = SCORED ? kEmptyRef12 : top[h];
+        l_v[h] = 0.f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) av[h][c] = 0.f;
+    }
+    const int32_t* idx_v = p.idx_v + (int64_t)bg * p.k_v;
+    const half_t* rows = p.rows_v + (int64_t)bg * p.k_v * kD + 2 * DS * pr + 8 * (lane % LR);
+    const float4_t* scores = p.v_scores + (int64_t)bg * p.k_v;
 #pragma unroll 1
     for (; __any(ve < p.k_v); ve += kUV * v_step) {
-        fetch_entries();
-        weigh_entries();
+        uint4_t vrow[kUV];
+        uint32_t w2[kUV][2];
+        float4_t from[kUV];                                            // score, or reference of the token's tile
+        int tok[kUV];
+#pragma unroll
+        for (int u = 0; u < kUV; ++u) {
+            const int e = ve + u * v_step;
+            tok[u] = -1;
+            vrow[u] = uint4_t{0u, 0u, 0u, 0u};
+            from[u] = float4_t{0.f, 0.f, 0.f, 0.f};
+            if (e < p.k_v) {
+                tok[u] = idx_v[e];
+                vrow[u] = *(const uint4_t*)(rows + (int64_t)e * kD);
+                if constexpr (SCORED) from[u] = scores[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kUV; ++u) {
+            const int t = tok[u] < 0 ? 0 : tok[u];
+            w2[u][0] = wt[0][t];
+            if constexpr (!SCORED) {
+                w2[u][1] = wt[1][t];
+                from[u] = refs[t >> 6];
+            }
+        }
+        float w[kUV][kNH];
+        if constexpr (SCORED) {
+#pragma unroll
+            for (int h = 0; h < kNH; ++h) {
+                float t = kNegBig;
+#pragma unroll
+                for (int u = 0; u < kUV; ++u) {
+                    w[u][h] = tok[u] >= 0 && (w2[u][0] & 0x8000u) != 0u ? from[u][h] : kNegBig;
+                    t = fmaxf(t, w[u][h]);
+                }
+                t = all_max(t);
+                if (t > m_v[h]) {
+                    const float alpha = fast_exp2(m_v[h] - t);
+                    l_v[h] *= alpha;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) av[h][c] *= alpha;
+                    m_v[h] = t;
+                }
+#pragma unroll
+                for (int u = 0; u < kUV; ++u) {
+                    w[u][h] = fast_exp2(w[u][h] - m_v[h] + kPShift12);
+                    l_v[h] += lane % LR == 0 ? w[u][h] : 0.f;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kUV; ++u)
+#pragma unroll
+                for (int h = 0; h < kNH; ++h)
+                    w[u][h] = tok[u] < 0 ? 0.f : -(float)__builtin_bit_cast(half2_t, w2[u][h >> 1])[h & 1] * fast_exp2(from[u][h] - top[h]);
+        }
 #pragma unroll
         for (int u = 0; u < kUV; ++u) {
             const half8_t v = __builtin_bit_cast(half8_t, vrow[u]);
@@ -638,12 +668,16 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
             for (int c = 0; c < 8; ++c) {
                 const float vf = (float)v[c];
 #pragma unroll
-                for (int h = 0; h < kNH; ++h) av[h][c] = fmaf(vw[u][h], vf, av[h][c]);
+                for (int h = 0; h < kNH; ++h) av[h][c] = fmaf(w[u][h], vf, av[h][c]);
             }
         }
     }
     float out_v[8];
     fold_heads<LR>(av, out_v);
+    if constexpr (SCORED) {
+#pragma unroll
+        for (int h = 0; h < kNH; ++h) l_v[h] = wave_sum(l_v[h]);
+    }
 
     // ---- the 2 x 4096 sums times their centroids: LPC lanes per centroid, a wave takes 256 codes of either sub-space, the next
     // four centroids are on their way while four are multiplied
@@ -695,6 +729,8 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
     __syncthreads();                                                   // the sums are no longer read
     float* s_o = (float*)smem_u4;                                      // [waves][heads][2 DS], then the same of the V list
     float* s_ov = s_o + kW12 * kNH * 2 * DS;
+    float* s_mv = s_ov + kW12 * kNH * 2 * DS;                          // [waves][heads] its references and sums
+    float* s_lv = s_mv + kW12 * kNH;
     const int row = wave * kNH + (lane >> 4);
     if ((lane & 15) < LPC) {
 #pragma unroll
@@ -707,21 +743,37 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
 #pragma unroll
         for (int c = 0; c < 8; ++c) s_ov[row * 2 * DS + 8 * (lane % LR) + c] = out_v[c];
     }
+    if (SCORED && lane == 0) {
+#pragma unroll
+        for (int h = 0; h < kNH; ++h) {
+            s_mv[wave * kNH + h] = m_v[h];
+            s_lv[wave * kNH + h] = l_v[h];
+        }
+    }
     __syncthreads();
     if (tid < kNH * 2 * DS) {
         const int h = tid / (2 * DS), ch = tid % (2 * DS);
         if (h < p.G) {
-            float a = 0.f, v = 0.f;
+            float a = 0.f, v = 0.f, m = s_top[h], l = 0.f;
+#pragma unroll
+            for (int w = 0; w < kW12; ++w) a += s_o[(w * kNH + h) * 2 * DS + ch];
+            a *= fast_exp2(-s_exp[h]);
+            if constexpr (SCORED) {
+#pragma unroll
+                for (int w = 0; w < kW12; ++w) m = fmaxf(m, s_mv[w * kNH + h]);
+                a *= fast_exp2(s_top[h] - m);
+            }
 #pragma unroll
             for (int w = 0; w < kW12; ++w) {
-                a += s_o[(w * kNH + h) * 2 * DS + ch];
-                v += s_ov[(w * kNH + h) * 2 * DS + ch];
+                const float f = SCORED ? fast_exp2(s_mv[w * kNH + h] - m) : 1.f;
+                v = fmaf(s_ov[(w * kNH + h) * 2 * DS + ch], f, v);
+                if constexpr (SCORED) l = fmaf(s_lv[w * kNH + h], f, l);
             }
             float* dst = p.part + (((int64_t)b * p.Hq + g * p.G + h) * p.slots + p.S + r) * (kD + 2);
-            dst[2 + 2 * DS * pr + ch] = fmaf(a, fast_exp2(-s_exp[h]), v);
-            if (pr == 0 && ch == 0) {                                  // (the weights are counted in d12_weights_kernel's sums)
-                dst[0] = s_top[h];
-                dst[1] = 0.f;
+            dst[2 + 2 * DS * pr + ch] = a + v;
+            if (pr == 0 && ch == 0) {                                  // (the stream's weights are counted in d12_weights_kernel's sums)
+                dst[0] = m;
+                dst[1] = l;
             }
         }
     }
@@ -730,11 +782,13 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
 template <int DS>
 hipError_t launch(const Geom& g, const D12LongParams& p, hipStream_t st)
 {
+    constexpr bool kApart = heads_per_table(DS) < kNH;
     static OncePerDevice once;
     const hipError_t setup = on_this_device(once, []() {
         const std::pair<const void*, size_t> kernels[] = {{(const void*)d12_weights_kernel<DS, false>, kWLds},
                                                           {(const void*)d12_weights_kernel<DS, true>, kWLds},
-                                                          {(const void*)d12_values_kernel<DS>, kVLds}};
+                                                          {(const void*)d12_values_kernel<DS, kApart>, kVLds},
+                                                          {(const void*)d12_values_kernel<DS, false>, kVLds}};
         for (const auto& k : kernels) {
             const hipError_t e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second);
             if (e != hipSuccess) return e;
@@ -742,10 +796,14 @@ hipError_t launch(const Geom& g, const D12LongParams& p, hipStream_t st)
         return hipSuccess;
     });
     if (setup != hipSuccess) return setup;
-    const dim3 ranges((unsigned)(g.B * g.Hkv * p.S));
-    if (p.given) hipLaunchKernelGGL((d12_weights_kernel<DS, true>), ranges, dim3(kT12), kWLds, st, p);
-    else hipLaunchKernelGGL((d12_weights_kernel<DS, false>), ranges, dim3(kT12), kWLds, st, p);
-    hipLaunchKernelGGL(d12_values_kernel<DS>, dim3((unsigned)(g.B * g.Hkv * p.S2 * (g.M / 2))), dim3(kT12), kVLds, st, p);
+    const dim3 ranges((unsigned)(g.B * g.Hkv * p.S)), parts((unsigned)(g.B * g.Hkv * p.S2 * (g.M / 2)));
+    if (p.given) {
+        hipLaunchKernelGGL((d12_weights_kernel<DS, true>), ranges, dim3(kT12), kWLds, st, p);
+        hipLaunchKernelGGL((d12_values_kernel<DS, false>), parts, dim3(kT12), kVLds, st, p);
+    } else {
+        hipLaunchKernelGGL((d12_weights_kernel<DS, false>), ranges, dim3(kT12), kWLds, st, p);
+        hipLaunchKernelGGL((d12_values_kernel<DS, kApart>), parts, dim3(kT12), kVLds, st, p);
+    }
     return hipGetLastError();
 }
 

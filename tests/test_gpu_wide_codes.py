@@ -233,6 +233,82 @@ def test_decode12_values_by_code_sections_and_unused_centroids(books):
     assert err <= 4e-3
 
 
+def _pack12_dev(codes):
+    """pack12 on the GPU: [..., M] codes -> [..., 3M/2] bytes."""
+    out = torch.empty((*codes.shape[:-1], codes.shape[-1] * 3 // 2), dtype=torch.uint8, device="cuda")
+    for m in range(0, codes.shape[-1], 2):
+        w = codes[..., m] | codes[..., m + 1] << 12
+        for i in range(3):
+            out[..., 3 * m // 2 + i] = (w >> 8 * i & 255).to(torch.uint8)
+    return out
+
+
+def _effective(codes, cb, idx, rows):
+    """float64 [Hkv, N, 128] of one sequence: the centroids of the codes, the FP16 rows in the anchored places."""
+    Hkv, N, M = codes.shape
+    out = torch.empty((Hkv, N, 128), dtype=torch.float64, device="cuda")
+    for m in range(M):
+        d = 128 // M
+        for g in range(Hkv):
+            out[g, :, m * d:(m + 1) * d] = cb[g, m].double()[codes[g, :, m]]
+    if idx is not None:
+        for g in range(Hkv):
+            out[g, idx[g].long()] = rows[g].double()
+    return out
+
+
+def _decode_exact(q, scale, codes_k, codes_v, cb_k, cb_v, idx_k, rows_k, idx_v, rows_v):
+    """Decode attention of unpacked codes in float64: (output [B, Hq, 128], softmax weights [B, Hq, N])."""
+    outs, ps = [], []
+    for b in range(q.shape[0]):
+        k = _effective(codes_k[b], cb_k, None if idx_k is None else idx_k[b], None if rows_k is None else rows_k[b])
+        s = scale * (q[b].double().view(k.shape[0], -1, 128) @ k.transpose(1, 2).contiguous())
+        del k
+        p = torch.softmax(s, dim=-1)
+        v = _effective(codes_v[b], cb_v, None if idx_v is None else idx_v[b], None if rows_v is None else rows_v[b])
+        outs.append((p @ v).view(-1, 128))
+        ps.append(p.view(-1, p.shape[-1]))
+    return torch.stack(outs), torch.stack(ps)
+
+
+def _by_code_shape(books):
+    """(B, Hkv, N) at which the values are added up by code, one range per KV head."""
+    return (16, 8, 14400) if books.d == 32 else (8, 8, 8257)
+
+
+@pytest.mark.parametrize("by_code", [True, False])
+def test_decode12_scores_of_v_anchors(books, by_code):
+    """Where a table does not hold every head, a V-anchored token outside the K list is scored by fp32 products and not through the
+    16-bit table, whichever way the values are added up.  The V centroids are zero and every V row has one channel, so that a
+    channel of the output is one token's softmax weight, and a centroid that no token uses makes the table coarse: its rounding alone
+    would move a weight by 8e-4 rms.  Bound: the output's rounding 2^-11, gathering also the fp16 weight's; 1e-4 for the rest."""
+    if books.d == 32:
+        pytest.skip("the table holds every head")
+    B, Hkv, N = _by_code_shape(books)
+    Hq, k_k, k_v, M, d = 4 * Hkv, 90, 128, books.M, books.d
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes_k, codes_v = (torch.randint(0, C - 1, (B, Hkv, N, M), device="cuda", generator=gen) for _ in range(2))
+    cb_k = rnd(Hkv, M, C, d) * 0.5
+    cb_k[:, :, C - 1] = 45 * rnd(Hkv, M, d).sign()
+    cb_v = torch.zeros((Hkv, M, C, d), dtype=torch.float16, device="cuda")
+    order = torch.rand((B, Hkv, N), device="cuda", generator=gen).argsort(dim=-1)
+    idx_v = order[..., :k_v].sort(dim=-1).values.int().contiguous()
+    idx_k = order[..., k_v - 30:k_v - 30 + k_k].sort(dim=-1).values.int().contiguous()      # 30 tokens in both lists
+    rows_k = rnd(B, Hkv, k_k, 128) * 0.5
+    rows_v = (1024 * torch.eye(128, dtype=torch.float16, device="cuda")).expand(B, Hkv, k_v, 128).contiguous()
+    q, scale = rnd(B, Hq, 128), 128 ** -0.5
+    geom = antkv.Geometry(B, Hq, Hkv, d, n_centroids=C)
+    ws = antkv.DecodeWorkspace(geom, N, k_k, k_v, 0, "cuda")
+    got = antkv.decode_attn(geom, q, scale, _pack12_dev(codes_k), _pack12_dev(codes_v), cb_k, cb_v, idx_k, rows_k, idx_v, rows_v,
+                            workspace=ws if by_code else _least(ws)).double()
+    _, p = _decode_exact(q, scale, codes_k, codes_v, cb_k, cb_v, idx_k, rows_k, idx_v, rows_v)
+    want = 1024 * p.gather(-1, idx_v.long().repeat_interleave(Hq // Hkv, dim=1))
+    err = ((got - want) / want).abs()
+    print(f"d{d} by code {by_code}: largest {err.max().item():.2e}, rms {err.pow(2).mean().sqrt().item():.2e}")
+    assert err.max().item() <= (1 if by_code else 2) * 2.0 ** -11 + 1e-4
+
+
 def test_encode12_then_decode12(oracle, books):
     """Codes produced by the library's own encode feed its decode; the oracle decodes the oracle's codes."""
     from workloads import make_decode_query
