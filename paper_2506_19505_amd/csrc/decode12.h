@@ -88,6 +88,7 @@ struct D12LongParams {
     const float* tab_amax;                // [B][Hkv][table blocks][4] per-block maxima of |score|
     const float4_t* given;                // or, instead of a table, [B][Hkv][N] the four heads' scores (then k_k is 0)
     float* part;                          // [B][Hq][slots][kD + 2]: S slots of the first kernel, S2 of the second
+    float2* stat;                         // [B][Hq][S] reference and sum of the weights that the first kernel wrote
     uint32_t* wts;                        // [pairs of heads][B][Hkv][N] weights, two fp16; both negative: a V-anchored token, where
                                           // it is scored apart -1 if it is not in the K list
     const float4_t* v_scores;             // those scores: [B][Hkv][k_v] of four heads

@@ -892,7 +892,12 @@ D12Plan d12_plan(const Geom& g, int64_t N, int64_t k_v, bool by_code)
 // fraction of the gather's time.  One step, gather and by code, us: d32, 8 KV heads (16 ranges) 200000 tokens 61 and 65, 420000
 // 102 and 81, 840000 169 and 102; 64 heads (2 ranges) 16000 57 and 60, 33333 81 and 67; d16, 8 heads (8 ranges) 50000 61 and 63,
 // 70000 67 and 66, 840000 308 and 153; 64 heads (1 range) 4096 54 and 56, 9001 66 and 59, 70000 229 and 106.
-bool d12_by_code(const Geom& g, int64_t N) { return d12_plan(g, N, 0, true).range >= (g.d == 32 ? 14336 : 8192); }
+// (The fixed-point sums have room for 2^27 tokens.)
+bool d12_by_code(const Geom& g, int64_t N)
+{
+    const int64_t range = d12_plan(g, N, 0, true).range;
+    return range >= (g.d == 32 ? 14336 : 8192) && range <= (1 << 27);
+}
 
 template <int DS>
 hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool by_code, hipStream_t st)
@@ -928,7 +933,7 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool 
         D12LongParams l;
         l.q = p.q; l.codes_k = p.codes_k; l.codes_v = p.codes_v; l.cb_v = p.cb_v; l.idx_k = p.idx_k; l.idx_v = p.idx_v;
         l.rows_k = p.rows_k; l.rows_v = p.rows_v; l.tab = p.tab; l.tab_amax = p.tab_amax; l.given = p.given; l.part = p.part;
-        l.wts = (uint32_t*)(w + pl.off_wts); l.v_scores = vs.out; l.tile_ref = (float*)(w + pl.off_ref); l.N = p.N; l.N_cap = p.N_cap; l.range = pl.range;
+        l.stat = (float2*)(w + pl.off_stat); l.wts = (uint32_t*)(w + pl.off_wts); l.v_scores = vs.out; l.tile_ref = (float*)(w + pl.off_ref); l.N = p.N; l.N_cap = p.N_cap; l.range = pl.range;
         l.k_k = p.k_k; l.k_v = p.k_v; l.c1 = p.c1; l.Hq = p.Hq; l.Hkv = p.Hkv; l.G = p.G; l.S = pl.S; l.chunk = pl.chunk;
         l.S2 = pl.S2; l.slots = pl.slots;
         const hipError_t e = launch_decode12_by_code(g, l, st);

@@ -41,6 +41,13 @@ __device__ __forceinline__ float swap_add16(float a, float b)      // even rows 
     const uint2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+__device__ __forceinline__ float rows_max(float v)                 // of the lanes l mod 16 of the four rows
+{
+    uint2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 __device__ __forceinline__ float all_max(float v)                  // of the wave, in every lane
 {
 #define ANTKV_ROR_MAX(N) v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + N, 0xf, 0xf, true)))
@@ -49,10 +56,16 @@ __device__ __forceinline__ float all_max(float v)                  // of the wav
     ANTKV_ROR_MAX(2);
     ANTKV_ROR_MAX(1);
 #undef ANTKV_ROR_MAX
-    uint2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    return rows_max(v);
+}
+// four heads' values, added up over the wave: lane 16 h + anything then holds head h
+__device__ __forceinline__ float fold_sums(const float (&l)[kNH])
+{
+    float v = swap_add16(swap_add32(l[0], l[2]), swap_add32(l[1], l[3]));
+    v = row_ror_add<8>(v);
+    v = row_ror_add<4>(v);
+    v = row_ror_add<2>(v);
+    return row_ror_add<1>(v);
 }
 // four heads' values of a lane's eight channels, added up over the lanes that hold the same channels (l mod STEP): lane
 // 16 h + l then holds head h
@@ -69,8 +82,9 @@ __device__ __forceinline__ void fold_heads(const float (&a)[kNH][8], float (&out
     }
 }
 
-// LDS of d12_weights_kernel: table, bitmaps of the range's K- and V-anchored tokens, q, samples of the V list, words
-constexpr size_t kWLds = (size_t)128 * 1024 + 2 * 1024 * 4 + kNH * kD * 2 + kProbes * 4 + 16 * 4;
+// LDS of d12_weights_kernel: table, bitmaps of the range's K- and V-anchored tokens, q, samples of the V list, words, the waves'
+// references and sums of the stream
+constexpr size_t kWLds = (size_t)128 * 1024 + 2 * 1024 * 4 + kNH * kD * 2 + kProbes * 4 + 16 * 4 + 2 * kW12 * kNH * 4;
 static_assert(kWLds <= 160 * 1024, "LDS budget");
 
 template <int DS, bool GIVEN>
@@ -88,6 +102,8 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
     half_t* s_q = (half_t*)(s_mask + 2 * 1024);
     int* s_probe = (int*)(s_q + kNH * kD);
     int* s_misc = s_probe + kProbes;
+    float* s_ms = (float*)(s_misc + 16);                               // [waves][heads]
+    float* s_ls = s_ms + kW12 * kNH;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = blockIdx.x % p.Hkv, rest = blockIdx.x / p.Hkv;       // KV head g on XCD g mod 8
@@ -368,12 +384,19 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
         }
     }
 
-    // ---- the K list's entries
+    // ---- the K list's entries.  (Their weights are summed apart: the fixed-point unit of d12_values_kernel follows the stream's.)
+    {
+        const float l = fold_sums(l_lane);
+        if (li == 0) s_ls[wave * kNH + grp] = l;
+    }
+    if (lane == 0) *(float4_t*)(s_ms + wave * kNH) = float4_t{m_ref[0], m_ref[1], m_ref[2], m_ref[3]};
     float acc[kNH][8];
 #pragma unroll
-    for (int h = 0; h < kNH; ++h)
+    for (int h = 0; h < kNH; ++h) {
+        l_lane[h] = 0.f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[h][c] = 0.f;
+    }
 #pragma unroll 1
     for (; blk < n_blocks; blk += p.S * kW12) {
         fetch_block(blk);
@@ -394,8 +417,7 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
             float t = sc[0][h];
 #pragma unroll
             for (int i = 1; i < kKI; ++i) t = fmaxf(t, sc[i][h]);
-            t = fmaxf(t, __shfl_xor(t, 16, 64));
-            top[h] = fmaxf(t, __shfl_xor(t, 32, 64));
+            top[h] = rows_max(t);
             if (top[h] > m_ref[h]) {
                 const float alpha = fast_exp2(m_ref[h] - top[h]);
                 l_lane[h] *= alpha;
@@ -426,14 +448,10 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
     float* s_m = (float*)smem;                                         // [waves][heads] references
     float* s_l = s_m + kW12 * kNH;                                     // [waves][heads] sums
     float* s_acc = s_l + kW12 * kNH;                                   // [waves][heads][128]
-#pragma unroll
-    for (int h = 0; h < kNH; ++h) {
-        const float lw = wave_sum(l_lane[h]);
-        if (lane == 0) {
-            s_m[wave * kNH + h] = m_ref[h];
-            s_l[wave * kNH + h] = lw;
-        }
-    }
+    const float l_entries = fold_sums(l_lane);
+    if (lane == 0) *(float4_t*)(s_m + wave * kNH) = float4_t{m_ref[0], m_ref[1], m_ref[2], m_ref[3]};
+    __builtin_amdgcn_wave_barrier();                                   // LDS operations of one wave stay in order
+    if (li == 0) s_l[wave * kNH + grp] = fmaf(s_ls[wave * kNH + grp], fast_exp2(s_ms[wave * kNH + grp] - s_m[wave * kNH + grp]), l_entries);
     float fold[8];
     fold_heads<16>(acc, fold);
 #pragma unroll
@@ -457,6 +475,12 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
                 dst[1] = l;
             }
         }
+    } else if (tid < kNH * kD + nh) {
+        const int h = tid - kNH * kD;
+        float m = kEmptyRef12, l = 0.f;
+        for (int w = 0; w < kW12; ++w) m = fmaxf(m, s_ms[w * kNH + h]);
+        for (int w = 0; w < kW12; ++w) l = fmaf(s_ls[w * kNH + h], fast_exp2(s_ms[w * kNH + h] - m), l);
+        p.stat[((int64_t)b * p.Hq + g * nh + h) * p.S + sp] = float2{m, l};
     }
 }
 
@@ -465,7 +489,7 @@ __global__ __launch_bounds__(kT12) void d12_weights_kernel(const D12LongParams p
 constexpr int kU = 4;
 constexpr int kUV = 5;                      // entries of the V list per lane in flight
 constexpr int kSec = 1792;
-constexpr size_t kVLds = (size_t)128 * 1024 + kSec * 16 + 2 * kNH * sizeof(float);
+constexpr size_t kVLds = (size_t)128 * 1024 + kSec * 16 + 3 * kNH * sizeof(float);
 static_assert(kVLds <= 160 * 1024, "LDS budget");
 
 // SCORED: the V list's entries come with scores, not with the stream's weights
@@ -476,8 +500,9 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
     extern __shared__ uint4_t smem_u4[];
     unsigned long long* s_hist = (unsigned long long*)smem_u4;         // [2 sub-spaces][2 head pairs][4096]
     float4_t* s_f = (float4_t*)((char*)smem_u4 + 128 * 1024);          // [tiles of the section] factors of the four heads
-    float* s_top = (float*)(s_f + kSec);                               // [heads] reference of the sequence
-    float* s_exp = s_top + kNH;                                        // [heads] log2 of the fixed-point scale
+    float* s_top = (float*)(s_f + kSec);                               // [heads] reference of the range,
+    float* s_all = s_top + kNH;                                        // and of the sequence
+    int* s_exp = (int*)(s_all + kNH);                                  // [heads] log2 of the fixed-point scale
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = blockIdx.x % p.Hkv;                                  // KV head g on XCD g mod 8
@@ -496,34 +521,49 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
     int ve = (r * kW12 + wave) * RP + lane / LR;
 #pragma unroll
     for (int i = 0; i < 8; ++i) smem_u4[i * kT12 + tid] = uint4_t{0u, 0u, 0u, 0u};
-    // Reference of the sequence and sum of the range's weights against it, from the ranges of d12_weights_kernel.  The fixed-point
-    // unit is 2^-31 of (at least) that sum, so no sum of weights overflows, and a token's rounding is 2^-32 of it.
+    // References, and the sum of the stream's weights over the ranges of d12_weights_kernel that this one touches.  The fixed-point
+    // unit is 2^-e, so that 17/16 of that sum has at most 2^32 of them and at least 2^31: no sum of weights overflows, since a
+    // sixteenth is more than their rounding to fp16 and one unit for each of 2^27 tokens (rule: d12_by_code).
     if (wave < kNH) {
-        float top = kEmptyRef12, e2 = 0.f;
+        float all = kEmptyRef12, top = kEmptyRef12;
+        int e = 0;
         if (wave < p.G) {
-            const float* pb = p.part + ((int64_t)b * p.Hq + g * p.G + wave) * p.slots * (kD + 2);
+            const float2* st = p.stat + ((int64_t)b * p.Hq + g * p.G + wave) * p.S;
             const int s_lo = (int)(r0 / p.chunk), s_hi = (int)((r1 - 1) / p.chunk);
-            for (int s = lane; s < p.S; s += 64) top = fmaxf(top, pb[(int64_t)s * (kD + 2)]);
+            for (int s = lane; s < p.S; s += 64) {
+                const float x = st[s].x;
+                all = fmaxf(all, x);
+                if (s >= s_lo && s <= s_hi) top = fmaxf(top, x);
+            }
+            all = all_max(all);
             top = all_max(top);
             float l = 0.f;
-            for (int s = s_lo + lane; s <= s_hi; s += 64) l += pb[(int64_t)s * (kD + 2) + 1] * fast_exp2(pb[(int64_t)s * (kD + 2)] - top);
+            for (int s = s_lo + lane; s <= s_hi; s += 64) l = fmaf(st[s].y, fast_exp2(st[s].x - top), l);
             l = wave_sum(l);
-            int e = 0;
-            (void)frexpf(l, &e);                                       // l <= 2^e
-            e2 = (float)(31 - e);
+            (void)frexpf(l * 1.0625f, &e);
+            e = 32 - e;
         }
         if (lane == 0) {
+            s_all[wave] = all;
             s_top[wave] = top;
-            s_exp[wave] = e2;
+            s_exp[wave] = e;
         }
     }
     __syncthreads();
-    float top[kNH], shift[kNH];                                        // weight to fixed point: 2^(reference of the tile + shift)
+    float top[kNH], scale[kNH];                                        // weight to fixed point: 2^(reference of the tile - top) scale
 #pragma unroll
     for (int h = 0; h < kNH; ++h) {
         top[h] = s_top[h];
-        shift[h] = s_exp[h] - top[h];
+        scale[h] = h < p.G ? ldexpf(1.f, s_exp[h]) : 0.f;              // (0: the slot has no head)
     }
+    // What a weight is short of whole units counts as one or none by the lane's share of a unit, spread evenly over the 64 tokens
+    // of a tile: rounded to the nearest, the small weights beside a large one would all err the same way.
+    const float share = ((float)(__brev((uint32_t)lane) >> 26) + 0.5f) * (1.f / 64.f);
+    auto to_fixed = [&](float w, float f) -> uint32_t {
+        uint32_t r;
+        asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(fmaf(w, f, share)));    // (0 for marked weights, which are negative, and NaN)
+        return r;
+    };
     const int coff = (3 * pr) & ~1, cshift = 8 * ((3 * pr) & 1);       // the pair's three bytes of a row lie in two 16-bit words
     const uint8_t* cv = p.codes_v + (int64_t)bg * p.N_cap * CB + coff;
 
@@ -563,8 +603,7 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
                     if (pl >= planes) continue;
                     const half2_t w2 = __builtin_bit_cast(half2_t, t.w[u][pl]);
                     // (marked weights are negative and become 0)
-                    const uint32_t x = (uint32_t)fmaf((float)w2[0], f[2 * pl], 0.5f);
-                    const uint32_t y = (uint32_t)fmaf((float)w2[1], f[2 * pl + 1], 0.5f);
+                    const uint32_t x = to_fixed((float)w2[0], f[2 * pl]), y = to_fixed((float)w2[1], f[2 * pl + 1]);
                     if (on && (x | y) != 0u) {
                         const unsigned long long v = (unsigned long long)y << 32 | x;
                         atomicAdd(h0 + pl * kC12, v);
@@ -577,8 +616,10 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
         fetch(0, cur);
         for (int t = tid; t < (n + 63) / 64; t += kT12) {
             const float4_t ref = refs[(s0 >> 6) + t];
-            s_f[t] = float4_t{fast_exp2(ref[0] + shift[0]), fast_exp2(ref[1] + shift[1]), fast_exp2(ref[2] + shift[2]),
-                              fast_exp2(ref[3] + shift[3])};
+            float4_t f;
+#pragma unroll
+            for (int h = 0; h < kNH; ++h) f[h] = fast_exp2(ref[h] - top[h]) * scale[h];
+            s_f[t] = f;
         }
         lds_barrier();
 #pragma unroll 1
@@ -595,7 +636,7 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
     float av[kNH][8], m_v[kNH], l_v[kNH];
 #pragma unroll
     for (int h = 0; h < kNH; ++h) {
-        m_v[h] = SCORED ? kEmptyRef12 : top[h];
+        m_v[h] = SCORED ? kEmptyRef12 : s_all[h];
         l_v[h] = 0.f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) av[h][c] = 0.f;
@@ -659,7 +700,7 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
             for (int u = 0; u < kUV; ++u)
 #pragma unroll
                 for (int h = 0; h < kNH; ++h)
-                    w[u][h] = tok[u] < 0 ? 0.f : -(float)__builtin_bit_cast(half2_t, w2[u][h >> 1])[h & 1] * fast_exp2(from[u][h] - top[h]);
+                    w[u][h] = tok[u] < 0 ? 0.f : -(float)__builtin_bit_cast(half2_t, w2[u][h >> 1])[h & 1] * fast_exp2(from[u][h] - m_v[h]);
         }
 #pragma unroll
         for (int u = 0; u < kUV; ++u) {
@@ -754,15 +795,14 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
     if (tid < kNH * 2 * DS) {
         const int h = tid / (2 * DS), ch = tid % (2 * DS);
         if (h < p.G) {
-            float a = 0.f, v = 0.f, m = s_top[h], l = 0.f;
+            float a = 0.f, v = 0.f, m = SCORED ? s_top[h] : s_all[h], l = 0.f;
 #pragma unroll
             for (int w = 0; w < kW12; ++w) a += s_o[(w * kNH + h) * 2 * DS + ch];
-            a *= fast_exp2(-s_exp[h]);
             if constexpr (SCORED) {
 #pragma unroll
                 for (int w = 0; w < kW12; ++w) m = fmaxf(m, s_mv[w * kNH + h]);
-                a *= fast_exp2(s_top[h] - m);
             }
+            a = ldexpf(a, -s_exp[h]) * fast_exp2(s_top[h] - m);
 #pragma unroll
             for (int w = 0; w < kW12; ++w) {
                 const float f = SCORED ? fast_exp2(s_mv[w * kNH + h] - m) : 1.f;

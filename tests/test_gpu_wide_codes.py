@@ -309,6 +309,48 @@ def test_decode12_scores_of_v_anchors(books, by_code):
     assert err.max().item() <= (1 if by_code else 2) * 2.0 ** -11 + 1e-4
 
 
+@pytest.mark.parametrize("gap", [24.5, 28.25, 30.5, 31.5])
+@pytest.mark.parametrize("large", ["code", "anchor"])
+def test_decode12_small_weights_beside_a_large_one(books, large, gap):
+    """One token whose value is zero outweighs every other one by 2^gap: what is left of the output is the sum of the small weights,
+    all equal and rounded alike.  Added up by code, a weight is a number of units of at most 17/16 2^-31 of the streamed sum, what
+    is left of one being counted for the right part of a tile's 64 tokens: a tile's sum is off by less than a unit.  An FP16 row's
+    token is not part of that sum.  Besides: 2^-11 for the output, half a unit of the smallest fp16 weights (2^-36 of the
+    large one) in a wave that has the large token, 2e-4 for table, exponentials and fp32 sums."""
+    B, Hkv, N = _by_code_shape(books)
+    M, d = books.M, books.d
+    codes_k = torch.zeros((B, Hkv, N, M), dtype=torch.int64, device="cuda")
+    codes_v = torch.ones_like(codes_k)
+    cb_k = torch.zeros((Hkv, M, C, d), dtype=torch.float16, device="cuda")
+    cb_v = torch.zeros_like(cb_k)
+    cb_k[:, 0, 1, 0] = gap
+    cb_v[:, :, 1] = 30000
+    at = 777
+    codes_v[:, :, at] = 0
+    idx_k = rows_k = None
+    if large == "code":
+        codes_k[:, :, at, 0] = 1
+    else:
+        idx_k = torch.full((B, Hkv, 1), at, dtype=torch.int32, device="cuda")
+        rows_k = torch.zeros((B, Hkv, 1, 128), dtype=torch.float16, device="cuda")
+        rows_k[..., 0] = gap
+    q = torch.zeros((B, Hkv, 128), dtype=torch.float16, device="cuda")
+    q[..., 0] = 1
+    geom = antkv.Geometry(B, Hkv, Hkv, d, n_centroids=C)
+    ck, cv = _pack12_dev(codes_k), _pack12_dev(codes_v)
+    want = 30000 * (N - 1) / (2.0 ** gap + N - 1)
+    for by_code in (True, False):
+        ws = antkv.DecodeWorkspace(geom, N, 1 if idx_k is not None else 0, 0, 0, "cuda")
+        got = antkv.decode_attn(geom, q, float(np.log(2)), ck, cv, cb_k, cb_v, idx_k, rows_k, None, None,
+                                workspace=ws if by_code else _least(ws)).double()
+        bound = 2.0 ** -11 + 2e-4
+        if large == "code":
+            bound += 2.0 ** (gap - 37) + (17 / 16 * 2.0 ** (gap - 31) / 64 if by_code else 0)
+        err = ((got - want) / want).abs().max().item()
+        print(f"d{d} {large} 2^{gap}, by code {by_code}: {err:.2e}, bound {bound:.2e}")
+        assert err <= bound
+
+
 def test_encode12_then_decode12(oracle, books):
     """Codes produced by the library's own encode feed its decode; the oracle decodes the oracle's codes."""
     from workloads import make_decode_query
