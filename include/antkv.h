@@ -115,8 +115,6 @@ int antkv_anchor_select(const antkv_geom* geom, const void* q, const void* k_fp1
 /*
  * Selection alone: for each of n_rows score rows (fp32 [n_rows][N], finite values), the positions
  * of the k largest, ascending; ties to the lower position.  idx: int32 [n_rows][k].
- * (Here and wherever a selection is part of a call: a workspace sized for a smaller k is not refused, the selection may then
- * take longer.)
  */
 size_t antkv_topk_workspace(int64_t n_rows, int64_t N, int64_t k);
 int antkv_topk(const float* scores, int64_t n_rows, int64_t N, int64_t k, int32_t* idx,

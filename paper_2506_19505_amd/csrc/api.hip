@@ -29,7 +29,7 @@ int check_geom(const antkv_geom* gm, Geom& g)
 inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0; }
 
 struct SelPlan {
-    size_t off_score, off_topk, least, total;                    // least: what a call does not refuse
+    size_t off_score, off_topk, total;
 };
 
 SelPlan sel_plan(const Geom& g, int64_t N, int64_t Nq, int64_t k)
@@ -37,14 +37,12 @@ SelPlan sel_plan(const Geom& g, int64_t N, int64_t Nq, int64_t k)
     SelPlan p;
     p.off_score = 0;
     p.off_topk = align_up(anchor_score_workspace_bytes(g, N, Nq));
-    const int64_t rows = 2 * (int64_t)g.B * g.Hkv;               // K and V rows in one go
-    p.total = p.off_topk + align_up(topk_workspace_bytes(rows, N, k));
-    p.least = p.off_topk + align_up(topk_workspace_least(rows, N, k));
+    p.total = p.off_topk + align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k));   // K and V rows in one go
     return p;
 }
 
 struct DecPlan {
-    size_t off_dec, off_topk, least, total;
+    size_t off_dec, off_topk, total;
 };
 
 DecPlan dec_plan(const Geom& g, int64_t N, int64_t k_k, int64_t k_v, int64_t k_resel, bool want_ans)
@@ -52,9 +50,7 @@ DecPlan dec_plan(const Geom& g, int64_t N, int64_t k_k, int64_t k_v, int64_t k_r
     DecPlan p;
     p.off_dec = 0;
     p.off_topk = align_up(decode_workspace_bytes(g, N, k_k, k_v, want_ans));
-    const int64_t rows = 2 * (int64_t)g.B * g.Hkv;
-    p.total = p.off_topk + (k_resel > 0 ? align_up(topk_workspace_bytes(rows, N, k_resel)) : 0);
-    p.least = p.off_topk + (k_resel > 0 ? align_up(topk_workspace_least(rows, N, k_resel)) : 0);
+    p.total = p.off_topk + (k_resel > 0 ? align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0);
     return p;
 }
 
@@ -86,7 +82,7 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
     const bool want_ans = ans_k || ans_v;
     if (want_ans && !(ans_k && ans_v)) return ANTKV_EINVAL;   // the two scores are produced together
     if (wide) {
-        const size_t topk_bytes = k_resel > 0 ? align_up(topk_workspace_least(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0;
+        const size_t topk_bytes = k_resel > 0 ? align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k_resel)) : 0;
         const size_t least = align_up(decode12_workspace_least(g, N)), best = align_up(decode12_workspace_bytes(g, N, k_v));
         if (!workspace || misaligned(workspace, 256) || workspace_bytes < least + topk_bytes) return ANTKV_EWORKSPACE;
         const size_t off_topk = workspace_bytes < best + topk_bytes ? least : best;
@@ -106,16 +102,15 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
             const int64_t rows = (int64_t)g.B * g.Hkv;
             const hipError_t e =
                 (resel_idx_k && resel_idx_v)
-                    ? launch_topk2_finish(ans_k, resel_idx_k, ans_v, resel_idx_v, rows, N, k_resel,
-                                          w + off_topk, workspace_bytes - off_topk, st)
+                    ? launch_topk2_finish(ans_k, resel_idx_k, ans_v, resel_idx_v, rows, N, k_resel, w + off_topk, st)
                     : launch_topk(resel_idx_k ? ans_k : ans_v, rows, N, k_resel, resel_idx_k ? resel_idx_k : resel_idx_v,
-                                  w + off_topk, workspace_bytes - off_topk, st);
+                                  w + off_topk, st);
             if (e != hipSuccess) return ANTKV_ELAUNCH;
         }
         return ANTKV_OK;
     }
     const DecPlan dp = dec_plan(g, N, k_k, k_v, k_resel, true);
-    if (N > 0 && (!workspace || misaligned(workspace, 256) || workspace_bytes < dp.least)) return ANTKV_EWORKSPACE;
+    if (N > 0 && (!workspace || misaligned(workspace, 256) || workspace_bytes < dp.total)) return ANTKV_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     DecodeArgs a;
     a.q = (const half_t*)q; a.scale = scale; a.codes_k = codes_k; a.codes_v = codes_v; a.N = N; a.N_cap = N_cap;
@@ -132,12 +127,11 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
         char* w = (char*)workspace;
         const int64_t rows = (int64_t)g.B * g.Hkv;
         if (resel_idx_k && resel_idx_v) {
-            e = launch_topk2_finish(ans_k, resel_idx_k, ans_v, resel_idx_v, rows, N, k_resel,
-                                    w + dp.off_topk, workspace_bytes - dp.off_topk, st);
+            e = launch_topk2_finish(ans_k, resel_idx_k, ans_v, resel_idx_v, rows, N, k_resel, w + dp.off_topk, st);
             if (e != hipSuccess) return ANTKV_ELAUNCH;
         } else if (resel_idx_k || resel_idx_v) {
             e = launch_topk(resel_idx_k ? ans_k : ans_v, rows, N, k_resel, resel_idx_k ? resel_idx_k : resel_idx_v,
-                            w + dp.off_topk, workspace_bytes - dp.off_topk, st);
+                            w + dp.off_topk, st);
             if (e != hipSuccess) return ANTKV_ELAUNCH;
         }
     }
@@ -216,9 +210,9 @@ int antkv_topk(const float* scores, int64_t n_rows, int64_t N, int64_t k, int32_
     if (n_rows < 0 || N < 0 || k < 0 || k > N || N > 0x7fffffffLL || n_rows > 65535) return ANTKV_EINVAL;
     if (k == 0 || n_rows == 0) return ANTKV_OK;
     if (!scores || !idx) return ANTKV_EINVAL;
-    if (!workspace || misaligned(workspace, 256) || workspace_bytes < topk_workspace_least(n_rows, N, k))
+    if (!workspace || misaligned(workspace, 256) || workspace_bytes < topk_workspace_bytes(n_rows, N, k))
         return ANTKV_EWORKSPACE;
-    hipError_t e = launch_topk(scores, n_rows, N, k, idx, workspace, workspace_bytes, (hipStream_t)stream);
+    hipError_t e = launch_topk(scores, n_rows, N, k, idx, workspace, (hipStream_t)stream);
     return e == hipSuccess ? ANTKV_OK : ANTKV_ELAUNCH;
 }
 
@@ -295,7 +289,7 @@ int antkv_anchor_select(const antkv_geom* geom, const void* q, const void* k_fp1
     if (misaligned(q, 16) || misaligned(k_fp16, 16)) return ANTKV_EINVAL;
     if (!(scale > 0.f)) return ANTKV_EINVAL;
     const SelPlan sp = sel_plan(g, N, Nq, k);
-    if (!workspace || misaligned(workspace, 256) || workspace_bytes < sp.least) return ANTKV_EWORKSPACE;
+    if (!workspace || misaligned(workspace, 256) || workspace_bytes < sp.total) return ANTKV_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     char* w = (char*)workspace;
     // scores default to the tail of the score workspace
@@ -308,10 +302,10 @@ int antkv_anchor_select(const antkv_geom* geom, const void* q, const void* k_fp1
     if (e != hipSuccess) return ANTKV_ELAUNCH;
     const int64_t rows = (int64_t)g.B * g.Hkv;
     if (idx_k && idx_v && k > 0) {
-        e = launch_topk2(sk, idx_k, sv, idx_v, rows, N, k, w + sp.off_topk, workspace_bytes - sp.off_topk, st);
+        e = launch_topk2(sk, idx_k, sv, idx_v, rows, N, k, w + sp.off_topk, st);
         if (e != hipSuccess) return ANTKV_ELAUNCH;
     } else if ((idx_k || idx_v) && k > 0) {
-        e = launch_topk(idx_k ? sk : sv, rows, N, k, idx_k ? idx_k : idx_v, w + sp.off_topk, workspace_bytes - sp.off_topk, st);
+        e = launch_topk(idx_k ? sk : sv, rows, N, k, idx_k ? idx_k : idx_v, w + sp.off_topk, st);
         if (e != hipSuccess) return ANTKV_ELAUNCH;
     }
     return ANTKV_OK;

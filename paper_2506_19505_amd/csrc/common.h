@@ -111,12 +111,11 @@ hipError_t launch_encode12(const Geom& g, const half_t* x, int64_t xs_b, int64_t
                            int64_t n_tok, const half_t* cb, uint8_t* codes, int64_t N_cap,
                            int64_t token_offset, hipStream_t st);
 
-size_t topk_workspace_bytes(int64_t n_rows, int64_t N, int64_t k);    // what the selection can use,
-size_t topk_workspace_least(int64_t n_rows, int64_t N, int64_t k);    // and what it can do with
+size_t topk_workspace_bytes(int64_t n_rows, int64_t N, int64_t k);
 hipError_t launch_topk(const float* scores, int64_t n_rows, int64_t N, int64_t k, int32_t* idx,
-                       void* ws, size_t ws_bytes, hipStream_t st);
+                       void* ws, hipStream_t st);
 hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                        int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st);
+                        int64_t N, int64_t k, void* ws, hipStream_t st);
 // The same selection in two halves, for a producer that counts its scores while it writes them: `begin` clears the
 // workspace's counters and returns the first-level histograms, uint32 [2 n_rows][2 * kTopkBins] (row r < n_rows belongs
 // to scores row r, row n_rows + r to scores_b row r; the first kTopkBins words of a row count float_key(score) >> 21);
@@ -125,7 +124,7 @@ hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b
 constexpr int kTopkBins = 2048;
 uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st);
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                               int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st);
+                               int64_t N, int64_t k, void* ws, hipStream_t st);
 
 hipError_t launch_gather_rows(const Geom& g, const half_t* x, int64_t N, const int32_t* idx,
                               int64_t k, half_t* rows, hipStream_t st);

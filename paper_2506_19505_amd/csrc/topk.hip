@@ -3,19 +3,20 @@
 //
 // Exact radix select on an order-preserving 32-bit key:
 //   1. histogram of the top 11 key bits per row;
-//   2. every workgroup (slice of 8192 scores) finds the bin d0 that holds the k-th largest key.  If the keys of that bin and
-//      above are few (at most N/8 + 4096 + k, the usual case for heavy-tailed scores) the workgroup appends its own ones, with
-//      their positions and in their order, to the row's list, as a segment of it; otherwise (scores crowded into a narrow
-//      range) it adds its keys of bin d0 to a second histogram over the next 11 bits;
-//   3. only for rows that took the second branch: the same once more, one level down (the keys from prefix (d0, d1) up are
-//      listed); workgroups of other rows return at once;
+//   2. every workgroup (slice of 8192 scores) finds the bin d0 that holds the k-th largest key.  Where k is small beside all
+//      scores (rule: list_above) and the keys of that bin and above fit the row's list (about N/8 + 4096 entries; the usual case
+//      for heavy-tailed scores), the workgroup appends its own ones, with their positions and in their order, as a segment of
+//      it.  Otherwise it lists its keys of bin d0 alone, if those fit, and counts the ones above.  If they don't (scores crowded
+//      into a narrow range) it adds its keys of bin d0 to a second histogram over the next 11 bits;
+//   3. only for rows that took the last branch: the same once more, one level down, with prefix (d0, d1) in the place of d0;
+//      workgroups of other rows return at once;
 //   4. one workgroup per row selects the exact k-th largest key tau among the list's (radix rounds on the remaining bits,
 //      histograms in LDS) and counts every slice's keys > tau and == tau; a row whose keys agree in 22 bits for more than the
 //      list holds is walked by that workgroup instead;
-//   5. an ordered emission pass over the segments (over the scores of a row that is not listed) writes the positions of all
-//      keys > tau plus the lowest-positioned keys == tau needed to reach k, in ascending position order.  (By the one
-//      workgroup per row of step 4 it took 20 us for 16 rows of 840000.)
-// The scores are read once, or twice where the producer has not counted them for the first histogram.
+//   5. an ordered emission pass over the segments, or over the scores of rows without them, writes the positions of all keys > tau
+//      plus the lowest-positioned keys == tau needed to reach k, in ascending position order.  (By the one workgroup per row
+//      of step 4 it took 20 us for 16 rows of 840000.)
+// The scores are read once with segments, and once more where the producer has not counted them for the first histogram.
 // Rows of up to 32768 scores fit the registers of one workgroup: topk_row does all of it in one launch (the launches
 // above cost 38 us for 128 rows of 1531 scores, this one 6).  The kernels for
 // longer rows are bound by latency up to some 100000 scores and by reading the scores beyond.  16 rows of
@@ -81,7 +82,7 @@ __device__ __forceinline__ const float* row_scores(const float* scores, const fl
 }
 
 // per-row header in the workspace
-enum { kHeadCount = 0, kHeadTau = 1, kHeadNeedEq = 2, kHeadCrowded = 3, kHeadUnlisted = 4, kHeadWords = 8 };
+enum { kHeadCount = 0, kHeadTau = 1, kHeadNeedEq = 2, kHeadCrowded = 3, kHeadSegments = 4, kHeadWords = 8 };
 
 __global__ __launch_bounds__(kTopkThreads) void topk_hist0(const float* __restrict__ scores,
                                                            const float* __restrict__ scores_b, int rows_a, int64_t N,
@@ -115,18 +116,28 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist0(const float* __restri
 // threads, 20 by waves; 840003 scores, not aligned, 87 by threads (a dword at a time), 16 by waves.)
 constexpr int kPer = kSlice / kTopkThreads;
 
-// LEVEL 1: list the keys from bin d0 up, or (crowded) histogram the next 11 bits of bin d0's.  LEVEL 2, crowded rows only: list
-// the keys from the prefix (d0, d1) up.  segs: [rows][slices] (start, length) of the slice's segment of the row's list.
+// What a row's list holds, for `above` keys in higher bins and `bin` in the k-th key's: every key from that bin up (in segments),
+// the bin's, or nothing
+enum { kListAbove, kListBin, kListNone };
+__device__ __forceinline__ int list_kind(uint32_t above, uint32_t bin, uint32_t cap, bool list_above)
+{
+    return list_above && above + bin <= cap ? kListAbove : (bin <= cap ? kListBin : kListNone);
+}
+
+// LEVEL 1: list the keys from bin d0 up, or bin d0's, or (crowded) histogram the next 11 bits of bin d0's.  LEVEL 2, crowded rows
+// only: the same for the prefix (d0, d1).  segs: [rows][slices] (start, length) of the slice's segment of the row's list;
+// counts, where the list holds the bin alone: [rows][slices] (keys above it, 0).
 template <int LEVEL>
 __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __restrict__ scores,
                                                              const float* __restrict__ scores_b, int rows_a, int64_t N,
                                                              uint32_t k, uint32_t* __restrict__ ws_hist,
                                                              uint32_t* __restrict__ head, uint2_t* __restrict__ segs,
-                                                             int n_slices, uint2_t* __restrict__ cand, uint32_t cap)
+                                                             uint2_t* __restrict__ counts, int n_slices,
+                                                             uint2_t* __restrict__ cand, uint32_t cap, bool list_above)
 {
     __shared__ uint32_t lh[LEVEL == 1 ? kBins : 1];
     __shared__ uint32_t sh[8];
-    __shared__ uint32_t red[4];
+    __shared__ uint32_t red[2][4];
     __shared__ uint32_t s_base;
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -154,18 +165,19 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
     const int own = fast ? kPer : (lo < N ? (int)((N - lo + 63) / 64 < kPer ? (N - lo + 63) / 64 : kPer) : 0);
     uint32_t d0, k_rem;
     find_digit(hist0, kBins, k, d0, k_rem, sh);
-    const bool crowded = k - k_rem + hist0[d0] > cap;           // the same for every workgroup of the row
-    uint32_t prefix = d0;                                       // the keys from it up are listed
+    int kind = list_kind(k - k_rem, hist0[d0], cap, list_above);   // the same for every workgroup of the row
+    uint32_t prefix = d0;
     if (LEVEL == 2) {
         uint32_t d1;
         find_digit(hist1, kBins, k_rem, d1, k_rem, sh);
         prefix = (d0 << 11) | d1;
-        if (k - k_rem + hist1[d1] > cap) return;                // topk_resolve walks the row
+        kind = list_kind(k - k_rem, hist1[d1], cap, list_above);
+        if (kind == kListNone) return;                          // topk_resolve walks the row
     }
     constexpr int kShift = LEVEL == 1 ? 21 : 10;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) key[j] = float_key(__uint_as_float(key[j]));
-    if (LEVEL == 1 && crowded) {                                // bin d0's next 11 bits go to the second histogram
+    if (LEVEL == 1 && kind == kListNone) {                      // bin d0's next 11 bits go to the second histogram
         if (blockIdx.x == 0 && tid == 0) head[row * kHeadWords + kHeadCrowded] = 1u;
         for (int i = tid; i < kBins; i += kTopkThreads) lh[i] = 0u;
         __syncthreads();
@@ -177,11 +189,19 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
             if (lh[i]) atomicAdd(&hist1[i], lh[i]);
         return;
     }
-    // entries of the thread (aligned slices) or of the wave, and what comes before them in the slice
+    // entries (keys from first to first + span) of the thread (aligned slices) or of the wave, and what comes before them in the slice
+    uint32_t first = prefix << kShift, span = kind == kListAbove ? ~first : (1u << kShift) - 1u;
     uint32_t mine = 0, incl;
+    if (kind == kListBin) {
+        uint32_t gt = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) gt += key[j] > first + span;
+        gt = wave_sum_u32(gt);
+        if (lane == 0) red[1][wave] = gt;
+    }
     if (fast) {
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) mine += (key[j] >> kShift) >= prefix;
+        for (int j = 0; j < kPer; ++j) mine += key[j] - first <= span;
         incl = mine;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -190,27 +210,28 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) mine += (uint32_t)__popcll(__ballot(j < own && (key[j] >> kShift) >= prefix));
+        for (int j = 0; j < kPer; ++j) mine += (uint32_t)__popcll(__ballot(j < own && key[j] - first <= span));
         incl = mine;
     }
-    if (lane == 63) red[wave] = incl;
+    if (lane == 63) red[0][wave] = incl;
     __syncthreads();
     if (tid == 0) {
-        const uint32_t n = red[0] + red[1] + red[2] + red[3];
+        const uint32_t n = red[0][0] + red[0][1] + red[0][2] + red[0][3];
         s_base = n ? atomicAdd(&head[row * kHeadWords + kHeadCount], n) : 0u;
-        segs[row * n_slices + blockIdx.x] = uint2_t{s_base, n};
+        if (kind == kListAbove) segs[row * n_slices + blockIdx.x] = uint2_t{s_base, n};
+        else counts[row * n_slices + blockIdx.x] = uint2_t{red[1][0] + red[1][1] + red[1][2] + red[1][3], 0u};
     }
     __syncthreads();
     uint32_t at = s_base + incl - mine;
-    for (int w = 0; w < wave; ++w) at += red[w];
+    for (int w = 0; w < wave; ++w) at += red[0][w];
     uint2_t* out = cand + row * (int64_t)cap;
     // (compared again: kept, 32 results spilled scalar registers and cost a wave per SIMD)
-    pin(prefix);
+    pin(first);
     if (fast) {
         if (mine == 0) return;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            if ((key[j] >> kShift) >= prefix) {
+            if (key[j] - first <= span) {
                 if (at < cap) out[at] = uint2_t{key[j], (uint32_t)(lo + j)};
                 ++at;
             }
@@ -219,7 +240,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_collect(const float* __rest
         const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const bool in = j < own && (key[j] >> kShift) >= prefix;
+            const bool in = j < own && key[j] - first <= span;
             const uint64_t m = __ballot(in);
             if (m == 0ull) continue;
             const uint32_t my = at + (uint32_t)__popcll(m & below);
@@ -247,7 +268,8 @@ __global__ __launch_bounds__(kResolveThreads) void topk_resolve(const float* __r
                                                              const float* __restrict__ scores_b, int rows_a, int64_t N,
                                                              uint32_t k, const uint32_t* __restrict__ ws_hist,
                                                              uint32_t* __restrict__ head, uint2_t* __restrict__ counts,
-                                                             int n_slices, const uint2_t* __restrict__ cand, uint32_t cap)
+                                                             int n_slices, const uint2_t* __restrict__ cand, uint32_t cap,
+                                                             bool list_above)
 {
     __shared__ uint32_t lh[kBins];
     __shared__ uint32_t lh_eq[kBins];
@@ -258,30 +280,45 @@ __global__ __launch_bounds__(kResolveThreads) void topk_resolve(const float* __r
     const uint32_t* hist1 = hist0 + kBins;
     uint32_t d0, d1 = 0, d2, k_rem, need_eq;
     find_digit<kResolveThreads>(hist0, kBins, k, d0, k_rem, sh);
-    uint32_t n_list = k - k_rem + hist0[d0];
-    const bool crowded = n_list > cap;
-    bool listed = true;
+    uint32_t bin = hist0[d0];
+    int kind = list_kind(k - k_rem, bin, cap, list_above);
+    const bool crowded = kind == kListNone;
     if (crowded) {
         find_digit<kResolveThreads>(hist1, kBins, k_rem, d1, k_rem, sh);
-        n_list = k - k_rem + hist1[d1];
-        listed = n_list <= cap;                                  // else more than the list holds agree in 22 bits: walk the row
+        bin = hist1[d1];
+        kind = list_kind(k - k_rem, bin, cap, list_above);
     }
+    const bool listed = kind != kListNone;                       // else more than the list holds agree in 22 bits: walk the row
+    const uint32_t n_list = kind == kListAbove ? k - k_rem + bin : bin;
     const uint2_t* list = cand + row * (int64_t)cap;
     const float* src = row_scores(scores, scores_b, rows_a, row, N);
-    constexpr int kAhead = 8;                                    // loads of a thread in flight
     auto for_each = [&](auto fn) {
-        const int64_t n = listed ? (int64_t)n_list : N;
-        for (int64_t i0 = tid; i0 < n; i0 += kAhead * kResolveThreads) {
-            uint2_t e[kAhead];
+        if (listed) {
+            constexpr int kAhead = 4;                            // loads of a thread in flight (8: 2 us slower on short lists)
+            for (uint32_t i0 = tid; i0 < n_list; i0 += kAhead * kResolveThreads) {
+                uint2_t e[kAhead];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int64_t i = i0 + u * kResolveThreads, at = i < n ? i : n - 1;
-                if (listed) e[u] = list[at];
-                else e[u] = uint2_t{__float_as_uint(src[at]), (uint32_t)at};
+                for (int u = 0; u < kAhead; ++u) {
+                    const uint32_t i = i0 + u * kResolveThreads;
+                    e[u] = list[i < n_list ? i : n_list - 1];
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+                    if (i0 + u * kResolveThreads < n_list) fn(e[u][0], e[u][1]);
             }
+        } else {
+            constexpr int kAhead = 8;
+            for (int64_t i0 = tid; i0 < N; i0 += kAhead * kResolveThreads) {
+                float e[kAhead];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u)
-                if (i0 + u * kResolveThreads < n) fn(listed ? e[u][0] : float_key(__uint_as_float(e[u][0])), e[u][1]);
+                for (int u = 0; u < kAhead; ++u) {
+                    const int64_t i = i0 + u * kResolveThreads;
+                    e[u] = src[i < N ? i : N - 1];
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+                    if (i0 + u * kResolveThreads < N) fn(float_key(e[u]), (uint32_t)(i0 + u * kResolveThreads));
+            }
         }
     };
     if (!crowded) {                                              // the k-th key shares d0 only: round on bits 20..10
@@ -311,12 +348,13 @@ __global__ __launch_bounds__(kResolveThreads) void topk_resolve(const float* __r
             else if (key == tau) count_in(lh_eq, s);
         });
         __syncthreads();
-        for (int i = tid; i < kBins && s0 + i < n_slices; i += kResolveThreads) c[s0 + i] = uint2_t{lh[i], lh_eq[i]};
+        for (int i = tid; i < kBins && s0 + i < n_slices; i += kResolveThreads)
+            c[s0 + i] = uint2_t{lh[i] + (kind == kListBin ? c[s0 + i][0] : 0u), lh_eq[i]};
     }
     if (tid == 0) {
         head[row * kHeadWords + kHeadTau] = tau;
         head[row * kHeadWords + kHeadNeedEq] = need_eq;
-        head[row * kHeadWords + kHeadUnlisted] = listed ? 0u : 1u;
+        head[row * kHeadWords + kHeadSegments] = kind == kListAbove ? 1u : 0u;
     }
 }
 
@@ -339,7 +377,9 @@ __device__ __forceinline__ void emit_ordered(const uint32_t (&key)[PER], uint32_
     }
 }
 
-// A wave per 2048 scores of the slice, or per quarter of its segment of the list: coalesced, ranked through ballots.
+// SEGMENTS: a row's segments are read if it has them, a wave per quarter of one, ranked through ballots.  Otherwise the scores,
+// requested ahead of the counts, whose latency they share.
+template <bool SEGMENTS>
 __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restrict__ scores,
                                                           const float* __restrict__ scores_b, int rows_a, int64_t N,
                                                           uint32_t k, const uint32_t* __restrict__ head,
@@ -350,9 +390,30 @@ __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restric
     __shared__ uint32_t red[4][4];
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint2_t seg = segs[row * n_slices + blockIdx.x];
+    const int64_t slice_lo = (int64_t)blockIdx.x * kSlice;
+    const float* src = row_scores(scores, scores_b, rows_a, row, N);
+    const bool fast = slice_lo + kSlice <= N && (((uintptr_t)(src + slice_lo)) & 15) == 0;
+    const int64_t lo = slice_lo + (fast ? tid * kPer : wave * (64 * kPer) + lane);
+    uint32_t key[kPer];
+    // (Past the end keys are 0, the lowest.  The NaN 0xffffffff has it too, but at earlier positions, and need_eq counts only
+    // those.)
+    auto request = [&]() {
+        if (fast) {
+#pragma unroll
+            for (int j = 0; j < kPer / 4; ++j) {
+                const float4_t v = *(const float4_t*)(src + lo + 4 * j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) key[4 * j + e] = __float_as_uint(v[e]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? __float_as_uint(src[lo + 64 * j]) : 0xffffffffu;
+        }
+    };
+    if constexpr (!SEGMENTS) request();
     const uint32_t tau = head[row * kHeadWords + kHeadTau], need_eq = head[row * kHeadWords + kHeadNeedEq];
-    const bool listed = head[row * kHeadWords + kHeadUnlisted] == 0u;
+    const bool segments = SEGMENTS && head[row * kHeadWords + kHeadSegments] != 0u;
+    const uint2_t seg = SEGMENTS ? segs[row * n_slices + blockIdx.x] : uint2_t{0u, 0u};
     // keys > tau and == tau in the slices before this one
     uint32_t bgt = 0, beq = 0;
     for (int s = tid; s < (int)blockIdx.x; s += kTopkThreads) {
@@ -360,54 +421,80 @@ __global__ __launch_bounds__(kTopkThreads) void topk_emit(const float* __restric
         bgt += c[0];
         beq += c[1];
     }
-    const uint2_t* list = cand + row * (int64_t)cap;
+    bgt = wave_sum_u32(bgt);
+    beq = wave_sum_u32(beq);
+    if (lane == 0) { red[0][wave] = bgt; red[1][wave] = beq; }
     int32_t* out = (row < rows_a) ? idx + row * (int64_t)k : idx_b + (row - rows_a) * (int64_t)k;
-    uint32_t key[kPer];
-    uint32_t gt = 0, eq = 0;
-    const int64_t lo = (int64_t)blockIdx.x * kSlice + wave * (64 * kPer) + lane;
-    // the wave's entries of the segment
-    const uint32_t quarter = (seg[1] + 255) / 256 * 64, e_lo = wave * quarter, e_hi = e_lo + quarter < seg[1] ? e_lo + quarter : seg[1];
-    if (listed) {
+    uint32_t gt = 0, eq = 0, my_gt = 0, my_eq = 0;               // of the wave; of the thread and, then, of the lanes up to it
+    if (segments) {
+        const uint2_t* list = cand + row * (int64_t)cap + seg[0];
+        const uint32_t quarter = (seg[1] + 255) / 256 * 64, e_lo = wave * quarter, e_hi = e_lo + quarter < seg[1] ? e_lo + quarter : seg[1];
         for (uint32_t i = e_lo + lane; i < e_hi; i += 64) {
-            const uint32_t x = list[seg[0] + i][0];
+            const uint32_t x = list[i][0];
             gt += x > tau;
             eq += x == tau;
         }
         gt = wave_sum_u32(gt);
         eq = wave_sum_u32(eq);
-    } else {
-        const float* src = row_scores(scores, scores_b, rows_a, row, N);
-        // (Past the end keys are 0, the lowest.  The NaN 0xffffffff has it too, but at earlier positions, and need_eq counts
-        // only those.)
+        if (lane == 0) { red[2][wave] = gt; red[3][wave] = eq; }
+        __syncthreads();
+        uint32_t run_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3], run_eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+        for (int w = 0; w < wave; ++w) { run_gt += red[2][w]; run_eq += red[3][w]; }
+        const uint64_t below = (1ull << lane) - 1ull;
+        for (uint32_t i0 = e_lo; i0 < e_hi; i0 += 64) {
+            const bool in = i0 + lane < e_hi;
+            const uint2_t e = list[in ? i0 + lane : e_lo];
+            const bool is_gt = in && e[0] > tau, is_eq = in && e[0] == tau;
+            const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
+            const uint32_t at_gt = run_gt + (uint32_t)__popcll(mg & below), at_eq = run_eq + (uint32_t)__popcll(me & below);
+            if (is_gt) out[at_gt + (at_eq < need_eq ? at_eq : need_eq)] = (int32_t)e[1];
+            else if (is_eq && at_eq < need_eq) out[at_gt + at_eq] = (int32_t)e[1];
+            run_gt += (uint32_t)__popcll(mg);
+            run_eq += (uint32_t)__popcll(me);
+        }
+        return;
+    }
+    if constexpr (SEGMENTS) request();
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) key[j] = lo + 64 * j < N ? float_key(src[lo + 64 * j]) : 0u;
+    for (int j = 0; j < kPer; ++j) key[j] = float_key(__uint_as_float(key[j]));
+    if (fast) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) { my_gt += key[j] > tau; my_eq += key[j] == tau; }
+        gt = my_gt;
+        eq = my_eq;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t a = __shfl_up(gt, off, 64), b = __shfl_up(eq, off, 64);
+            if (lane >= off) { gt += a; eq += b; }
+        }
+        if (lane == 63) { red[2][wave] = gt; red[3][wave] = eq; }
+    } else {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             gt += (uint32_t)__popcll(__ballot(key[j] > tau));
             eq += (uint32_t)__popcll(__ballot(key[j] == tau));
         }
+        if (lane == 0) { red[2][wave] = gt; red[3][wave] = eq; }
     }
-    bgt = wave_sum_u32(bgt);
-    beq = wave_sum_u32(beq);
-    if (lane == 0) { red[0][wave] = bgt; red[1][wave] = beq; red[2][wave] = gt; red[3][wave] = eq; }
     __syncthreads();
     uint32_t run_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3], run_eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
     for (int w = 0; w < wave; ++w) { run_gt += red[2][w]; run_eq += red[3][w]; }
-    if (!listed) {
+    if (!fast) {
         emit_ordered<kPer>(key, tau, need_eq, run_gt, run_eq, lane, lo, out);
         return;
     }
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (uint32_t i0 = e_lo; i0 < e_hi; i0 += 64) {
-        const bool in = i0 + lane < e_hi;
-        const uint2_t e = list[seg[0] + (in ? i0 + lane : e_lo)];
-        const bool is_gt = in && e[0] > tau, is_eq = in && e[0] == tau;
-        const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
-        const uint32_t my_gt = run_gt + (uint32_t)__popcll(mg & below), my_eq = run_eq + (uint32_t)__popcll(me & below);
-        if (is_gt) out[my_gt + (my_eq < need_eq ? my_eq : need_eq)] = (int32_t)e[1];
-        else if (is_eq && my_eq < need_eq) out[my_gt + my_eq] = (int32_t)e[1];
-        run_gt += (uint32_t)__popcll(mg);
-        run_eq += (uint32_t)__popcll(me);
+    run_gt += gt - my_gt;
+    run_eq += eq - my_eq;
+    if (my_gt == 0 && (my_eq == 0 || run_eq >= need_eq)) return; // nothing of this thread is selected
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (key[j] > tau) {
+            out[run_gt + (run_eq < need_eq ? run_eq : need_eq)] = (int32_t)(lo + j);
+            ++run_gt;
+        } else if (key[j] == tau) {
+            if (run_eq < need_eq) out[run_gt + run_eq] = (int32_t)(lo + j);
+            ++run_eq;
+        }
     }
 }
 
@@ -489,43 +576,36 @@ struct TopkPlan {
     size_t off_hist, off_head, off_segs, off_counts, off_cand, total;
 };
 
-// ws_bytes: the list, which comes last, takes what k needs or what there is
-TopkPlan topk_plan(int64_t rows, int64_t N, int64_t k, size_t ws_bytes)
+TopkPlan topk_plan(int64_t rows, int64_t N)
 {
     TopkPlan p;
     p.n_slices = (int)((N + kSlice - 1) / kSlice);
     if (p.n_slices < 1) p.n_slices = 1;
-    // the keys listed are the k and the rest of a bin, which usually holds a few percent of a row; more keys that agree in 22
-    // bits make topk_resolve walk the row
-    int64_t cap = N / 8 + 4096 + k;
-    if (cap > N) cap = N;
+    // the bin of the k-th key usually holds a few percent of a row; a fuller bin makes topk_resolve walk the row
+    p.cap = (uint32_t)(N / 8 + 4096 - p.n_slices);
     size_t off = 0;
     p.off_hist = off;   off += align_up((size_t)rows * 2 * kBins * 4);            // two histogram levels per row
     p.off_head = off;   off += align_up((size_t)rows * kHeadWords * 4);     // directly after the histograms: zeroed together
-    p.off_segs = off;   off += align_up((size_t)rows * p.n_slices * sizeof(uint2_t));
     p.off_counts = off; off += align_up((size_t)rows * p.n_slices * sizeof(uint2_t));
-    p.off_cand = off;
-    const size_t room = ws_bytes > off && rows > 0 ? (ws_bytes - off) / ((size_t)rows * sizeof(uint2_t)) : 0;
-    if ((size_t)cap > room) cap = (int64_t)room;
-    p.cap = (uint32_t)cap;
-    off += align_up((size_t)rows * p.cap * sizeof(uint2_t));
+    p.off_segs = off;                                                             // segments and lists together N / 8 + 4096 per row
+    p.off_cand = off + (size_t)rows * p.n_slices * sizeof(uint2_t);
+    off += align_up((size_t)rows * (p.n_slices + p.cap) * sizeof(uint2_t));
     p.total = off;
     return p;
 }
+
+// Listing every key from the threshold's bin up saves the emission a second pass over the scores; in return the one workgroup per
+// row that resolves the threshold walks k more entries, some 0.7 ns each.  The two meet at a k of about 4000 (2 rows of 840000),
+// 6500 (16 of 131072), 6000 (2 of 2000000), 15000 (16 of 840000) and 21000 (64 of 400000).  One call, us, listed above and
+// not: 16 rows of 840000, k 1 % 54 and 59, 5 % 81 and 64, 25 % 218 and 76; 2 of 2000000, 0.1 % 36 and 38, 1 % 50 and 41, 25 % 404 and 57.
+bool list_above(int64_t rows, int64_t N, int64_t k) { return k <= 3000 + rows * N / 1280; }
 
 }  // namespace
 
 size_t topk_workspace_bytes(int64_t n_rows, int64_t N, int64_t k)
 {
-    return topk_plan(n_rows, N, k, SIZE_MAX).total;
-}
-
-// A list of N/8 + 4096 entries less the segments: large k then make rows go the way of crowded ones
-size_t topk_workspace_least(int64_t n_rows, int64_t N, int64_t k)
-{
-    const TopkPlan p = topk_plan(n_rows, N, k, SIZE_MAX);
-    const size_t least = p.off_counts + align_up((size_t)n_rows * (N / 8 + 4096) * sizeof(uint2_t));
-    return least < p.total ? least : p.total;
+    (void)k;
+    return topk_plan(n_rows, N).total;
 }
 
 // Two score arrays of n_rows rows each can be selected in one go (scores_b / idx_b may be NULL): the launches then
@@ -535,19 +615,19 @@ namespace {
 // clears the histograms and headers of `rows` rows
 uint32_t* topk_clear(int64_t rows, int64_t N, void* ws, hipStream_t st)
 {
-    const TopkPlan p = topk_plan(rows, N, 0, SIZE_MAX);         // (the list is the last part)
+    const TopkPlan p = topk_plan(rows, N);
     uint32_t* hist = (uint32_t*)((char*)ws + p.off_hist);
-    const int64_t nz = (int64_t)(p.off_segs / 4);             // histograms and headers
+    const int64_t nz = (int64_t)(p.off_counts / 4);             // histograms and headers
     hipLaunchKernelGGL(zero_u32, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, hist, nz);
     return hist;
 }
 
 // everything after the first-level histogram
 hipError_t topk_select(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                       int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st)
+                       int64_t N, int64_t k, void* ws, hipStream_t st)
 {
     const int64_t rows = scores_b ? 2 * n_rows : n_rows;
-    const TopkPlan p = topk_plan(rows, N, k, ws_bytes);
+    const TopkPlan p = topk_plan(rows, N);
     char* w = (char*)ws;
     uint32_t* hist = (uint32_t*)(w + p.off_hist);
     uint32_t* head = (uint32_t*)(w + p.off_head);
@@ -555,15 +635,16 @@ hipError_t topk_select(const float* scores, int32_t* idx, const float* scores_b,
     uint2_t* counts = (uint2_t*)(w + p.off_counts);
     uint2_t* cand = (uint2_t*)(w + p.off_cand);
     const int ra = (int)n_rows;
+    const bool above = list_above(rows, N, k);
     dim3 grid(p.n_slices, (unsigned)rows);
     hipLaunchKernelGGL(topk_collect<1>, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k, hist, head,
-                       segs, p.n_slices, cand, p.cap);
+                       segs, counts, p.n_slices, cand, p.cap, above);
     hipLaunchKernelGGL(topk_collect<2>, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k, hist, head,
-                       segs, p.n_slices, cand, p.cap);
+                       segs, counts, p.n_slices, cand, p.cap, above);
     hipLaunchKernelGGL(topk_resolve, dim3((unsigned)rows), dim3(kResolveThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k,
-                       hist, head, counts, p.n_slices, cand, p.cap);
-    hipLaunchKernelGGL(topk_emit, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k, head, counts, segs,
-                       p.n_slices, cand, p.cap, idx, idx_b);
+                       hist, head, counts, p.n_slices, cand, p.cap, above);
+    hipLaunchKernelGGL(above ? topk_emit<true> : topk_emit<false>, grid, dim3(kTopkThreads), 0, st, scores, scores_b, ra, N, (uint32_t)k,
+                       head, counts, segs, p.n_slices, cand, p.cap, idx, idx_b);
     return hipGetLastError();
 }
 
@@ -597,16 +678,16 @@ static hipError_t launch_topk_rows(const float* scores, int32_t* idx, const floa
 }
 
 hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                        int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st)
+                        int64_t N, int64_t k, void* ws, hipStream_t st)
 {
     if (k == 0 || n_rows == 0) return hipSuccess;
     if (topk_in_rows(N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
     const int64_t rows = scores_b ? 2 * n_rows : n_rows;
     uint32_t* hist = topk_clear(rows, N, ws, st);
-    const TopkPlan p = topk_plan(rows, N, k, ws_bytes);
+    const TopkPlan p = topk_plan(rows, N);
     dim3 grid(p.n_slices, (unsigned)rows);
     hipLaunchKernelGGL(topk_hist0, grid, dim3(kTopkThreads), 0, st, scores, scores_b, (int)n_rows, N, hist);
-    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, ws_bytes, st);
+    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
 }
 
 uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st)
@@ -615,17 +696,17 @@ uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st
 }
 
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
-                               int64_t N, int64_t k, void* ws, size_t ws_bytes, hipStream_t st)
+                               int64_t N, int64_t k, void* ws, hipStream_t st)
 {
     if (k == 0 || n_rows == 0) return hipSuccess;
     if (topk_in_rows_counted(2 * n_rows, N)) return launch_topk_rows(scores, idx, scores_b, idx_b, n_rows, N, k, st);
-    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, ws_bytes, st);
+    return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
 }
 
 hipError_t launch_topk(const float* scores, int64_t n_rows, int64_t N, int64_t k, int32_t* idx, void* ws,
-                       size_t ws_bytes, hipStream_t st)
+                       hipStream_t st)
 {
-    return launch_topk2(scores, idx, nullptr, nullptr, n_rows, N, k, ws, ws_bytes, st);
+    return launch_topk2(scores, idx, nullptr, nullptr, n_rows, N, k, ws, st);
 }
 
 hipError_t launch_gather_rows(const Geom& g, const half_t* x, int64_t N, const int32_t* idx, int64_t k,

@@ -183,3 +183,10 @@ def test_anchor_select_of_an_empty_batch(lib):
             assert lib.antkv_anchor_select_workspace(ctypes.byref(g), N, Nq, 1) >= 0
             assert lib.antkv_anchor_select(ctypes.byref(g), fake, fake, N, Nq, 0.1, 1, None, None, None, None, fake, fake, None, 0,
                                            None) == OK
+
+
+def test_selection_workspace_does_not_depend_on_k(lib):
+    """A row's list holds a fixed share of the row, whatever k is: a larger k takes no more room, and no longer list."""
+    for rows, N in ((1, 1), (3, 33000), (16, 840000), (2, 17000000)):
+        need = {lib.antkv_topk_workspace(rows, N, k) for k in (1, N // 100, N // 4, N - 1, N) if k > 0}
+        assert len(need) == 1 and need.pop() <= rows * (8 * (N // 8 + 4096) + 8 * (N // 8192 + 1) + 4 * (4096 + 8)) + 4 * 256

@@ -124,10 +124,28 @@ def test_topk_listed_crowded_and_walked(oracle, N, k):
     assert np.array_equal(got, oracle.topk(rows, k))
 
 
+@pytest.mark.parametrize("rows,N", [(2, 33000), (7, 40963), (16, 73728)])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_topk_either_side_of_the_list_rule(oracle, rows, N, more):
+    """k at 3000 + rows N / 1280, up to which a row's list holds every key from the threshold's bin up, beyond that the bin's alone:
+    heavy tails, a crowded bin, a bin that fits the list only by itself, ties in 22 bits, at aligned and other row lengths."""
+    k = 3000 + rows * N // 1280 + more
+    rng = np.random.default_rng(N + more)
+    s = np.exp(2 * rng.standard_normal((rows, N))).astype(np.float32)
+    s[0, rng.permutation(N)[:N // 9]] += 1e6                   # k and the bin together are more than the list
+    s[1] = 5 + 0.2 * rng.standard_normal(N)
+    if rows > 2:
+        s[2] = np.round(s[2], 1)
+        s[3] = 0
+        s[4, :N // 8] = 3.0
+        s[5] = -s[5]
+    assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), oracle.topk(s, k))
+
+
 @pytest.mark.parametrize("N", [33000, 65543])
 @pytest.mark.parametrize("k", [20, 4125, 20000, 32999])
 def test_topk_workspace_of_a_smaller_k(oracle, N, k):
-    """A workspace sized for k = 1 serves any k: the list then holds fewer keys than k, and the row is walked."""
+    """A workspace sized for k = 1 serves any k."""
     s = np.exp(np.random.default_rng(N + k).standard_normal((3, N))).astype(np.float32)
     s[1] = np.round(s[1], 2)
     s[2] = 0.25
