@@ -887,16 +887,33 @@ D12Plan d12_plan(const Geom& g, int64_t N, int64_t k_v, bool by_code)
     return pl;
 }
 
-// The values are added up by code (decode12_by_code.hip) where a workgroup of its second kernel has enough tokens: clearing the
-// 2 x 4096 sums and multiplying them by their centroids costs it 15 (d16) or 20 us whatever their number, a token then takes a
-// fraction of the gather's time.  One step, gather and by code, us: d32, 8 KV heads (16 ranges) 200000 tokens 61 and 65, 420000
-// 102 and 81, 840000 169 and 102; 64 heads (2 ranges) 16000 57 and 60, 33333 81 and 67; d16, 8 heads (8 ranges) 50000 61 and 63,
-// 70000 67 and 66, 840000 308 and 153; 64 heads (1 range) 4096 54 and 56, 9001 66 and 59, 70000 229 and 106.
+// The values are added up by code (decode12_by_code.hip) where that takes less time.  What it saves is the gather, `a` us per 1000
+// tokens of a range of the K side (ranges that wait for a CU count again); what it costs is a pass over the weights, `b` us
+// per 1000 tokens of a range of d12_values_kernel, and what does not depend on the tokens: one more kernel, its partials (`slot`
+// each), and in every round of workgroups clearing the 2 x 4096 sums and multiplying them by their centroids (`round`).
+// Fitted to both routes' times, of which some (one step, us, by code and gathering):
+//   d32, 8 heads of 4 query heads   160000 tokens 61 and 53, 240000 66 and 64, 420000 80 and 102, 840000 101 and 169
+//        80 heads (a range each)    14336 66 and 59, 20000 71 and 68, 33333 84 and 89, 60000 103 and 134
+//        128 heads                  8192 67 and 60, 14336 74 and 75, 33333 96 and 124;  one query head each 8500 64 and 60, 12000 66 and 68
+//        192 heads (two rounds)     8192 101 and 81, 14336 112 and 111, 20000 123 and 135
+//   d16, 8 heads                    52000 62 and 61, 96000 68 and 74, 240000 80 and 107;  one query head each 80000 56 and 52, 96000 56 and 59
+//        64 heads                   4096 63 and 62, 8192 67 and 70, 33333 92 and 127
+//        96 heads (two rounds)      8192 91 and 85, 14336 103 and 107, 33333 139 and 185
+//        192 heads (three)          8192 137 and 127, 14336 157 and 177
 // (The fixed-point sums have room for 2^27 tokens.)
+struct D12Cost {
+    double a, b, fixed, slot, round;
+};
 bool d12_by_code(const Geom& g, int64_t N)
 {
-    const int64_t range = d12_plan(g, N, 0, true).range;
-    return range >= (g.d == 32 ? 14336 : 8192) && range <= (1 << 27);
+    const D12Plan pl = d12_plan(g, N, 0, true);
+    const bool one_pair = g.G <= 2;                                    // one pair of heads per KV head
+    const D12Cost c = g.d == 32 ? (one_pair ? D12Cost{3.15, 0.17, 16.5, 0.03, 17.5} : D12Cost{3.15, 0.17, 20.0, 0.03, 19.0})
+                                : (one_pair ? D12Cost{7.8, 0.68, 8.0, 0.17, 23.0} : D12Cost{8.4, 0.68, 5.0, 0.17, 25.0});
+    const int64_t pairs = (int64_t)g.B * g.Hkv, rounds = (pairs * pl.S2 * (g.M / 2) + 255) / 256;
+    if (rounds == 0 || pl.range > (1 << 27)) return false;
+    const double saved = c.a * 1e-3 * (double)((pairs * pl.S + 255) / 256 * pl.chunk);
+    return saved > c.b * 1e-3 * (double)(rounds * pl.range) + c.fixed + c.slot * pl.slots + c.round * (double)(rounds - 1);
 }
 
 template <int DS>

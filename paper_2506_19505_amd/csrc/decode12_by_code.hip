@@ -715,10 +715,7 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
     }
     float out_v[8];
     fold_heads<LR>(av, out_v);
-    if constexpr (SCORED) {
-#pragma unroll
-        for (int h = 0; h < kNH; ++h) l_v[h] = wave_sum(l_v[h]);
-    }
+    const float sum_v = SCORED ? fold_sums(l_v) : 0.f;
 
     // ---- the 2 x 4096 sums times their centroids: LPC lanes per centroid, a wave takes 256 codes of either sub-space, the next
     // four centroids are on their way while four are multiplied
@@ -784,12 +781,9 @@ __global__ __launch_bounds__(kT12) void d12_values_kernel(const D12LongParams p)
 #pragma unroll
         for (int c = 0; c < 8; ++c) s_ov[row * 2 * DS + 8 * (lane % LR) + c] = out_v[c];
     }
-    if (SCORED && lane == 0) {
-#pragma unroll
-        for (int h = 0; h < kNH; ++h) {
-            s_mv[wave * kNH + h] = m_v[h];
-            s_lv[wave * kNH + h] = l_v[h];
-        }
+    if constexpr (SCORED) {
+        if ((lane & 15) == 0) s_lv[row] = sum_v;
+        if (lane == 0) *(float4_t*)(s_mv + wave * kNH) = float4_t{m_v[0], m_v[1], m_v[2], m_v[3]};
     }
     __syncthreads();
     if (tid < kNH * 2 * DS) {

@@ -190,3 +190,16 @@ def test_selection_workspace_does_not_depend_on_k(lib):
     for rows, N in ((1, 1), (3, 33000), (16, 840000), (2, 17000000)):
         need = {lib.antkv_topk_workspace(rows, N, k) for k in (1, N // 100, N // 4, N - 1, N) if k > 0}
         assert len(need) == 1 and need.pop() <= rows * (8 * (N // 8 + 4096) + 8 * (N // 8192 + 1) + 4 * (4096 + 8)) + 4 * 256
+
+
+@pytest.mark.parametrize("d,heads,G,by_code,gather", [
+    (32, 8, 4, 420000, 160000), (32, 80, 4, 60000, 14400), (32, 128, 4, 33333, 8192), (32, 192, 4, 20000, 8192),
+    (16, 8, 1, 240000, 52000), (16, 64, 1, 14336, 5000), (16, 96, 1, 20000, 8192)])
+def test_which_contexts_are_added_up_by_code(lib, d, heads, G, by_code, gather):
+    """4096 centroids: the workspace holds a weight of every token (4 bytes per token, KV head and pair of query heads) where the
+    values are added up by code.  Context lengths that were measured faster by code and gathering, for KV heads that leave
+    CUs of the second kernel without work, fill them, and need a second round of them."""
+    g = _g(B=heads // 8, Hkv=8, Hq=8 * G, d=d, C=4096)
+    need = lambda N: lib.antkv_decode_attn_workspace(ctypes.byref(g), N, 0, 0, 0) - lib.antkv_decode_attn_workspace(ctypes.byref(g), 64, 0, 0, 0)
+    assert need(by_code) > 4 * heads * by_code
+    assert need(gather) < 4 * heads * gather // 2

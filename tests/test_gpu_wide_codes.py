@@ -173,10 +173,11 @@ def _least(ws):
     return ws
 
 
-# (ranges of the second kernel: sequences x KV heads x M / 2 workgroups share the chip; it is used from 14336 (d32) or 8192 tokens per range)
+# (ranges of the second kernel: sequences x KV heads x M / 2 workgroups share the chip, the last two shapes in two rounds)
 @pytest.mark.parametrize("d,B,Hq,Hkv,N,k_k,k_v", [(32, 16, 8, 8, 14335, 30, 30), (32, 16, 8, 8, 14337, 150, 140), (32, 8, 16, 8, 28673, 0, 290),
                                                   (32, 32, 16, 4, 14400, 145, 0), (16, 8, 8, 8, 8191, 20, 20), (16, 8, 32, 8, 8257, 83, 90),
-                                                  (16, 8, 16, 8, 8192, 0, 0), (16, 16, 8, 2, 16449, 700, 1100)])
+                                                  (16, 8, 16, 8, 8192, 0, 0), (16, 16, 8, 2, 16449, 700, 1100),
+                                                  (32, 24, 8, 8, 16001, 161, 30), (16, 12, 16, 8, 13001, 131, 140)])
 def test_decode12_values_by_code(oracle, books, d, B, Hq, Hkv, N, k_k, k_v):
     """Around the token counts where the values are added up by code: against the oracle, and against the gathering stream that a
     smaller workspace leaves (2e-3 is the bound of either against the oracle, so 4e-3 between them)."""
