@@ -189,6 +189,7 @@ __global__ __launch_bounds__(kEncThreads, DSUB == 16 ? 4 : 6) void encode_kernel
         const uint32_t next = unit + (uint32_t)chunks * kSlots;
         half8_t nx[NG];
         fetch(next < units ? next : unit, nx);
+        const uint64_t active = __builtin_amdgcn_read_exec();
         float16_t acc[2], nb;
         half8_t a[2];
 #pragma unroll
@@ -209,8 +210,7 @@ __global__ __launch_bounds__(kEncThreads, DSUB == 16 ? 4 : 6) void encode_kernel
         };
         // Running maximum over tiles of 16 candidates per lane: a chain of max3 over the best so far and four quads (rows
         // 8 q + 4 h .. + 3).  When a tile raises it (strictly, so the lowest tile wins ties) the tile's id and the chain's value
-        // after each of the first three quads are kept, by moves under the lanes' mask (every lane is active before and
-        // after).  The next step's product is in flight meanwhile; a tile's operands serve the wave's NG groups.
+        // after each of the first three quads are kept, by moves under the lanes' mask, which is put back.  The next step's product is in flight meanwhile; a tile's operands serve the wave's NG groups.
         pair_t keep[NG];                                               // chain after quads 0, 1 of the best tile,
         float keep2[NG], best[NG];                                     // after quad 2, and its end
         int tile[NG];
@@ -236,9 +236,9 @@ __global__ __launch_bounds__(kEncThreads, DSUB == 16 ? 4 : 6) void encode_kernel
                     keep2[i] = hi;
                     tile[i] = 0;
                 } else {
-                    asm volatile("v_cmpx_gt_f32 vcc, %6, %7\n\tv_mov_b64 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5\n\ts_mov_b64 exec, -1"
+                    asm volatile("v_cmpx_gt_f32 vcc, %6, %7\n\tv_mov_b64 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5\n\ts_mov_b64 exec, %8"
                                  : "+v"(keep[i]), "+v"(keep2[i]), "+v"(tile[i])
-                                 : "v"(lo), "v"(hi), "n"(t), "v"(top), "v"(best[i])
+                                 : "v"(lo), "v"(hi), "n"(t), "v"(top), "v"(best[i]), "s"(active)
                                  : "vcc");
                 }
                 best[i] = top;
