@@ -142,6 +142,23 @@ def test_topk_either_side_of_the_list_rule(oracle, rows, N, more):
     assert np.array_equal(antkv.topk(dev(s), k).cpu().numpy(), oracle.topk(s, k))
 
 
+@pytest.mark.parametrize("k", [9, 1000, 300000])
+def test_topk_more_than_2048_slices(k):
+    """Rows of more than 2048 x 8192 scores, whose slices are counted in windows of 2048: selected scores and ties at the threshold on
+    both sides of slice 2048 and in the short last slice, in a row whose list holds them and in one that is walked."""
+    edge, N = 2048 * 8192, 2049 * 8192 + 5
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    s = torch.rand((3, N), dtype=torch.float32, device="cuda", generator=gen)
+    s[0] = torch.exp(6 * s[0])
+    s[1] = 0.5
+    s[2] = torch.where(s[2] < 0.4, s[2], torch.full_like(s[2], 0.5))
+    for at in (0, 5, edge - 2, edge - 1, edge, edge + 1, edge + 8191, edge + 8192, N - 1):
+        s[:, at] = 1000.0 + (at % 3)
+    got = antkv.topk(s, k)
+    want = torch.sort(s, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values
+    assert torch.equal(got.long(), want)
+
+
 @pytest.mark.parametrize("N", [33000, 65543])
 @pytest.mark.parametrize("k", [20, 4125, 20000, 32999])
 def test_topk_workspace_of_a_smaller_k(oracle, N, k):

@@ -168,9 +168,19 @@ def test_decode12_tiny_contexts_and_capacity(oracle, books):
 
 
 def _least(ws):
-    """The same workspace without room for the weights that adding the values up by code needs."""
+    """The same workspace without room for the weights that adding the values up by code needs.  (One that has no such room is
+    refused when it is cut short: a call with this workspace shows that the whole one is used by code.)"""
     ws.buf = ws.buf[:ws.buf.numel() - 256]
     return ws
+
+
+def _switch(geom):
+    """The smallest context whose values are added up by code (one or two heads per KV head: its workspace holds four bytes per
+    token and KV head that the gathering kernel does not need)."""
+    size = lambda n: antkv.DecodeWorkspace(geom, n, 0, 0, 0, "meta").nbytes
+    by_code = lambda n: size(n) - size(64) > 4 * geom.B * geom.Hkv * n
+    n = next(n for n in range(1024, 1 << 20, 64) if by_code(n))
+    return next(m for m in range(n - 63, n + 1) if by_code(m))
 
 
 # (ranges of the second kernel: sequences x KV heads x M / 2 workgroups share the chip, the last two shapes in two rounds)
@@ -179,8 +189,8 @@ def _least(ws):
                                                   (16, 8, 16, 8, 8192, 0, 0), (16, 16, 8, 2, 16449, 700, 1100),
                                                   (32, 24, 8, 8, 16001, 161, 30), (16, 12, 16, 8, 13001, 131, 140)])
 def test_decode12_values_by_code(oracle, books, d, B, Hq, Hkv, N, k_k, k_v):
-    """Around the token counts where the values are added up by code: against the oracle, and against the gathering stream that a
-    smaller workspace leaves (2e-3 is the bound of either against the oracle, so 4e-3 between them)."""
+    """Contexts whose values are added up by code, among them ranges of a tile more, less and not quite: against the oracle, and
+    against the gathering stream that a smaller workspace leaves (2e-3 is the bound of either against the oracle, so 4e-3)."""
     if d != books.d:
         pytest.skip("the other format's case")
     from workloads import make_decode_query, normal_fp16, random_anchor_sets
@@ -203,9 +213,8 @@ def test_decode12_values_by_code(oracle, books, d, B, Hq, Hkv, N, k_k, k_v):
     want = oracle.decode_attn(q, ck, cv, cbk, cbv, ik, rk, iv, rv, scale)
     err = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
     assert err.max() <= 2e-3, err.max()
-    if N not in (14335, 8191):                                 # one token short of the rule the workspace has no such room
-        gather = antkv.decode_attn(*args, workspace=_least(antkv.DecodeWorkspace(geom, N, k_k, k_v, 0, "cuda"))).cpu().numpy().astype(np.float64)
-        assert (np.linalg.norm(got - gather, axis=-1) / np.linalg.norm(want, axis=-1)).max() <= 4e-3
+    gather = antkv.decode_attn(*args, workspace=_least(antkv.DecodeWorkspace(geom, N, k_k, k_v, 0, "cuda"))).cpu().numpy().astype(np.float64)
+    assert (np.linalg.norm(got - gather, axis=-1) / np.linalg.norm(want, axis=-1)).max() <= 4e-3
     print(f"d{d} B={B} {Hq}/{Hkv} N={N} anchors {k_k}/{k_v}: rel-L2 max {err.max():.2e}")
 
 
@@ -350,6 +359,77 @@ def test_decode12_small_weights_beside_a_large_one(books, large, gap):
         err = ((got - want) / want).abs().max().item()
         print(f"d{d} {large} 2^{gap}, by code {by_code}: {err:.2e}, bound {bound:.2e}")
         assert err <= bound
+
+
+@pytest.mark.parametrize("B,Hkv", [(8, 8), (3, 2), (12, 8)])
+def test_decode12_either_side_of_the_switch(books, B, Hkv):
+    """The first context that is added up by code and the last that is not, against float64; the workspace of the latter is refused when
+    it is cut short, that of the former is not."""
+    geom = antkv.Geometry(B, Hkv, Hkv, books.d, n_centroids=C)
+    n, k = _switch(geom), 40
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes_k, codes_v = (torch.randint(0, C, (B, Hkv, n, books.M), device="cuda", generator=gen) for _ in range(2))
+    cb_k, cb_v = rnd(Hkv, books.M, C, books.d), rnd(Hkv, books.M, C, books.d)
+    q, rows_k, rows_v = rnd(B, Hkv, 128), rnd(B, Hkv, k, 128), rnd(B, Hkv, k, 128)
+    for N in (n - 1, n):
+        idx_k, idx_v = (torch.rand((B, Hkv, N), device="cuda", generator=gen).argsort(dim=-1)[..., :k].sort(dim=-1).values.int() for _ in range(2))
+        args = (geom, q, 128 ** -0.5, _pack12_dev(codes_k[:, :, :N]), _pack12_dev(codes_v[:, :, :N]), cb_k, cb_v, idx_k, rows_k, idx_v, rows_v)
+        want, _ = _decode_exact(q, 128 ** -0.5, codes_k[:, :, :N], codes_v[:, :, :N], cb_k, cb_v, idx_k, rows_k, idx_v, rows_v)
+        got = antkv.decode_attn(*args).double()
+        assert ((got - want).norm(dim=-1) / want.norm(dim=-1)).max().item() <= 2e-3
+        least = _least(antkv.DecodeWorkspace(geom, N, k, k, 0, "cuda"))
+        if N == n:
+            antkv.decode_attn(*args, workspace=least)
+        else:
+            with pytest.raises(antkv.AntkvError):
+                antkv.decode_attn(*args, workspace=least)
+
+
+@pytest.mark.parametrize("gain", [1, 4, 16])
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_decode12_values_by_code_query_gain(books, gain, G):
+    """Sharp softmaxes by code: references that rise late in a wave's walk, ranges far below the sequence's reference, tokens and FP16
+    rows with most of the weight.  Bound: as in test_decode12_query_gain, 2e-3 inside the table's range and growing with it beyond.
+    Several ranges of the second kernel per KV head, the last one ragged."""
+    from gpu_util import attn_tol_for_range, table_range
+    B, Hkv, N, k, M = 4, 2, 260077 if books.d == 32 else 100077, 200, books.M
+    gen = torch.Generator(device="cuda").manual_seed(10 * gain + G)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes_k, codes_v = (torch.randint(0, C, (B, Hkv, N, M), device="cuda", generator=gen) for _ in range(2))
+    cb_k, cb_v = dev(books[0][:Hkv]), dev(books[1][:Hkv])
+    order = torch.rand((B, Hkv, N), device="cuda", generator=gen).argsort(dim=-1)
+    idx_k, idx_v = order[..., :k].sort(dim=-1).values.int().contiguous(), order[..., k - 50:2 * k - 50].sort(dim=-1).values.int().contiguous()
+    q, rows_k, rows_v, scale = rnd(B, G * Hkv, 128), rnd(B, Hkv, k, 128), rnd(B, Hkv, k, 128), gain * 128 ** -0.5
+    geom = antkv.Geometry(B, G * Hkv, Hkv, books.d, n_centroids=C)
+    args = (geom, q, scale, _pack12_dev(codes_k), _pack12_dev(codes_v), cb_k, cb_v, idx_k, rows_k, idx_v, rows_v)
+    got = antkv.decode_attn(*args)
+    gather = antkv.decode_attn(*args, workspace=_least(antkv.DecodeWorkspace(geom, N, k, k, 0, "cuda")))
+    want, _ = _decode_exact(q, scale, codes_k, codes_v, cb_k, cb_v, idx_k, rows_k, idx_v, rows_v)
+    tol = attn_tol_for_range(table_range(q.cpu().numpy(), books[0][:Hkv], scale, G), M, 32767)
+    err, err_g = (((x.double() - want).norm(dim=-1) / want.norm(dim=-1)).cpu().numpy() for x in (got, gather))
+    print(f"d{books.d} G={G} gain {gain}: {err.max():.2e}, gathering {err_g.max():.2e}, bound {tol.min():.1e} .. {tol.max():.1e}")
+    assert (err <= tol).all() and (err_g <= tol).all()
+
+
+def test_decode12_values_by_code_every_token_anchored(books):
+    """Every token has an FP16 K row, and some or all an FP16 V row: all the stream's weights are zero."""
+    B, Hkv, N = _by_code_shape(books)
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes_k, codes_v = (torch.randint(0, C, (B, Hkv, N, books.M), device="cuda", generator=gen) for _ in range(2))
+    cb_k, cb_v = rnd(Hkv, books.M, C, books.d), rnd(Hkv, books.M, C, books.d)
+    q, rows_k = rnd(B, Hkv, 128), rnd(B, Hkv, N, 128)
+    every = torch.arange(N, dtype=torch.int32, device="cuda")
+    idx_k = every.expand(B, Hkv, N).contiguous()
+    geom = antkv.Geometry(B, Hkv, Hkv, books.d, n_centroids=C)
+    for idx in (every[::7], every):
+        idx_v = idx.expand(B, Hkv, -1).contiguous()
+        rows_v = rnd(B, Hkv, idx_v.shape[-1], 128)
+        got = antkv.decode_attn(geom, q, 128 ** -0.5, _pack12_dev(codes_k), _pack12_dev(codes_v), cb_k, cb_v, idx_k, rows_k, idx_v, rows_v,
+                                workspace=antkv.DecodeWorkspace(geom, N, N, idx_v.shape[-1], 0, "cuda")).double()
+        want, _ = _decode_exact(q, 128 ** -0.5, codes_k, codes_v, cb_k, cb_v, idx_k, rows_k, idx_v, rows_v)
+        assert ((got - want).norm(dim=-1) / want.norm(dim=-1)).max().item() <= 2e-3
 
 
 def test_encode12_then_decode12(oracle, books):
