@@ -400,7 +400,6 @@ def main() -> int:
                 f"{tagw}_decode_plus_reselection_ms": ms_w2,
                 f"{tagw}_prerope_decode_ms": ms_w3,
                 f"{tagw}_decode_tokens_per_s": r.B * r.N / (ms_w * 1e-3),
-                f"{tagw}_decode_L2_gather_GBs": r.B * r.Hkv * r.N * 256 / (ms_w * 1e-3) / 1e9,
                 f"{tagw}_encode_ms": ms_e12,
                 f"{tagw}_encode_TFLOPs": 2.0 * p.B * p.Hkv * p.N * p.D * 4096 / (ms_e12 * 1e-3) / 1e12,
                 f"{tagw}_kmeans_step_ms": ms_km12,

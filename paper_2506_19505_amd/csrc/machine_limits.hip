@@ -8,8 +8,13 @@
 //            on different banks, and float atomics
 //   issue    VALU and MFMA issue rates per SIMD, alone, interleaved inside a wave and split over the waves of a SIMD
 //            (do the two pipes overlap?), and both together with LDS reads in flight
+//   instr    clocks per wave instruction and SIMD of single VALU and MFMA instructions on registers, four waves per SIMD
+//   atomic   integer and float LDS atomics on addresses picked by the data, per CU
+//   gather   16-byte loads out of a 1 MB table that the L2s hold, in pieces of 16 to 1024 consecutive bytes, per CU
 //
-// Every kernel runs 256 workgroups of 1024 threads (one per CU, 4 waves per SIMD), like the decode kernel.
+// The lds and issue lines turn elapsed time into clocks at the rate that one busy wave sees; the instr, atomic and gather lines
+// count the shader clocks of the kernel itself (clock64 around its loop), whatever the chip's clock under that load, which
+// they print.  Every kernel runs 256 workgroups of 1024 threads (one per CU, 4 waves per SIMD), like the decode kernel.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -245,6 +250,117 @@ __global__ __launch_bounds__(1024) void issue_probe(float* out, int iters, int s
     out[blockIdx.x * 1024 + threadIdx.x] = s;
 }
 
+// ---------------------------------------------------------------------------------------- instr, atomic, gather
+// Eight independent registers, 32 instructions per iteration.
+enum Op { FMA, FMA_SCALAR, FMA_LITERAL, ADD, MUL, MOV, AND, ADD_U32, MAX, MAX3, CVT_F16, CVT_U32, PERM, DOT2, BFE, CMP, LSHL, PK_FMA_F16, EXP, MFMA_16, MFMA_32 };
+
+struct Clocks {
+    long long shader, wall;
+};
+
+template <int OP>
+__global__ __launch_bounds__(1024) void instr_probe(float* out, Clocks* clocks, int iters)
+{
+    const int lane = threadIdx.x & 63;
+    float v[8], a = 0.999f + lane * 1e-6f, b = 0.01f;
+    const int scalar = __float_as_int(0.999f) + (int)blockIdx.x;
+    for (int i = 0; i < 8; ++i) v[i] = lane + i;
+    half8 ha, hb;
+    for (int i = 0; i < 8; ++i) { ha[i] = (_Float16)(lane * 0.001f + i); hb[i] = (_Float16)(lane * 0.002f - i); }
+    float4v c4[4] = {};
+    float16v c16[4] = {};
+    __syncthreads();
+    const long long c0 = clock64(), w0 = wall_clock64();
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int u = 0; u < 32; ++u) {
+            float& x = v[u & 7];
+            if constexpr (OP == FMA) asm volatile("v_fma_f32 %0, %0, %1, %2" : "+v"(x) : "v"(a), "v"(b));
+            else if constexpr (OP == FMA_SCALAR) asm volatile("v_fma_f32 %0, %0, %1, 0.5" : "+v"(x) : "s"(scalar));
+            else if constexpr (OP == FMA_LITERAL) asm volatile("v_fmaak_f32 %0, %0, %1, 0x3f000000" : "+v"(x) : "v"(a));
+            else if constexpr (OP == ADD) asm volatile("v_add_f32 %0, %0, %1" : "+v"(x) : "v"(a));
+            else if constexpr (OP == MUL) asm volatile("v_mul_f32 %0, %0, %1" : "+v"(x) : "v"(a));
+            else if constexpr (OP == MOV) asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "v"(a));
+            else if constexpr (OP == AND) asm volatile("v_and_b32 %0, %0, %1" : "+v"(x) : "v"(a));
+            else if constexpr (OP == ADD_U32) asm volatile("v_add_u32 %0, %0, %1" : "+v"(x) : "v"(a));
+            else if constexpr (OP == MAX) asm volatile("v_max_f32 %0, %0, %1" : "+v"(x) : "v"(a));
+            else if constexpr (OP == MAX3) asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(x) : "v"(a), "v"(b));
+            else if constexpr (OP == CVT_F16) asm volatile("v_cvt_f16_f32 %0, %0" : "+v"(x));
+            else if constexpr (OP == CVT_U32) asm volatile("v_cvt_u32_f32 %0, %0" : "+v"(x));
+            else if constexpr (OP == PERM) asm volatile("v_perm_b32 %0, %0, %1, %2" : "+v"(x) : "v"(a), "v"(b));
+            else if constexpr (OP == DOT2) asm volatile("v_dot2_f32_f16 %0, %1, %2, %0" : "+v"(x) : "v"(a), "v"(b));
+            else if constexpr (OP == BFE) asm volatile("v_bfe_u32 %0, %0, %1, %2" : "+v"(x) : "v"(a), "v"(b));
+            else if constexpr (OP == CMP) asm volatile("v_cmp_gt_f32 vcc, %0, %1" :: "v"(x), "v"(a) : "vcc");
+            else if constexpr (OP == LSHL) asm volatile("v_lshlrev_b32 %0, 1, %0" : "+v"(x));
+            else if constexpr (OP == PK_FMA_F16) asm volatile("v_pk_fma_f16 %0, %0, %1, %2" : "+v"(x) : "v"(a), "v"(b));
+            else if constexpr (OP == EXP) asm volatile("v_exp_f32 %0, %0\n s_nop 0" : "+v"(x));
+            else if constexpr (OP == MFMA_16) c4[u & 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ha, hb, c4[u & 3], 0, 0, 0);
+            else c16[u & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ha, hb, c16[u & 3], 0, 0, 0);
+        }
+    }
+    __syncthreads();                                                       // (the oldest waves are served first and done early)
+    const long long c1 = clock64(), w1 = wall_clock64();
+    float s = 0.f;
+    for (int i = 0; i < 8; ++i) s += v[i];
+    for (int i = 0; i < 4; ++i) s += c4[i][0] + c16[i][5];
+    out[blockIdx.x * 1024 + threadIdx.x] = s;
+    if (threadIdx.x == 0) clocks[blockIdx.x] = Clocks{c1 - c0, w1 - w0};
+}
+
+enum Atomic { ADD_LDS_U32, ADD_LDS_U64, ADD_LDS_F32 };
+
+template <int OP>
+__global__ __launch_bounds__(1024) void atomic_probe(uint32_t* out, Clocks* clocks, int iters)
+{
+    extern __shared__ uint4v smem[];
+    uint32_t* s32 = (uint32_t*)smem;
+    for (int i = threadIdx.x; i < 65536 / 4; i += blockDim.x) s32[i] = 0u;
+    uint32_t at[8];
+    for (int u = 0; u < 8; ++u) at[u] = mix(threadIdx.x * 8u + u + 1u) & 4095u;
+    __syncthreads();
+    const long long c0 = clock64(), w0 = wall_clock64();
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t i = (at[u] + (uint32_t)it) & 4095u;
+            if constexpr (OP == ADD_LDS_U64) atomicAdd((unsigned long long*)smem + i, 1ull);
+            else if constexpr (OP == ADD_LDS_U32) atomicAdd(s32 + i, 1u);
+            else unsafeAtomicAdd((float*)smem + i, 1.f);
+        }
+    }
+    __syncthreads();
+    const long long c1 = clock64(), w1 = wall_clock64();
+    if (threadIdx.x == 0) clocks[blockIdx.x] = Clocks{c1 - c0, w1 - w0};
+    out[blockIdx.x * 1024 + threadIdx.x] = s32[threadIdx.x];
+}
+
+// PIECE lanes read 16 consecutive bytes each, pieces anywhere in the table
+template <int PIECE>
+__global__ __launch_bounds__(1024) void gather_probe(const uint4v* __restrict__ table, uint32_t* out, Clocks* clocks, int iters)
+{
+    constexpr uint32_t kPieces = 65536u / PIECE;                           // 1 MB
+    const uint32_t lane = threadIdx.x & 63u, in = lane % PIECE;
+    uint32_t at[8], acc = 0;
+    for (int u = 0; u < 8; ++u) at[u] = mix((threadIdx.x / PIECE) * 8u + u + blockIdx.x * 65536u);
+    for (uint32_t i = threadIdx.x; i < 65536u; i += blockDim.x) acc ^= table[i][0];     // the L2 has it
+    __syncthreads();
+    const long long c0 = clock64(), w0 = wall_clock64();
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+        uint4v r[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r[u] = table[(((at[u] + 2654435761u * (uint32_t)it) >> 8) % kPieces) * PIECE + in];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc ^= r[u][0] ^ r[u][1] ^ r[u][2] ^ r[u][3];
+    }
+    __syncthreads();
+    const long long c1 = clock64(), w1 = wall_clock64();
+    if (threadIdx.x == 0) clocks[blockIdx.x] = Clocks{c1 - c0, w1 - w0};
+    out[blockIdx.x * 1024 + threadIdx.x] = acc;
+}
+
 template <typename F>
 static float time_ms(F f, int reps)
 {
@@ -285,6 +401,51 @@ static void run_issue(const char* name, float* out, int split)
     const float ms = time_ms([&] { hipLaunchKernelGGL((issue_probe<KIND, NM, NV, LDS>), dim3(kCUs), dim3(1024), 65536, 0, out, iters, split); }, 3);
     const double clk_per_iter = ms * 1e-3 * g_clk_hz / iters;           // SIMD clocks per loop iteration (4 waves per SIMD)
     printf("issue %-58s %8.3f ms  %7.1f clk per iteration per SIMD\n", name, ms, clk_per_iter);
+    fflush(stdout);
+}
+
+// mean shader clocks of the workgroups' loops, and the clock rate they ran at
+template <typename F>
+static double loop_clocks(F launch, Clocks* d, double* mhz)
+{
+    static Clocks h[kCUs];
+    launch();
+    launch();
+    CK(hipMemcpy(h, d, sizeof h, hipMemcpyDeviceToHost));
+    double shader = 0, wall = 0;
+    for (int i = 0; i < kCUs; ++i) { shader += (double)h[i].shader; wall += (double)h[i].wall; }
+    *mhz = shader / wall * 100.;
+    return shader / kCUs;
+}
+
+template <int OP>
+static void run_instr(const char* name, float* out, Clocks* d)
+{
+    const int iters = 4000;
+    double mhz;
+    const double clk = loop_clocks([&] { hipLaunchKernelGGL((instr_probe<OP>), dim3(kCUs), dim3(1024), 0, 0, out, d, iters); }, d, &mhz);
+    printf("instr %-46s %6.2f clk per wave instruction per SIMD (at %.0f MHz)\n", name, clk / (4. * 32 * iters), mhz);
+    fflush(stdout);
+}
+
+template <int OP>
+static void run_atomic(const char* name, uint32_t* out, Clocks* d, int iters)
+{
+    double mhz;
+    const double clk = loop_clocks([&] { hipLaunchKernelGGL((atomic_probe<OP>), dim3(kCUs), dim3(1024), 65536, 0, out, d, iters); }, d, &mhz);
+    printf("atomic %-45s %6.2f clk per wave instruction per CU (at %.0f MHz)\n", name, clk / (16. * 8 * iters), mhz);
+    fflush(stdout);
+}
+
+template <int PIECE>
+static void run_gather(const uint4v* table, uint32_t* out, Clocks* d)
+{
+    const int iters = 400;
+    double mhz;
+    const double clk = loop_clocks([&] { hipLaunchKernelGGL((gather_probe<PIECE>), dim3(kCUs), dim3(1024), 0, 0, table, out, d, iters); }, d, &mhz);
+    const double per = clk / (16. * 8 * iters);
+    printf("gather pieces of %4d bytes %38.2f clk per wave instruction per CU (at %.0f MHz)  %6.1f TB/s\n", 16 * PIECE, per, mhz,
+           1024. / per * mhz * 1e6 * kCUs / 1e12);
     fflush(stdout);
 }
 
@@ -344,6 +505,41 @@ int main()
     run_issue<0, 16, 128, 0>("16 MFMA f16 | 128 VALU, roles split over the waves", fo, 1);
     run_issue<0, 0, 128, 1>("128 VALU + 32 LDS reads", fo, 0);
     run_issue<0, 16, 128, 1>("16 MFMA f16 + 128 VALU + 32 LDS reads, interleaved", fo, 0);
+
+    Clocks* d;
+    CK(hipMalloc(&d, kCUs * sizeof(Clocks)));
+    run_instr<FMA>("v_fma_f32", fo, d);
+    run_instr<FMA_SCALAR>("v_fma_f32, one operand scalar, one inline", fo, d);
+    run_instr<FMA_LITERAL>("v_fmaak_f32 (a literal in the instruction)", fo, d);
+    run_instr<ADD>("v_add_f32", fo, d);
+    run_instr<MUL>("v_mul_f32", fo, d);
+    run_instr<MOV>("v_mov_b32", fo, d);
+    run_instr<AND>("v_and_b32", fo, d);
+    run_instr<ADD_U32>("v_add_u32", fo, d);
+    run_instr<MAX>("v_max_f32", fo, d);
+    run_instr<MAX3>("v_max3_f32", fo, d);
+    run_instr<CVT_F16>("v_cvt_f16_f32", fo, d);
+    run_instr<CVT_U32>("v_cvt_u32_f32", fo, d);
+    run_instr<PERM>("v_perm_b32", fo, d);
+    run_instr<DOT2>("v_dot2_f32_f16", fo, d);
+    run_instr<BFE>("v_bfe_u32", fo, d);
+    run_instr<CMP>("v_cmp_gt_f32", fo, d);
+    run_instr<LSHL>("v_lshlrev_b32", fo, d);
+    run_instr<PK_FMA_F16>("v_pk_fma_f16", fo, d);
+    run_instr<EXP>("v_exp_f32", fo, d);
+    run_instr<MFMA_16>("v_mfma_f32_16x16x32_f16", fo, d);
+    run_instr<MFMA_32>("v_mfma_f32_32x32x16_f16", fo, d);
+    run_atomic<ADD_LDS_U32>("ds_add_u32, 4096 addresses at random", out, d, 400);
+    run_atomic<ADD_LDS_U64>("ds_add_u64, 4096 addresses at random", out, d, 400);
+    run_atomic<ADD_LDS_F32>("ds_add_f32, 4096 addresses at random", out, d, 40);
+    uint4v* table;
+    CK(hipMalloc(&table, 1 << 20));
+    CK(hipMemset(table, 1, 1 << 20));
+    run_gather<1>(table, out, d);
+    run_gather<2>(table, out, d);
+    run_gather<4>(table, out, d);
+    run_gather<8>(table, out, d);
+    run_gather<64>(table, out, d);
     printf("done\n");
     return 0;
 }
