@@ -14,9 +14,10 @@
 //            rows times their tokens' weights, W_h times the centroids at the end.
 // Where a table does not hold every head (d16) a V-anchored token outside the K list is scored in fp32, as in decode12_kernel: by
 // workgroups beside those of d12_table_kernel.  Its weight then counts in d12_values_kernel alone.
-// Bound: d12_values_kernel by the LDS atomics (64-bit, two heads each: 13 clocks per wave instruction on random codes; a
-// float atomic takes 192), d12_weights_kernel by VALU issue.  Gathering centroids costs 37 clocks per KB as pieces of 64 bytes
-// (d32) and 73 as pieces of 32 (d16).
+// Bound: VALU issue first, with no pipe full: d12_weights_kernel is VALU-busy for 73 % of its cycles, d12_values_kernel for 67 %
+// beside 45 % of LDS (d32) or 63 and 59 % (d16: twice the atomics per weight).  A 64-bit integer atomic, two heads each, takes 12.5
+// clocks per wave instruction on random codes, a float atomic 192.  Gathering centroids instead costs 36 clocks per KB as
+// pieces of 64 bytes (d32) and 71 as pieces of 32 (d16).
 #include "decode12.h"
 
 #include <type_traits>

@@ -9,7 +9,7 @@
 //   level 1  per 32 tokens x 32 centroids: v_mfma_f32_32x32x16_f16 (one per 16 channels) with centroids on the row
 //            axis and tokens on the column axis, the C operand being -||c||^2/2.  A lane owns one token and 16 of the 32
 //            centroid scores; it keeps the best score and the tile it came from (a max3 tree, one compare, one select:
-//            ten VALU instructions per 16 candidates).  A wave holds up to four (three) token groups, which share every
+//            ten VALU instructions per 16 candidates, and one or two of addressing).  A wave holds up to four (three) token groups, which share every
 //            operand it reads from LDS.
 //   level 2  the 16 scores of the winning tile and half-wave again, with packed dot products (v_dot2_f32_f16), eight in
 //            each of the token's two lanes; lanes start at different rows so that the reads spread over the banks.
@@ -17,7 +17,9 @@
 // reach the same score in the same tile, level 2 looks at all 32.  Both levels are fp32-accurate; they may order two
 // centroids differently only when their scores agree to fp32 rounding.
 //
-// Bound: VALU issue of level 1 (40 clocks per tile and group beside 32 or 64 of MFMA).  With the centroids read from the
+// Bound: VALU issue first: level 1 takes 50 clocks of it per tile and group beside 32 or 64 of MFMA.  Over the whole kernel a tile
+// and group takes 81 clocks (d16, 32768 tokens; VALU busy 73 %, MFMA 39 %): the rest is level 2 and bringing a sub-space's
+// centroids into LDS, behind barriers with nothing running beside it.  With the centroids read from the
 // L2 by four-wave workgroups that walked all sub-spaces, short inputs left one wave per SIMD and nothing hid the reads:
 // 8 heads x 9001 tokens, d16, took 381 us; this one 104 (32768 tokens: 760 to 338; d32: 578 to 305).
 #include "common.h"

@@ -20,8 +20,8 @@
 // Rows of up to 32768 scores fit the registers of one workgroup: topk_row does all of it in one launch (the launches
 // above cost 38 us for 128 rows of 1531 scores, this one 6).  The kernels for
 // longer rows are bound by latency up to some 100000 scores and by reading the scores beyond.  16 rows of
-// 840000 scores whose histogram the producer counted, kernel trace: 61 us when step 2 listed bin d0 alone and step 5 read all
-// scores again, 46 now; 256 rows of 40000 with the histogram 57 and 47.
+// 840000 scores whose histogram the producer counted, k 1 %, kernel trace: 61 us when step 2 listed bin d0 alone and step 5 read all
+// scores again, 44 now; one call with 256 rows of 40000, k 1 %, 53 and 43.
 #include "common.h"
 
 namespace antkv {

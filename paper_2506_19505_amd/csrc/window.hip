@@ -9,7 +9,8 @@
 // four per lane) or, with 4096 centroids, an eighth of one, and finds the arg-max with row rotations instead of LDS
 // exchanges.  Neighbouring lanes read one centroid, so that a load instruction covers whole cache lines (one lane per
 // 64-byte centroid cost four times the L1 cycles).  8 KV heads, kernel trace: d_sub 4 / 8 / 16 at batch 1 from
-// 25 / 13 / 10 us (one workgroup looping over the sub-spaces) to 4.0 / 4.0 / 4.6 us, d32m4096 from 35 to 8 us.
+// 25 / 13 / 10 us (one workgroup looping over the sub-spaces) to 4.0 / 4.0 / 4.6 us, d32m4096 from 35 to 8 us
+// (12 where a step in between has pushed the codebooks out of the L2).
 #include "common.h"
 
 namespace antkv {
