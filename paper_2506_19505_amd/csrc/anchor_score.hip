@@ -419,7 +419,278 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     }
 }
 
+// -------------------------------------------------------------------------------------------------
+// Few query rows (an observation window): steps = heads of the group x query tiles <= kWinSteps.  Both phases then keep the
+// query tiles in LDS and stream the keys once: a wave takes tiles of 32 keys, the next tile's rows on their way into registers while
+// this one meets every step, without a barrier in the loop.
+// Bound: bytes in flight.  A tile is 8 KB of a wave, three workgroups of four waves per CU have 96 KB on the way, and a step
+// costs about 550 clocks of the SIMD (matrix instructions and the epilogue).
+// -------------------------------------------------------------------------------------------------
+constexpr int kWinSteps = 4, kWinWaves = 4, kWinThreads = kWinWaves * 64, kWinPerCu = 3;
+
+// query tiles of the (sequence, KV head) into LDS: step = (head of the group, query tile)
+template <int STEPS>
+__device__ __forceinline__ void stage_window(const half_t* __restrict__ q, int64_t head0, int64_t Nq, int q_tiles, uint32_t to, int wave, int lane)
+{
+    constexpr int kParts = 8 / kWinWaves;                       // pieces of 1 KB of a tile per wave
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        const int hh = s / q_tiles, qt = s - hh * q_tiles;
+        const int64_t left = Nq - 32 * qt;
+#pragma unroll
+        for (int i = 0; i < kParts; ++i)
+            load_to_lds16(q + ((head0 + hh) * Nq + 32 * qt) * kD, stage_off(wave * kParts + i, lane, left < 32 ? (int)left - 1 : 31),
+                          to + s * kTileBytes + (wave * kParts + i) * 1024);
+    }
+}
+
+// the keys of a tile as an MFMA operand; keys past N repeat the last one
+__device__ __forceinline__ void load_keys(half8_t (&t)[8], const half_t* __restrict__ kb, int64_t key0, int64_t N, int n, int kh)
+{
+    const int64_t key = key0 + n;
+    const half_t* kp = kb + (key < N ? key : N - 1) * kD + 8 * kh;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) t[s] = *(const half8_t*)(kp + 16 * s);
+}
+
+// phase 1: keys on the row axis, queries on the column axis, so that a lane owns a query.  part as above, KS = S.
+template <int STEPS>
+__global__ __launch_bounds__(kWinThreads, kWinPerCu) void ans_window_stats(
+    const half_t* __restrict__ q, const half_t* __restrict__ k, int64_t N, int64_t Nq, float c1, float* __restrict__ part,
+    int Hq, int Hkv, int G, int S, int64_t tiles_per_wg)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char s_mem[STEPS * kTileBytes];
+    lds_byte* lds = (lds_byte*)s_mem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, kh = lane >> 5;
+    const int bg = blockIdx.x / S, sp = blockIdx.x % S, b = bg / Hkv, g = bg % Hkv;
+    const int q_tiles = STEPS / G;
+    const int64_t n_tiles = (N + 31) / 32, tile0 = sp * tiles_per_wg;
+    const int64_t tile1 = tile0 + tiles_per_wg < n_tiles ? tile0 + tiles_per_wg : n_tiles;
+    const int64_t head0 = (int64_t)b * Hq + (int64_t)g * G;
+    const half_t* kb = k + (int64_t)bg * N * kD;
+    stage_window<STEPS>(q, head0, Nq, q_tiles, (uint32_t)(uintptr_t)lds, wave, lane);
+    half8_t tk[2][8];
+    int64_t tile = tile0 + wave;
+    load_keys(tk[0], kb, tile * 32, N, n, kh);
+    uint32_t q_at[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) { q_at[s] = tile_at(n, s, kh); pin(q_at[s]); }
+    auto q_op = [&](int s, int step) { return *(lds_half8*)(lds + q_at[s] + step * kTileBytes); };
+    float m_run[STEPS], l_run[STEPS];
+    int64_t qpos[STEPS], q_first[STEPS];                         // positions of this lane's query and of the tile's first
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        m_run[s] = kNegBig;
+        l_run[s] = 0.f;
+        const int64_t i0 = 32 * (s % q_tiles), i = i0 + n;
+        q_first[s] = N - Nq + i0;
+        qpos[s] = N - Nq + (i < Nq ? i : Nq - 1);
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) pin(tk[0][s]);
+    wait_all_loads();
+    __syncthreads();
+    // scores of one step; the statistics of the step before are updated between the matrix instructions
+    float16_t sc[2];
+    auto run_tile = [&](half8_t (&cur)[8], half8_t (&nxt)[8]) __attribute__((always_inline)) {
+        if (tile + kWinWaves < tile1) load_keys(nxt, kb, (tile + kWinWaves) * 32, N, n, kh);
+        const int64_t kt = tile * 32;
+#pragma unroll
+        for (int s = 0; s <= STEPS; ++s) {                       // products of step s, statistics of step s - 1
+            half8_t op[8];
+            if (s < STEPS) {
+                op[0] = q_op(0, s);
+                op[1] = q_op(1, s);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sc[s & 1][r] = 0.f;
+            }
+            const int u = s > 0 ? s - 1 : 0;
+            const bool init = m_run[u] > kNegBig;
+            const float base = init ? m_run[u] : 0.f;
+            float arg[16];
+            float mx = kNegBig, sum = 0.f;
+            auto body = [&](auto masked) {
+                const int lim_q = (int)(qpos[u] - kt);           // visible: offset <= lim_q (the last query sees the last key)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (s < STEPS) {
+                        if (i + 2 < 8) op[i + 2] = q_op(i + 2, s);
+                        sc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[i], op[i], sc[s & 1], 0, 0, 0);
+                    }
+                    if (s > 0) {
+#pragma unroll
+                        for (int e2 = 0; e2 < 2; ++e2) {
+                            const int r = 2 * i + e2;
+                            float x = fmaf(sc[u & 1][r], c1, -base);
+                            if (decltype(masked)::value && 8 * (r >> 2) + 4 * kh + (r & 3) > lim_q) x = kNegBig;
+                            arg[r] = x;
+                            mx = fmaxf(mx, x);
+                            sum += fast_exp2(x);
+                        }
+                        pin(sum);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            if (s == 0 || kt + 31 <= q_first[u]) body(std::false_type{});
+            else body(std::true_type{});
+            if (s > 0) {
+                if (init && mx <= 64.f) {
+                    l_run[u] += sum;
+                } else if (mx > 0.5f * kNegBig) {                // the tile has a visible element: move the reference
+                    float sum2 = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum2 += fast_exp2(arg[r] - mx);
+                    l_run[u] = (init ? l_run[u] * fast_exp2(-mx) : 0.f) + sum2;
+                    m_run[u] = base + mx;
+                }
+            }
+        }
+        tile += kWinWaves;
+    };
+    while (tile < tile1) {
+        run_tile(tk[0], tk[1]);
+        if (tile >= tile1) break;
+        run_tile(tk[1], tk[0]);
+    }
+    // the half-waves saw complementary keys of the same queries, the waves other tiles
+    __syncthreads();                                             // the query tiles are no longer needed
+    float2* s_ml = (float2*)s_mem;                               // [wave][step][32]
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        const float m_o = __shfl_xor(m_run[s], 32, 64), l_o = __shfl_xor(l_run[s], 32, 64);
+        const float m_f = fmaxf(m_run[s], m_o);
+        const float l_f = l_run[s] * fast_exp2(m_run[s] - m_f) + l_o * fast_exp2(m_o - m_f);
+        if (kh == 0) s_ml[(wave * STEPS + s) * 32 + n] = float2{m_f, l_f};
+    }
+    __syncthreads();
+    if (tid < STEPS * 32) {
+        float2 w[kWinWaves];
+#pragma unroll
+        for (int i = 0; i < kWinWaves; ++i) w[i] = s_ml[i * STEPS * 32 + tid];
+        float m = w[0].x;
+#pragma unroll
+        for (int i = 1; i < kWinWaves; ++i) m = fmaxf(m, w[i].x);
+        float l = 0.f;
+#pragma unroll
+        for (int i = 0; i < kWinWaves; ++i) l += w[i].y * fast_exp2(w[i].x - m);
+        const int s = tid >> 5, hh = s / q_tiles;
+        const int64_t i = 32 * (s - hh * q_tiles) + (tid & 31);
+        if (i < Nq) *(float2*)(part + (((head0 + hh) * Nq + i) * S + sp) * 2) = float2{m, l};
+    }
+}
+
+// phase 2: queries on the row axis, keys on the column axis, sums as in ans_col_reduce.  The tiles go backwards: the last ones
+// that phase 1 read are the ones that the caches still hold.
+template <int STEPS>
+__global__ __launch_bounds__(kWinThreads, kWinPerCu) void ans_window_cols(
+    const half_t* __restrict__ q, const half_t* __restrict__ k, int64_t N, int64_t Nq, float c1, const float* __restrict__ stat,
+    float* __restrict__ ans_k, float* __restrict__ ans_v, int Hq, int Hkv, int G, int S, int64_t tiles_per_wg)
+{
+    constexpr int kStatBytes = kStatTile * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char s_mem[STEPS * (kTileBytes + kStatBytes)];
+    lds_byte* lds = (lds_byte*)s_mem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, kh = lane >> 5;
+    const int bg = blockIdx.x / S, sp = blockIdx.x % S, b = bg / Hkv, g = bg % Hkv;
+    const int q_tiles = STEPS / G;
+    const int64_t n_tiles = (N + 31) / 32, tile0 = sp * tiles_per_wg;
+    const int64_t tile1 = tile0 + tiles_per_wg < n_tiles ? tile0 + tiles_per_wg : n_tiles;
+    const int64_t head0 = (int64_t)b * Hq + (int64_t)g * G;
+    const half_t* kb = k + (int64_t)bg * N * kD;
+    stage_window<STEPS>(q, head0, Nq, q_tiles, (uint32_t)(uintptr_t)lds, wave, lane);
+    if (wave < STEPS) load_to_lds4(stat + (head0 * q_tiles + wave) * kStatTile, lane * 4, (uint32_t)(uintptr_t)lds + STEPS * kTileBytes + wave * kStatBytes);
+    half8_t tk[2][8];
+    int64_t tile = tile1 - 1 - wave;
+    if (tile < tile0) tile = tile0 - 1;                          // (nothing to do; tile0 - 1 may be -1, which is not loaded)
+    load_keys(tk[0], kb, (tile < 0 ? 0 : tile) * 32, N, n, kh);
+    uint32_t q_at[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) { q_at[s] = tile_at(n, s, kh); pin(q_at[s]); }
+    const uint32_t s_at = STEPS * kTileBytes + 16 * kh;
+    auto q_op = [&](int s, int step) { return *(lds_half8*)(lds + q_at[s] + step * kTileBytes); };
+    auto stat_op = [&](int qd, int which, int step) { return *(lds_float4*)(lds + s_at + step * kStatBytes + which * 128 + qd * 32); };
+#pragma unroll
+    for (int s = 0; s < 8; ++s) pin(tk[0][s]);
+    wait_all_loads();
+    __syncthreads();
+    int q_off[STEPS];                                            // first row of the step's query tile
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) q_off[s] = 32 * (s % q_tiles);
+    float16_t sc[2];
+    auto run_tile = [&](half8_t (&cur)[8], half8_t (&nxt)[8]) __attribute__((always_inline)) {
+        if (tile - kWinWaves >= tile0) load_keys(nxt, kb, (tile - kWinWaves) * 32, N, n, kh);
+        double sum_v = 0.0, sum_k = 0.0;
+        const int rel0 = (int)(N - Nq - tile * 32);              // position of the first query minus the tile's first key
+#pragma unroll
+        for (int s = 0; s <= STEPS; ++s) {                       // products of step s, sums of step s - 1
+            half8_t a[8];
+            float4_t c4[4], n4[4];
+            const int u = s > 0 ? s - 1 : 0;
+            if (s < STEPS) {
+                a[0] = q_op(0, s);
+                a[1] = q_op(1, s);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sc[s & 1][r] = 0.f;
+            }
+            if (s > 0) {
+                c4[0] = stat_op(0, 0, u);
+                n4[0] = stat_op(0, 1, u);
+                const int rel = rel0 + q_off[u];
+                if (__builtin_expect(rel < 31, 0)) {             // some query of the tile does not see some key
+                    const int lim = n - rel;                     // tile row r sees this lane's key iff r >= lim
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (8 * (r >> 2) + 4 * kh + (r & 3) < lim) sc[u & 1][r] = -INFINITY;
+                }
+            }
+            float pv = 0.f, pk = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {                        // tile rows 8 qd + 4 kh + e live in register 4 qd + e
+                if (s < STEPS) {
+                    if (i + 2 < 8) a[i + 2] = q_op(i + 2, s);
+                    sc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], cur[i], sc[s & 1], 0, 0, 0);
+                }
+                if (s > 0) {
+                    if ((i & 1) == 1 && i < 7) { c4[(i >> 1) + 1] = stat_op((i >> 1) + 1, 0, u); n4[(i >> 1) + 1] = stat_op((i >> 1) + 1, 1, u); }
+#pragma unroll
+                    for (int e2 = 0; e2 < 2; ++e2) {
+                        const int r = 2 * i + e2;
+                        const float c = c4[r >> 2][r & 3], nn = n4[r >> 2][r & 3];
+                        const float w = fast_exp2(fmaf(sc[u & 1][r], c1, c));
+                        pv += w;
+                        pk = fmaf(w, fmaf(-w, nn, nn), pk);      // a (1 - a) ||q||
+                    }
+                    pin(pv);
+                    pin(pk);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (s > 0) {                                         // fp32 per tile, fp64 over tiles
+                sum_v += (double)pv;
+                sum_k += (double)pk;
+            }
+        }
+        const double ov = __shfl_xor(sum_v, 32, 64), ok = __shfl_xor(sum_k, 32, 64);   // lanes l and l + 32: the same key
+        const int64_t key = tile * 32 + n;
+        if (kh == 0 && key < N) {
+            ans_v[(int64_t)bg * N + key] = (float)(sum_v + ov);
+            ans_k[(int64_t)bg * N + key] = (float)(sum_k + ok);
+        }
+        tile -= kWinWaves;
+    };
+    while (tile >= tile0) {
+        run_tile(tk[0], tk[1]);
+        if (tile < tile0) break;
+        run_tile(tk[1], tk[0]);
+    }
+}
+
 struct AsPlan {
+    int steps;                                                  // 0, or what the window kernels take
     int KS;
     int64_t keys_per_split;
     size_t off_part, off_stat, off_ans_k, off_ans_v, total;
@@ -428,6 +699,8 @@ struct AsPlan {
 AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
 {
     AsPlan p;
+    const int64_t n_steps = g.G * ((Nq + 31) / 32), n_bg = (int64_t)g.B * g.Hkv;
+    p.steps = n_steps <= kWinSteps ? (int)n_steps : 0;
     const int qspan = 32 * (8 / (g.G >= 4 ? 4 : g.G));          // query rows per workgroup of phase 1
     const int64_t qblocks = (Nq + qspan - 1) / qspan;
     const int64_t base_wgs = (int64_t)g.B * g.Hkv * qblocks;
@@ -441,13 +714,25 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
     per = (per + 31) / 32 * 32;
     p.keys_per_split = per;
     p.KS = (int)((N + per - 1) / per);
-    const size_t rows = (size_t)g.B * g.Hq * Nq;
+    if (p.steps) {
+        // workgroups of a (sequence, KV head): all CUs full once, at least a tile per wave
+        const int64_t n_tiles = (N + 31) / 32, fill = n_bg > 0 ? 256 * kWinPerCu / n_bg : 1, most = (n_tiles + kWinWaves - 1) / kWinWaves;
+        const int64_t S = fill < 1 ? 1 : (fill < most ? fill : most);
+        const int64_t tiles = (n_tiles + S - 1) / S;
+        p.keys_per_split = 32 * tiles;
+        p.KS = (int)((n_tiles + tiles - 1) / tiles);
+    }
+    const size_t rows = (size_t)g.B * g.Hq * Nq, part = align_up(rows * p.KS * 2 * sizeof(float));
     size_t off = 0;
-    p.off_part = off; off += align_up(rows * p.KS * 2 * sizeof(float));
+    p.off_part = off; off += p.steps ? 0 : part;
     p.off_stat = off; off += align_up(((size_t)g.B * g.Hq * ((Nq + 31) / 32) + 1) * kStatTile * sizeof(float));
     p.off_ans_k = off; off += align_up((size_t)g.B * g.Hkv * N * sizeof(float));
     p.off_ans_v = off; off += align_up((size_t)g.B * g.Hkv * N * sizeof(float));
     p.total = off;
+    if (p.steps) {                                              // the partials lie where phase 2 puts its scores afterwards
+        p.off_part = p.off_ans_k;
+        if (p.total < p.off_part + part) p.total = p.off_part + part;
+    }
     return p;
 }
 
@@ -467,13 +752,26 @@ hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, 
     if (!ans_k) ans_k = (float*)(w + p.off_ans_k);
     if (!ans_v) ans_v = (float*)(w + p.off_ans_v);
     const float c1 = scale * kLog2e;
-    if (!row_max) {
+    const int64_t n_bg = (int64_t)g.B * g.Hkv;
+#define ANTKV_WIN(KERNEL, STEPS, ...)                                                                                      \
+    hipLaunchKernelGGL((KERNEL<STEPS>), dim3((unsigned)(p.KS * n_bg)), dim3(kWinThreads), 0, st, q, k, N, Nq, c1, __VA_ARGS__, \
+                       g.Hq, g.Hkv, g.G, p.KS, p.keys_per_split / 32)
+#define ANTKV_WIN_STEPS(KERNEL, ...)                                                                                       \
+    do {                                                                                                                   \
+        if (p.steps == 1) ANTKV_WIN(KERNEL, 1, __VA_ARGS__);                                                               \
+        else if (p.steps == 2) ANTKV_WIN(KERNEL, 2, __VA_ARGS__);                                                          \
+        else if (p.steps == 3) ANTKV_WIN(KERNEL, 3, __VA_ARGS__);                                                          \
+        else ANTKV_WIN(KERNEL, 4, __VA_ARGS__);                                                                            \
+    } while (0)
+    if (!row_max && p.steps) {
+        ANTKV_WIN_STEPS(ans_window_stats, part);
+    } else if (!row_max) {
         const int qspan = 32 * (8 / (g.G >= 4 ? 4 : g.G));
         dim3 grid((unsigned)p.KS, (unsigned)((Nq + qspan - 1) / qspan), (unsigned)(g.B * g.Hkv));
         hipLaunchKernelGGL(ans_row_stats, grid, dim3(kAsThreads), 0, st, q, k, N, Nq, c1, part, g.Hq, g.Hkv, g.G,
                            p.KS, p.keys_per_split);
     }
-    const int64_t q_tiles = (Nq + 31) / 32, n_heads = (int64_t)g.B * g.Hq, n_bg = (int64_t)g.B * g.Hkv;
+    const int64_t q_tiles = (Nq + 31) / 32, n_heads = (int64_t)g.B * g.Hq;
     const int64_t padded = (n_heads * q_tiles + 1) * 32;
     hipLaunchKernelGGL(ans_finalize_stats, dim3((unsigned)((padded * 16 + 255) / 256)), dim3(256), 0, st, q, part, p.KS,
                        row_max, row_sum, stat, Nq, (int)q_tiles, n_heads);
@@ -483,9 +781,12 @@ hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, 
 #define ANTKV_CR(KT, NW)                                                                                                  \
     hipLaunchKernelGGL((ans_col_reduce<KT, NW>), dim3((unsigned)((N + 32 * KT * NW - 1) / (32 * KT * NW) * n_bg)), dim3(NW * 64), \
                        0, st, q, k, N, Nq, c1, stat, ans_k, ans_v, g.Hq, g.Hkv, g.G, n_bg, (int)q_tiles)
-    if (Nq > 256 && (N + 511) / 512 * n_bg >= 512) ANTKV_CR(2, 8);
+    if (p.steps) ANTKV_WIN_STEPS(ans_window_cols, stat, ans_k, ans_v);
+    else if (Nq > 256 && (N + 511) / 512 * n_bg >= 512) ANTKV_CR(2, 8);
     else ANTKV_CR(1, 4);
 #undef ANTKV_CR
+#undef ANTKV_WIN_STEPS
+#undef ANTKV_WIN
     return hipGetLastError();
 }
 

@@ -62,6 +62,14 @@ def test_anchor_select_key_ranges(oracle, B, Hq, Hkv, N, Nq):
     _run(oracle, 28, B, Hq, Hkv, N, Nq, anchor_count(N))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(1, 1, 1, 7, 1), (1, 4, 1, 31, 31), (2, 4, 2, 33, 32), (1, 4, 2, 1000, 20), (1, 2, 1, 4099, 64),
+                                           (1, 1, 1, 12345, 128), (2, 1, 1, 260, 96), (5, 24, 24, 129, 7), (1, 32, 8, 24611, 32)])
+def test_anchor_select_windows(oracle, B, Hq, Hkv, N, Nq):
+    """Every step count of the window kernels (heads of the group x query tiles, 1 to 4): fewer tiles than waves, ragged keys and
+    queries, a diagonal over several key tiles, and ranges of several rounds of the waves."""
+    _run(oracle, 31, B, Hq, Hkv, N, Nq, anchor_count(N))
+
+
 def test_anchor_select_k_edges(oracle):
     _run(oracle, 22, 1, 4, 1, 200, 200, 0)
     _run(oracle, 22, 1, 4, 1, 200, 200, 200)
