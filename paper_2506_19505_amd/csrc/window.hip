@@ -9,8 +9,8 @@
 // four per lane) or, with 4096 centroids, an eighth of one, and finds the arg-max with row rotations instead of LDS
 // exchanges.  Neighbouring lanes read one centroid, so that a load instruction covers whole cache lines (one lane per
 // 64-byte centroid cost four times the L1 cycles).  8 KV heads, kernel trace: d_sub 4 / 8 / 16 at batch 1 from
-// 25 / 13 / 10 us (one workgroup looping over the sub-spaces) to 4.0 / 4.0 / 4.6 us, d32m4096 from 35 to 8 us
-// (12 where a step in between has pushed the codebooks out of the L2).
+// 25 / 13 / 10 us (one workgroup looping over the sub-spaces) to 4.0 / 4.0 / 4.6 us, d32m4096 from 35 to 7.8 us
+// with codebooks that a step in between has pushed out of the L2 (12.5 with a workgroup per pair of sub-spaces).
 #include "common.h"
 
 namespace antkv {
@@ -47,11 +47,11 @@ __device__ __forceinline__ uint32_t wave_min_all(uint32_t x)
     return min(min(r[0], r[1]), min(r[2], r[3]));
 }
 
-// Channels per workgroup and waves: 256 centroids, 32 channels x 4 waves (16 KB of codebook); 4096 centroids, two
-// sub-spaces (their 12-bit codes fill whole bytes) x 16 waves (256 or 512 KB of codebook).
-template <int DSUB, int NC>
+// Channels per workgroup and waves: 256 centroids, 32 channels x 4 waves (16 KB of codebook); 4096 centroids, one sub-space
+// x 16 waves (128 or 256 KB of codebook) or, PAIR, two of them, whose 12-bit codes fill whole bytes.
+template <int DSUB, int NC, bool PAIR>
 struct Ap {
-    static constexpr int channels = NC == 256 ? 32 : 2 * DSUB;
+    static constexpr int channels = NC == 256 ? 32 : (PAIR ? 2 : 1) * DSUB;
     static constexpr int waves = NC == 256 ? 4 : 16;
     static constexpr int threads = waves * 64;
     static constexpr int subs = channels / DSUB;                          // sub-spaces of the workgroup
@@ -65,14 +65,14 @@ struct Ap {
 };
 
 // NC = centroids per sub-space: 256 (one code byte per sub-space) or 4096 (M 12-bit codes packed into 3 M / 2 bytes)
-template <int DSUB, int NC>
-__global__ __launch_bounds__((Ap<DSUB, NC>::threads)) void append_kernel(
+template <int DSUB, int NC, bool PAIR>
+__global__ __launch_bounds__((Ap<DSUB, NC, PAIR>::threads)) void append_kernel(
     const half_t* __restrict__ k_new, const half_t* __restrict__ v_new, const half_t* __restrict__ cb_k,
     const half_t* __restrict__ cb_v, uint8_t* __restrict__ codes_k, uint8_t* __restrict__ codes_v, int64_t N_cap,
     int32_t* __restrict__ idx_k, half_t* __restrict__ rows_k, int64_t k_k, int32_t* __restrict__ idx_v,
     half_t* __restrict__ rows_v, int64_t k_v, int64_t N, int W, int Hkv)
 {
-    using P = Ap<DSUB, NC>;
+    using P = Ap<DSUB, NC, PAIR>;
     typedef half_t piece_t __attribute__((ext_vector_type(P::chunk)));
     constexpr int M = kD / DSUB;
     constexpr int kCodeBytes = NC == 256 ? M : 3 * M / 2;
@@ -97,6 +97,19 @@ __global__ __launch_bounds__((Ap<DSUB, NC>::threads)) void append_kernel(
     const int e = tid / kPieces, off = ch0 + 8 * (tid % kPieces);
     uint4_t mv = {0u, 0u, 0u, 0u};
     if (e < W) mv = (e + 1 < W) ? *(const uint4_t*)(rows + (e + 1) * kD + off) : *(const uint4_t*)(fresh + off);
+
+    // one 12-bit code per workgroup: the words that it lies in, as they are (nobody else changes its bits)
+    uint32_t* word = nullptr;
+    uint32_t bit = 0, old0 = 0, old1 = 0;
+    if constexpr (NC == 4096 && !PAIR) {
+        const int64_t at = (bg * N_cap + (N - W)) * kCodeBytes * 8 + 12 * (int64_t)blockIdx.z;
+        word = (uint32_t*)(is_v ? codes_v : codes_k) + (at >> 5);
+        bit = (uint32_t)at & 31;
+        if (tid == 0) {
+            old0 = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (bit > 20) old1 = __hip_atomic_load(word + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
 
     // the row that becomes codes: the window's oldest, or the new row itself when there is no window
     const half_t* src = (W > 0) ? rows : fresh;
@@ -149,6 +162,19 @@ __global__ __launch_bounds__((Ap<DSUB, NC>::threads)) void append_kernel(
                 if (s_val[tid * P::waves_per_sub + w] > val) { val = s_val[tid * P::waves_per_sub + w]; c = s_who[tid * P::waves_per_sub + w]; }
             codes[ch0 / DSUB + tid] = (uint8_t)c;
         }
+    } else if constexpr (!PAIR) {
+        if (wave == 0) {                                                          // the lowest index among the waves' equals
+            const float val = lane < P::waves ? s_val[lane] : -3.0e38f;
+            const float top = wave_max_all(val);
+            const uint32_t code = wave_min_all(lane < P::waves && val == top ? s_who[lane] : 0xffffffffu) & 0xfffu;
+            if (lane == 0) {
+                // Other workgroups change other bits of these words at the same time: what differs in the code's own bits is flipped.
+                __hip_atomic_fetch_xor(word, (old0 ^ (code << bit)) & (0xfffu << bit), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (bit > 20)
+                    __hip_atomic_fetch_xor(word + 1, (old1 ^ (code >> (32 - bit))) & (0xfffu >> (32 - bit)), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
     } else if (tid == 0) {
         uint32_t c2[2];
 #pragma unroll
@@ -178,15 +204,22 @@ hipError_t launch_append(const Geom& g, const half_t* k_new, const half_t* v_new
                          int32_t* idx_v, half_t* rows_v, int64_t k_v, int64_t N, int W, hipStream_t st)
 {
     if (g.B == 0) return hipSuccess;
-#define ANTKV_AP(DS, NCEN)                                                                                           \
-    hipLaunchKernelGGL((append_kernel<DS, NCEN>), dim3((unsigned)(g.B * g.Hkv), 2, kD / Ap<DS, NCEN>::channels),        \
-                       dim3(Ap<DS, NCEN>::threads), 0, st, k_new, v_new, cb_k, cb_v, codes_k, codes_v, N_cap, idx_k,    \
+#define ANTKV_AP(DS, NCEN, PAIR)                                                                                     \
+    hipLaunchKernelGGL((append_kernel<DS, NCEN, PAIR>), dim3((unsigned)(g.B * g.Hkv), 2, kD / Ap<DS, NCEN, PAIR>::channels), \
+                       dim3(Ap<DS, NCEN, PAIR>::threads), 0, st, k_new, v_new, cb_k, cb_v, codes_k, codes_v, N_cap, idx_k,    \
                        rows_k, k_k, idx_v, rows_v, k_v, N, W, g.Hkv)
-    if (g.C == 4096 && g.d == 32) ANTKV_AP(32, 4096);
-    else if (g.C == 4096) ANTKV_AP(16, 4096);
-    else if (g.d == 4) ANTKV_AP(4, 256);
-    else if (g.d == 8) ANTKV_AP(8, 256);
-    else ANTKV_AP(16, 256);
+    // 12-bit codes: a workgroup per sub-space while that leaves each a CU of its own (a CU takes 57 GB/s of a cold codebook: d 32,
+    // 8 heads 12.5 us in pairs, 7.8 alone; d 16, 24 heads are 384 workgroups, a whole step 71.1 us in pairs and 72.3 alone).  It
+    // changes its bits of 32-bit words, which the buffer has to consist of (d 32 has rows of six bytes).
+    const int64_t rows = (int64_t)g.B * g.Hkv;
+    const bool alone = rows * 2 * g.M <= 256 && rows * N_cap * g.code_bytes % 4 == 0;
+    if (g.C == 4096 && g.d == 32 && alone) ANTKV_AP(32, 4096, false);
+    else if (g.C == 4096 && g.d == 32) ANTKV_AP(32, 4096, true);
+    else if (g.C == 4096 && alone) ANTKV_AP(16, 4096, false);
+    else if (g.C == 4096) ANTKV_AP(16, 4096, true);
+    else if (g.d == 4) ANTKV_AP(4, 256, false);
+    else if (g.d == 8) ANTKV_AP(8, 256, false);
+    else ANTKV_AP(16, 256, false);
 #undef ANTKV_AP
     return hipGetLastError();
 }

@@ -90,6 +90,29 @@ def test_append_ties_and_window_edges(oracle, d, C, W):
             assert (rr.cpu().numpy() == np.concatenate([rows[:, :, 1:], new[:, :, None]], axis=2)).all()
 
 
+@pytest.mark.parametrize("d", [32, 16])
+@pytest.mark.parametrize("Hkv,N", [(1, 70), (2, 70), (2, 71), (1, 71), (1, 73), (18, 70), (33, 70)])
+def test_append_12_bit_codes_leave_other_bits(oracle, d, Hkv, N):
+    """12-bit codes share bytes and 32-bit words with their neighbours: every position of a code inside a word, rows that end in the
+    middle of one, buffers that are no whole number of words, and more heads than have a workgroup per sub-space.  Every other byte
+    stays."""
+    W, C, M = 2, 4096, 128 // d
+    cb = normal_fp16(44, "cb12_k", (Hkv, M, C, d))
+    rows, new = normal_fp16(45, "win_rows_k", (1, Hkv, W, 128)), normal_fp16(46, "new_k", (1, Hkv, 128))
+    want, margin = oracle.encode(rows[:, :, :1], cb, want_margin=True)
+    geom = antkv.Geometry(1, 4 * Hkv, Hkv, d, n_centroids=C)
+    before = np.random.default_rng(N).integers(0, 256, (1, Hkv, N + 1, geom.code_bytes), dtype=np.uint8)
+    ck, cv, r = dev(before), dev(before), dev(rows)
+    idx = dev(np.broadcast_to(np.arange(N - W, N), (1, Hkv, W)).astype(np.int32))
+    antkv.append_token(geom, dev(new), dev(new), N, W, dev(cb), dev(cb), ck, cv, idx, r, idx.clone(), r.clone())
+    for c in (ck, cv):
+        got = c.cpu().numpy()
+        bad = unpack12(got[:, :, N - W])[:, :, None] != want
+        assert not (bad & (margin >= NEAR_TIE)).any()
+        got[:, :, N - W] = before[:, :, N - W]
+        assert (got == before).all()
+
+
 def test_append_rejects_bad_arguments():
     geom = antkv.Geometry(1, 4, 1, 8)
     z16 = lambda *s: torch.zeros(s, dtype=torch.float16, device="cuda")
