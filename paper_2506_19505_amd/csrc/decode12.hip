@@ -23,6 +23,7 @@
 // Long contexts take the kernels of decode12_by_code.hip instead, which add the values up by code (rule: d12_by_code below);
 // the table and merge kernels here serve both.
 #include "decode12.h"
+#include "decode_short.h"
 
 #include <type_traits>
 
@@ -917,7 +918,7 @@ bool d12_by_code(const Geom& g, int64_t N)
 }
 
 template <int DS>
-hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool by_code, hipStream_t st)
+hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool by_code, const ShortPlan& brief, hipStream_t st)
 {
     const D12Plan pl = d12_plan(g, a.N, a.k_v, by_code);
     constexpr size_t lds = d12_lds(DS);
@@ -941,12 +942,19 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool 
     p.given = (const float4_t*)a.given_scores;
     if (a.given_scores && (a.k_k != 0 || a.ans_k || a.ans_v)) return hipErrorInvalidValue;     // the scores cover the K anchors already
     const D12VScores vs = {p.codes_k, p.idx_v, (float4_t*)(w + pl.off_vsc), p.N_cap, p.k_v};
-    if (a.N > 0 && !a.given_scores) {
+    // (ahead of the table, which shares the workspace with its partials)
+    if (brief.on) {
+        const hipError_t e = launch_decode_short(g, brief, a, ws, next_launch_tag(), st);
+        if (e != hipSuccess) return e;
+    }
+    if (a.N > 0 && !a.given_scores && (!brief.on || a.ans_k)) {
         const int64_t blocks = tab_blocks(DS) + (by_code && heads_per_table(DS) < kNH ? (a.k_v + kVBlock - 1) / kVBlock : 0);
         hipLaunchKernelGGL(d12_table_kernel<DS>, dim3((unsigned)(g.B * g.Hkv * blocks)), dim3(kTabThreads), 0, st, a.q, a.cb_k, p.c1, g.Hq,
                            g.Hkv, g.G, g.B * g.Hkv, (float2*)(w + pl.off_tab), (float*)(w + pl.off_amax), vs);
     }
-    if (a.N > 0 && by_code) {
+    if (brief.on) {
+        // the output is written
+    } else if (a.N > 0 && by_code) {
         D12LongParams l;
         l.q = p.q; l.codes_k = p.codes_k; l.codes_v = p.codes_v; l.cb_v = p.cb_v; l.idx_k = p.idx_k; l.idx_v = p.idx_v;
         l.rows_k = p.rows_k; l.rows_v = p.rows_v; l.tab = p.tab; l.tab_amax = p.tab_amax; l.given = p.given; l.part = p.part;
@@ -960,7 +968,7 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool 
     } else if (a.N > 0) {
         hipLaunchKernelGGL((decode12_kernel<DS, false>), dim3((unsigned)(g.B * g.Hkv * pl.S)), dim3(kT12), lds, st, p);
     }
-    hipLaunchKernelGGL(decode12_merge, dim3((unsigned)(g.B * g.Hq)), dim3(kD), 0, st, (const float*)p.part, a.N > 0 ? pl.slots : 0, a.out);
+    if (!brief.on) hipLaunchKernelGGL(decode12_merge, dim3((unsigned)(g.B * g.Hq)), dim3(kD), 0, st, (const float*)p.part, a.N > 0 ? pl.slots : 0, a.out);
     if (a.ans_k && a.N > 0) {
         static OncePerDevice once_ans;
         const hipError_t setup_ans = on_this_device(once_ans, []() {
@@ -985,13 +993,19 @@ hipError_t launch_decode12_t(const Geom& g, const DecodeArgs& a, void* ws, bool 
 
 }  // namespace
 
-size_t decode12_workspace_bytes(const Geom& g, int64_t N, int64_t k_v) { return d12_plan(g, N, k_v, d12_by_code(g, N)).total; }
+size_t decode12_workspace_bytes(const Geom& g, int64_t N, int64_t k_v)
+{
+    const size_t full = d12_plan(g, N, k_v, d12_by_code(g, N)).total, brief = short_plan(g, N).total;
+    return full > brief ? full : brief;
+}
 size_t decode12_workspace_least(const Geom& g, int64_t N) { return d12_plan(g, N, 0, false).total; }
 
 hipError_t launch_decode12(const Geom& g, const DecodeArgs& a, void* ws, size_t ws_bytes, hipStream_t st)
 {
-    const bool by_code = d12_by_code(g, a.N) && ws_bytes >= d12_plan(g, a.N, a.k_v, true).total;
-    return g.d == 32 ? launch_decode12_t<32>(g, a, ws, by_code, st) : launch_decode12_t<16>(g, a, ws, by_code, st);
+    ShortPlan brief = short_plan(g, a.N);
+    brief.on = brief.on && brief.total <= ws_bytes && !a.given_scores;
+    const bool by_code = !brief.on && d12_by_code(g, a.N) && ws_bytes >= d12_plan(g, a.N, a.k_v, true).total;
+    return g.d == 32 ? launch_decode12_t<32>(g, a, ws, by_code, brief, st) : launch_decode12_t<16>(g, a, ws, by_code, brief, st);
 }
 
 }  // namespace antkv

@@ -2007,7 +2007,7 @@ static std::atomic<int> g_options{0};
 
 // Launch tags are unique within the process (a wrap after 2^32 launches could only matter for a workspace
 // last used exactly 2^32 launches earlier); 0 is never handed out.
-static unsigned int next_launch_tag()
+unsigned int next_launch_tag()
 {
     static std::atomic<unsigned int> counter{1u};
     unsigned int t = counter.fetch_add(1u, std::memory_order_relaxed);

@@ -386,6 +386,33 @@ def test_decode12_either_side_of_the_switch(books, B, Hkv):
                 antkv.decode_attn(*args, workspace=least)
 
 
+# Edges of a tile (32 tokens), of the waves (8 tiles), of the split (128 tokens a range, 32 ranges), groups of 1, 2 and 4, all
+# or no tokens anchored; the longest ranges that are gathered row by row (8 heads: 32 x 3072 and 32 x 1792 tokens) and one more.
+@pytest.mark.parametrize("B,Hq,Hkv,N,k_k,k_v", [(1, 4, 1, 1, 1, 0), (3, 2, 2, 31, 0, 31), (1, 8, 2, 33, 33, 33), (2, 4, 2, 127, 1, 1),
+                                                (1, 8, 8, 129, 5, 7), (300, 1, 1, 257, 3, 9), (1, 4, 2, 4095, 700, 1300), (1, 16, 4, 4097, 41, 41),
+                                                (5, 32, 8, 3001, 62, 62), (1, 32, 8, -1, 300, 310), (1, 32, 8, -2, 310, 300)])
+def test_decode12_short_ranges(books, B, Hq, Hkv, N, k_k, k_v):
+    """Row by row, against float64.  Bound: a weight's rounding to fp16 and the output's, 2^-11 each; 1e-4 for the rest (through
+    the table, one token past the longest, the bound that its other tests have)."""
+    longest = 32 * (3072 if books.d == 32 else 1792)
+    by_table = N == -2
+    N = longest - 1 - N if N < 0 else N
+    gen = torch.Generator(device="cuda").manual_seed(N + B)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes_k, codes_v = (torch.randint(0, C, (B, Hkv, N, books.M), device="cuda", generator=gen) for _ in range(2))
+    cb_k, cb_v = rnd(Hkv, books.M, C, books.d), rnd(Hkv, books.M, C, books.d)
+    pick = lambda k: torch.rand((B, Hkv, N), device="cuda", generator=gen).argsort(dim=-1)[..., :k].sort(dim=-1).values.int().contiguous()
+    q, rows_k, rows_v, idx_k, idx_v = rnd(B, Hq, 128), rnd(B, Hkv, k_k, 128), rnd(B, Hkv, k_v, 128), pick(k_k), pick(k_v)
+    room = torch.nn.functional.pad
+    got = antkv.decode_attn(antkv.Geometry(B, Hq, Hkv, books.d, n_centroids=C), q, 128 ** -0.5, room(_pack12_dev(codes_k), (0, 0, 0, 3), value=255),
+                            room(_pack12_dev(codes_v), (0, 0, 0, 3), value=255), cb_k, cb_v, idx_k if k_k else None,
+                            rows_k if k_k else None, idx_v if k_v else None, rows_v if k_v else None, N=N).double()
+    want, _ = _decode_exact(q, 128 ** -0.5, codes_k, codes_v, cb_k, cb_v, idx_k, rows_k, idx_v, rows_v)
+    err = ((got - want).norm(dim=-1) / want.norm(dim=-1)).max().item()
+    print(f"d{books.d} N{N}: {err:.2e}")
+    assert err <= (2e-3 if by_table else 2.0 ** -10 + 1e-4)
+
+
 @pytest.mark.parametrize("gain", [1, 4, 16])
 @pytest.mark.parametrize("G", [1, 2, 4])
 def test_decode12_values_by_code_query_gain(books, gain, G):
