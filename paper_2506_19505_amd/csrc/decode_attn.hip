@@ -1791,40 +1791,55 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
 #pragma unroll
     for (int h = 0; h < kNH; ++h) { m_run[h] = kNegBig; l_run[h] = 0.f; }
 
+    // No branches over the heads, so that their exponentials are in flight together: pass 1 gives a head that the group does not
+    // have weight 0, and what a masked lane adds is 0.
+    if (PASS == 1) {
+#pragma unroll
+        for (int h = 0; h < kNH; ++h) lse[h] = h < p.G ? lse[h] : -kNegBig;
+    }
+    float* const row_v = PASS == 1 ? p.ans_v + (int64_t)bg * p.N : nullptr;
+    float* const row_k = PASS == 1 ? p.ans_k + (int64_t)bg * p.N : nullptr;
     // PASS 0 keeps, per lane and head, a sum of exp2(score - reference); the reference only moves when a score
     // exceeds it by more than 64 (or on the lane's first token), so the common token costs one exp2 per head.
-    auto consume = [&](const float (&s)[kNH], int64_t tok, bool on) {
-        if (PASS == 0) {
-            float over = 0.f;
+    auto consume = [&](const float (&s)[kNH], int64_t from, uint32_t rel, bool on) {       // token from + rel
+        if constexpr (PASS == 0) {
+            float x[kNH];
 #pragma unroll
-            for (int h = 0; h < kNH; ++h) over = fmaxf(over, s[h] - m_run[h]);
-            if (__any(on && over > 64.f)) {
+            for (int h = 0; h < kNH; ++h) x[h] = s[h] - m_run[h];
+            const float over = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+            if (__ballot(on && over > 64.f) != 0ull) {
 #pragma unroll
                 for (int h = 0; h < kNH; ++h) {
-                    if (on && s[h] - m_run[h] > 64.f) {
-                        l_run[h] *= fast_exp2(m_run[h] - s[h]);
-                        m_run[h] = s[h];
-                    }
+                    const bool moves = on && x[h] > 64.f;
+                    const float kept = l_run[h] * fast_exp2(m_run[h] - s[h]);
+                    l_run[h] = moves ? kept : l_run[h];
+                    m_run[h] = moves ? s[h] : m_run[h];
+                    x[h] = s[h] - m_run[h];
                 }
             }
 #pragma unroll
-            for (int h = 0; h < kNH; ++h) l_run[h] += fast_exp2(on ? s[h] - m_run[h] : kNegBig);
-        } else if (on) {
+            for (int h = 0; h < kNH; ++h) {
+                x[h] = on ? x[h] : kNegBig;
+                pin(x[h]);                                           // (selected here: not turned into branches around the exponentials)
+            }
+#pragma unroll
+            for (int h = 0; h < kNH; ++h) l_run[h] += fast_exp2(x[h]);
+        } else {
             float av = 0.f, ak = 0.f;
 #pragma unroll
             for (int h = 0; h < kNH; ++h) {
-                if (h < p.G) {
-                    const float a = fast_exp2(s[h] - lse[h]);
-                    const float t = a * qn[h];
-                    av += a;
-                    ak += fmaf(-a, t, t);
-                }
+                const float a = fast_exp2(s[h] - lse[h]);
+                const float t = a * qn[h];
+                av += a;
+                ak += fmaf(-a, t, t);
             }
-            p.ans_v[(int64_t)bg * p.N + tok] = av;
-            p.ans_k[(int64_t)bg * p.N + tok] = ak;
-            if (count_scores) {                                  // the selection that follows starts from these counts
-                atomicAdd(&s_hist[float_key(ak) >> 21], 1u);
-                atomicAdd(&s_hist[kTopkBins + (float_key(av) >> 21)], 1u);
+            if (on) {
+                row_v[from + rel] = av;
+                row_k[from + rel] = ak;
+                if (count_scores) {                                  // the selection that follows starts from these counts
+                    atomicAdd(&s_hist[float_key(ak) >> 21], 1u);
+                    atomicAdd(&s_hist[kTopkBins + (float_key(av) >> 21)], 1u);
+                }
             }
         }
     };
@@ -1857,7 +1872,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
 #pragma unroll
     for (int e = 0; e < 4; ++e) sel[e] = 0x0c0c0000u | (uint32_t)(4 + (e ^ (r & 3))) << 8 | (uint32_t)e;
     const uint32_t upper = (uint32_t)(r >> 4) << 16;              // d = 4: the table of sub-space r
-    const char* lut_bytes = (const char*)s_lut;
+    typedef __attribute__((address_space(3))) const float4_t lds_cfloat4;
     uint32_t kw_next[CW];
     load_kw(tid, kw_next);
 #pragma unroll 1
@@ -1866,7 +1881,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
 #pragma unroll
         for (int i = 0; i < CW; ++i) kw[i] = kw_next[i];
         load_kw(rel + kDaThreads, kw_next);
-        const bool on = rel < n_tok && ((s_mask[(rel >> 5) & 1023] >> (rel & 31)) & 1u) == 0u;
+        const uint32_t mask = s_mask[(rel >> 5) & 1023] >> (rel & 31);
         // code dwords XOR-permuted by r / 4, so that step st finds its dword at the compile-time index st / 4
 #pragma unroll
         for (int bit = 0; (4 << bit) < M; ++bit) {
@@ -1890,7 +1905,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
             for (int k = 0; k < 4; ++k) {
                 uint32_t off = __builtin_amdgcn_perm(kw[q], slots[q & 3], sel[k]);
                 if constexpr (M == 32) off |= q < 4 ? upper : upper ^ 0x10000u;
-                ent[q & 1][k] = *(const float4_t*)(lut_bytes + off);
+                ent[q & 1][k] = *(lds_cfloat4*)(uintptr_t)off;      // (the table starts at LDS address 0)
             }
         };
         request(0);
@@ -1901,12 +1916,12 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int h = 0; h < kNH; ++h) s[h] += ent[q & 1][k][h];
+                for (int h = 0; h < kNH; ++h) s[h] = q == 0 && k == 0 ? ent[0][0][h] : s[h] + ent[q & 1][k][h];
 #pragma unroll
             for (int h = 0; h < kNH; ++h) pin(s[h]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        consume(s, t0 + rel, on);
+        consume(s, t0, (uint32_t)rel, (rel < n_tok) & ((mask & 1u) == 0u));
     }
     // ---- K-anchored tokens: the prefetched rounds, then any further ones
     {
@@ -1925,7 +1940,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
                 for (int e = 0; e < 8; ++e) d = fmaf(qv[h][e], (float)v[e], d);
                 s[h] = row16_sum(d) * p.c1;
             }
-            consume(s, tok, tok >= 0 && l16 == 0);
+            consume(s, tok, 0u, tok >= 0 && l16 == 0);
         };
 #pragma unroll
         for (int u = 0; u < kPre; ++u)
@@ -2079,11 +2094,15 @@ static hipError_t launch_decode_t(const Geom& g, const DecodeArgs& a, void* ws, 
         const size_t sh2 = (size_t)(g.M < 16 ? 16 : g.M) * 256 * 16 + kNH * kD * 4 + kDaWaves * 32 + 64 + 4096 + 2 * kTopkBins * 4;
         static OncePerDevice once_ans;
         const hipError_t ans_setup = on_this_device(once_ans, [sh2]() {
-            hipError_t e1 = hipFuncSetAttribute((const void*)decode_ans_kernel<DSUB, 0>,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh2);
-            if (e1 != hipSuccess) return e1;
-            return hipFuncSetAttribute((const void*)decode_ans_kernel<DSUB, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)sh2);
+            for (const void* f : {(const void*)decode_ans_kernel<DSUB, 0>, (const void*)decode_ans_kernel<DSUB, 1>}) {
+                hipFuncAttributes attr;                              // (absolute LDS addresses, as above)
+                hipError_t r = hipFuncGetAttributes(&attr, f);
+                if (r != hipSuccess) return r;
+                if (attr.sharedSizeBytes != 0) return hipErrorInvalidConfiguration;
+                r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh2);
+                if (r != hipSuccess) return r;
+            }
+            return hipSuccess;
         });
         if (ans_setup != hipSuccess) return ans_setup;
         const unsigned grid2 = (unsigned)((int64_t)g.B * g.Hkv * pl.S);
