@@ -95,7 +95,7 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
         a.given_scores = given_scores;
         // with both index sets wanted, the score pass counts its scores into the selection's first histogram
         const bool fused = N > 0 && k_resel > 0 && resel_idx_k && resel_idx_v;
-        a.topk_hist = fused ? launch_topk2_begin((int64_t)g.B * g.Hkv, N, (char*)workspace + off_topk, st) : nullptr;
+        a.topk = fused ? topk2_begin((int64_t)g.B * g.Hkv, N, (char*)workspace + off_topk) : TopkCounts{nullptr, 0};
         if (launch_decode12(g, a, workspace, off_topk, st) != hipSuccess) return ANTKV_ELAUNCH;
         if (N > 0 && k_resel > 0 && (resel_idx_k || resel_idx_v)) {
             char* w = (char*)workspace;
@@ -120,7 +120,7 @@ int decode_attn_impl(const antkv_geom* geom, const void* q, float scale, const u
     a.given_scores = given_scores;
     // with both index sets wanted, the score pass counts its scores into the selection's first histogram
     const bool fused = N > 0 && k_resel > 0 && resel_idx_k && resel_idx_v;
-    a.topk_hist = fused ? launch_topk2_begin((int64_t)g.B * g.Hkv, N, (char*)workspace + dp.off_topk, st) : nullptr;
+    a.topk = fused ? topk2_begin((int64_t)g.B * g.Hkv, N, (char*)workspace + dp.off_topk) : TopkCounts{nullptr, 0};
     hipError_t e = launch_decode_attn(g, a, workspace, st);
     if (e != hipSuccess) return ANTKV_ELAUNCH;
     if (N > 0 && k_resel > 0) {

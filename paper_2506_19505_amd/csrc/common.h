@@ -116,13 +116,17 @@ hipError_t launch_topk(const float* scores, int64_t n_rows, int64_t N, int64_t k
                        void* ws, hipStream_t st);
 hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
                         int64_t N, int64_t k, void* ws, hipStream_t st);
-// The same selection in two halves, for a producer that counts its scores while it writes them: `begin` clears the
-// workspace's counters and returns the first-level histograms, uint32 [2 n_rows][2 * kTopkBins] (row r < n_rows belongs
-// to scores row r, row n_rows + r to scores_b row r; the first kTopkBins words of a row count float_key(score) >> 21);
-// the producer adds every score it writes to them; `finish` selects from there without reading the scores for a histogram.
+// The same selection in two halves, for a producer that counts its scores while it writes them: `begin` returns the first-level
+// histograms, uint32 [2 n_rows][2 * kTopkBins] (row r < n_rows belongs to scores row r, row n_rows + r to scores_b row r; the
+// first kTopkBins words of a row count float_key(score) >> 21), and how many words from there on the producer has to clear
+// first; it then adds every score it writes to them; `finish` selects from there without reading the scores for a histogram.
 // Rows that one workgroup selects by itself need no histograms: `begin` then returns NULL.
 constexpr int kTopkBins = 2048;
-uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st);
+struct TopkCounts {
+    uint32_t* hist;
+    int64_t words;
+};
+TopkCounts topk2_begin(int64_t n_rows, int64_t N, void* ws);
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
                                int64_t N, int64_t k, void* ws, hipStream_t st);
 
@@ -157,7 +161,7 @@ struct DecodeArgs {
     int64_t k_v;
     half_t* out;
     float *ans_k, *ans_v;
-    uint32_t* topk_hist;   // optional: first-level top-k histograms that the score pass fills (see launch_topk2_begin)
+    TopkCounts topk;       // optional: first-level top-k histograms that the score passes clear and fill (see topk2_begin)
     // optional (k_k = 0, no Anchor Scores): the K side's scores in log2 units as launch_rope_scores writes them (one-byte
     // codes: grouped by four tokens; 12-bit codes: [B][Hkv][N][4 heads]); the K codes, the K codebook and scale are then not used
     const float* given_scores = nullptr;

@@ -1630,7 +1630,8 @@ struct DsParams {
     float c1;
     int Hq, Hkv, G, S;
     int64_t chunk;
-    uint32_t* hist;             // optional (pass 1): first-level top-k histograms, [2 B Hkv][2 * kTopkBins], K rows then V rows
+    TopkCounts topk;            // optional: first-level top-k histograms, [2 B Hkv][2 * kTopkBins], K rows then V rows: pass 0
+                                // clears them, pass 1 adds what it writes
 };
 
 template <int DSUB, int PASS>
@@ -1650,7 +1651,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
     float* s_red = s_qf + kNH * kD;                         // [waves][8]
     int* s_misc = (int*)(s_red + kDaWaves * 8);             // 16 ints
     uint32_t* s_mask = (uint32_t*)(s_misc + 16);            // bitmap of K-anchored tokens, 1024 words
-    uint32_t* s_hist = s_mask + 1024;                       // pass 1 with p.hist: [2][kTopkBins] counts of the scores written
+    uint32_t* s_hist = s_mask + 1024;                       // pass 1 with p.topk: [2][kTopkBins] counts of the scores written
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bg = blockIdx.x / p.S, sp = blockIdx.x % p.S;
     const int b = bg / p.Hkv, g = bg % p.Hkv;
@@ -1698,7 +1699,9 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
     }
     if (tid < kNH * kD) s_qf[tid] = ((tid >> 7) < p.G) ? (float)qb[tid] : 0.f;
     for (int i = tid; i < 1024; i += kDaThreads) s_mask[i] = 0u;
-    const bool count_scores = PASS == 1 && p.hist != nullptr;
+    const bool count_scores = PASS == 1 && p.topk.hist != nullptr;
+    if (PASS == 0)
+        for (int64_t i = (int64_t)blockIdx.x * kDaThreads + tid; i < p.topk.words; i += (int64_t)gridDim.x * kDaThreads) p.topk.hist[i] = 0u;
     if (count_scores)
         for (int i = tid; i < 2 * kTopkBins; i += kDaThreads) s_hist[i] = 0u;
     // K-anchored positions of this range: a list of up to 16 K entries is scanned whole (independent loads, one load
@@ -1973,8 +1976,8 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
     }
     if (count_scores) {
         __syncthreads();
-        uint32_t* hk = p.hist + (int64_t)bg * 2 * kTopkBins;
-        uint32_t* hv = p.hist + ((int64_t)gridDim.x / p.S + bg) * 2 * kTopkBins;     // V rows follow the B * Hkv K rows
+        uint32_t* hk = p.topk.hist + (int64_t)bg * 2 * kTopkBins;
+        uint32_t* hv = p.topk.hist + ((int64_t)gridDim.x / p.S + bg) * 2 * kTopkBins;     // V rows follow the B * Hkv K rows
         for (int i = tid; i < kTopkBins; i += kDaThreads) {
             if (s_hist[i]) atomicAdd(&hk[i], s_hist[i]);
             if (s_hist[kTopkBins + i]) atomicAdd(&hv[i], s_hist[kTopkBins + i]);
@@ -2090,7 +2093,7 @@ static hipError_t launch_decode_t(const Geom& g, const DecodeArgs& a, void* ws, 
         d.stat_part = (float*)(w + pl.off_stat); d.ans_k = a.ans_k; d.ans_v = a.ans_v;
         d.N = a.N; d.N_cap = a.N_cap; d.k_k = (int)a.k_k; d.c1 = p.c1; d.Hq = g.Hq; d.Hkv = g.Hkv; d.G = g.G;
         d.S = pl.S; d.chunk = pl.chunk;
-        d.hist = a.topk_hist;
+        d.topk = a.topk;
         const size_t sh2 = (size_t)(g.M < 16 ? 16 : g.M) * 256 * 16 + kNH * kD * 4 + kDaWaves * 32 + 64 + 4096 + 2 * kTopkBins * 4;
         static OncePerDevice once_ans;
         const hipError_t ans_setup = on_this_device(once_ans, [sh2]() {

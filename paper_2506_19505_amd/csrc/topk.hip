@@ -690,9 +690,11 @@ hipError_t launch_topk2(const float* scores, int32_t* idx, const float* scores_b
     return topk_select(scores, idx, scores_b, idx_b, n_rows, N, k, ws, st);
 }
 
-uint32_t* launch_topk2_begin(int64_t n_rows, int64_t N, void* ws, hipStream_t st)
+TopkCounts topk2_begin(int64_t n_rows, int64_t N, void* ws)
 {
-    return topk_in_rows_counted(2 * n_rows, N) ? nullptr : topk_clear(2 * n_rows, N, ws, st);
+    if (topk_in_rows_counted(2 * n_rows, N)) return {nullptr, 0};
+    const TopkPlan p = topk_plan(2 * n_rows, N);
+    return {(uint32_t*)((char*)ws + p.off_hist), (int64_t)(p.off_counts / 4)};    // histograms and headers
 }
 
 hipError_t launch_topk2_finish(const float* scores, int32_t* idx, const float* scores_b, int32_t* idx_b, int64_t n_rows,
