@@ -248,7 +248,7 @@ int antkv_kmeans_step(const antkv_geom* geom, const void* x, const float* w, int
     if (have_tokens) {
         const hipError_t e =
             g.C == kC ? launch_encode(g, (const half_t*)x, (int64_t)g.Hkv * n_tok * kD, n_tok * kD, kD, n_tok,
-                                      (const half_t*)codebook_in, codes, n_tok, 0, st)
+                                      (const half_t*)codebook_in, codes, n_tok, 0, st, kmeans_clear(g, n_tok, workspace))
                       : launch_encode12(g, (const half_t*)x, (int64_t)g.Hkv * n_tok * kD, n_tok * kD, kD, n_tok,
                                         (const half_t*)codebook_in, codes, n_tok, 0, st);
         if (e != hipSuccess) return ANTKV_ELAUNCH;

@@ -103,9 +103,14 @@ struct Geom {
     int code_bytes;   // bytes of one token's codes: M, or 3 M / 2 for packed 12-bit codes (6 for d = 32, 12 for d = 16)
 };
 
+// words that a kernel sets to zero beside its work, for one that follows it
+struct ClearWords {
+    uint32_t* at;
+    int64_t n;
+};
 hipError_t launch_encode(const Geom& g, const half_t* x, int64_t xs_b, int64_t xs_h, int64_t xs_t,
                          int64_t n_tok, const half_t* cb, uint8_t* codes, int64_t N_cap,
-                         int64_t token_offset, hipStream_t st);
+                         int64_t token_offset, hipStream_t st, ClearWords clear = {nullptr, 0});
 
 hipError_t launch_encode12(const Geom& g, const half_t* x, int64_t xs_b, int64_t xs_h, int64_t xs_t,
                            int64_t n_tok, const half_t* cb, uint8_t* codes, int64_t N_cap,
@@ -138,6 +143,7 @@ hipError_t launch_append(const Geom& g, const half_t* k_new, const half_t* v_new
 
 size_t anchor_score_workspace_bytes(const Geom& g, int64_t N, int64_t Nq);
 size_t kmeans_workspace_bytes(const Geom& g);
+ClearWords kmeans_clear(const Geom& g, int64_t n_tok, void* ws);   // what has to be zero before the update (256 centroids)
 hipError_t launch_kmeans_update(const Geom& g, const half_t* x, const float* w, int64_t n_tok, const half_t* cb_in,
                                 half_t* cb_out, const uint8_t* codes, float* wsum_out, double* objective, void* ws,
                                 hipStream_t st);

@@ -8,12 +8,15 @@
 // 1024).  It sorts a chunk's sub-vectors by their code into LDS (counting sort: the rank comes from the histogram's
 // fetch-add), every thread adds up a run of consecutive sorted tokens in registers, and the runs of a code meet without
 // atomics: a code that ends inside a thread's run has exactly one such thread, and a thread ends with exactly one code, so
-// both kinds of partial sums have slots of their own.  Totals stay in registers over the chunks; at the end one addition
-// per centroid and channel goes to the global sums with hardware float atomics.  Sums are fp32 and their order is not
-// fixed: results agree to fp32 rounding, not bit for bit, from run to run.
+// both kinds of partial sums have slots of their own.  Totals stay in registers over the chunks.  A workgroup that has a
+// sub-space to itself writes the new centroids from there; otherwise one addition per centroid and channel goes to the global
+// sums, which the encode kernel has cleared, with hardware float atomics, and km_finalize divides them.  (The ranges' sums as plain
+// stores that km_finalize adds up: d 16, 8 ranges, 3 us more; added up by the last workgroup to arrive 7 us more.)  Sums are fp32
+// and their order is not fixed: results agree to fp32 rounding, not bit for bit, from run to run.
 // The workgroups of one range's sub-spaces run on one XCD, since they read the same lines of x.  Bound: the latency of
 // the chain of six barriers per chunk (loads, ranks, sums and merge take about 6 us each).  Adding every product into LDS
-// with ds_add_f32, as before, runs at three clocks per lane: 8 heads x 32768 tokens (d8) 195 us, 38 now; sorting indices
+// with ds_add_f32, as before, runs at three clocks per lane: 8 heads x 32768 tokens (d8) 195 us, 38 now (a call, with the encode: 87, 83 without a launch that clears the sums; 500 tokens 22 and 17);
+// sorting indices
 // and gathering the sub-vectors from memory in sorted order thrashes the L2: 55 us.
 // With 4096 centroids (12-bit codes) a workgroup owns up to 512 centroids of one sub-space, picks their tokens out of all
 // codes and writes the new centroids itself (km_update12).
@@ -38,6 +41,25 @@ __global__ __launch_bounds__(256) void km_zero(uint32_t* a, int64_t n_a, uint32_
     else if (i < n_a + n_b) b[i - n_a] = 0u;
 }
 
+// no tokens: the codebook stays
+__global__ __launch_bounds__(256) void km_keep(const uint32_t* from, uint32_t* to, int64_t n, uint32_t* a, int64_t n_a, uint32_t* b, int64_t n_b)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) to[i] = from[i];
+    else if (i < n + n_a) a[i - n] = 0u;
+    else if (i < n + n_a + n_b) b[i - n - n_a] = 0u;
+}
+
+// The sums of several ranges, and what one range's workgroup writes itself
+struct KmOut {
+    float* sums;                                                // [Hkv][M][kC][DSUB]
+    float* wsum;                                                // [Hkv][M][kC]
+    double* obj;                                                // [Hkv][M]
+    half_t* cb;
+    float* wsum_out;                                            // optional
+    double* objective;                                          // optional
+};
+
 // LDS of km_accumulate: the sorted sub-vectors, weights and codes, later the last runs of the threads (row e at stride
 // kKsThreads + 1: neighbouring e fall on neighbouring banks); runs that ended inside a thread; the centroids
 constexpr size_t km_lds_sort(int d)
@@ -51,8 +73,7 @@ constexpr size_t km_lds(int d) { return km_lds_sort(d) + (size_t)kC * (d + 1) * 
 template <int DSUB>
 __global__ __launch_bounds__(kKsThreads, 4) void km_accumulate(
     const half_t* __restrict__ x, const float* __restrict__ w, const uint8_t* __restrict__ codes,
-    const half_t* __restrict__ cb, int64_t n_tok, int64_t total, int64_t range, int Hkv, int units, float* __restrict__ sums,
-    float* __restrict__ wsum, double* __restrict__ objective)
+    const half_t* __restrict__ cb, int64_t n_tok, int64_t total, int64_t range, int Hkv, int units, const KmOut out)
 {
     constexpr int M = kD / DSUB, NV = DSUB + 1;                 // values of a run: DSUB sums and the weight
     constexpr int kPer = ks_per(DSUB), kChunk = ks_chunk(DSUB), kStride = kKsThreads + 1;
@@ -72,6 +93,7 @@ __global__ __launch_bounds__(kKsThreads, 4) void km_accumulate(
     const int unit = (int)(blockIdx.x / (8 * M)) * 8 + (int)(blockIdx.x & 7), m = (int)(blockIdx.x >> 3) % M;
     if (unit >= units) return;
     const int g = unit % Hkv;
+    const bool alone = units == Hkv;                            // one range
     const int64_t j_lo = (int64_t)(unit / Hkv) * range;         // tokens are counted over all sequences
     const int64_t j_hi = total - j_lo < range ? total : j_lo + range;
 
@@ -187,17 +209,41 @@ __global__ __launch_bounds__(kKsThreads, 4) void km_accumulate(
     for (int off = 1; off < 64; off <<= 1) obj += __shfl_xor(obj, off, 64);
     if (lane == 0) s_obj[wave] = obj;
     __syncthreads();
-    if (tid == 0 && objective) {
+    const int64_t gm = (int64_t)g * M + m;
+    if (tid == 0) {
         double o = 0.0;
         for (int i = 0; i < kKsThreads / 64; ++i) o += s_obj[i];
-        unsafeAtomicAdd(objective + (int64_t)g * M + m, o);
+        if (!alone) unsafeAtomicAdd(out.obj + gm, o);
+        else if (out.objective) out.objective[gm] = o;
     }
-    float* gs = sums + ((int64_t)g * M + m) * kC * DSUB;
-    float* gw = wsum + ((int64_t)g * M + m) * kC;
+    if (!alone) {
+        float* gs = out.sums + gm * kC * DSUB;
+        float* gw = out.wsum + gm * kC;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const int i = tid + k * kKsThreads;
+            if (i < kC * NV && sum[k] != 0.f) unsafeAtomicAdd(i < kC * DSUB ? gs + i : gw + (i - kC * DSUB), sum[k]);
+        }
+        return;
+    }
+    // weighted means; a centroid without assigned weight keeps its old value
+    float* s_ws = s_end;                                        // [kC] weights
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
         const int i = tid + k * kKsThreads;
-        if (i < kC * NV && sum[k] != 0.f) unsafeAtomicAdd(i < kC * DSUB ? gs + i : gw + (i - kC * DSUB), sum[k]);
+        if (i >= kC * DSUB && i < kC * NV) {
+            s_ws[i - kC * DSUB] = sum[k];
+            if (out.wsum_out) out.wsum_out[gm * kC + i - kC * DSUB] = sum[k];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = tid + k * kKsThreads;
+        if (i < kC * DSUB) {
+            const float ws = s_ws[i / DSUB];
+            out.cb[gm * kC * DSUB + i] = ws > 0.f ? (half_t)(sum[k] / ws) : cb[gm * kC * DSUB + i];
+        }
     }
 }
 
@@ -392,11 +438,9 @@ __global__ __launch_bounds__(kKwThreads) void km_update12(
     }
 }
 
-// weighted means; a centroid without assigned weight keeps its old value
+// the same from the sums of several ranges
 template <int DSUB>
-__global__ __launch_bounds__(256) void km_finalize(const float* __restrict__ sums, const float* __restrict__ wsum,
-                                                   const half_t* __restrict__ cb_in, half_t* __restrict__ cb_out,
-                                                   float* __restrict__ wsum_out, int64_t n_centroids)
+__global__ __launch_bounds__(256) void km_finalize(const half_t* __restrict__ cb_in, const KmOut out, int64_t n_centroids)
 {
     // a thread takes up to 8 channels of one centroid, so that neighbouring threads touch neighbouring memory
     constexpr int PER = DSUB < 8 ? DSUB : 8, PARTS = DSUB / PER;
@@ -404,11 +448,12 @@ __global__ __launch_bounds__(256) void km_finalize(const float* __restrict__ sum
     const int64_t i = t / PARTS;                                         // (g, m, c) flattened
     const int part = (int)(t % PARTS);
     if (i >= n_centroids) return;
-    const float ws = wsum[i];
-    if (wsum_out && part == 0) wsum_out[i] = ws;
+    const float ws = out.wsum[i];
+    if (out.wsum_out && part == 0) out.wsum_out[i] = ws;
+    if (out.objective && part == 0 && i % kC == 0) out.objective[i / kC] = out.obj[i / kC];
 #pragma unroll
     for (int e = PER * part; e < PER * part + PER; ++e)
-        cb_out[i * DSUB + e] = ws > 0.f ? (half_t)(sums[i * DSUB + e] / ws) : cb_in[i * DSUB + e];
+        out.cb[i * DSUB + e] = ws > 0.f ? (half_t)(out.sums[i * DSUB + e] / ws) : cb_in[i * DSUB + e];
 }
 
 struct KmPlan {
@@ -426,32 +471,36 @@ KmPlan km_plan(const Geom& g)
     return p;
 }
 
+// tokens of a workgroup: about two workgroups per CU; a range is whole chunks, since every range adds 256 x (DSUB + 1) values to
+// the sums
+int64_t km_range(const Geom& g, int64_t n_tok)
+{
+    const int64_t total = (int64_t)g.B * n_tok, pairs = (int64_t)g.Hkv * g.M, chunk = ks_chunk(g.d);
+    return ((total * pairs + 511) / 512 + chunk - 1) / chunk * chunk;
+}
+
 template <int DSUB>
 hipError_t launch_t(const Geom& g, const half_t* x, const float* w, int64_t n_tok, const half_t* cb_in, half_t* cb_out,
                     const uint8_t* codes, float* wsum_out, double* objective, char* ws, hipStream_t st)
 {
-    const KmPlan p = km_plan(g);
-    float* sums = (float*)(ws + p.off_sums);
-    float* wsum = (float*)(ws + p.off_wsum);
-    double* obj = objective ? objective : (double*)(ws + p.off_obj);
-    const int64_t n_zero = (int64_t)(p.total / 4), n_obj = objective ? (int64_t)g.Hkv * g.M * 2 : 0;
-    hipLaunchKernelGGL(km_zero, dim3((unsigned)((n_zero + n_obj + 255) / 256)), dim3(256), 0, st, (uint32_t*)ws, n_zero,
-                       (uint32_t*)objective, n_obj);
-    if (n_tok > 0) {
-        static OncePerDevice once;
-        const hipError_t setup = allow_lds(once, (const void*)km_accumulate<DSUB>, km_lds(DSUB));
-        if (setup != hipSuccess) return setup;
-        // about two workgroups per CU; a range is whole chunks, since every range adds 256 x (DSUB + 1) values to the sums
-        const int64_t total = (int64_t)g.B * n_tok, pairs = (int64_t)g.Hkv * g.M, chunk = ks_chunk(DSUB);
-        int64_t range = ((total * pairs + 511) / 512 + chunk - 1) / chunk * chunk;
-        const int64_t units = (total + range - 1) / range * g.Hkv;
-        hipLaunchKernelGGL(km_accumulate<DSUB>, dim3((unsigned)((units + 7) / 8 * 8 * g.M)), dim3(kKsThreads), km_lds(DSUB), st,
-                           x, w, codes, cb_in, n_tok, total, range, g.Hkv, (int)units, sums, wsum, obj);
+    if (n_tok == 0) {
+        const int64_t n_cb = (int64_t)g.Hkv * kD * kC / 2, n_w = wsum_out ? (int64_t)g.Hkv * g.M * kC : 0, n_obj = objective ? (int64_t)g.Hkv * g.M * 2 : 0;
+        hipLaunchKernelGGL(km_keep, dim3((unsigned)((n_cb + n_w + n_obj + 255) / 256)), dim3(256), 0, st, (const uint32_t*)cb_in,
+                           (uint32_t*)cb_out, n_cb, (uint32_t*)wsum_out, n_w, (uint32_t*)objective, n_obj);
+        return hipGetLastError();
     }
-    const int64_t n_cen = (int64_t)g.Hkv * g.M * g.C;
-    const int64_t n_fin = n_cen * (DSUB < 8 ? 1 : DSUB / 8);
-    hipLaunchKernelGGL(km_finalize<DSUB>, dim3((unsigned)((n_fin + 255) / 256)), dim3(256), 0, st, sums, wsum, cb_in,
-                       cb_out, wsum_out, n_cen);
+    const KmPlan p = km_plan(g);
+    const KmOut out = {(float*)(ws + p.off_sums), (float*)(ws + p.off_wsum), (double*)(ws + p.off_obj), cb_out, wsum_out, objective};
+    static OncePerDevice once;
+    const hipError_t setup = allow_lds(once, (const void*)km_accumulate<DSUB>, km_lds(DSUB));
+    if (setup != hipSuccess) return setup;
+    const int64_t total = (int64_t)g.B * n_tok, range = km_range(g, n_tok), units = (total + range - 1) / range * g.Hkv;
+    hipLaunchKernelGGL(km_accumulate<DSUB>, dim3((unsigned)((units + 7) / 8 * 8 * g.M)), dim3(kKsThreads), km_lds(DSUB), st,
+                       x, w, codes, cb_in, n_tok, total, range, g.Hkv, (int)units, out);
+    if (units > g.Hkv) {
+        const int64_t n_cen = (int64_t)g.Hkv * g.M * kC, n_fin = n_cen * (DSUB < 8 ? 1 : DSUB / 8);
+        hipLaunchKernelGGL(km_finalize<DSUB>, dim3((unsigned)((n_fin + 255) / 256)), dim3(256), 0, st, cb_in, out, n_cen);
+    }
     return hipGetLastError();
 }
 
@@ -479,7 +528,13 @@ hipError_t launch_wide(const Geom& g, const half_t* x, const float* w, int64_t n
 
 size_t kmeans_workspace_bytes(const Geom& g) { return km_plan(g).total; }
 
-// codes [B][Hkv][n_tok][code bytes] must already hold the assignment of x to cb_in
+ClearWords kmeans_clear(const Geom& g, int64_t n_tok, void* ws)
+{
+    if ((int64_t)g.B * n_tok <= km_range(g, n_tok)) return {nullptr, 0};       // one range: no sums to share
+    return {(uint32_t*)ws, (int64_t)(km_plan(g).total / 4)};
+}
+
+// codes [B][Hkv][n_tok][code bytes] must already hold the assignment of x to cb_in, and kmeans_clear's words be zero
 hipError_t launch_kmeans_update(const Geom& g, const half_t* x, const float* w, int64_t n_tok, const half_t* cb_in,
                                 half_t* cb_out, const uint8_t* codes, float* wsum_out, double* objective, void* ws,
                                 hipStream_t st)

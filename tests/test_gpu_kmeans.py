@@ -61,6 +61,23 @@ def test_kmeans_step_ranges_and_skew(oracle, d, B, Hkv, n):
     _compare(oracle, x, _weights(8, (B, Hkv, n)), cb, d)
 
 
+@pytest.mark.parametrize("d,n", [(4, 2048), (4, 2049), (8, 2048), (8, 2049), (16, 1024), (16, 1025)])
+def test_kmeans_step_one_range_and_two(oracle, d, n):
+    """As many tokens as one workgroup per sub-space takes, and one more; the workspace holds NaN on entry, optional outputs or not."""
+    _, x, _ = make_qkv(76, 1, 1, 1, n, 1, 128, want_v=False)
+    cb = make_codebooks(76, x, d, 256, "k", max_sample=1024)
+    w = _weights(9, (1, 1, n))
+    want = _compare(oracle, x, w, cb, d)
+    lib, g = antkv.load_library(), antkv.Geometry(1, 1, 1, d).c()
+    ws = torch.full(((lib.antkv_kmeans_step_workspace(ctypes.byref(g)) + 3) // 4,), float("nan"), device="cuda")
+    xd, wd, cbd, out, codes = dev(x), dev(w), dev(cb), torch.empty_like(want), torch.empty((1, 1, n, 128 // d), dtype=torch.uint8, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert lib.antkv_kmeans_step(ctypes.byref(g), p(xd), p(wd), n, p(cbd), p(out), p(codes), None, None, p(ws), ws.numel() * 4, None) == 0
+    torch.cuda.synchronize()
+    # two fp32 sums in different orders, each rounded to fp16: one fp16 spacing apart at most
+    assert ((out.float() - want.float()).abs() <= want.float().abs() * 2.0 ** -10 + 2.0 ** -24).all()
+
+
 def test_kmeans_zero_weights_and_no_tokens_keep_the_codebook(oracle):
     _, x, _ = make_qkv(72, 1, 2, 2, 500, 1, 128, want_v=False)
     cb = make_codebooks(72, x, 8, 256, "k", max_sample=500)
