@@ -1,7 +1,8 @@
 // Causal attention over the prompt (paper Sec. 2.1) that also writes the softmax row statistics which the
 // Anchor Score pass consumes (Alg. 1, first step: attention extended to return row maximum and row sum).
 //
-// A workgroup is 8 waves = G heads of a KV head's group x 8/G query tiles of 32 (4 x 2, 2 x 4 or 1 x 8).  Its waves share
+// A workgroup is 8 waves = G heads of a KV head's group x 8/G query tiles of 32 (4 x 2, 2 x 4 or 1 x 8), or 4 waves and half the
+// query tiles: short prompts leave CUs idle or end with their longest rows, which then take half as long.  Its waves share
 // the 32-key tiles of K and V, which go from global memory straight into LDS (16 bytes per lane, no registers), four
 // tiles of each in flight or in use.
 //   scores   S^T tile (keys on the MFMA row axis, queries on the column axis): lane (n, kh) owns query n and
@@ -25,20 +26,21 @@ namespace antkv {
 
 namespace {
 
-constexpr int kPaWaves = 8;
-constexpr int kPaThreads = kPaWaves * 64;
 constexpr int kRing = 4;                                // tiles of K, and of V, in LDS
 constexpr float kPMax = 12.f;
+constexpr int64_t kPaMany = 384;                        // workgroups of eight waves from which they are used
 constexpr float kMasked = -INFINITY;                    // a score that takes no part
 
 __device__ __forceinline__ float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-__global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
+template <int NW>                                       // waves of a workgroup: 8 or 4
+__global__ __launch_bounds__(NW * 64, 2) void prefill_attn_kernel(
     const half_t* __restrict__ q, const half_t* __restrict__ k, const half_t* __restrict__ v, int64_t N, int64_t Nq,
     float c1, half_t* __restrict__ out, float* __restrict__ row_max, float* __restrict__ row_sum, int Hq, int Hkv, int G,
     int q_blocks)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char s_kv[2 * kRing * kTileBytes];     // K ring, V ring
+    constexpr int kParts = 8 / NW;                                 // pieces of 1 KB of a tile that a wave moves
     lds_byte* lds = (lds_byte*)s_kv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // scalar, so that per-wave conditions are scalar branches
@@ -46,7 +48,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     const int bgs = gridDim.x / q_blocks;                          // B * Hkv
     const int bg = blockIdx.x % bgs, b = bg / Hkv, g = bg % Hkv;   // (heads fastest: 8 heads, one per XCD)
     const int64_t qblk = q_blocks - 1 - blockIdx.x / bgs;          // longest rows first
-    const int q_tiles = kPaWaves / G;                              // query tiles of the workgroup
+    const int q_tiles = NW / G;                                    // query tiles of the workgroup
     const int64_t q0 = (qblk * q_tiles + wave / G) * 32;
     const int h = g * G + wave % G;
     const int64_t qi = q0 + n;
@@ -59,14 +61,22 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     const half_t* kbase = k + (int64_t)bg * N * kD;
     const half_t* vbase = v + (int64_t)bg * N * kD;
 
-    // staging: wave w moves rows 4 w .. 4 w + 3 of a tile, a lane the chunk that belongs at its place of the 1 KB; rows
+    // staging: a wave moves kParts x 4 rows of a tile, a lane the chunk that belongs at its place of the 1 KB; rows
     // past the end repeat the last one, tiles past the end the last tile
     const int last_tile = (int)((N - 1) >> 5);
-    const uint32_t soff = stage_off(wave, lane, 31), soff_last = stage_off(wave, lane, (int)(N - 1) & 31);
-    const uint32_t to0 = (uint32_t)(uintptr_t)lds + wave * 1024;
+    uint32_t soff[kParts], soff_last[kParts];
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) {
+        soff[i] = stage_off(wave * kParts + i, lane, 31);
+        soff_last[i] = stage_off(wave * kParts + i, lane, (int)(N - 1) & 31);
+    }
+    const uint32_t to0 = (uint32_t)(uintptr_t)lds + wave * (kParts * 1024);
     auto stage = [&](const half_t* base, int tile, uint32_t slot) {
         const int tc = tile < last_tile ? tile : last_tile;
-        load_to_lds16((const unsigned char*)base + (int64_t)tc * kTileBytes, tc == last_tile ? soff_last : soff, to0 + slot * kTileBytes);
+#pragma unroll
+        for (int i = 0; i < kParts; ++i)
+            load_to_lds16((const unsigned char*)base + (int64_t)tc * kTileBytes, tc == last_tile ? soff_last[i] : soff[i],
+                          to0 + slot * kTileBytes + 1024 * i);
     };
     // operand addresses inside a tile: K row n, channels 16 s + 8 kh .. + 7; V transposed: inside a 16-lane block, lane
     // 4 e + c reads key row e of the lane's four, channels 4 c .. 4 c + 3 of 16; blocks 0/1 cover the two channel halves
@@ -89,7 +99,8 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
     for (int i = 0; i < 4; ++i) stage(kbase, i, i);
     for (int i = 0; i < 2; ++i) stage(vbase, i, kRing + i);
     // the V slot of "tile -1" is multiplied with zero probabilities: it has to be finite
-    *(uint4_t*)(s_kv + (2 * kRing - 1) * kTileBytes + tid * 16) = uint4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) *(uint4_t*)(s_kv + (2 * kRing - 1) * kTileBytes + (i * NW * 64 + tid) * 16) = uint4_t{0u, 0u, 0u, 0u};
     half8_t tq[8];
     {
         const half_t* qp = q + (((int64_t)b * Hq + h) * Nq + qrow) * kD + 8 * kh;
@@ -192,7 +203,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
         }
         l_run += sum[0] + sum[1];
         if (__builtin_expect(moves, 0)) rescale(alpha);
-        landed_but<4>();                                            // this step's two loads and the last one's
+        landed_but<4 * kParts>();                                   // this step's two tiles and the last one's
     };
     // Whole groups of four tiles are interleaved; up to three more go one after the other, so that the loop has one end with
     // the registers in the same roles (four ends spill).  No tile past the wave's last is touched: its V rows, which no
@@ -230,12 +241,12 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
 #pragma unroll
         for (int i = 0; i < 8; ++i) sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(k_op(i, (t + 1) & 3), tq[i], sc[0], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        landed_but<4>();
+        landed_but<4 * kParts>();
     }
     last_product(t);
     for (; t < n_tiles; ++t) {                                      // waves that are done keep staging for the others
         stage_ahead(t);
-        landed_but<4>();
+        landed_but<4 * kParts>();
     }
     wait_all_loads();                                               // nothing may land in LDS after the workgroup's end
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
@@ -265,9 +276,17 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(
 hipError_t launch_prefill_attn(const Geom& g, const half_t* q, const half_t* k, const half_t* v, int64_t N, int64_t Nq,
                                float scale, half_t* out, float* row_max, float* row_sum, hipStream_t st)
 {
-    const int64_t qspan = 32 * (kPaWaves / g.G), q_blocks = (Nq + qspan - 1) / qspan;
-    hipLaunchKernelGGL(prefill_attn_kernel, dim3((unsigned)(q_blocks * g.B * g.Hkv)), dim3(kPaThreads), 0, st, q, k, v, N, Nq,
-                       scale * kLog2e, out, row_max, row_sum, g.Hq, g.Hkv, g.G, (int)q_blocks);
+    const int64_t pairs = (int64_t)g.B * g.Hkv;
+    auto blocks = [&](int nw) { const int64_t span = 32 * (nw / g.G); return (Nq + span - 1) / span; };
+#define ANTKV_PA(NW)                                                                                                       \
+    hipLaunchKernelGGL(prefill_attn_kernel<NW>, dim3((unsigned)(blocks(NW) * pairs)), dim3(NW * 64), 0, st, q, k, v, N, Nq, scale * kLog2e, \
+                       out, row_max, row_sum, g.Hq, g.Hkv, g.G, (int)blocks(NW))
+    // Twice the workgroups read K and V twice as often.  32 heads, 8 and 4 waves, by workgroups of 8: 64 (500 tokens) 19.1 and 14.7 us,
+    // 128 29.5 and 22.9, 192 41.2 and 34.5, 256 33.5 and 29.7, 320 69.8 and 63.7, 376 161 and 150, 384 52.0 and 52.2, 512 136 and 140,
+    // 640 123 and 119, 1024 271 and 272, 2048 560 and 580.
+    if (blocks(8) * pairs < kPaMany) ANTKV_PA(4);
+    else ANTKV_PA(8);
+#undef ANTKV_PA
     return hipGetLastError();
 }
 

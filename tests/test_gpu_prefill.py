@@ -127,3 +127,24 @@ def test_prefill_attn_rejects_bad_arguments():
     assert call(scale=0.0) != 0
     assert call(q=ctypes.c_void_p(x.data_ptr() + 2)) != 0
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(47, 8, 8, 70, 70), (48, 8, 8, 70, 70), (95, 16, 4, 33, 33), (96, 16, 4, 33, 33), (1, 16, 8, 289, 130),
+                                           (96, 8, 4, 129, 97), (1, 4, 1, 1, 1)])
+def test_prefill_either_workgroup_size(B, Hq, Hkv, N, Nq):
+    """Workgroups of four waves up to 383 of eight, of eight from there; groups of 1, 2 and 4, ragged tiles, queries behind a
+    cached prefix; against float64.  Bounds: fp16 weights and output, 2^-11 each, 1e-4 for the rest; statistics as fp32 gives them."""
+    gen = torch.Generator(device="cuda").manual_seed(N + B)
+    rnd = lambda *s: torch.randn(s, dtype=torch.float16, device="cuda", generator=gen)
+    q, k, v, scale = rnd(B, Hq, Nq, 128), rnd(B, Hkv, N, 128), rnd(B, Hkv, N, 128), 128 ** -0.5
+    out, row_max, row_sum = antkv.prefill_attn(antkv.Geometry(B, Hq, Hkv, 8), q, k, v, scale)
+    kx, vx = (t.double().repeat_interleave(Hq // Hkv, dim=1) for t in (k, v))
+    s = scale * (q.double() @ kx.transpose(2, 3).contiguous())
+    s = s.masked_fill(torch.arange(N, device="cuda")[None, :] > torch.arange(N - Nq, N, device="cuda")[:, None], -float("inf"))
+    m = s.amax(-1)
+    e = torch.exp(s - m[..., None])
+    want = (e @ vx) / e.sum(-1, keepdim=True)
+    err = ((out.double() - want).norm(dim=-1) / want.norm(dim=-1)).max().item()
+    print(f"B{B} {Hq}/{Hkv} {Nq} of {N}: {err:.2e}")
+    assert err <= 2.0 ** -10 + 1e-4
+    assert (row_max.double() - m).abs().max().item() <= 1e-5 and ((row_sum.double() / e.sum(-1)) - 1).abs().max().item() <= 1e-4
