@@ -112,6 +112,7 @@ __global__ __launch_bounds__(kAsThreads) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_cur[r] = 0.f;
         if (head_on && k_lo < k_hi) acc_cur = tile_dot_lds_a(s_k[0], tq, n, kh);   // rows = keys, cols = queries
+        __syncthreads();                                            // the first step writes tile 2 over the tile that has just been read
         int buf = 0;                                                // buffer of tile t
         for (int64_t kt = k_lo; kt < k_end; kt += 32) {
             const bool more = kt + 64 < k_end;
