@@ -244,11 +244,20 @@ __global__ __launch_bounds__(256) void ans_finalize_stats(
 // Bound: VALU issue, per element one fma, one exp2 (8 clocks), one add and two fma (2.6 each).  32768 x 32768, 32 heads:
 // 8.8 ms with tiles staged through registers and 32 keys per wave, 5.4 ms now.
 // -------------------------------------------------------------------------------------------------
-template <int KT, int NW>
+// SPLIT: few keys leave CUs idle while a workgroup walks all heads and queries; `splits` workgroups then take a part of the steps
+// each, and the last of a key block to arrive adds up their fp64 sums.
+struct ColSplit {
+    int splits;
+    double* sums;                                               // [splits][V, K][B * Hkv][N]
+    unsigned long long* done;                                   // [key blocks][B * Hkv] arrival words: launch tag << 32 | arrivals
+    unsigned int tag;
+};
+
+template <int KT, int NW, bool SPLIT>
 __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     const half_t* __restrict__ q, const half_t* __restrict__ k, int64_t N, int64_t Nq, float c1,
     const float* __restrict__ stat, float* __restrict__ ans_k, float* __restrict__ ans_v, int Hq, int Hkv, int G,
-    int64_t n_bg, int q_tiles)
+    int64_t n_bg, int q_tiles, const ColSplit sp)
 {
     constexpr int kRing = 4, kParts = 8 / NW;                   // pieces of 1 KB of a query tile per wave
     constexpr int kStatBytes = kStatTile * 4;
@@ -258,7 +267,12 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, kh = lane >> 5;
     const int bg = (int)(blockIdx.x % n_bg), b = bg / Hkv, g = bg % Hkv;    // (heads fastest: 8 heads, one per XCD)
-    const int64_t kblk0 = (int64_t)(blockIdx.x / n_bg) * (32 * KT * NW);    // the first keys have the most queries: longest first
+    const int64_t rest = blockIdx.x / n_bg, kblk = SPLIT ? rest / sp.splits : rest;
+    const int part = SPLIT ? (int)(rest % sp.splits) : 0;
+    const int64_t kblk0 = kblk * (32 * KT * NW);                            // the first keys have the most queries: longest first
+    // (an arrival word of another launch, or of this one if it is replayed, is swapped by whoever gets there first)
+    unsigned long long seen = 0ull;
+    if (SPLIT && tid == 0) seen = __hip_atomic_load(&sp.done[kblk * n_bg + bg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t k0 = kblk0 + wave * (32 * KT);                            // first key of this wave
     half8_t tk[KT][8];
 #pragma unroll
@@ -272,8 +286,11 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     int64_t i_first = kblk0 - (N - Nq);
     if (i_first < 0) i_first = 0;
     const int qt_first = (int)(i_first >> 5);
-    const int n_qt = q_tiles - qt_first, n_steps = n_qt * G;     // query tiles per head; step = (head of the group, query tile)
-    const int64_t head0 = (int64_t)b * Hq + (int64_t)g * G;
+    const int n_qt = q_tiles - qt_first, all_steps = n_qt * G;   // query tiles per head; step = (head of the group, query tile)
+    const int step0 = SPLIT ? (int)((int64_t)all_steps * part / sp.splits) : 0;
+    const int n_steps = (SPLIT ? (int)((int64_t)all_steps * (part + 1) / sp.splits) : all_steps) - step0;    // (a part may be empty)
+    const int qt_0 = SPLIT ? step0 % n_qt : 0;                   // query tile of the first step
+    const int64_t head0 = (int64_t)b * Hq + (int64_t)g * G + (SPLIT ? step0 / n_qt : 0);
 
     uint32_t soff[kParts], soff_last[kParts];
 #pragma unroll
@@ -285,10 +302,10 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     // the steps are staged in order: from tile to tile, from a head's last tile to the next head's first, and behind the
     // last step the last tile again with the neutral statistics
     const int64_t q_wrap = Nq * (kD * 2) - (int64_t)(n_qt - 1) * kTileBytes, s_wrap = (int64_t)(qt_first + 1) * kStatBytes;
-    const unsigned char* q_ptr = (const unsigned char*)(q + (head0 * Nq + (int64_t)qt_first * 32) * kD);
-    const unsigned char* s_ptr = (const unsigned char*)(stat + (head0 * q_tiles + qt_first) * kStatTile);
+    const unsigned char* q_ptr = (const unsigned char*)(q + (head0 * Nq + (int64_t)(qt_first + qt_0) * 32) * kD);
+    const unsigned char* s_ptr = (const unsigned char*)(stat + (head0 * q_tiles + qt_first + qt_0) * kStatTile);
     const unsigned char* s_none = (const unsigned char*)(stat + (n_bg / Hkv) * Hq * q_tiles * kStatTile);
-    int q_left = n_steps, s_left = n_steps, q_row = n_qt, s_row = n_qt;      // steps to stage, tiles left of the head
+    int q_left = n_steps, s_left = n_steps, q_row = n_qt - qt_0, s_row = n_qt - qt_0;      // steps to stage, tiles left of the head
     auto stage_q = [&](uint32_t slot) {
         const bool last = q_row == 1;
 #pragma unroll
@@ -320,6 +337,9 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
 #pragma unroll
         for (int s = 0; s < 8; ++s) pin(tk[kt][s]);
     wait_all_loads();
+    if (SPLIT && tid == 0 && ((unsigned int)(seen >> 32) != sp.tag || (unsigned int)seen >= (unsigned int)sp.splits))
+        __hip_atomic_compare_exchange_strong(&sp.done[kblk * n_bg + bg], &seen, (unsigned long long)sp.tag << 32, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     float16_t sc[2][KT];
 #pragma unroll
@@ -337,7 +357,7 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     double sum_v[KT], sum_k[KT];
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) sum_v[kt] = sum_k[kt] = 0.0;
-    int qt = 0;                                                  // query tile of the current step
+    int qt = qt_0;                                               // query tile of the current step
     const int rel0 = (int)(N - Nq + (int64_t)qt_first * 32 - k0);   // position of tile 0's first query minus this wave's first key
 
     auto step = [&](auto phase) __attribute__((always_inline)) { // a step whose number is T mod 4
@@ -409,6 +429,31 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     if (left > 1) step(std::integral_constant<int, 1>{});
     if (left > 2) step(std::integral_constant<int, 2>{});
     wait_all_loads();                                            // nothing may land in LDS after the workgroup's end
+    if constexpr (SPLIT) {
+        static_assert(KT == 1, "a key per lane");
+        double v = sum_v[0] + __shfl_xor(sum_v[0], 32, 64), kk = sum_k[0] + __shfl_xor(sum_k[0], 32, 64);
+        const int64_t key = k0 + n, plane = n_bg * N, at = (int64_t)bg * N + key;
+        const bool on = kh == 0 && key < N;
+        if (on) {                                                // device-scope stores: the last workgroup may sit on another die
+            __hip_atomic_store(sp.sums + 2 * part * plane + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(sp.sums + (2 * part + 1) * plane + at, kk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_s_waitcnt(0);                           // acknowledged before the workgroup arrives
+        __syncthreads();
+        int* s_last = (int*)s_mem;
+        if (tid == 0)
+            *s_last = (int)(unsigned int)__hip_atomic_fetch_add(&sp.done[kblk * n_bg + bg], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+        __syncthreads();
+        if (*s_last != sp.splits || !on) return;
+        v = kk = 0.0;
+        for (int i = 0; i < sp.splits; ++i) {
+            v += __hip_atomic_load(sp.sums + 2 * i * plane + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            kk += __hip_atomic_load(sp.sums + (2 * i + 1) * plane + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        ans_v[at] = (float)v;
+        ans_k[at] = (float)kk;
+        return;
+    }
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {                            // lanes l and l+32 hold complementary query rows of the same key
         const double ov = __shfl_xor(sum_v[kt], 32, 64), ok = __shfl_xor(sum_k[kt], 32, 64);
@@ -690,14 +735,32 @@ __global__ __launch_bounds__(kWinThreads, kWinPerCu) void ans_window_cols(
     }
 }
 
+constexpr int kColKeys = 128;                                   // keys of the small workgroups of phase 2
+
+// Workgroups that share the steps of a key block.  Unsplit, the first block's workgroup walks every query of every head, 0.27 us a step,
+// while most CUs have nothing: 32 heads of 8 KV heads, whole selection, unsplit and as below: 500 tokens 41 and 23 us, 1200 79 and 30,
+// 3000 179 and 80, 7000 422 and 288, 16000 1443 and 1351.  A part costs some 8 us besides its steps, so that it has at least 16 of them;
+// short walks are split up to 512 blocks (one query head per KV head, 2 x 32 heads, 640 blocks of at most 38 steps: 40 us, in halves
+// 48; 320 blocks 33 and 31), longer ones up to 2048, into more than four parts below 128 blocks (3 x 8 heads, 240 blocks:
+// quarters 52 us, eighths 58; 80 blocks 35 and 30).
+int col_splits(int64_t blocks, int64_t n_steps)
+{
+    const int most = blocks < 128 ? 8 : 4;
+    const int64_t few = n_steps >= 128 ? 2048 : 512;
+    int s = 1;
+    while (s < most && blocks * s < few && n_steps >= 32 * s) s *= 2;
+    return s;
+}
+
 struct AsPlan {
+    int splits;                                                 // workgroups that share the heads of a key block, phase 2
     int steps;                                                  // 0, or what the window kernels take
     int KS;
     int64_t keys_per_split;
-    size_t off_part, off_stat, off_ans_k, off_ans_v, total;
+    size_t off_done, off_part, off_stat, off_ans_k, off_ans_v, total;
 };
 
-AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
+AsPlan plan(const Geom& g, int64_t N, int64_t Nq, bool room)
 {
     AsPlan p;
     const int64_t n_steps = g.G * ((Nq + 31) / 32), n_bg = (int64_t)g.B * g.Hkv;
@@ -723,7 +786,13 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
         p.keys_per_split = 32 * tiles;
         p.KS = (int)((n_tiles + tiles - 1) / tiles);
     }
-    const size_t rows = (size_t)g.B * g.Hq * Nq, part = align_up(rows * p.KS * 2 * sizeof(float));
+    const int64_t blocks = (N + kColKeys - 1) / kColKeys;
+    p.splits = room && !p.steps ? col_splits(blocks * n_bg, n_steps) : 1;
+    // phase 1's partials, or phase 2's: they are done with when phase 2 starts
+    const size_t rows = (size_t)g.B * g.Hq * Nq, sums = (size_t)p.splits * 2 * n_bg * N * sizeof(double);
+    size_t part = align_up(rows * p.KS * 2 * sizeof(float));
+    if (p.splits > 1 && part < align_up(sums) + align_up(blocks * n_bg * 8)) part = align_up(sums) + align_up(blocks * n_bg * 8);
+    p.off_done = align_up(sums);
     size_t off = 0;
     p.off_part = off; off += p.steps ? 0 : part;
     p.off_stat = off; off += align_up(((size_t)g.B * g.Hq * ((Nq + 31) / 32) + 1) * kStatTile * sizeof(float));
@@ -739,14 +808,14 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq)
 
 }  // namespace
 
-size_t anchor_score_workspace_bytes(const Geom& g, int64_t N, int64_t Nq) { return plan(g, N, Nq).total; }
+size_t anchor_score_workspace_bytes(const Geom& g, int64_t N, int64_t Nq, bool room) { return plan(g, N, Nq, room).total; }
 
 // ans_k / ans_v may be NULL: the scores then live in the workspace at the offsets of the plan.
 hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, int64_t N, int64_t Nq, float scale,
-                               const float* row_max, const float* row_sum, float* ans_k, float* ans_v, void* ws,
+                               const float* row_max, const float* row_sum, float* ans_k, float* ans_v, void* ws, bool room,
                                hipStream_t st)
 {
-    const AsPlan p = plan(g, N, Nq);
+    const AsPlan p = plan(g, N, Nq, room);
     char* w = (char*)ws;
     float* part = (float*)(w + p.off_part);
     float* stat = (float*)(w + p.off_stat);
@@ -779,12 +848,14 @@ hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, 
     // 64 keys per wave (the query tiles and statistics are read once for two key tiles) while that fills the chip and the
     // walk over the queries is long beside loading the keys (131072 keys, 32 queries: 92 us against 80); smaller workgroups
     // otherwise
-#define ANTKV_CR(KT, NW)                                                                                                  \
-    hipLaunchKernelGGL((ans_col_reduce<KT, NW>), dim3((unsigned)((N + 32 * KT * NW - 1) / (32 * KT * NW) * n_bg)), dim3(NW * 64), \
-                       0, st, q, k, N, Nq, c1, stat, ans_k, ans_v, g.Hq, g.Hkv, g.G, n_bg, (int)q_tiles)
+    const ColSplit split = {p.splits, (double*)part, (unsigned long long*)(w + p.off_part + p.off_done), p.splits > 1 ? next_launch_tag() : 0u};
+#define ANTKV_CR(KT, NW, SPLIT)                                                                                           \
+    hipLaunchKernelGGL((ans_col_reduce<KT, NW, SPLIT>), dim3((unsigned)((N + 32 * KT * NW - 1) / (32 * KT * NW) * n_bg * (SPLIT ? p.splits : 1))), \
+                       dim3(NW * 64), 0, st, q, k, N, Nq, c1, stat, ans_k, ans_v, g.Hq, g.Hkv, g.G, n_bg, (int)q_tiles, split)
     if (p.steps) ANTKV_WIN_STEPS(ans_window_cols, stat, ans_k, ans_v);
-    else if (Nq > 256 && (N + 511) / 512 * n_bg >= 512) ANTKV_CR(2, 8);
-    else ANTKV_CR(1, 4);
+    else if (p.splits > 1) ANTKV_CR(1, kColKeys / 32, true);
+    else if (Nq > 256 && (N + 511) / 512 * n_bg >= 512) ANTKV_CR(2, 8, false);
+    else ANTKV_CR(1, 4, false);
 #undef ANTKV_CR
 #undef ANTKV_WIN_STEPS
 #undef ANTKV_WIN

@@ -32,11 +32,12 @@ struct SelPlan {
     size_t off_score, off_topk, total;
 };
 
-SelPlan sel_plan(const Geom& g, int64_t N, int64_t Nq, int64_t k)
+// room: what the call can use; otherwise what it does not refuse
+SelPlan sel_plan(const Geom& g, int64_t N, int64_t Nq, int64_t k, bool room)
 {
     SelPlan p;
     p.off_score = 0;
-    p.off_topk = align_up(anchor_score_workspace_bytes(g, N, Nq));
+    p.off_topk = align_up(anchor_score_workspace_bytes(g, N, Nq, room));
     p.total = p.off_topk + align_up(topk_workspace_bytes(2 * (int64_t)g.B * g.Hkv, N, k));   // K and V rows in one go
     return p;
 }
@@ -220,7 +221,7 @@ size_t antkv_anchor_select_workspace(const antkv_geom* geom, int64_t N, int64_t 
 {
     Geom g;
     if (check_geom(geom, g) || N <= 0 || Nq <= 0 || Nq > N || k < 0) return 0;
-    return sel_plan(g, N, Nq, k).total;
+    return sel_plan(g, N, Nq, k, true).total;
 }
 
 size_t antkv_kmeans_step_workspace(const antkv_geom* geom)
@@ -288,17 +289,18 @@ int antkv_anchor_select(const antkv_geom* geom, const void* q, const void* k_fp1
     if (!q || !k_fp16) return ANTKV_EINVAL;
     if (misaligned(q, 16) || misaligned(k_fp16, 16)) return ANTKV_EINVAL;
     if (!(scale > 0.f)) return ANTKV_EINVAL;
-    const SelPlan sp = sel_plan(g, N, Nq, k);
+    const bool room = workspace_bytes >= sel_plan(g, N, Nq, k, true).total;
+    const SelPlan sp = sel_plan(g, N, Nq, k, room);
     if (!workspace || misaligned(workspace, 256) || workspace_bytes < sp.total) return ANTKV_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     char* w = (char*)workspace;
     // scores default to the tail of the score workspace
-    const size_t as_bytes = anchor_score_workspace_bytes(g, N, Nq);
+    const size_t as_bytes = anchor_score_workspace_bytes(g, N, Nq, room);
     const size_t score_bytes = align_up((size_t)g.B * g.Hkv * N * sizeof(float));
     float* sk = ans_k ? ans_k : (float*)(w + as_bytes - 2 * score_bytes);
     float* sv = ans_v ? ans_v : (float*)(w + as_bytes - score_bytes);
     hipError_t e = launch_anchor_score(g, (const half_t*)q, (const half_t*)k_fp16, N, Nq, scale, row_max, row_sum, sk, sv,
-                                       w + sp.off_score, st);
+                                       w + sp.off_score, room, st);
     if (e != hipSuccess) return ANTKV_ELAUNCH;
     const int64_t rows = (int64_t)g.B * g.Hkv;
     if (idx_k && idx_v && k > 0) {

@@ -141,7 +141,7 @@ hipError_t launch_append(const Geom& g, const half_t* k_new, const half_t* v_new
                          uint8_t* codes_k, uint8_t* codes_v, int64_t N_cap, int32_t* idx_k, half_t* rows_k, int64_t k_k,
                          int32_t* idx_v, half_t* rows_v, int64_t k_v, int64_t N, int W, hipStream_t st);
 
-size_t anchor_score_workspace_bytes(const Geom& g, int64_t N, int64_t Nq);
+size_t anchor_score_workspace_bytes(const Geom& g, int64_t N, int64_t Nq, bool room);    // room: what it can use, not the least
 size_t kmeans_workspace_bytes(const Geom& g);
 ClearWords kmeans_clear(const Geom& g, int64_t n_tok, void* ws);   // what has to be zero before the update (256 centroids)
 hipError_t launch_kmeans_update(const Geom& g, const half_t* x, const float* w, int64_t n_tok, const half_t* cb_in,
@@ -151,7 +151,7 @@ hipError_t launch_prefill_attn(const Geom& g, const half_t* q, const half_t* k, 
                                float scale, half_t* out, float* row_max, float* row_sum, hipStream_t st);
 hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, int64_t N, int64_t Nq,
                                float scale, const float* row_max, const float* row_sum,
-                               float* ans_k, float* ans_v, void* ws, hipStream_t st);
+                               float* ans_k, float* ans_v, void* ws, bool room, hipStream_t st);
 
 struct DecodeArgs {
     const half_t* q;

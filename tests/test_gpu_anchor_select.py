@@ -1,4 +1,6 @@
 """GPU parity: Anchor Score (paper Eq. (4)) + selection against the CPU oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -154,3 +156,32 @@ def test_row_statistics_of_every_call(B, Hq, Hkv, N, Nq):
         _, _, *got = antkv.anchor_select(antkv.Geometry(B, Hq, Hkv, 8), q, k, 128 ** -0.5, 4)
         for a, b in zip(got, want):
             assert ((a.double() - b).abs() / b).max().item() <= 3e-5
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(1, 4, 1, 257, 257), (1, 4, 1, 500, 500), (1, 8, 2, 1201, 1201), (1, 16, 8, 1031, 1031), (3, 8, 8, 1025, 1025),
+                                           (2, 16, 8, 700, 650), (1, 32, 8, 2100, 2100), (1, 4, 1, 1000, 255)])
+def test_column_sums_in_parts(B, Hq, Hkv, N, Nq):
+    """Key blocks whose steps are dealt to two, four and eight workgroups, parts without a step among them, against one workgroup per
+    block, which a workspace without room for the parts' sums leaves.  The parts' sums are fp64: the fp32 scores differ by their
+    last rounding at most."""
+    gen = torch.Generator(device="cuda").manual_seed(N + Hq)
+    rnd = lambda *s: torch.randn(s, dtype=torch.float16, device="cuda", generator=gen)
+    q, k, lib = rnd(B, Hq, Nq, 128), rnd(B, Hkv, N, 128), antkv.load_library()
+    g = antkv.Geometry(B, Hq, Hkv, 8).c()
+    need = lib.antkv_anchor_select_workspace(ctypes.byref(g), N, Nq, 0)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    res, want = [], _scores64(q, k, 128 ** -0.5)
+    for cut in (0, 256):
+        ws = torch.full((need // 4,), float("nan"), device="cuda")
+        for _ in range(3):                                     # (on what the call before left, too)
+            ans = [torch.full((B, Hkv, N), float("nan"), device="cuda") for _ in range(2)]
+            rc = lib.antkv_anchor_select(ctypes.byref(g), p(q), p(k), N, Nq, 128 ** -0.5, 0, None, None, p(ans[0]), p(ans[1]), None, None,
+                                         p(ws), need - cut, None)
+            if cut and rc == 3:                                # (phase 1's partials are larger than the parts' sums)
+                return
+            assert rc == 0
+            for a, b in zip(ans, want):
+                assert ((a.double() - b).abs() / b).max().item() <= 3e-5
+        res.append(ans)
+    for a, b in zip(*res):
+        assert ((a - b).abs() <= 2.0 ** -23 * b.abs()).all()
