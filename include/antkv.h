@@ -105,6 +105,8 @@ int antkv_encode(const antkv_geom* geom, const void* x, int64_t xs_b, int64_t xs
  *            by position; equal scores resolve to the lower position.  0 <= k <= N.
  *            Either may be NULL to skip that selection.
  * Scores are accumulated in fp64 and rounded once to fp32; selection compares those fp32 values.
+ * For short contexts the workspace includes fp64 partial sums of the scores; a smaller one that holds everything else is not
+ * refused, the call then takes longer.
  */
 size_t antkv_anchor_select_workspace(const antkv_geom* geom, int64_t N, int64_t Nq, int64_t k);
 int antkv_anchor_select(const antkv_geom* geom, const void* q, const void* k_fp16, int64_t N,
@@ -179,7 +181,8 @@ int antkv_decode_attn(const antkv_geom* geom, const void* q, float scale, const 
  *   ANTKV_DECODE_WIDE_TABLE   Score range (see "Precision" at antkv_decode_attn).  The q . centroid table carries a
  *       second, residual entry per (code, sub-space): 30-bit instead of 15-bit fixed point, which lifts the limit on R_h
  *       for d_sub 8 and 16 at the price of a second table walk per token (about a quarter more time per step).
- *       d_sub 4 has no room for the second entry and ignores the bit; the 12-bit formats have 16-bit entries throughout.
+ *       d_sub 4 has no room for the second entry and ignores the bit; the 12-bit formats have 16-bit entries, and short
+ *       contexts of them no table.
  */
 #define ANTKV_DECODE_FIXED_ORDER 1
 #define ANTKV_DECODE_WIDE_TABLE 2

@@ -15,9 +15,9 @@
 // and their order is not fixed: results agree to fp32 rounding, not bit for bit, from run to run.
 // The workgroups of one range's sub-spaces run on one XCD, since they read the same lines of x.  Bound: the latency of
 // the chain of six barriers per chunk (loads, ranks, sums and merge take about 6 us each).  Adding every product into LDS
-// with ds_add_f32, as before, runs at three clocks per lane: 8 heads x 32768 tokens (d8) 195 us, 38 now (a call, with the encode: 87, 83 without a launch that clears the sums; 500 tokens 22 and 17);
-// sorting indices
-// and gathering the sub-vectors from memory in sorted order thrashes the L2: 55 us.
+// with ds_add_f32, as before, runs at three clocks per lane: 8 heads x 32768 tokens (d8) 195 us, 38 now (a call, with the encode:
+// 87, 84 without a launch that clears the sums; 500 tokens 22 and 17); sorting indices and gathering the sub-vectors from memory in
+// sorted order thrashes the L2: 55 us.
 // With 4096 centroids (12-bit codes) a workgroup owns up to 512 centroids of one sub-space, picks their tokens out of all
 // codes and writes the new centroids itself (km_update12).
 #include "common.h"
