@@ -660,3 +660,28 @@ def test_kmeans12_iterations_descend(oracle, books):
         hist.append(obj.cpu().numpy().sum())
     assert all(b <= a * (1 + 1e-4) for a, b in zip(hist, hist[1:])), hist
     assert hist[-1] < 0.9 * hist[0], hist
+
+
+def test_decode12_short_ranges_replayed(books):
+    """A captured step, replayed: the arrival words still hold the launch's own tag from the replay before."""
+    B, Hq, Hkv, N, k = 1, 8, 2, 1500, 20
+    gen = torch.Generator(device="cuda").manual_seed(21)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes = [_pack12_dev(torch.randint(0, C, (B, Hkv, N, books.M), device="cuda", generator=gen)) for _ in range(2)]
+    cb = [rnd(Hkv, books.M, C, books.d) for _ in range(2)]
+    idx = [torch.rand((B, Hkv, N), device="cuda", generator=gen).argsort(dim=-1)[..., :k].sort(dim=-1).values.int().contiguous() for _ in range(2)]
+    q, rows = rnd(B, Hq, 128), [rnd(B, Hkv, k, 128) for _ in range(2)]
+    geom, out = antkv.Geometry(B, Hq, Hkv, books.d, n_centroids=C), torch.empty((B, Hq, 128), dtype=torch.float16, device="cuda")
+    ws = antkv.DecodeWorkspace(geom, N, k, k, 0, "cuda")
+    step = lambda o: antkv.decode_attn(geom, q, 128 ** -0.5, *codes, *cb, idx[0], rows[0], idx[1], rows[1], out=o, workspace=ws)
+    step(out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(out)
+    for _ in range(6):
+        q.copy_(rnd(B, Hq, 128))
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, step(torch.empty_like(out)))
