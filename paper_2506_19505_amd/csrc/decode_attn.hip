@@ -1731,7 +1731,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
                 float s = 0.f;
 #pragma unroll
                 for (int t = 0; t < DSUB; ++t) s = fmaf(s_qf[h * kD + m * DSUB + t], cf[t], s);
-                o[h] = s * p.c1;
+                o[h] = h < p.G ? s * p.c1 : 0.f;                 // (a centroid with an infinity times no head is not 0)
             }
 #pragma unroll
             for (int c = 0; c < SLOTS / M; ++c) s_lut[(m >> 4) * 4096 + (e & 255) * 16 + (m & 15) + M * c] = o;
@@ -1795,7 +1795,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
     for (int h = 0; h < kNH; ++h) { m_run[h] = kNegBig; l_run[h] = 0.f; }
 
     // No branches over the heads, so that their exponentials are in flight together: pass 1 gives a head that the group does not
-    // have weight 0, and what a masked lane adds is 0.
+    // have, whose scores are 0 whatever the keys hold, weight 0, and what a masked lane adds is 0.
     if (PASS == 1) {
 #pragma unroll
         for (int h = 0; h < kNH; ++h) lse[h] = h < p.G ? lse[h] : -kNegBig;
@@ -1941,7 +1941,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
                 float d = 0.f;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) d = fmaf(qv[h][e], (float)v[e], d);
-                s[h] = row16_sum(d) * p.c1;
+                s[h] = h < p.G ? row16_sum(d) * p.c1 : 0.f;
             }
             consume(s, tok, 0u, tok >= 0 && l16 == 0);
         };

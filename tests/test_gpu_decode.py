@@ -327,6 +327,34 @@ def test_decode_time_anchor_score_without_key_anchors(oracle, k_v):
         check_index_sets(got.cpu().numpy(), wi, margin, "re-selection")
 
 
+@pytest.mark.parametrize("d", [4, 8, 16])
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_decode_time_anchor_score_of_an_infinite_key(oracle, d, G):
+    """An anchored key, or centroid, with an infinity that every head scores -inf weighs nothing: both its scores are 0 and the other
+    tokens' are those beside a key so far off that its weight is 0 in float64.  Heads that the group does not have add nothing."""
+    B, Hkv, N, k, at = 1, 2, 900, 9, 4
+    c = _cache_from_kv(oracle, 60 + G, B, G * Hkv, Hkv, N, d, k, 5)
+    c["q"][..., 0] = 1 + np.abs(c["q"][..., 0])
+    geom = antkv.Geometry(B, G * Hkv, Hkv, d)
+    c["rk"][:, :, at, 0] = -60000
+    _, (_, want) = _run_decode(oracle, c, geom, 1 / np.sqrt(128), want_ans=True)
+    assert (np.take_along_axis(want["ans_v"], c["ik"].astype(np.int64), axis=2)[:, :, at] == 0).all()
+    t = {n: dev(a) for n, a in c.items()}
+    t["rk"][:, :, at, 0] = -float("inf")
+    out, ans_k, ans_v, *_ = antkv.decode_attn(geom, t["q"], 1 / np.sqrt(128), t["ck"], t["cv"], t["cbk"], t["cbv"], t["ik"], t["rk"], t["iv"],
+                                              t["rv"], want_ans=True)
+    assert torch.isfinite(out).all()
+    np.testing.assert_allclose(ans_v.cpu().numpy(), want["ans_v"], rtol=3e-5, atol=1e-12)
+    np.testing.assert_allclose(ans_k.cpu().numpy(), want["ans_k"], rtol=3e-5, atol=1e-12)
+    c["cbk"][:, 0, c["ck"][0, 0, 5, 0], 0] = -60000            # (the codes' table: the attention itself has none for such a centroid)
+    _, (_, want) = _run_decode(oracle, c, geom, 1 / np.sqrt(128), want_ans=True)
+    t["cbk"] = dev(np.where(c["cbk"] == -60000, np.float16(-np.inf), c["cbk"]))
+    _, ans_k, ans_v, *_ = antkv.decode_attn(geom, t["q"], 1 / np.sqrt(128), t["ck"], t["cv"], t["cbk"], t["cbv"], t["ik"], t["rk"], t["iv"],
+                                            t["rv"], want_ans=True)
+    np.testing.assert_allclose(ans_v.cpu().numpy(), want["ans_v"], rtol=3e-5, atol=1e-12)
+    np.testing.assert_allclose(ans_k.cpu().numpy(), want["ans_k"], rtol=3e-5, atol=1e-12)
+
+
 def test_extreme_context_reselection(oracle):
     """Config 4: 840000-token context at 0.5 bit, decode step plus anchor re-selection of 8400 tokens."""
     w = CONFIGS["cfg4"]
