@@ -239,6 +239,11 @@ __global__ __launch_bounds__(kThreads) void decode_short_kernel(const ShortParam
             }
         // ---- values: slab s is channels 16 s .. + 15; a lane asks for 8 bytes (piece tq) of token 16 u + 4 kg + tj
         wait_all_loads();
+        if (n - base < kTile) {                                     // rows behind the last token: whatever their code names, zeros
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (4 * i + kg >= n - base) *(uint4_t*)(smem + Lds::rows + wave * kTileBytes + 1024 * i + 16 * lane) = uint4_t{0u, 0u, 0u, 0u};
+        }
         uint32_t at[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {

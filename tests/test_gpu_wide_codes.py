@@ -662,6 +662,26 @@ def test_kmeans12_iterations_descend(oracle, books):
     assert hist[-1] < 0.9 * hist[0], hist
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N", [(1, 4, 1, 1), (2, 2, 2, 45), (1, 8, 2, 3007), (1, 8, 8, 20001)])
+def test_decode12_short_ranges_unused_codes_of_anchors(books, B, Hq, Hkv, N):
+    """The newest tokens are in the V list and their codes, which nothing has written, name a centroid with infinities that no other
+    token uses: they are ignored, also behind the last token of a tile that is not full.  Bound as in test_decode12_short_ranges."""
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    W = min(N, 32)
+    codes_k, codes_v = (torch.randint(0, C - 1, (B, Hkv, N, books.M), device="cuda", generator=gen) for _ in range(2))
+    codes_k[:, :, N - W:] = codes_v[:, :, N - W:] = C - 1
+    cb_k, cb_v = rnd(Hkv, books.M, C, books.d), rnd(Hkv, books.M, C, books.d)
+    cb_v[:, :, C - 1] = float("inf")
+    idx = torch.arange(N - W, N, dtype=torch.int32, device="cuda").expand(B, Hkv, W).contiguous()
+    q, rows_k, rows_v = rnd(B, Hq, 128), rnd(B, Hkv, W, 128), rnd(B, Hkv, W, 128)
+    got = antkv.decode_attn(antkv.Geometry(B, Hq, Hkv, books.d, n_centroids=C), q, 128 ** -0.5, _pack12_dev(codes_k), _pack12_dev(codes_v),
+                            cb_k, cb_v, idx, rows_k, idx, rows_v).double()
+    assert torch.isfinite(got).all()
+    want, _ = _decode_exact(q, 128 ** -0.5, codes_k, codes_v, cb_k, cb_v, idx, rows_k, idx, rows_v)
+    assert ((got - want).norm(dim=-1) / want.norm(dim=-1)).max().item() <= 2.0 ** -10 + 1e-4
+
+
 def test_decode12_short_ranges_replayed(books):
     """A captured step, replayed: the arrival words still hold the launch's own tag from the replay before."""
     B, Hq, Hkv, N, k = 1, 8, 2, 1500, 20
