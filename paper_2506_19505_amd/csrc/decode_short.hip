@@ -28,7 +28,6 @@ namespace {
 
 constexpr int kThreads = 512, kWaves = kThreads / 64;
 constexpr int kTile = 32;               // tokens of a wave's tile
-constexpr float kPShift = 8.0f;         // weights are kept scaled by 2^8 so that small ones stay normal in fp16
 
 struct Lds {
     static constexpr int rows = 0;                                  // [waves][32 rows of 256 bytes]
@@ -215,7 +214,7 @@ __global__ __launch_bounds__(kThreads) void decode_short_kernel(const ShortParam
         }
         m_tile = fmaxf(m_tile, __shfl_xor(m_tile, 16, 64));
         m_tile = fmaxf(m_tile, __shfl_xor(m_tile, 32, 64));
-        const float m_new = fmaxf(m_ref, m_tile - kPShift);
+        const float m_new = fmaxf(m_ref, m_tile - kPShift12);
         if (tile != wave) {
             const float alpha = fast_exp2(m_ref - m_new);
             l_sum *= alpha;

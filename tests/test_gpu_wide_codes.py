@@ -682,6 +682,30 @@ def test_decode12_short_ranges_unused_codes_of_anchors(books, B, Hq, Hkv, N):
     assert ((got - want).norm(dim=-1) / want.norm(dim=-1)).max().item() <= 2.0 ** -10 + 1e-4
 
 
+@pytest.mark.parametrize("N", [32, 1000])
+@pytest.mark.parametrize("gap", [24.5, 26.1, 28.25, 30.5])
+def test_decode12_short_ranges_small_weights(books, N, gap):
+    """One token whose value is zero outweighs every other one by 2^gap (test_decode12_small_weights_beside_a_large_one): 2^-11 for the
+    output, half a unit of the smallest fp16 weights (2^-36 of the large one), 2e-4 for exponentials and fp32 sums."""
+    B, Hkv, M, at = 1, 2, books.M, 7
+    codes_k = torch.zeros((B, Hkv, N, M), dtype=torch.int64, device="cuda")
+    codes_v = torch.ones_like(codes_k)
+    cb_k = torch.zeros((Hkv, M, C, books.d), dtype=torch.float16, device="cuda")
+    cb_v = torch.zeros_like(cb_k)
+    cb_k[:, 0, 1, 0] = gap
+    cb_v[:, :, 1] = 30000
+    codes_k[:, :, at, 0], codes_v[:, :, at] = 1, 0
+    q = torch.zeros((B, Hkv, 128), dtype=torch.float16, device="cuda")
+    q[..., 0] = 1
+    real = float(cb_k[0, 0, 1, 0])
+    got = antkv.decode_attn(antkv.Geometry(B, Hkv, Hkv, books.d, n_centroids=C), q, float(np.log(2)), _pack12_dev(codes_k),
+                            _pack12_dev(codes_v), cb_k, cb_v, None, None, None, None).double()
+    want = 30000 * (N - 1) / (2.0 ** real + N - 1)
+    err = ((got - want) / want).abs().max().item()
+    print(f"d{books.d} N={N} 2^{gap}: {err:.2e}")
+    assert err <= 2.0 ** -11 + 2e-4 + 2.0 ** (gap - 37)
+
+
 def test_decode12_short_ranges_replayed(books):
     """A captured step, replayed: the arrival words still hold the launch's own tag from the replay before."""
     B, Hq, Hkv, N, k = 1, 8, 2, 1500, 20
