@@ -186,13 +186,15 @@ __global__ __launch_bounds__(kAsThreads) __attribute__((amdgpu_waves_per_eu(4, 4
 
 // merge key splits -> c_i = m + log2(l); also ||Q_i||_2.  One 16-lane group per (b, h, i).  Written as tiles of 32 rows,
 // {-c_i x 32, ||Q_i|| x 32}; rows past Nq and one tile behind the last hold {-inf, 0}, which makes their weights zero.
+// Clears the arrival counters of phase 2, too.
 constexpr int kStatTile = 64;
 
 __global__ __launch_bounds__(256) void ans_finalize_stats(
     const half_t* __restrict__ q, const float* __restrict__ part, int KS, const float* __restrict__ row_max,
-    const float* __restrict__ row_sum, float* __restrict__ stat, int64_t Nq, int q_tiles, int64_t n_heads)
+    const float* __restrict__ row_sum, float* __restrict__ stat, int64_t Nq, int q_tiles, int64_t n_heads, const ClearWords clear)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = t; i < clear.n; i += (int64_t)gridDim.x * blockDim.x) clear.at[i] = 0u;
     const int64_t slot = t >> 4;                                 // padded row
     const int part_i = (int)(t & 15);
     const int64_t head = slot / ((int64_t)q_tiles * 32), i = slot - head * q_tiles * 32;
@@ -249,8 +251,7 @@ __global__ __launch_bounds__(256) void ans_finalize_stats(
 struct ColSplit {
     int splits;
     double* sums;                                               // [splits][V, K][B * Hkv][N]
-    unsigned long long* done;                                   // [key blocks][B * Hkv] arrival words: launch tag << 32 | arrivals
-    unsigned int tag;
+    uint32_t* done;                                             // [key blocks][B * Hkv] arrivals, cleared by ans_finalize_stats
 };
 
 template <int KT, int NW, bool SPLIT>
@@ -270,9 +271,6 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
     const int64_t rest = blockIdx.x / n_bg, kblk = SPLIT ? rest / sp.splits : rest;
     const int part = SPLIT ? (int)(rest % sp.splits) : 0;
     const int64_t kblk0 = kblk * (32 * KT * NW);                            // the first keys have the most queries: longest first
-    // (an arrival word of another launch, or of this one if it is replayed, is swapped by whoever gets there first)
-    unsigned long long seen = 0ull;
-    if (SPLIT && tid == 0) seen = __hip_atomic_load(&sp.done[kblk * n_bg + bg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t k0 = kblk0 + wave * (32 * KT);                            // first key of this wave
     half8_t tk[KT][8];
 #pragma unroll
@@ -337,9 +335,6 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
 #pragma unroll
         for (int s = 0; s < 8; ++s) pin(tk[kt][s]);
     wait_all_loads();
-    if (SPLIT && tid == 0 && ((unsigned int)(seen >> 32) != sp.tag || (unsigned int)seen >= (unsigned int)sp.splits))
-        __hip_atomic_compare_exchange_strong(&sp.done[kblk * n_bg + bg], &seen, (unsigned long long)sp.tag << 32, __ATOMIC_RELAXED,
-                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     float16_t sc[2][KT];
 #pragma unroll
@@ -442,7 +437,7 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
         __syncthreads();
         int* s_last = (int*)s_mem;
         if (tid == 0)
-            *s_last = (int)(unsigned int)__hip_atomic_fetch_add(&sp.done[kblk * n_bg + bg], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+            *s_last = (int)__hip_atomic_fetch_add(&sp.done[kblk * n_bg + bg], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
         __syncthreads();
         if (*s_last != sp.splits || !on) return;
         v = kk = 0.0;
@@ -756,7 +751,7 @@ struct AsPlan {
     int splits;                                                 // workgroups that share the heads of a key block, phase 2
     int steps;                                                  // 0, or what the window kernels take
     int KS;
-    int64_t keys_per_split;
+    int64_t keys_per_split, n_done;
     size_t off_done, off_part, off_stat, off_ans_k, off_ans_v, total;
 };
 
@@ -788,11 +783,18 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq, bool room)
     }
     const int64_t blocks = (N + kColKeys - 1) / kColKeys;
     p.splits = room && !p.steps ? col_splits(blocks * n_bg, n_steps) : 1;
-    // phase 1's partials, or phase 2's: they are done with when phase 2 starts
+    // phase 1's partials, or phase 2's: the former are done with when phase 2 starts.  The arrival counters lie behind both, since they
+    // are cleared while phase 1's are read.
     const size_t rows = (size_t)g.B * g.Hq * Nq, sums = (size_t)p.splits * 2 * n_bg * N * sizeof(double);
     size_t part = align_up(rows * p.KS * 2 * sizeof(float));
-    if (p.splits > 1 && part < align_up(sums) + align_up(blocks * n_bg * 8)) part = align_up(sums) + align_up(blocks * n_bg * 8);
-    p.off_done = align_up(sums);
+    p.n_done = p.splits > 1 ? blocks * n_bg : 0;
+    if (p.splits > 1) {
+        if (part < align_up(sums)) part = align_up(sums);
+        p.off_done = part;
+        part += align_up(p.n_done * sizeof(uint32_t));
+    } else {
+        p.off_done = 0;
+    }
     size_t off = 0;
     p.off_part = off; off += p.steps ? 0 : part;
     p.off_stat = off; off += align_up(((size_t)g.B * g.Hq * ((Nq + 31) / 32) + 1) * kStatTile * sizeof(float));
@@ -843,12 +845,12 @@ hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, 
     }
     const int64_t q_tiles = (Nq + 31) / 32, n_heads = (int64_t)g.B * g.Hq;
     const int64_t padded = (n_heads * q_tiles + 1) * 32;
+    const ColSplit split = {p.splits, (double*)part, (uint32_t*)(w + p.off_part + p.off_done)};
     hipLaunchKernelGGL(ans_finalize_stats, dim3((unsigned)((padded * 16 + 255) / 256)), dim3(256), 0, st, q, part, p.KS,
-                       row_max, row_sum, stat, Nq, (int)q_tiles, n_heads);
+                       row_max, row_sum, stat, Nq, (int)q_tiles, n_heads, ClearWords{split.done, p.n_done});
     // 64 keys per wave (the query tiles and statistics are read once for two key tiles) while that fills the chip and the
     // walk over the queries is long beside loading the keys (131072 keys, 32 queries: 92 us against 80); smaller workgroups
     // otherwise
-    const ColSplit split = {p.splits, (double*)part, (unsigned long long*)(w + p.off_part + p.off_done), p.splits > 1 ? next_launch_tag() : 0u};
 #define ANTKV_CR(KT, NW, SPLIT)                                                                                           \
     hipLaunchKernelGGL((ans_col_reduce<KT, NW, SPLIT>), dim3((unsigned)((N + 32 * KT * NW - 1) / (32 * KT * NW) * n_bg * (SPLIT ? p.splits : 1))), \
                        dim3(NW * 64), 0, st, q, k, N, Nq, c1, stat, ans_k, ans_v, g.Hq, g.Hkv, g.G, n_bg, (int)q_tiles, split)

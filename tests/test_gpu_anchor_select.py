@@ -185,3 +185,25 @@ def test_column_sums_in_parts(B, Hq, Hkv, N, Nq):
         res.append(ans)
     for a, b in zip(*res):
         assert ((a - b).abs() <= 2.0 ** -23 * b.abs()).all()
+
+
+def test_column_sums_in_parts_on_any_workspace():
+    """Pairs of small integers, as index lists and counters leave them, where the arrival counters lie: the result is that of a
+    workspace of zeros, bit for bit (the parts are added up in their order)."""
+    B, Hq, Hkv, N = 1, 8, 2, 1201
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    q, k = (torch.randn((B, h, N, 128), dtype=torch.float16, device="cuda", generator=gen) for h in (Hq, Hkv))
+    lib, g = antkv.load_library(), antkv.Geometry(B, Hq, Hkv, 8).c()
+    need = lib.antkv_anchor_select_workspace(ctypes.byref(g), N, N, 0)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    ws, word = torch.zeros((need // 8,), dtype=torch.int64, device="cuda"), torch.arange(need // 8, device="cuda") % 16
+    ans, want = ([torch.empty((B, Hkv, N), device="cuda") for _ in range(2)] for _ in range(2))
+    call = lambda out: lib.antkv_anchor_select(ctypes.byref(g), p(q), p(k), N, N, 128 ** -0.5, 0, None, None, p(out[0]), p(out[1]), None, None,
+                                               p(ws), need, None)
+    assert call(want) == 0
+    wrong = torch.zeros((), dtype=torch.int64, device="cuda")
+    for high in range(0, 4096, 16):
+        ws.copy_((high + word) << 32 | 1 + word % 3)
+        assert call(ans) == 0
+        wrong += sum((a != b).sum() for a, b in zip(ans, want))
+    assert wrong.item() == 0
