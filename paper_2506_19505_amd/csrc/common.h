@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/antkv.h"
+#include "launch_tag.h"
 #include "once_per_device.h"
 
 namespace antkv {
@@ -185,7 +186,6 @@ inline int64_t token_ranges(int64_t pairs, int64_t N)
     return S < 1 ? 1 : S;
 }
 size_t decode_workspace_bytes(const Geom& g, int64_t N, int64_t k_k, int64_t k_v, bool want_ans);
-unsigned int next_launch_tag();        // unique within the process, never 0: marks the arrival words of one launch
 hipError_t launch_decode_attn(const Geom& g, const DecodeArgs& a, void* ws, hipStream_t st);
 // scores_out fp32 = scale * log2(e) * q_h . RoPE_{pos0 + j}(K_eff[j]) for the group's heads (K_eff: the FP16 anchor row or the
 // centroids of the codes), in the layout that DecodeArgs::given_scores describes

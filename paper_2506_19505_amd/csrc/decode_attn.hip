@@ -243,8 +243,8 @@ struct DaParams {
     half_t* out;                // [B][Hq][kD]
     int32_t* info;              // [B][Hkv][k_k + k_v] cross membership of the anchor entries, filled in the prologue:
                                 // K entry: its slot in the V list or -1; V entry: 1 if the token is a K anchor too (skipped), else 0
-    unsigned long long* done;   // [B][Hkv] arrival words (launch tag << 32 | count); the last workgroup of a (b, g) merges
-    unsigned int tag;           // this launch's tag: words carrying another tag count as zero, so no clearing pass
+    unsigned long long* done;   // [B][Hkv] arrival words (launch_tag.h); the last workgroup of a (b, g) merges
+    uint64_t tag;               // this launch's tag: words carrying another tag count as zero, so no clearing pass
     int64_t N, N_cap;
     int k_k, k_v;
     float c1;                   // scale * log2(e)
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
     // anchor entries are processed in tiles dealt round-robin over the S workgroups: K tiles of 16 entries, then V tiles of 32
     const int ntk = (p.k_k + 15) >> 4, ntv = (p.k_v + 31) >> 5;
     const int n_atiles = ntk + ntv;
-    // Arrival word of this (b, g): (launch tag << 32 | arrivals).  A word left by an earlier launch (another tag,
+    // Arrival word of this (b, g): launch tag and arrivals.  A word left by an earlier launch (another tag,
     // or this tag with all S arrivals when a captured launch is replayed) is replaced by (tag, 0) now, by
     // whichever workgroup gets there first, so that the arrival at the end is a single fetch-add.  Launches
     // that share a workspace do not overlap, hence nobody of an earlier launch still touches the word.
@@ -562,9 +562,9 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
         for (int i = tid; i < L::mask_words; i += kDaThreads) s_mask[i] = 0u;
         if (tid == 0) s_misc[8] = kDaWaves;                      // next stream tile to hand out (wave w starts with tile w)
         lds_barrier();
-        if (tid == 0 && ((unsigned int)(done_seen >> 32) != p.tag || (unsigned int)done_seen >= (unsigned int)p.S))
-            __hip_atomic_compare_exchange_strong(&p.done[bg], &done_seen, (unsigned long long)p.tag << 32, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0 && arrivals_are_stale(done_seen, p.tag, (uint32_t)p.S))
+            __hip_atomic_compare_exchange_strong(&p.done[bg], &done_seen, (unsigned long long)p.tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
         // bitmap of anchored tokens in this range
         const uint32_t range_len = (uint32_t)(t1 - t0);
         if (lists_in_lds) {
@@ -1495,7 +1495,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_attn_kernel(const DaParams 
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (tid == 0)
-        s_misc[10] = (int)(unsigned int)__hip_atomic_fetch_add(&p.done[bg], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+        s_misc[10] = (int)(__hip_atomic_fetch_add(&p.done[bg], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kArrivalMask) + 1;
     __syncthreads();
     if (s_misc[10] == p.S) {
         auto ld = [](const float* q) { return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
@@ -2022,16 +2022,6 @@ size_t decode_workspace_bytes(const Geom& g, int64_t N, int64_t k_k, int64_t k_v
 
 // process-wide option mask of antkv_set_decode_options (see the MODE parameter of decode_attn_kernel)
 static std::atomic<int> g_options{0};
-
-// Launch tags are unique within the process (a wrap after 2^32 launches could only matter for a workspace
-// last used exactly 2^32 launches earlier); 0 is never handed out.
-unsigned int next_launch_tag()
-{
-    static std::atomic<unsigned int> counter{1u};
-    unsigned int t = counter.fetch_add(1u, std::memory_order_relaxed);
-    if (t == 0u) t = counter.fetch_add(1u, std::memory_order_relaxed);
-    return t;
-}
 
 template <int DSUB>
 static hipError_t launch_decode_t(const Geom& g, const DecodeArgs& a, void* ws, hipStream_t st)

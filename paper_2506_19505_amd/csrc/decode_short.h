@@ -16,9 +16,9 @@ struct ShortParams {
     const int32_t *idx_k, *idx_v;
     const half_t *rows_k, *rows_v;
     half_t* out;
-    unsigned long long* done;           // [B][Hkv] arrival words: launch tag << 32 | arrivals
+    unsigned long long* done;           // [B][Hkv] arrival words (launch_tag.h)
     float* part;                        // [B][Hq][S][kD + 2]: sums, reference, sum of weights
-    unsigned int tag;
+    uint64_t tag;
     int64_t N, N_cap;
     int k_k, k_v;
     float c1;                           // scale * log2(e)
@@ -33,6 +33,6 @@ struct ShortPlan {
 };
 
 ShortPlan short_plan(const Geom& g, int64_t N);
-hipError_t launch_decode_short(const Geom& g, const ShortPlan& pl, const DecodeArgs& a, void* ws, unsigned int tag, hipStream_t st);
+hipError_t launch_decode_short(const Geom& g, const ShortPlan& pl, const DecodeArgs& a, void* ws, uint64_t tag, hipStream_t st);
 
 }  // namespace antkv

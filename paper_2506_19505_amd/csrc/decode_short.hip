@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kThreads) void decode_short_kernel(const ShortParam
     const int ln = lane & 15, kg = lane >> 4, tj = lane >> 2 & 3, tq = lane & 3;
 
     // ------------------------------------------------------------------------------------------ prologue
-    unsigned long long seen = 0ull;                                 // arrival word: launch tag << 32 | arrivals
+    unsigned long long seen = 0ull;                                 // arrival word
     if (tid == 0 && p.S > 1) seen = __hip_atomic_load(&p.done[bg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int first_k = tid < p.k_k ? idx_k[tid] : -1, first_v = tid < p.k_v ? idx_v[tid] : -1;
     Codes codes;
@@ -156,8 +156,8 @@ __global__ __launch_bounds__(kThreads) void decode_short_kernel(const ShortParam
     for (int j = tid + kThreads; j < p.k_k; j += kThreads) note(s_slot_k, idx_k[j], j);
     for (int j = tid + kThreads; j < p.k_v; j += kThreads) note(s_slot_v, idx_v[j], j);
     // a word left by another launch, or by this one if it is replayed, is replaced by (tag, 0) by whoever gets there first
-    if (tid == 0 && p.S > 1 && ((unsigned int)(seen >> 32) != p.tag || (unsigned int)seen >= (unsigned int)p.S))
-        __hip_atomic_compare_exchange_strong(&p.done[bg], &seen, (unsigned long long)p.tag << 32, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+    if (tid == 0 && p.S > 1 && arrivals_are_stale(seen, p.tag, (uint32_t)p.S))
+        __hip_atomic_compare_exchange_strong(&p.done[bg], &seen, (unsigned long long)p.tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
     lds_barrier();
 
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kThreads) void decode_short_kernel(const ShortParam
     // arrival reads partials that have all reached the level its device-scope loads read from.
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (tid == 0) *s_count = (int)(unsigned int)__hip_atomic_fetch_add(&p.done[bg], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    if (tid == 0) *s_count = (int)(__hip_atomic_fetch_add(&p.done[bg], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kArrivalMask) + 1;
     __syncthreads();
     if (*s_count != p.S) return;
     auto ld = [](const float* q) { return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
@@ -412,7 +412,7 @@ ShortPlan short_plan(const Geom& g, int64_t N)
     return pl;
 }
 
-hipError_t launch_decode_short(const Geom& g, const ShortPlan& pl, const DecodeArgs& a, void* ws, unsigned int tag, hipStream_t st)
+hipError_t launch_decode_short(const Geom& g, const ShortPlan& pl, const DecodeArgs& a, void* ws, uint64_t tag, hipStream_t st)
 {
     ShortParams p;
     p.q = a.q; p.codes_k = a.codes_k; p.codes_v = a.codes_v; p.cb_k = a.cb_k; p.cb_v = a.cb_v;

@@ -425,6 +425,32 @@ def test_decode_repeated_on_one_workspace(oracle):
     assert spread.max() <= 1e-3          # one fp16 unit in the last place of the largest channels
 
 
+@pytest.mark.parametrize("d,C,B,N", [(8, 256, 2, 1237), (16, 256, 1, 4100), (32, 4096, 2, 1500), (16, 4096, 4, 700)])
+def test_decode_on_any_workspace(d, C, B, N):
+    """Pairs of small integers, as index lists and counters leave them, where the arrival words lie: no workgroup takes them for arrivals
+    and merges parts that are not stored yet.  Sums in a fixed order, so the result is that of a workspace of zeros, bit for bit."""
+    Hq, Hkv, k, M = 8, 4, 20, 128 // d
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float16, device="cuda", generator=gen)
+    codes = [torch.randint(0, 256, (B, Hkv, N, M if C == 256 else 3 * M // 2), dtype=torch.uint8, device="cuda", generator=gen) for _ in range(2)]
+    idx = [torch.rand((B, Hkv, N), device="cuda", generator=gen).argsort(dim=-1)[..., :k].sort(dim=-1).values.int() for _ in range(2)]
+    geom = antkv.Geometry(B, Hq, Hkv, d, n_centroids=C)
+    args = (geom, rnd(B, Hq, 128), 128 ** -0.5, *codes, rnd(Hkv, M, C, d), rnd(Hkv, M, C, d), idx[0], rnd(B, Hkv, k, 128), idx[1], rnd(B, Hkv, k, 128))
+    ws = antkv.DecodeWorkspace(geom, N, k, k, 0, "cuda")
+    words = ws.buf[:ws.buf.numel() // 8 * 8].view(torch.int64)
+    low = torch.arange(words.numel(), device="cuda")
+    old = antkv.set_decode_options(antkv.DECODE_FIXED_ORDER)
+    try:
+        words.zero_()
+        want, wrong = antkv.decode_attn(*args, workspace=ws), torch.zeros((), dtype=torch.int64, device="cuda")
+        for high in range(0, 8192, 4):
+            words.copy_((high + low % 4) << 32 | 1 + low % 3)
+            wrong += (antkv.decode_attn(*args, workspace=ws) != want).sum()
+    finally:
+        antkv.set_decode_options(old)
+    assert wrong.item() == 0
+
+
 def test_decode_graph_replay(oracle):
     """The decode step captured into a HIP graph and replayed: every replay must equal the eager result for the inputs
     of that moment (the launch tag of the arrival words is frozen in the captured launch)."""
