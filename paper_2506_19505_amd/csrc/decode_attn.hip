@@ -1699,6 +1699,9 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
     }
     if (tid < kNH * kD) s_qf[tid] = ((tid >> 7) < p.G) ? (float)qb[tid] : 0.f;
     for (int i = tid; i < 1024; i += kDaThreads) s_mask[i] = 0u;
+    // the score of a head that the group does not have: 0 also where the key holds an infinity (a mask: the compiler turns selects
+    // into branches around the heads' products)
+    auto of_head = [&](int h, float v) { return __uint_as_float(__float_as_uint(v) & (h < p.G ? ~0u : 0u)); };
     const bool count_scores = PASS == 1 && p.topk.hist != nullptr;
     if (PASS == 0)
         for (int64_t i = (int64_t)blockIdx.x * kDaThreads + tid; i < p.topk.words; i += (int64_t)gridDim.x * kDaThreads) p.topk.hist[i] = 0u;
@@ -1731,7 +1734,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
                 float s = 0.f;
 #pragma unroll
                 for (int t = 0; t < DSUB; ++t) s = fmaf(s_qf[h * kD + m * DSUB + t], cf[t], s);
-                o[h] = h < p.G ? s * p.c1 : 0.f;                 // (a centroid with an infinity times no head is not 0)
+                o[h] = of_head(h, s * p.c1);
             }
 #pragma unroll
             for (int c = 0; c < SLOTS / M; ++c) s_lut[(m >> 4) * 4096 + (e & 255) * 16 + (m & 15) + M * c] = o;
@@ -1941,7 +1944,7 @@ __global__ __launch_bounds__(kDaThreads) void decode_ans_kernel(const DsParams p
                 float d = 0.f;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) d = fmaf(qv[h][e], (float)v[e], d);
-                s[h] = h < p.G ? row16_sum(d) * p.c1 : 0.f;
+                s[h] = of_head(h, row16_sum(d) * p.c1);
             }
             consume(s, tok, 0u, tok >= 0 && l16 == 0);
         };
