@@ -5,7 +5,8 @@
 // anchor lists as work of their own.  Here a workgroup (8 waves) has a few hundred tokens of one (sequence, KV head):
 //
 //  prologue  one round of loads: the anchor lists (their entries in the range leave their slot numbers in LDS, one word
-//            per token and side), the codes of the waves' first tiles, the query.  The codebooks (1 MB each) stay in the L2.
+//            per token and side; long lists are cut to the range by a search first), the codes of the waves' first tiles, the
+//            query.  The codebooks (1 MB each) stay in the L2.
 //  tile      32 tokens per wave.  Scores: 16 tokens x 128 channels on the rows of the MFMA, the query heads on its
 //            columns, a lane's eight channels being one 16-byte piece of a centroid or of an FP16 K row: anchored tokens
 //            differ in the address only.  The result leaves four consecutive tokens of one head in a lane, which is the
@@ -28,6 +29,10 @@ namespace {
 
 constexpr int kThreads = 512, kWaves = kThreads / 64;
 constexpr int kTile = 32;               // tokens of a wave's tile
+// A list of up to kScan entries is read whole by every workgroup, a longer one cut to its range by a search (two or three dependent
+// loads).  8 heads, read whole and cut: d 32, 90000 tokens, all anchored 216 and 77 us (165 through a table), one in ten 50.6 and 43;
+// 16384 tokens, all 35 and 21; d 16, 57000 tokens, all 104 and 43, one in ten 51 and 42.
+constexpr int kScan = 4 * kThreads;
 
 struct Lds {
     static constexpr int rows = 0;                                  // [waves][32 rows of 256 bytes]
@@ -126,14 +131,16 @@ __global__ __launch_bounds__(kThreads) void decode_short_kernel(const ShortParam
     int* s_slot_k = (int*)(smem + Lds::slot_k);
     int* s_slot_v = (int*)(smem + Lds::slot_v);
     float* s_red = (float*)(smem + Lds::red);
-    int* s_count = (int*)(smem + Lds::red + kWaves * 32);
+    int* s_count = (int*)(smem + Lds::red + kWaves * 32);           // one word; then the bounds of the K and of the V list
+    int* s_cut = s_count + 1;
     // MFMA lane coordinates: row / column and k-group; token and 8-byte piece of a transposed read
     const int ln = lane & 15, kg = lane >> 4, tj = lane >> 2 & 3, tq = lane & 3;
 
     // ------------------------------------------------------------------------------------------ prologue
     unsigned long long seen = 0ull;                                 // arrival word
     if (tid == 0 && p.S > 1) seen = __hip_atomic_load(&p.done[bg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int first_k = tid < p.k_k ? idx_k[tid] : -1, first_v = tid < p.k_v ? idx_v[tid] : -1;
+    const bool cut_k = p.k_k > kScan, cut_v = p.k_v > kScan;
+    const int first_k = !cut_k && tid < p.k_k ? idx_k[tid] : -1, first_v = !cut_v && tid < p.k_v ? idx_v[tid] : -1;
     Codes codes;
     if (wave < n_tiles) codes.load(ck, cv, wave, n, lane);
     half8_t qop[4];                                                 // query: column ln is head ln % 4
@@ -153,8 +160,31 @@ __global__ __launch_bounds__(kThreads) void decode_short_kernel(const ShortParam
     };
     note(s_slot_k, first_k, tid);
     note(s_slot_v, first_v, tid);
-    for (int j = tid + kThreads; j < p.k_k; j += kThreads) note(s_slot_k, idx_k[j], j);
-    for (int j = tid + kThreads; j < p.k_v; j += kThreads) note(s_slot_v, idx_v[j], j);
+    if (cut_k || cut_v) {
+        if (wave < 4 && (wave < 2 ? cut_k : cut_v)) {
+            const int at = lower_bound64(wave < 2 ? idx_k : idx_v, wave < 2 ? p.k_k : p.k_v, wave & 1 ? t0 + n : t0, lane);
+            if (lane == 0) s_cut[wave] = at;
+        }
+        lds_barrier();
+        const int lo_k = cut_k ? s_cut[0] : kThreads, len_k = (cut_k ? s_cut[1] : p.k_k) - lo_k;
+        const int lo_v = cut_v ? s_cut[2] : kThreads, len_v = (cut_v ? s_cut[3] : p.k_v) - lo_v;
+        for (int j = tid; j < max(len_k, len_v); j += 2 * kThreads) {
+            int e[2][2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                e[0][u] = j + u * kThreads < len_k ? idx_k[lo_k + j + u * kThreads] : -1;
+                e[1][u] = j + u * kThreads < len_v ? idx_v[lo_v + j + u * kThreads] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                note(s_slot_k, e[0][u], lo_k + j + u * kThreads);
+                note(s_slot_v, e[1][u], lo_v + j + u * kThreads);
+            }
+        }
+    } else {
+        for (int j = tid + kThreads; j < p.k_k; j += kThreads) note(s_slot_k, idx_k[j], j);
+        for (int j = tid + kThreads; j < p.k_v; j += kThreads) note(s_slot_v, idx_v[j], j);
+    }
     // a word left by another launch, or by this one if it is replayed, is replaced by (tag, 0) by whoever gets there first
     if (tid == 0 && p.S > 1 && arrivals_are_stale(seen, p.tag, (uint32_t)p.S))
         __hip_atomic_compare_exchange_strong(&p.done[bg], &seen, (unsigned long long)p.tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,

@@ -387,10 +387,11 @@ def test_decode12_either_side_of_the_switch(books, B, Hkv):
 
 
 # Edges of a tile (32 tokens), of the waves (8 tiles), of the split (128 tokens a range, 32 ranges), groups of 1, 2 and 4, all
-# or no tokens anchored; the longest ranges that are gathered row by row (8 heads: 32 x 3072 and 32 x 1792 tokens) and one more.
+# or no tokens anchored, lists that are cut to the ranges; the longest ranges that are gathered row by row (8 heads: 32 x 3072 and 32 x 1792 tokens) and one more.
 @pytest.mark.parametrize("B,Hq,Hkv,N,k_k,k_v", [(1, 4, 1, 1, 1, 0), (3, 2, 2, 31, 0, 31), (1, 8, 2, 33, 33, 33), (2, 4, 2, 127, 1, 1),
                                                 (1, 8, 8, 129, 5, 7), (300, 1, 1, 257, 3, 9), (1, 4, 2, 4095, 700, 1300), (1, 16, 4, 4097, 41, 41),
-                                                (5, 32, 8, 3001, 62, 62), (1, 32, 8, -1, 300, 310), (1, 32, 8, -2, 310, 300)])
+                                                (5, 32, 8, 3001, 62, 62), (1, 32, 8, -1, 300, 310), (1, 32, 8, -2, 310, 300),
+                                                (1, 8, 2, 9000, 2048, 2049), (2, 4, 2, 20001, 20001, 0), (1, 2, 2, 30000, 2049, 29000)])
 def test_decode12_short_ranges(books, B, Hq, Hkv, N, k_k, k_v):
     """Row by row, against float64.  Bound: a weight's rounding to fp16 and the output's, 2^-11 each; 1e-4 for the rest (through
     the table, one token past the longest, the bound that its other tests have)."""
