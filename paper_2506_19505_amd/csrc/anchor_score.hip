@@ -468,6 +468,7 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
 // costs about 550 clocks of the SIMD (matrix instructions and the epilogue).
 // -------------------------------------------------------------------------------------------------
 constexpr int kWinSteps = 4, kWinWaves = 4, kWinThreads = kWinWaves * 64, kWinPerCu = 3;
+constexpr int kWinPairs = 192;                                  // (sequence, KV head) pairs from which a wave has at least two tiles
 
 // query tiles of the (sequence, KV head) into LDS: step = (head of the group, query tile)
 template <int STEPS>
@@ -774,8 +775,13 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq, bool room)
     p.keys_per_split = per;
     p.KS = (int)((N + per - 1) / per);
     if (p.steps) {
-        // workgroups of a (sequence, KV head): all CUs full once, at least a tile per wave
-        const int64_t n_tiles = (N + 31) / 32, fill = n_bg > 0 ? 256 * kWinPerCu / n_bg : 1, most = (n_tiles + kWinWaves - 1) / kWinWaves;
+        // Workgroups of a (sequence, KV head): all CUs full once, at least a tile per wave, and two where the pairs themselves come
+        // near a workgroup per CU (query tiles are then loaded less often).  Whole selection, 4 heads x 32 queries, through the general
+        // kernels, with one tile and with two: 224 pairs x 300 keys 32.7, 34.3, 31.7 us, 256 x 450 39.9, 40.3, 36.1, 384 x 150 38.5,
+        // 40.2, 36.9; 128 x 150 23.7, 22.5, 24.7.  General and these, 8192 keys: 8 pairs 44 and 33, 64 88 and 80, 128 160 and 129, 384
+        // 505 and 361, 400 524 and 413 (a workgroup per pair from 385 on), 768 959 and 712, 800 1040 and 863, 2048 2527 and 1894.
+        const int64_t n_tiles = (N + 31) / 32, fill = n_bg > 0 ? 256 * kWinPerCu / n_bg : 1, least = kWinWaves * (n_bg < kWinPairs ? 1 : 2);
+        const int64_t most = (n_tiles + least - 1) / least;
         const int64_t S = fill < 1 ? 1 : (fill < most ? fill : most);
         const int64_t tiles = (n_tiles + S - 1) / S;
         p.keys_per_split = 32 * tiles;

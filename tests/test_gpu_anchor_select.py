@@ -207,3 +207,15 @@ def test_column_sums_in_parts_on_any_workspace():
         assert call(ans) == 0
         wrong += sum((a != b).sum() for a, b in zip(ans, want))
     assert wrong.item() == 0
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,Nq", [(23, 8, 8, 300, 32), (24, 32, 8, 33, 32), (28, 32, 8, 300, 32), (48, 16, 8, 257, 33), (400, 4, 1, 150, 7),
+                                           (100, 8, 8, 1031, 128)])
+def test_window_of_many_pairs(B, Hq, Hkv, N, Nq):
+    """A window's Anchor Score on either side of the number of pairs from which a wave has two key tiles, and with one workgroup per
+    pair; ragged keys and queries, the diagonal inside the last tiles.  Bound: the 3e-5 that scores are held to."""
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    q, k = (torch.randn((B, h, n, 128), dtype=torch.float16, device="cuda", generator=gen) for h, n in ((Hq, Nq), (Hkv, N)))
+    _, _, *got = antkv.anchor_select(antkv.Geometry(B, Hq, Hkv, 8), q, k, 128 ** -0.5, 4)
+    for a, b in zip(got, _scores64(q, k, 128 ** -0.5)):
+        assert ((a.double() - b).abs() / b).max().item() <= 3e-5
