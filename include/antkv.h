@@ -150,6 +150,10 @@ int antkv_gather_rows(const antkv_geom* geom, const void* x, int64_t N, const in
  * about 14, 20, 29 for d_sub 4, 8, 16 and 82, 58 for the 12-bit formats with d_sub 32, 16); for larger entries the
  * bound grows in proportion to R_h (d_sub 8 and 16: unless ANTKV_DECODE_WIDE_TABLE is set, see
  * antkv_set_decode_options).  Anchor tokens are scored from their FP16 rows and are not affected.
+ * Short contexts of 12-bit codes have no table: every token is scored by an fp32 sum of the fp16 products of its centroids (or row),
+ * without a limit on R_h, and the output stays within 2^-10 + 1e-4.  They end between 1280 tokens (256 sequences x KV heads or more)
+ * and 98304 (8 KV heads of d_sub 32), wherever the table becomes the faster one for the shape; a growing context passes from this
+ * bound to the table's.  Anchor Scores of 12-bit codes are fp32 table sums at every length.
  * Optional decode-time Anchor Score (Eq. (4) with the single query row over K_eff):
  *   ans_k, ans_v      fp32 [B][Hkv][N], both or neither (NULL):  ans_v[j] = sum_h p_hj,
  *            ans_k[j] = sum_h p_hj (1 - p_hj) ||q_h||_2

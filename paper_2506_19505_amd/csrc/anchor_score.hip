@@ -412,7 +412,7 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
         landed_but<2 * (kParts + 1)>();                          // this step's loads and the last one's
     };
     // Whole groups of four in the loop, the rest behind it: rounded up to four (with neutral statistics) 300 queries x 131072
-    // keys x 8 heads of one query head each took 350 us for the whole selection, now 327; 32 queries 167 and 149.
+    // keys x 8 heads of one query head each took 350 us for the whole selection, now 327.
     int left = n_steps;
     for (; left >= 4; left -= 4) {
         step(std::integral_constant<int, 0>{});
@@ -464,8 +464,10 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
 // Few query rows (an observation window): steps = heads of the group x query tiles <= kWinSteps.  Both phases then keep the
 // query tiles in LDS and stream the keys once: a wave takes tiles of 32 keys, the next tile's rows on their way into registers while
 // this one meets every step, without a barrier in the loop.
-// Bound: bytes in flight.  A tile is 8 KB of a wave, three workgroups of four waves per CU have 96 KB on the way, and a step
-// costs about 550 clocks of the SIMD (matrix instructions and the epilogue).
+// Bound: neither the keys nor the arithmetic alone.  131072 keys x 8 heads, four steps, kernel trace and counters: phase 1 57 us,
+// phase 2 59, of which reading the keys once (268 MB) takes 46 at the rate of a large copy and the steps 32 (550 clocks of a SIMD
+// each); VALU 57 and 63 % of the time, MFMA 36 and 35 %, waves wait for memory or a counter 36 and 33 % of theirs: a wave asks for
+// its next tile at once and meets four steps before it needs it, and loads and steps of the three waves of a SIMD overlap in part.
 // -------------------------------------------------------------------------------------------------
 constexpr int kWinSteps = 4, kWinWaves = 4, kWinThreads = kWinWaves * 64, kWinPerCu = 3;
 constexpr int kWinPairs = 192;                                  // (sequence, KV head) pairs from which a wave has at least two tiles
@@ -735,8 +737,9 @@ constexpr int kColKeys = 128;                                   // keys of the s
 
 // Workgroups that share the steps of a key block.  Unsplit, the first block's workgroup walks every query of every head, 0.27 us a step,
 // while most CUs have nothing: 32 heads of 8 KV heads, whole selection, unsplit and as below: 500 tokens 41 and 23 us, 1200 79 and 30,
-// 3000 179 and 80, 7000 422 and 288, 16000 1443 and 1351.  A part costs some 8 us besides its steps, so that it has at least 16 of them;
-// short walks are split up to 512 blocks (one query head per KV head, 2 x 32 heads, 640 blocks of at most 38 steps: 40 us, in halves
+// 3000 179 and 80, 7000 422 and 288, 16000 1443 and 1351.  A part costs some 8 us besides its steps, so that the longest walk, the
+// first key block's, has at least 16 of them per part (of a causal prompt's later blocks the parts have fewer, the last ones' one or
+// none; every block has the same number of parts); short walks are split up to 512 blocks (one query head per KV head, 2 x 32 heads, 640 blocks of at most 38 steps: 40 us, in halves
 // 48; 320 blocks 33 and 31), longer ones up to 2048, into more than four parts below 128 blocks (3 x 8 heads, 240 blocks:
 // quarters 52 us, eighths 58; 80 blocks 35 and 30).
 int col_splits(int64_t blocks, int64_t n_steps)
@@ -765,8 +768,9 @@ AsPlan plan(const Geom& g, int64_t N, int64_t Nq, bool room)
     const int64_t qblocks = (Nq + qspan - 1) / qspan;
     const int64_t base_wgs = (int64_t)g.B * g.Hkv * qblocks;
     int64_t ks = base_wgs > 0 ? (1024 + base_wgs - 1) / base_wgs : 1;
-    // Ranges of 1024 keys: a window's phase 1 has no other parallelism (131072 keys x 32 queries x 8 heads: 102 us with ranges of
-    // 4096, one workgroup per CU; 77 with these).
+    // Ranges of 1024 keys: few query rows leave phase 1 no other parallelism (whole selection, 131072 keys x 8 heads, one query head
+    // each, 160 queries: 229 us with ranges of 4096, 222 with these, 213 with 2048; four query heads each, 64 queries 256, 259, 252,
+    // 128 queries 427, 430, 430).
     const int64_t max_ks = (N + 1023) / 1024;
     if (ks > max_ks) ks = max_ks;
     if (ks < 1) ks = 1;
@@ -855,8 +859,8 @@ hipError_t launch_anchor_score(const Geom& g, const half_t* q, const half_t* k, 
     hipLaunchKernelGGL(ans_finalize_stats, dim3((unsigned)((padded * 16 + 255) / 256)), dim3(256), 0, st, q, part, p.KS,
                        row_max, row_sum, stat, Nq, (int)q_tiles, n_heads, ClearWords{split.done, p.n_done});
     // 64 keys per wave (the query tiles and statistics are read once for two key tiles) while that fills the chip and the
-    // walk over the queries is long beside loading the keys (131072 keys, 32 queries: 92 us against 80); smaller workgroups
-    // otherwise
+    // walk over the queries is long beside loading the keys (whole selection, 131072 keys x 32 heads: 64 queries 275 us against 259
+    // with the smaller ones, 300 988 and 985, 512 1396 and 1432); smaller workgroups otherwise
 #define ANTKV_CR(KT, NW, SPLIT)                                                                                           \
     hipLaunchKernelGGL((ans_col_reduce<KT, NW, SPLIT>), dim3((unsigned)((N + 32 * KT * NW - 1) / (32 * KT * NW) * n_bg * (SPLIT ? p.splits : 1))), \
                        dim3(NW * 64), 0, st, q, k, N, Nq, c1, stat, ans_k, ans_v, g.Hq, g.Hkv, g.G, n_bg, (int)q_tiles, split)

@@ -20,8 +20,9 @@
 //              the centroids) as the source.
 //   merge      waves through LDS, workgroups through a partial (max, sum, accumulator) per head and a second
 //              small kernel.
-// Long contexts take the kernels of decode12_by_code.hip instead, which add the values up by code (rule: d12_by_code below);
-// the table and merge kernels here serve both.
+// Short contexts take the kernel of decode_short.hip instead, which has neither a table nor a merge launch (rule: short_plan there;
+// their decode-time Anchor Scores come from the table and d12_ans_kernel here), long ones those of decode12_by_code.hip, which add the
+// values up by code (rule: d12_by_code below) and share the table and merge kernels.
 #include "decode12.h"
 #include "decode_short.h"
 
