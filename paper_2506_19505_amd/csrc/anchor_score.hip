@@ -464,7 +464,7 @@ __global__ __launch_bounds__(NW * 64, 2) void ans_col_reduce(
 // Few query rows (an observation window): steps = heads of the group x query tiles <= kWinSteps.  Both phases then keep the
 // query tiles in LDS and stream the keys once: a wave takes tiles of 32 keys, the next tile's rows on their way into registers while
 // this one meets every step, without a barrier in the loop.
-// Bound: neither the keys nor the arithmetic alone.  131072 keys x 8 heads, four steps, kernel trace and counters: phase 1 57 us,
+// Bound: neither the keys nor the arithmetic alone.  131072 keys x 8 heads, four steps, kernel trace and counters: phase 1 53 us,
 // phase 2 59, of which reading the keys once (268 MB) takes 46 at the rate of a large copy and the steps 32 (550 clocks of a SIMD
 // each); VALU 57 and 63 % of the time, MFMA 36 and 35 %, waves wait for memory or a counter 36 and 33 % of theirs: a wave asks for
 // its next tile at once and meets four steps before it needs it, and loads and steps of the three waves of a SIMD overlap in part.
